@@ -382,6 +382,7 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
         ISING_HIP(hipMalloc(&b->d_res, sizeof(PersistTile) * res_tiles.size()));
         ISING_HIP(hipMemcpy(b->d_res, res_tiles.data(), sizeof(PersistTile) * res_tiles.size(), hipMemcpyHostToDevice));
         ISING_HIP(hipMalloc(&b->d_exch, sizeof(uint64_t) * (size_t)b->exch_tile_words * res_tiles.size()));
+        ISING_HIP(hipMemset(b->d_exch, 0, sizeof(uint64_t) * (size_t)b->exch_tile_words * res_tiles.size()));
         ISING_HIP(hipMalloc(&b->d_flags, sizeof(uint64_t) * res_tiles.size()));
         ISING_HIP(hipMemset(b->d_flags, 0, sizeof(uint64_t) * res_tiles.size()));
         if (!b->d_err) {

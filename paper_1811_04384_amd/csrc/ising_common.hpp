@@ -155,11 +155,12 @@ struct PersistTile {
 // is a multiple of every (every = 0: none); the sample's partial sums go to
 // partials[ordinal * n_tiles + tile.part].  exch holds exch_tile_words
 // (>= 4 N) words per tile, flags one word per tile; both persist between
-// launches.  A tile's flag reaches 2 t + s + 1 when it has published its
-// boundary words of half-sweep s (0 or 1) of its lattice's absolute sweep
-// t, so flags only grow while sweep counters do (a counter set back needs
-// its lattice's flags zeroed).  A wait longer than wait_ticks (100 MHz
-// clock) sets *error and ends the launch early.
+// launches and are zeroed when they are made.  A tile's flag counts its
+// launches (in the form the published words carry, see the kernel); all
+// tiles of a lattice take part in the same launches, so their counts agree,
+// and a word left by an earlier launch is never taken for one of this launch.
+// A launch has fewer than 2^20 sweeps.  A wait longer than wait_ticks (100
+// MHz clock) sets *error and ends the launch early.
 struct PersistLaunch {
     const PersistTile* tiles;
     const LatticeDesc* descs;

@@ -245,17 +245,9 @@ int ising_create_in(int32_t L, uint64_t seed, int32_t init, void* dev_words, siz
     return create_impl(L, seed, init, dev_words, bytes, stream, out);
 }
 
-// Resident-tile flags follow the sweep counter: zero them when it goes back.
-static int counter_set_back(ising_lattice* h) {
-    if (h->d_flags) ISING_HIP(hipMemsetAsync(h->d_flags, 0, sizeof(uint64_t) * h->n_res, h->stream));
-    return ISING_OK;
-}
-
 int ising_reset(ising_lattice* h, uint64_t seed, int32_t init) {
     if (!h) return fail(ISING_EINVAL, "ising_reset: null handle");
     if (init != ISING_COLD && init != ISING_HOT) return fail(ISING_EINVAL, "ising_reset: init must be 0 or 1");
-    const int rc = counter_set_back(h);
-    if (rc != ISING_OK) return rc;
     h->seed = seed;
     h->t = 0;
     ISING_HIP(launch_init(h->W, h->g, seed, init, h->stream));
@@ -609,10 +601,6 @@ int ising_get_sweep_count(ising_lattice* h, uint64_t* t) {
 
 int ising_set_sweep_count(ising_lattice* h, uint64_t t) {
     if (!h) return fail(ISING_EINVAL, "ising_set_sweep_count: null handle");
-    if (t < h->t) {
-        const int rc = counter_set_back(h);
-        if (rc != ISING_OK) return rc;
-    }
     h->t = t;
     return ISING_OK;
 }
@@ -778,6 +766,7 @@ int ising_set_resident_tiles(ising_lattice* h, int32_t tile_cols, int32_t block,
     hipError_t e = hipMalloc(&h->d_res, sizeof(PersistTile) * n);
     if (e == hipSuccess) e = hipMemcpy(h->d_res, tiles.data(), sizeof(PersistTile) * n, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc(&h->d_exch, sizeof(uint64_t) * 4 * (size_t)N * n);
+    if (e == hipSuccess) e = hipMemset(h->d_exch, 0, sizeof(uint64_t) * 4 * (size_t)N * n);
     if (e == hipSuccess) e = hipMalloc(&h->d_flags, sizeof(uint64_t) * n);
     if (e == hipSuccess) e = hipMemset(h->d_flags, 0, sizeof(uint64_t) * n);
     if (e == hipSuccess && !h->d_err) e = hipMalloc(&h->d_err, sizeof(uint64_t));

@@ -12,24 +12,32 @@
 // colour c in a tile is one pass over its words of colour c:
 //   - the boundary words (local columns 1 and w) come first; each reads its
 //     ghost neighbour straight from the neighbouring tile's publication of
-//     half-sweep s - 1 (from LDS in a launch's first half-sweep), and is
-//     published at once to an exchange buffer in global memory; the thread
-//     that publishes the last of them raises the tile's flag (to a value
-//     that grows with the lattice's sweep counter and the half-sweep);
+//     half-sweep s - 1 (from LDS in a launch's first half-sweep) and is
+//     published at once to an exchange buffer in global memory;
 //   - then the interior words (columns 2 .. w - 1), while the boundary words
 //     travel, and the Philox blocks of the next half-sweep's position 20
 //     (and, with at most two words of a colour per thread, the acceptance
-//     codes of the next half-sweep's words, drawn into an LDS code table
-//     while each word's own loads are in flight);
-//   - at the end, before the workgroup barrier, one thread waits until both
-//     neighbours' flags show this half-sweep (their publications are
-//     normally done long before).
+//     codes of the next half-sweep's words, drawn into an LDS code table:
+//     by the interior words' wavefronts while their own loads are in flight,
+//     by the boundary words' wavefronts after they have published, so that
+//     the neighbours never wait for draws).
+// A published word carries its own tag in the two bits of every field that
+// the spin coding leaves 0: the half-sweep in the middle bits and the launch
+// in the upper ones.  A reader polls the word itself until the tag is the one
+// it waits for, so that one store and one load are all that lies between the
+// update of a boundary word and its use next door; no flag is raised behind
+// the data and no store is waited for.  Small bands are bound by that path:
+// 126 bands of 8 columns of L = 1008 take 1.35 us per half-sweep, against 2.69
+// with a flag per tile, raised after every publisher's store had completed
+// and polled before the barrier (three memory round trips after each other);
+// bands of 16 columns (L = 4096: 3.90 against 3.97 us) are bound by the
+// vector unit.
 // Only colour-c words are exchanged, because the next half-sweep only reads
 // those from a ghost column.  The exchange buffer alternates between two
 // halves on the half-sweep's parity: a tile overwrites a half two
-// half-sweeps later, after its neighbours have raised their flags past the
-// half-sweep that read it (each publisher reads its ghost word before it
-// publishes).
+// half-sweeps later, after its neighbours have published the half-sweep that
+// read it (each publisher reads its ghost word before it publishes, and this
+// tile has read theirs).
 //
 // Every tile of a launch must be resident at once (the host launches at most
 // as many tiles as the device holds).  Each wait is bounded in time: when
@@ -76,18 +84,38 @@ __device__ __forceinline__ uint32_t lds_load32(uint32_t addr) { return *(const l
 struct WordItem {
     uint32_t w, lf, rt, up, dn, patch, u20, c1;
     int32_t I, side;
-    uint32_t code;  // byte offset of its codes in a half-sweep's code table
 };
 
+// What drawing a word's codes takes: its row and its Philox counter.
+struct DrawItem {
+    int32_t I;
+    uint32_t c1;
+};
 
-}  // namespace
+// The tag bits of a published word: the middle bit of every field counts the
+// launch's half-sweeps, the upper bit the launches of the tile's table.  A
+// number is kept with its bits spread to those places; adding one carries
+// through the bits between them when these are set first.
+constexpr uint64_t kStepBits = kSpinBits << 1;
+constexpr uint64_t kLaunchBits = kSpinBits << 2;
+template <uint64_t BITS>
+__device__ __forceinline__ uint64_t spread_next(uint64_t tag) {
+    return ((tag | ~BITS) + 1) & BITS;
+}
 
-__global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
-    extern __shared__ uint64_t lds[];
-    __shared__ uint32_t red[2 * (kPersistMaxBlock / 64)];
-    __shared__ int stop;
-    __shared__ uint32_t published;  // boundary words published in this launch
-    const PersistTile tp = a.tiles[blockIdx.x];
+// How a tile's threads hold its word items: formed in every half-sweep, or
+// once per launch with one or two items per thread and colour.
+enum Items { kFormed, kOne, kTwo };
+
+// Word items of a colour of a tile.
+__device__ __forceinline__ int tile_items(int L, int N, int tile_w) {
+    return tile_w >= L ? N * (L >> 1) : N + N * ((tile_w - 2) >> 1);
+}
+
+// One tile's launch.  WHOLE: the tile is the whole lattice.
+template <int ITEMS, bool WHOLE>
+__device__ __forceinline__ void persist_tile(const PersistLaunch& a, const PersistTile& tp, uint64_t* lds,
+                                             uint32_t* red, int& stop) {
     const LatticeDesc& d = a.descs[tp.lattice];
     const int L = d.L, N = d.N, istar = d.istar, sh_star = d.sh_star;
     const int pstar = (L - 1) / N;
@@ -107,7 +135,7 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
         t8 = a.t8;
     }
     const int K = a.K;
-    const bool whole = tp.w >= L;
+    constexpr bool whole = WHOLE;
     const int w = whole ? L : tp.w;
     const int width = whole ? L : w + 2;  // local column x <-> global c0 - 1 + x (halo form)
     const int gx0 = whole ? 0 : (tp.c0 == 0 ? L - 1 : tp.c0 - 1);
@@ -133,10 +161,9 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
         const uint64_t t = t0 + (uint64_t)(hs >> 1);
         return LdsSweep{L, N, istar, sh_star, pstar, (uint32_t)t, (uint32_t)(t >> 32), k0, k1, t4, t8, all_blocks};
     };
-    if (tid == 0) {
-        stop = 0;
-        published = 0;
-    }
+    if (tid == 0) stop = 0;
+    // the tag of this launch: every tile of a lattice counts the same launches
+    const uint64_t launch_tag = a.flags[blockIdx.x];
 
     // load the band and its ghost columns, eight loads in flight per thread
     {
@@ -178,7 +205,10 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
     const float rcp_P = P > 0 ? 1.0f / (float)P : 0.0f;
     const float rcp_g = 1.0f / (float)n_groups;
     const int64_t tw = a.exch_tile_words;
-    const int n_w = n_b + n_i;  // word items of a half-sweep
+    const int n_w = n_b + n_i;  // word items of a half-sweep (tile_items)
+    // wavefronts with a boundary word in their first / second item
+    const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);
+    const bool edge0 = wave0 < n_b, edge1 = wave0 + B < n_b;
     const lds_u64* T3 = (const lds_u64*)T;
     // word item f of a half-sweep of colour c: boundary items first (items
     // f < N/2 in column 1, the others in column w, on the rows with
@@ -200,8 +230,10 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
         const int row = I * width;
         WordItem it;
         it.w = lds_addr(T3 + row + x);
-        it.lf = lds_addr(T3 + row + xl);
-        it.rt = lds_addr(T3 + row + xr);
+        if (WHOLE) {  // otherwise the words beside it in the band
+            it.lf = lds_addr(T3 + row + xl);
+            it.rt = lds_addr(T3 + row + xr);
+        }
         it.up = lds_addr(T3 + (I > 0 ? I - 1 : N - 1) * width + x);
         it.dn = lds_addr(T3 + (I < N - 1 ? I + 1 : 0) * width + x);
         // the patch word (row I* for I = 0, row 0 for I = I*); other rows
@@ -211,40 +243,54 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
         it.c1 = (uint32_t)I * (uint32_t)L + (uint32_t)J;
         it.I = I;
         it.side = side;
-        it.code = 8u * (uint32_t)f;
         return it;
     };
-    // With at most two word items per thread and colour (the usual tile
-    // shapes), every thread's items are the same in every half-sweep of a
+    // With at most two word items per thread and colour (kOne, kTwo: the usual
+    // tile shapes), every thread's items are the same in every half-sweep of a
     // colour and are formed once, and the codes of positions 0..19 of every
     // word are drawn a half-sweep ahead into a code table (two, by the
     // half-sweep's parity, after the position-20 tables): in a half-sweep a
     // thread updates its words from the table and draws the codes of its
     // words of the other colour for the next one, while the loads of the
-    // word's neighbourhood are in flight.  Otherwise every item is formed
-    // and drawn in its half-sweep.
-    const bool pre = n_w <= 2 * B;
+    // word's neighbourhood are in flight.  With at most one item per thread
+    // (kOne: small bands, whose half-sweep is as long as the exchange of the
+    // boundary words) the codes are drawn by the threads from the last
+    // one down instead, so that the boundary words' wavefronts have nothing
+    // else to do.  Otherwise every item is formed and drawn in its half-sweep.
+    constexpr bool pre = ITEMS != kFormed;
+    constexpr bool split = ITEMS == kOne;
     const uint32_t ctab = lds_addr((const lds_u64*)(u5tab + (size_t)2 * n_groups * N));
     WordItem cur0{}, cur1{}, oth0{}, oth1{};  // word items, this colour and the other
-    auto draw_codes = [&](const WordItem& it, const LdsSweep& swc, uint32_t table) {
+    DrawItem dcur0{}, dcur1{}, doth0{}, doth1{};  // the items whose codes this thread draws
+    const int f0 = split ? B - 1 - tid : tid, f1 = tid + B;
+    auto draw_codes = [&](const DrawItem& it, int f, const LdsSweep& swc, uint32_t table) {
         // the sweep index made opaque to the compiler (see the words below)
         LdsSweep swi = swc;
         asm volatile("" : "+s"(swi.t_lo), "+s"(swi.t_hi));
-        lds_store64(table + it.code, lds_word_codes(swi, rk, it.I, it.c1));
+        lds_store64(table + 8u * (uint32_t)f, lds_word_codes(swi, rk, it.I, it.c1));
     };
     if (pre) {
-        if (tid < n_w) {
-            cur0 = make_item(tid, 0);
-            oth0 = make_item(tid, 1);
+        // a thread without an item holds the last one's addresses: its loads
+        // are in bounds and not used
+        cur0 = make_item(min(tid, n_w - 1), 0);
+        oth0 = make_item(min(tid, n_w - 1), 1);
+        if (tid >= n_w) cur0.side = oth0.side = -1;
+        if (!split) {
+            cur1 = make_item(min(f1, n_w - 1), 0);
+            oth1 = make_item(min(f1, n_w - 1), 1);
+            dcur1 = {cur1.I, cur1.c1};
+            doth1 = {oth1.I, oth1.c1};
+            if (f1 >= n_w) cur1.side = oth1.side = -1;
         }
-        if (tid + B < n_w) {
-            cur1 = make_item(tid + B, 0);
-            oth1 = make_item(tid + B, 1);
+        if (f0 < n_w) {
+            const WordItem d0 = make_item(f0, 0), d1 = make_item(f0, 1);
+            dcur0 = {d0.I, d0.c1};
+            doth0 = {d1.I, d1.c1};
         }
         // the codes of the first half-sweep
         const LdsSweep sw0 = sweep_of(0);
-        if (tid < n_w) draw_codes(cur0, sw0, ctab);
-        if (tid + B < n_w) draw_codes(cur1, sw0, ctab);
+        if (f0 < n_w) draw_codes(dcur0, f0, sw0, ctab);
+        if (!split && f1 < n_w) draw_codes(dcur1, f1, sw0, ctab);
         __syncthreads();
     }
     // the next half-sweep's position-20 blocks (of the rows with 21 live
@@ -272,11 +318,35 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
     // a long scalar routine)
     int64_t next_sample = a.every > 0 ? (int64_t)a.every - 1 - a.sample_base % a.every : -1;
     int n_taken = 0;
-    // one half-sweep: the word items of its colour (cur0, cur1) and of the
-    // other colour (oth0, oth1), whose codes it draws for the next one;
-    // returns whether the launch stops
+    auto fetch = [&](const uint64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    // one ghost word, first read as v: polled until it carries the tag
+    // `want`.  Bounded twice, by the clock (a failed poll counts for at least
+    // 100 ns) and by the number of polls; when a bound is reached, or another
+    // tile has set the error word, the launch is abandoned after this
+    // half-sweep.
+    auto ghost = [&](const uint64_t* p, uint64_t v, uint64_t want) -> uint64_t {
+        if ((v & ~kSpinBits) != want) {
+            const uint64_t start = clock_ticks() - 10;
+            for (uint32_t polls = 0;; ++polls) {
+                if (__hip_atomic_load(a.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
+                    clock_ticks() - start > a.wait_ticks || polls > kMaxPolls) {
+                    __hip_atomic_store(a.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    stop = 1;
+                    break;
+                }
+                v = fetch(p);
+                if ((v & ~kSpinBits) == want) break;
+            }
+        }
+        return v & kSpinBits;
+    };
+    uint64_t step_tag = 0;  // tag of the half-sweep before (0: none in this launch)
+    uint64_t ghost0 = 0;    // the ghost word of this half-sweep's first item (code-table mode)
+    // one half-sweep: the word items of its colour (cur0, cur1), the first
+    // item of the next one (oth0) and the items whose codes it draws for the
+    // next one (d0, d1); returns whether the launch stops
     auto half_sweep = [&](const int hs, const WordItem& cur0, const WordItem& cur1, const WordItem& oth0,
-                          const WordItem& oth1) __attribute__((always_inline)) -> bool {
+                          const DrawItem& d0, const DrawItem& d1) __attribute__((always_inline)) -> bool {
         const int c = hs & 1;
         const int j = hs >> 1;
         const LdsSweep sw = sweep_of(hs);
@@ -285,48 +355,54 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
         uint4* __restrict__ u5next = u5tab + (size_t)((hs + 1) & 1) * n_groups * N;
         const int n_u = hs + 1 < n_hs ? rows21 * n_groups : 0;
         const LdsSweep sw_next = sweep_of(hs + 1);
-        // where the neighbours published the ghost words this half-sweep
-        // reads: their boundary words of colour 1 - c, half-sweep hs - 1
-        const uint64_t* __restrict__ gl = a.exch + (size_t)tp.left * tw + (size_t)(1 - c) * 2 * N + N;  // its right side
-        const uint64_t* __restrict__ gr = a.exch + (size_t)tp.right * tw + (size_t)(1 - c) * 2 * N;      // its left side
+        // where the neighbours publish the ghost words of a boundary item
+        // that follows a half-sweep of colour cc: the left one's right side,
+        // the right one's left side
+        auto ghost_at = [&](const WordItem& it, int cc) -> const uint64_t* {
+            return it.side == 0 ? a.exch + (size_t)tp.left * tw + (size_t)cc * 2 * N + N + it.I
+                                : a.exch + (size_t)tp.right * tw + (size_t)cc * 2 * N + it.I;
+        };
         uint64_t* __restrict__ ex = a.exch + (size_t)blockIdx.x * tw + (size_t)c * 2 * N;
+        const uint64_t want = step_tag | launch_tag;
+        step_tag = spread_next<kStepBits>(step_tag);
+        const uint64_t tag = step_tag | launch_tag;
         uint32_t anti = 0, ups = 0;
+        bool fetch0 = false;
         // one word item: its neighbourhood from LDS (the ghost word of a
         // boundary item straight from the neighbour's publication after the
         // launch's first half-sweep) and the word `early` gives, then
-        // `between` (while the loads are in flight), the update (by `update`,
-        // from the neighbourhood, the position-20 uniform and that word),
-        // and the publication of a boundary word; the
-        // last of the N boundary words raises the flag (every publisher waits
-        // for its own store first, and the exchange words and flags are
-        // device-coherent atomics, so no cache writeback or invalidation is
-        // needed).  The loads of an item that does not exist (valid false)
-        // read LDS at the item's default address 0 and are not used.
-        auto word = [&](const WordItem& it, bool valid, auto early, auto between, auto update) {
+        // `between` (while the loads are in flight; after the update in a
+        // wavefront with boundary words, whose readers wait for it), the
+        // update (by `update`, from the neighbourhood, the position-20
+        // uniform and that word), and the publication of a boundary word.
+        // valid: whether the thread has this item.
+        auto poll = [&](const WordItem& it) {
+            const uint64_t* p = ghost_at(it, 1 - c);
+            return ghost(p, fetch(p), want);
+        };
+        auto word = [&](const WordItem& it, bool valid, bool edge, auto ghost_of, auto early, auto between, auto update) {
             Nbhd nb;
             nb.w = lds_load64(it.w);
-            nb.lf = lds_load64(it.lf);
-            nb.rt = lds_load64(it.rt);
+            nb.lf = lds_load64(WHOLE ? it.lf : it.w - 8u);
+            nb.rt = lds_load64(WHOLE ? it.rt : it.w + 8u);
             nb.up = lds_load64(it.up);
             nb.dn = lds_load64(it.dn);
             nb.patch = lds_load64(it.patch);
             const uint32_t u20 = lds_load32(u5cur_addr + it.u20);
             const uint64_t e = early(it);
-            if (!valid) return;
-            if (it.side >= 0 && hs > 0) {
-                if (it.side == 0) nb.lf = __hip_atomic_load(&gl[it.I], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                else nb.rt = __hip_atomic_load(&gr[it.I], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (edge && valid) {
+                if (it.side >= 0 && hs > 0) {
+                    const uint64_t g = ghost_of(it);
+                    nb.lf = it.side == 0 ? g : nb.lf;
+                    nb.rt = it.side == 0 ? nb.rt : g;
+                }
+                const uint64_t nw = update(it, nb, u20, e);
+                if (it.side >= 0)
+                    __hip_atomic_store(&ex[it.side * N + it.I], nw | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                lds_store64(it.w, nw);
             }
             between();
-            const uint64_t nw = update(it, nb, u20, e);
-            lds_store64(it.w, nw);
-            if (it.side >= 0) {
-                __hip_atomic_store(&ex[it.side * N + it.I], nw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __builtin_amdgcn_s_waitcnt(0);
-                if (atomicAdd(&published, 1u) == (uint32_t)(hs + 1) * (uint32_t)N - 1u)
-                    __hip_atomic_store(&a.flags[blockIdx.x], 2 * t0 + (uint64_t)hs + 1, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (!edge && valid) lds_store64(it.w, update(it, nb, u20, e));
         };
         if (pre) {
             // the words from the code table of this half-sweep; meanwhile the
@@ -335,12 +411,19 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
             const uint32_t ccur = ctab + (uint32_t)(hs & 1) * 8u * (uint32_t)n_w;
             const uint32_t cnext = ctab + (uint32_t)((hs + 1) & 1) * 8u * (uint32_t)n_w;
             const bool draw = hs + 1 < n_hs;
-            auto codes = [&](const WordItem& it) { return lds_load64(ccur + it.code); };
+            auto codes = [&](int f) { return [=](const WordItem&) { return lds_load64(ccur + 8u * (uint32_t)f); }; };
             auto from_table = [&](const WordItem& it, const Nbhd& nb, uint32_t u20, uint64_t cd) {
                 return lds_word_apply(sw, nb, it.I, cd, u20, meas, true, anti, ups);
             };
-            word(cur0, tid < n_w, codes, [&] { if (draw) draw_codes(oth0, sw_next, cnext); }, from_table);
-            word(cur1, tid + B < n_w, codes, [&] { if (draw) draw_codes(oth1, sw_next, cnext); }, from_table);
+            word(cur0, tid < n_w, edge0, [&](const WordItem&) { return ghost0; }, codes(min(tid, n_w - 1)),
+                 [&] { if (draw && f0 < n_w) draw_codes(d0, f0, sw_next, cnext); }, from_table);
+            // the ghost word of the next half-sweep's first item, on its way
+            // while the second item and the position-20 blocks are worked on
+            fetch0 = draw && edge0 && oth0.side >= 0;
+            if (fetch0) ghost0 = fetch(ghost_at(oth0, c));
+            if (!split)
+                word(cur1, f1 < n_w, edge1, poll, codes(min(f1, n_w - 1)),
+                     [&] { if (draw && f1 < n_w) draw_codes(d1, f1, sw_next, cnext); }, from_table);
         } else {
             // the words f = tid, tid + B, ..., each drawing its own codes:
             // the sweep index made opaque to the compiler, so that the
@@ -354,7 +437,7 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
                 return lds_word_update_c1(swi, rk, nb, it.I, it.c1, u20, meas, true, anti, ups);
             };
             auto none = [](const WordItem&) { return 0ull; };
-            for (int fw = tid; fw < n_w; fw += B) word(make_item(fw, c), true, none, [] {}, drawing);
+            for (int fw = tid; fw < n_w; fw += B) word(make_item(fw, c), true, true, poll, none, [] {}, drawing);
         }
         // then the next half-sweep's position-20 blocks, in a loop of their
         // own so that it keeps only its own wave-uniform values live
@@ -365,6 +448,7 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
                 u5next[(size_t)k * N + I] = block5(sw_next, rk, I, g_lo + k, c ^ 1);
             }
         }
+        if (fetch0) ghost0 = ghost(ghost_at(oth0, c), ghost0, tag);
         if (meas) {
             if (pre) {
                 // at most two words per thread: a wavefront's antiparallel
@@ -381,27 +465,6 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
                 red[2 * (tid >> 6)] = anti;
                 red[2 * (tid >> 6) + 1] = ups;
             }
-        }
-        // before the next half-sweep reads them: both neighbours' boundary
-        // words of this half-sweep must be published
-        if (!whole && tid == 0 && hs + 1 < n_hs) {
-            const uint64_t want = 2 * t0 + (uint64_t)hs + 1;
-            const uint64_t start = clock_ticks();
-            bool ok = true;
-            // bounded twice: by the clock and by the number of polls (each
-            // poll is two loads from memory and a short sleep)
-            for (uint32_t polls = 0; ok; ++polls) {
-                const uint64_t fl = __hip_atomic_load(&a.flags[tp.left], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint64_t fr = __hip_atomic_load(&a.flags[tp.right], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (fl >= want && fr >= want) break;
-                if (__hip_atomic_load(a.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
-                    clock_ticks() - start > a.wait_ticks || polls > kMaxPolls) {
-                    __hip_atomic_store(a.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    ok = false;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-            if (!ok) stop = 1;
         }
         __syncthreads();
         if (meas && tid >= B - 64) {
@@ -422,15 +485,16 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
         // two half-sweeps per trip, so that the items of each colour stay in
         // the same registers (no exchange of the two sets between half-sweeps)
         for (int hs = 0; hs < n_hs; hs += 2) {
-            if (half_sweep(hs, cur0, cur1, oth0, oth1)) break;
-            if (half_sweep(hs + 1, oth0, oth1, cur0, cur1)) break;
+            if (half_sweep(hs, cur0, cur1, oth0, doth0, doth1)) break;
+            if (half_sweep(hs + 1, oth0, oth1, cur0, dcur0, dcur1)) break;
         }
     } else {
         for (int hs = 0; hs < n_hs; ++hs)
-            if (half_sweep(hs, cur0, cur1, oth0, oth1)) break;
+            if (half_sweep(hs, cur0, cur1, oth0, doth0, doth1)) break;
     }
     // the ghost columns in LDS are stale past the first half-sweep, but the
     // band's own words are exact
+    if (tid == 0) a.flags[blockIdx.x] = spread_next<kLaunchBits>(launch_tag);  // also when abandoned
 
     // store the band (the ghost columns belong to the neighbours)
     {
@@ -442,6 +506,27 @@ __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
             const int x = xi0 + xi;
             G[(size_t)((uint32_t)I * (uint32_t)L + (uint32_t)col(x))] = T[I * width + x];
         }
+    }
+}
+
+}  // namespace
+
+__global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
+    extern __shared__ uint64_t lds[];
+    __shared__ uint32_t red[2 * (kPersistMaxBlock / 64)];
+    __shared__ int stop;
+    const PersistTile tp = a.tiles[blockIdx.x];
+    const LatticeDesc& d = a.descs[tp.lattice];
+    const int n_w = tile_items(d.L, d.N, tp.w), B = blockDim.x;
+    const int items = n_w <= B ? kOne : n_w <= 2 * B ? kTwo : kFormed;
+    if (tp.w >= d.L) {
+        if (items == kOne) persist_tile<kOne, true>(a, tp, lds, red, stop);
+        else if (items == kTwo) persist_tile<kTwo, true>(a, tp, lds, red, stop);
+        else persist_tile<kFormed, true>(a, tp, lds, red, stop);
+    } else {
+        if (items == kOne) persist_tile<kOne, false>(a, tp, lds, red, stop);
+        else if (items == kTwo) persist_tile<kTwo, false>(a, tp, lds, red, stop);
+        else persist_tile<kFormed, false>(a, tp, lds, red, stop);
     }
 }
 

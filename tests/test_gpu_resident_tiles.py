@@ -300,3 +300,32 @@ def test_resident_tiles_expired_wait_is_reported_and_recoverable():
     Es, Ms = oracle.sweep(s, seed, 0, 20, T, every=10)
     assert got_E == Es.tolist() and got_M == Ms.tolist()
     assert (got == s).all()
+
+
+@pytest.mark.parametrize("L,cols,block,max_sweeps", [
+    (84, 14, 128, 1),    # one sweep per launch: every launch reuses both halves of the exchange buffer once
+    (64, 32, 64, 1),     # two bands, each the other's left and right neighbour
+    (84, 2, 64, 2),      # two-column bands: every word is a boundary word
+    (2016, 2, 64, 3),    # more boundary words than threads: second items poll for their ghost words themselves
+    (1008, 8, 192, 3),   # as many words of a colour as threads
+    (1008, 8, 256, 3),   # wavefronts that draw codes and have no words
+])
+def test_resident_tiles_exchange_over_many_launches(L, cols, block, max_sweeps):
+    """Short launches one after another, so that words published by earlier
+    launches are still in the exchange buffer when later ones wait, and
+    the thread shapes at the edges of the item rules; series and state equal
+    the oracle's."""
+    T, seed = 2.269, 17
+    lat = ising.Lattice(L, seed, hot=True)
+    try:
+        lat.set_resident_tiles(cols, block, max_sweeps)
+        E, M = lat.sweep_measure(T, 24, 1)
+        lat.sweep(T, 1)
+        got, gE, gM = lat.spins(), E.cpu().numpy().tolist(), M.cpu().numpy().tolist()
+    finally:
+        lat.close()
+    s = oracle.init(L, seed, True)
+    Es, Ms = oracle.sweep(s, seed, 0, 24, T, every=1)
+    oracle.sweep(s, seed, 24, 1, T)
+    assert gE == Es.tolist() and gM == Ms.tolist()
+    assert (got == s).all()
