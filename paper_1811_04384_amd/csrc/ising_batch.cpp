@@ -55,7 +55,6 @@ struct ising_batch {
     // derived from the plan
     std::vector<int32_t> resident;  // 0 half-sweep launches, 1 resident in LDS, 2 resident in global memory, 3 tiles,
                                     // 4 resident tiles, 5 codes drawn chip-wide
-    std::vector<int64_t> units;
     std::vector<int32_t> part_begin, part_count;
     WaveItem* d_waves = nullptr;
     int64_t n_waves = 0;
@@ -66,7 +65,6 @@ struct ising_batch {
     int32_t* d_ids_glb = nullptr;
     int32_t n_glb = 0;
     int32_t n_tiled = 0;  // lattices advanced by half-sweep launches
-    bool off32 = true;  // every such lattice < 4 GiB
     // multi-sweep tiles
     TileWork* d_tiles = nullptr;
     int32_t n_tiles = 0;
@@ -213,13 +211,11 @@ int upload_descs(ising_batch* b, const double* T, int64_t* dev_E, int64_t* dev_M
         d.k1 = (uint32_t)(b->seed[i] >> 32);
         if (T) thresholds_of(T[i], &d.t4, &d.t8);
         else d.t4 = d.t8 = 0;
-        d.units = b->units.empty() ? 0 : b->units[i];
-        d.segs = segments_per_row(g.L, b->plan.words_per_thread);
+        d.pstar = (g.L - 1) / g.N;
         d.resident = b->resident.empty() ? 0 : (b->resident[i] != 0);
         d.part_begin = b->part_begin.empty() ? 0 : b->part_begin[i];
         d.part_count = b->part_count.empty() ? 0 : b->part_count[i];
         d.sweep_limit = 0x7FFFFFFF;
-        d.pad_ = 0;
         d.series_E = dev_E ? dev_E + (int64_t)i * samples_per_lattice : nullptr;
         d.series_M = dev_M ? dev_M + (int64_t)i * samples_per_lattice : nullptr;
     }
@@ -265,13 +261,11 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
     std::vector<TileWork> tiles;
     int64_t halo_stride = 0;
     b->resident.assign(b->n, 0);
-    b->units.assign(b->n, 0);
     b->part_begin.assign(b->n, 0);
     b->part_count.assign(b->n, 0);
     std::vector<int32_t> ids_lds, ids_glb, ids_draw;
     std::vector<WaveItem> waves;
     size_t max_lds = 0;
-    b->off32 = true;
     for (int32_t i = 0; i < b->n; ++i) {
         const Geometry& g = b->geo[i];
         if (g.L <= p.resident_max_L) {
@@ -326,13 +320,9 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
             if (!seen) b->tile_shapes.push_back({g, tw});
             continue;
         }
-        const int64_t u = units_per_colour(g, p.words_per_thread);
-        b->units[i] = u;
-        b->off32 = b->off32 && fits_off32(g);
         b->part_begin[i] = (int32_t)waves.size();
-        const int32_t segs = segments_per_row(g.L, p.words_per_thread);
         for (int32_t I = 0; I < g.N; ++I)
-            for (int32_t s0 = 0; s0 < segs; s0 += 64) waves.push_back({i, I, s0});
+            for (int32_t w0 = 0; w0 < g.L / 2; w0 += 64 * p.words_per_thread) waves.push_back({i, I, w0});
         b->part_count[i] = (int32_t)waves.size() - b->part_begin[i];
     }
     b->n_waves = (int64_t)waves.size();
@@ -509,11 +499,10 @@ int enqueue_chunk(ising_batch* b, int32_t k, int32_t every, hipStream_t s0, hipS
         for (int32_t s = 0; s < k; ++s) {
             ISING_HIP(launch_halfsweep_multi(p.words_per_thread, p.tiled_block, b->d_desc, b->d_state, b->d_waves,
                                              b->n_waves, 0, (uint32_t)s, nullptr,
-                                             measured(s - 1) ? b->d_partials : nullptr, (uint32_t)(s - 1), b->off32,
-                                             s0));
+                                             measured(s - 1) ? b->d_partials : nullptr, (uint32_t)(s - 1), s0));
             ISING_HIP(launch_halfsweep_multi(p.words_per_thread, p.tiled_block, b->d_desc, b->d_state, b->d_waves,
                                              b->n_waves, 1, (uint32_t)s, measured(s) ? b->d_partials : nullptr,
-                                             nullptr, 0, b->off32, s0));
+                                             nullptr, 0, s0));
         }
     }
     if (fork) {

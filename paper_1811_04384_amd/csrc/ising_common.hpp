@@ -31,6 +31,7 @@ inline Geometry make_geometry(int32_t L) {
 // Everything a half-sweep of one lattice needs; wave-uniform.
 struct SweepArgs {
     int32_t L, N, istar, sh_star;
+    int32_t pstar;        // (L-1) div N: word rows up to istar have pstar + 1 live positions, the others pstar
     uint32_t t_lo, t_hi;  // absolute sweep index
     uint32_t k0, k1;      // Philox key = seed
     uint32_t t4, t8;      // acceptance thresholds
@@ -56,13 +57,11 @@ struct LatticeDesc {
     int32_t L, N, istar, sh_star;
     uint32_t k0, k1;          // seed
     uint32_t t4, t8;          // thresholds of the current call
-    int64_t units;            // tiled work units (row segments) of one colour
-    int32_t segs;             // segments per row for the current tiled plan
+    int32_t pstar;            // (L-1) div N
     int32_t resident;         // 1: advanced by the resident kernel
     int32_t part_begin;       // first partial-sum slot of this lattice
     int32_t part_count;       // number of partial-sum slots
     int32_t sweep_limit;      // sweeps of the current chunk this lattice takes part in
-    int32_t pad_;
     int64_t* series_E;        // per-call sample outputs (may be null)
     int64_t* series_M;
 };
@@ -87,13 +86,13 @@ struct LatticeState {
     int64_t last_E, last_M;   // most recent sample or observation
 };
 
-// One wavefront of a tiled half-sweep launch: 64 consecutive row segments
-// of one word row of one lattice (segments beyond the row's `segs` idle), so
-// the lattice and the row are wave-uniform.
+// One wavefront of a tiled half-sweep launch: up to 64 words_per_thread
+// consecutive words of a colour of one word row of one lattice, so the
+// lattice and the row are wave-uniform.
 struct WaveItem {
     int32_t lattice;
-    int32_t row;   // word row I
-    int32_t seg0;  // segment handled by lane 0
+    int32_t row;  // word row I
+    int32_t w0;   // first word of the colour
 };
 
 // Partial sums of one wavefront (or tile): antiparallel bonds and up spins.

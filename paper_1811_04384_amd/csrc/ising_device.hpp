@@ -174,71 +174,139 @@ __device__ __forceinline__ uint64_t down_word(const Load& ld, int I, int J, int 
     return d;
 }
 
-// Acceptance code of one position: the number of thresholds above its
-// uniform, (u < t4) + (u < t8) in {0, 1, 2} (t8 <= t4, so u < t8 implies
-// u < t4).  A move with dE = +4 is accepted iff the code is >= 1, one with
-// dE = +8 iff it is 2 (Section 2, step 3 with the energies of Table 1).
-__device__ __forceinline__ uint32_t accept_code(uint32_t u, uint32_t t4, uint32_t t8) {
-    const uint32_t x = (u < t4) ? 1u : 0u;
-    return (u < t8) ? 2u : x;
+// Acceptance of one position: two bits, A = [u < t4] (a move with dE = +4 is
+// accepted) and B = [u < t8] (one with dE = +8 is; t8 <= t4, so B implies A)
+// (Section 2, step 3 with the energies of Table 1).  In mixed code every
+// vector instruction of gfx950 costs a wavefront about four cycles, so what
+// counts is their number.  Four per position: compare into the execution
+// mask, or a constant bit into the accumulator in the lanes that are left,
+// the same for t8 (whose lanes are among t4's), and the scalar unit puts the
+// mask back.  (Compares into lane masks, selects and a shift-or take five, and
+// the accumulators have to be shifted together afterwards.)  The execution
+// mask is the caller's again at the end of each block, and nothing else than
+// these vector instructions runs under the narrowed one.
+template <uint32_t KA, uint32_t KB>
+__device__ __forceinline__ void accept_bits(uint32_t& a, uint32_t& b, uint32_t u, uint32_t t4, uint32_t t8) {
+    uint64_t full;
+    asm("s_mov_b64 %[full], exec\n\t"
+        "v_cmpx_gt_u32_e32 %[t4], %[u]\n\t"
+        "v_or_b32_e32 %[a], %[ka], %[a]\n\t"
+        "v_cmpx_gt_u32_e32 %[t8], %[u]\n\t"
+        "v_or_b32_e32 %[b], %[kb], %[b]\n\t"
+        "s_mov_b64 exec, %[full]"
+        : [a] "+v"(a), [b] "+v"(b), [full] "=&s"(full)
+        : [u] "v"(u), [t4] "s"(t4), [t8] "s"(t8), [ka] "i"(KA), [kb] "i"(KB)
+        : "vcc");
 }
 
-// The 21 per-position acceptance codes of one word packed in word layout
-// (code of position p in field 20 - p).  They are appended in position order
-// with acc = (acc << 3) | code, so every code is a small inline constant.
-struct Codes {
-    uint32_t hi;  // positions 0..9  = fields 20..11 -> word bits 33..62 (bits 0..29 here)
-    uint32_t mid; // position 10     = field 10     -> word bits 30..31
-    uint32_t lo;  // positions 11..20 = fields 9..0  -> word bits 0..29
+// The same with both bits in one accumulator.
+template <uint32_t KA, uint32_t KB>
+__device__ __forceinline__ void accept_bits(uint32_t& c, uint32_t u, uint32_t t4, uint32_t t8) {
+    uint64_t full;
+    asm("s_mov_b64 %[full], exec\n\t"
+        "v_cmpx_gt_u32_e32 %[t4], %[u]\n\t"
+        "v_or_b32_e32 %[c], %[ka], %[c]\n\t"
+        "v_cmpx_gt_u32_e32 %[t8], %[u]\n\t"
+        "v_or_b32_e32 %[c], %[kb], %[c]\n\t"
+        "s_mov_b64 exec, %[full]"
+        : [c] "+v"(c), [full] "=&s"(full)
+        : [u] "v"(u), [t4] "s"(t4), [t8] "s"(t8), [ka] "i"(KA), [kb] "i"(KB)
+        : "vcc");
+}
+
+// The acceptance bits of a word in word layout (position p in field 20 - p):
+// A and B in words of their own, for a word that is updated at once ...
+struct AcceptPair {
+    uint32_t a_lo = 0, a_hi = 0, b_lo = 0, b_hi = 0;
+    template <int P>
+    __device__ __forceinline__ void add(uint32_t u, uint32_t t4, uint32_t t8) {
+        constexpr int bit = 3 * (20 - P);
+        constexpr uint32_t k = 1u << (bit & 31);
+        if (bit < 32) accept_bits<k, k>(a_lo, b_lo, u, t4, t8);
+        else accept_bits<k, k>(a_hi, b_hi, u, t4, t8);
+    }
+    template <int G>
+    __device__ __forceinline__ void skip() {}
+    __device__ __forceinline__ uint64_t a() const { return ((uint64_t)a_hi << 32) | a_lo; }
+    __device__ __forceinline__ uint64_t b() const { return ((uint64_t)b_hi << 32) | b_lo; }
 };
 
-__device__ __forceinline__ void append_code(Codes& c, int p, uint32_t code) {
-    if (p < 10) c.hi = (c.hi << 3) | code;
-    else if (p == 10) c.mid = code;
-    else c.lo = (c.lo << 3) | code;
+// ... or in one word (A in the lowest bit of the field, B in the middle one),
+// for codes that are kept until the word is updated.
+struct AcceptWord {
+    uint32_t lo = 0, hi = 0;
+    template <int P>
+    __device__ __forceinline__ void add(uint32_t u, uint32_t t4, uint32_t t8) {
+        constexpr int bit = 3 * (20 - P);
+        constexpr uint32_t k = 1u << (bit & 31);
+        if (bit < 32) accept_bits<k, 2 * k>(lo, u, t4, t8);
+        else accept_bits<k, 2 * k>(hi, u, t4, t8);
+    }
+    template <int G>
+    __device__ __forceinline__ void skip() {}
+    __device__ __forceinline__ uint64_t word() const { return ((uint64_t)hi << 32) | lo; }
+};
+
+// The same word for wavefronts that have few others beside them on their SIMD
+// (the LDS forms, whose half-sweep waits for its slowest wavefront): compares
+// into lane masks, selects and a shift-or, one instruction more per position
+// but no wait for the execution mask between them (L = 64 in one workgroup of
+// two wavefronts 1.18 us per half-sweep, 1.42 with the form above; L = 4096 in
+// resident tiles 3.79 / 3.83).  Positions are added in order.  The s_nop gives
+// the lane masks the wait states that a vector instruction's read of a
+// vector-written scalar register needs.
+struct AcceptSelect {
+    uint32_t hi = 0, mid = 0, lo = 0;  // positions 0..9, 10, 11..20
+    template <int P>
+    __device__ __forceinline__ void add(uint32_t u, uint32_t t4, uint32_t t8) {
+        uint32_t x;
+        uint64_t m4, m8;
+        asm("v_cmp_gt_u32_e64 %[m4], %[t4], %[u]\n\t"
+            "v_cmp_gt_u32_e64 %[m8], %[t8], %[u]\n\t"
+            "s_nop 1\n\t"
+            "v_cndmask_b32_e64 %[x], 0, 1, %[m4]\n\t"
+            "v_cndmask_b32_e64 %[x], %[x], 3, %[m8]"
+            : [x] "=&v"(x), [m4] "=&s"(m4), [m8] "=&s"(m8)
+            : [u] "v"(u), [t4] "s"(t4), [t8] "s"(t8));
+        if (P == 0) hi = x;
+        else if (P < 10) asm("v_lshl_or_b32 %0, %0, 3, %1" : "+v"(hi) : "v"(x));
+        else if (P == 10) mid = x;
+        else if (P == 11) lo = x;
+        else asm("v_lshl_or_b32 %0, %0, 3, %1" : "+v"(lo) : "v"(x));
+    }
+    template <int G>
+    __device__ __forceinline__ void skip() {
+        if (G < 2) hi <<= 12;
+        else if (G == 2) hi <<= 6;
+        else lo <<= 12;
+    }
+    __device__ __forceinline__ uint64_t word() const {
+        return ((uint64_t)((hi << 1) | (mid >> 2)) << 32) | (mid << 30) | lo;
+    }
+};
+
+// The four positions of Philox block G.
+template <int G, class Accept>
+__device__ __forceinline__ void accept_block(Accept& c, const U4& r, uint32_t t4, uint32_t t8) {
+    c.template add<4 * G + 0>(r.x, t4, t8);
+    c.template add<4 * G + 1>(r.y, t4, t8);
+    c.template add<4 * G + 2>(r.z, t4, t8);
+    c.template add<4 * G + 3>(r.w, t4, t8);
 }
 
-// acc = (acc << 3) | accept_code(u), as five VALU instructions: two compares
-// into lane masks, two selects of inline constants, one shift-or.  Written
-// out because the compiler otherwise folds the shift into selects of
-// pre-shifted literals, which need extra moves on this target.  The s_nop
-// gives the lane masks the wait states a VALU read of a VALU-written SGPR
-// needs.  ALU instructions only (no memory access).
-__device__ __forceinline__ uint32_t append_accept(uint32_t acc, uint32_t u, uint32_t t4, uint32_t t8) {
-    uint32_t x;
-    uint64_t m4, m8;
-    asm("v_cmp_gt_u32_e64 %[m4], %[t4], %[u]\n\t"
-        "v_cmp_gt_u32_e64 %[m8], %[t8], %[u]\n\t"
-        "s_nop 1\n\t"
-        "v_cndmask_b32_e64 %[x], 0, 1, %[m4]\n\t"
-        "v_cndmask_b32_e64 %[x], %[x], 2, %[m8]\n\t"
-        "v_lshl_or_b32 %[acc], %[acc], 3, %[x]"
-        : [acc] "+v"(acc), [x] "=&v"(x), [m4] "=&s"(m4), [m8] "=&s"(m8)
-        : [u] "v"(u), [t4] "s"(t4), [t8] "s"(t8));
-    return acc;
-}
-
-// accept_code(u) as four VALU instructions (the first code of an
-// accumulator needs no shift-or).
-__device__ __forceinline__ uint32_t first_accept(uint32_t u, uint32_t t4, uint32_t t8) {
-    uint32_t x;
-    uint64_t m4, m8;
-    asm("v_cmp_gt_u32_e64 %[m4], %[t4], %[u]\n\t"
-        "v_cmp_gt_u32_e64 %[m8], %[t8], %[u]\n\t"
-        "s_nop 1\n\t"
-        "v_cndmask_b32_e64 %[x], 0, 1, %[m4]\n\t"
-        "v_cndmask_b32_e64 %[x], %[x], 2, %[m8]"
-        : [x] "=&v"(x), [m4] "=&s"(m4), [m8] "=&s"(m8)
-        : [u] "v"(u), [t4] "s"(t4), [t8] "s"(t8));
-    return x;
-}
-
-__device__ __forceinline__ void append_draw(Codes& c, int p, uint32_t u, uint32_t t4, uint32_t t8) {
-    if (p == 0) c.hi = first_accept(u, t4, t8);
-    else if (p < 10) c.hi = append_accept(c.hi, u, t4, t8);
-    else if (p == 10) c.mid = first_accept(u, t4, t8);
-    else if (p == 11) c.lo = first_accept(u, t4, t8);
-    else c.lo = append_accept(c.lo, u, t4, t8);
+// Positions 0..19 of a word: block(g) draws block g; blocks past the last
+// live position (n_live positions) are not drawn, their slots are dead.
+template <class Accept, class Block>
+__device__ __forceinline__ void accept_word(Accept& c, const Block& block, int n_live, uint32_t t4, uint32_t t8) {
+    accept_block<0>(c, block(0), t4, t8);
+    if (4 < n_live) accept_block<1>(c, block(1), t4, t8);
+    else c.template skip<1>();
+    if (8 < n_live) accept_block<2>(c, block(2), t4, t8);
+    else c.template skip<2>();
+    if (12 < n_live) accept_block<3>(c, block(3), t4, t8);
+    else c.template skip<3>();
+    if (16 < n_live) accept_block<4>(c, block(4), t4, t8);
+    else c.template skip<4>();
 }
 
 // Three-input bitwise operation with truth table TT (operand bits x, y, z
@@ -249,38 +317,38 @@ __device__ __forceinline__ uint32_t lop3(uint32_t x, uint32_t y, uint32_t z) {
 }
 
 // One 32-bit half of the flip mask.  A spin flips iff n >= 2 antiparallel
-// neighbours (dE <= 0), or n = 1 and code >= 1 (dE = +4), or n = 0 and
-// code = 2 (dE = +8) (Table 1 and the Metropolis rule of Section 2).  With
-// t = [differs from up or down], p = [differs from both] and t', p' the
-// same for left and right: n >= 1 is t | t', n >= 2 is p | p' | (t & t').
-// With code bits c0 = [code = 1], c1 = [code = 2]:
-// flip = c1 | ((c0 | c1) & n>=1) | n>=2.
+// neighbours (dE <= 0), or n = 1 and A (dE = +4), or n = 0 and B (dE = +8)
+// (Table 1 and the Metropolis rule of Section 2).  With t = [differs from up
+// or down], p = [differs from both] and t', p' the same for left and right:
+// n >= 1 is t | t', n >= 2 is p | p' | (t & t').  As B implies A,
+// flip = B | (A & n>=1) | n>=2.
 __device__ __forceinline__ uint32_t flip_half(uint32_t w, uint32_t up, uint32_t dn, uint32_t lf, uint32_t rt,
-                                              uint32_t c0, uint32_t c1, uint32_t live) {
+                                              uint32_t a, uint32_t b, uint32_t live) {
     const uint32_t t1 = lop3<0x7E>(w, up, dn);  // (w ^ up) | (w ^ dn)
     const uint32_t p1 = lop3<0x18>(w, up, dn);  // (w ^ up) & (w ^ dn)
     const uint32_t t2 = lop3<0x7E>(w, lf, rt);
     const uint32_t p2 = lop3<0x18>(w, lf, rt);
-    const uint32_t ge1 = t1 | t2;
-    const uint32_t ge2 = lop3<0xFE>(p1, p2, t1 & t2);  // or of the three
-    const uint32_t x = lop3<0xA8>(c0, c1, ge1);         // (c0 | c1) & ge1
-    return lop3<0xFE>(c1, x, ge2) & live;
+    const uint32_t x = lop3<0xF8>(p1, t1, t2);  // p1 | (t1 & t2)
+    const uint32_t y = lop3<0xE0>(a, t1, t2);   // a & (t1 | t2)
+    const uint32_t z = lop3<0xFE>(y, b, p2);
+    return lop3<0xA8>(x, z, live);              // (x | z) & live
 }
 
-// Flip mask of a word (only bit 3k of each field is meaningful).
+// Flip mask of a word (only bit 3k of each field is meaningful): A and B
+// apart, or in one word of codes.
 __device__ __forceinline__ uint64_t flip_mask(uint64_t w, uint64_t up, uint64_t dn, uint64_t lf, uint64_t rt,
-                                              uint64_t codes, uint64_t live) {
-    const uint64_t c1 = codes >> 1;
-    const uint32_t lo = flip_half((uint32_t)w, (uint32_t)up, (uint32_t)dn, (uint32_t)lf, (uint32_t)rt, (uint32_t)codes,
-                                  (uint32_t)c1, (uint32_t)live);
+                                              uint64_t a, uint64_t b, uint64_t live) {
+    const uint32_t lo = flip_half((uint32_t)w, (uint32_t)up, (uint32_t)dn, (uint32_t)lf, (uint32_t)rt, (uint32_t)a,
+                                  (uint32_t)b, (uint32_t)live);
     const uint32_t hi = flip_half((uint32_t)(w >> 32), (uint32_t)(up >> 32), (uint32_t)(dn >> 32), (uint32_t)(lf >> 32),
-                                  (uint32_t)(rt >> 32), (uint32_t)(codes >> 32), (uint32_t)(c1 >> 32),
+                                  (uint32_t)(rt >> 32), (uint32_t)(a >> 32), (uint32_t)(b >> 32),
                                   (uint32_t)(live >> 32));
     return ((uint64_t)hi << 32) | lo;
 }
 
-__device__ __forceinline__ uint64_t assemble_codes(const Codes& c) {
-    return ((uint64_t)c.hi << 33) | ((uint64_t)c.mid << 30) | (uint64_t)c.lo;
+__device__ __forceinline__ uint64_t flip_mask(uint64_t w, uint64_t up, uint64_t dn, uint64_t lf, uint64_t rt,
+                                              uint64_t codes, uint64_t live) {
+    return flip_mask(w, up, dn, lf, rt, codes, codes >> 1, live);
 }
 
 // Antiparallel bonds (4 per live spin) of an updated colour-1 word and the up
@@ -291,6 +359,17 @@ __device__ __forceinline__ void measure_word(uint64_t w, uint64_t up, uint64_t d
     anti += __popcll((w ^ up) & live) + __popcll((w ^ dn) & live) + __popcll((w ^ lf) & live) +
             __popcll((w ^ rt) & live);
     ups += __popcll(w & live) + __popcll(lf & live);
+}
+
+// The sums of measure_word with fewer counts: live has only the spin bit 3k
+// of each field, so the masked bond words for up and down shifted by one
+// and two bits fill the two free bits of every field, and one count covers
+// three of them (likewise for the two up-spin counts).
+__device__ __forceinline__ void measure_word_packed(uint64_t w, uint64_t up, uint64_t dn, uint64_t lf, uint64_t rt,
+                                                    uint64_t live, uint32_t& anti, uint32_t& ups) {
+    const uint64_t b3 = ((w ^ lf) & live) | (((w ^ up) & live) << 1) | (((w ^ dn) & live) << 2);
+    anti += __popcll(b3) + __popcll((w ^ rt) & live);
+    ups += __popcll((w & live) | ((lf & live) << 1));
 }
 
 // Sums over the 64 lanes of a wavefront, returned to every lane; every lane
@@ -405,27 +484,19 @@ __device__ __forceinline__ void update_segment(const Load& ld, const Store& st, 
         const int J = J0 + 2 * k;
         if (J >= L) break;
 
-        Codes codes = {0u, 0u, 0u};
-#pragma unroll
-        for (int g = 0; g < 5; ++g) {
-            if (4 * g < n_live) {
-                const U4 r =
-                    philox_lane_c1(a.t_lo, row_base + (uint32_t)J, a.t_hi, (uint32_t)g | (1u << 3), a.k0, a.k1, rk);
-                append_draw(codes, 4 * g + 0, r.x, a.t4, a.t8);
-                append_draw(codes, 4 * g + 1, r.y, a.t4, a.t8);
-                append_draw(codes, 4 * g + 2, r.z, a.t4, a.t8);
-                append_draw(codes, 4 * g + 3, r.w, a.t4, a.t8);
-            } else {  // positions past the last live one are dead slots: code 0
-#pragma unroll
-                for (int j = 0; j < 4; ++j) append_code(codes, 4 * g + j, 0u);
-            }
-        }
-        append_draw(codes, 20, u5[k], a.t4, a.t8);  // dead slot when n_live < 21
+        AcceptPair acc;
+        accept_word(
+            acc,
+            [&](int g) {
+                return philox_lane_c1(a.t_lo, row_base + (uint32_t)J, a.t_hi, (uint32_t)g | (1u << 3), a.k0, a.k1, rk);
+            },
+            n_live, a.t4, a.t8);
+        acc.add<20>(u5[k], a.t4, a.t8);  // dead slot when n_live < 21
 
         const uint64_t w = nb[k].w, lf = nb[k].lf, rt = nb[k].rt;
         const uint64_t up = WPT == 1 ? nb[k].up : fix_up(nb[k], I, a.sh_star);
         const uint64_t dn = WPT == 1 ? nb[k].dn : fix_down(nb[k], I, N, a.istar, a.sh_star);
-        const uint64_t f = flip_mask(w, up, dn, lf, rt, assemble_codes(codes), live);
+        const uint64_t f = flip_mask(w, up, dn, lf, rt, acc.a(), acc.b(), live);
         const uint64_t nw = w ^ f;
         st(I, J, nw);
         if (MEASURE) measure_word(nw, up, dn, lf, rt, live, anti, ups);

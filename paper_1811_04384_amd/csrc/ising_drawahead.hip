@@ -84,23 +84,16 @@ __global__ void __launch_bounds__(kDrawBlock) k_draw_codes(const LatticeDesc* __
     for (int m = 0; m < 4; ++m) {
         const int J = 8 * grp + par + 2 * m;
         if (J >= L) break;
-        Codes cd = {0u, 0u, 0u};
-#pragma unroll
-        for (int g = 0; g < 5; ++g) {
-            if (4 * g < n_live) {
-                const U4 q = philox_lane_c1(t_lo, (uint32_t)I * (uint32_t)L + (uint32_t)J, t_hi, (uint32_t)g | (1u << 3),
-                                            d.k0, d.k1, rk);
-                append_draw(cd, 4 * g + 0, q.x, d.t4, d.t8);
-                append_draw(cd, 4 * g + 1, q.y, d.t4, d.t8);
-                append_draw(cd, 4 * g + 2, q.z, d.t4, d.t8);
-                append_draw(cd, 4 * g + 3, q.w, d.t4, d.t8);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) append_code(cd, 4 * g + k, 0u);
-            }
-        }
-        append_draw(cd, 20, pick4(u5, (uint32_t)m), d.t4, d.t8);  // a dead slot when n_live < 21
-        out[m] = assemble_codes(cd);
+        AcceptWord acc;
+        accept_word(
+            acc,
+            [&](int g) {
+                return philox_lane_c1(t_lo, (uint32_t)I * (uint32_t)L + (uint32_t)J, t_hi, (uint32_t)g | (1u << 3), d.k0,
+                                      d.k1, rk);
+            },
+            n_live, d.t4, d.t8);
+        acc.add<20>(pick4(u5, (uint32_t)m), d.t4, d.t8);  // a dead slot when n_live < 21
+        out[m] = acc.word();
     }
 }
 

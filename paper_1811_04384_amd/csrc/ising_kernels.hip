@@ -8,6 +8,7 @@
 #include "ising_device.hpp"
 #include "ising_launch.hpp"
 #include "ising_moments.hpp"
+#include "ising_row_words.hpp"
 
 namespace ising {
 
@@ -58,50 +59,76 @@ __global__ void __launch_bounds__(256) k_init(uint64_t* __restrict__ W, Geometry
 }
 
 // ---------------------------------------------------------------------------
-// Half-sweep of one lattice held in global memory.  One thread per row
-// segment; a segment holds WPT words of the colour being updated.
+// Half-sweep of one lattice held in global memory: every wavefront updates
+// 64 WPT words of the colour of one word row.
 // ---------------------------------------------------------------------------
-// Word accessors.  With OFF32 (lattice smaller than 4 GiB) the byte offset
-// is a 32-bit value added to the wave-uniform base, which the global loads
-// take directly (scalar base + 32-bit vector offset).
-template <bool OFF32>
-struct WordPtr {
-    // global address space: word pointers read from a descriptor would
-    // otherwise be generic, and generic (flat) accesses also wait on the
-    // scalar-load counter
-    using GlobalWord = __attribute__((address_space(1))) uint64_t;
-    uint64_t* __restrict__ W;
-    uint32_t L;
-    __device__ __forceinline__ GlobalWord* at(int i, int j) const {
-        GlobalWord* g = (GlobalWord*)W;
-        if (OFF32)
-            return (GlobalWord*)((__attribute__((address_space(1))) char*)g + (((uint32_t)i * L + (uint32_t)j) << 3));
-        return g + ((size_t)i * L + (size_t)j);
+// What a half-sweep of one lattice adds to a run of words of word row I.
+template <bool MEASURE>
+struct LatticeRule {
+    const SweepArgs& a;
+    int I;
+    uint64_t live;
+    uint32_t anti = 0, ups = 0;
+    template <class Block>
+    __device__ __forceinline__ void accept(AcceptPair& acc, const Block& block) const {
+        accept_word(acc, block, 21, a.t4, a.t8);  // the bits of dead slots are masked by `live`
+    }
+    __device__ __forceinline__ void accept20(AcceptPair& acc, uint32_t u) const {
+        acc.add<20>(u, a.t4, a.t8);  // a dead slot when n_live < 21
+    }
+    __device__ __forceinline__ void vertical(uint64_t& up, uint64_t& dn, uint64_t patch) const {
+        const Nbhd nb = {0, 0, 0, up, dn, patch};
+        up = fix_up(nb, I, a.sh_star);
+        dn = fix_down(nb, I, a.N, a.istar, a.sh_star);
+    }
+    __device__ __forceinline__ void after(uint64_t nw, uint64_t up, uint64_t dn, uint64_t lf, uint64_t rt) {
+        if (MEASURE) measure_word_packed(nw, up, dn, lf, rt, live, anti, ups);
     }
 };
 
-template <int WPT, bool MEASURE, bool OFF32>
-__global__ void __launch_bounds__(kTiledMaxBlock)
-    k_halfsweep_single(uint64_t* __restrict__ W, SweepArgs a, int32_t segs, int colour,
-                       Partial* __restrict__ partials) {
-    // word row = blockIdx.y: the row, its wrap cases, live slots and
-    // counter base are wave-uniform (scalar unit); segment along x
-    const int I = (int)blockIdx.y;
-    const int seg = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    uint32_t anti = 0, ups = 0;
-    if (seg < segs) {
-        const int J0 = seg * 2 * WPT + ((I + colour) & 1);
-        const WordPtr<OFF32> p{W, (uint32_t)a.L};
-        auto ld = [&](int i, int j) { return *p.at(i, j); };
-        auto st = [&](int i, int j, uint64_t v) { *p.at(i, j) = v; };
-        update_segment<WPT, MEASURE>(ld, st, I, J0, a, anti, ups);
-    }
+// The words w0 + 64 k + lane (k < WPT) of colour `colour` of word row I of
+// one lattice, by one wavefront; with MEASURE its sums go to *partial.
+template <int WPT, bool MEASURE>
+__device__ __forceinline__ void update_lattice_row(uint64_t* __restrict__ W, const SweepArgs& a, int I, int w0, int colour,
+                                                   uint32_t* __restrict__ table, Partial* __restrict__ partial) {
+    const size_t L = (size_t)a.L;
+    const int n_live = a.pstar + (I <= a.istar ? 1 : 0);
+    const RowRun r = {W + (size_t)I * L,
+                      W + (size_t)(I > 0 ? I - 1 : a.N - 1) * L,
+                      W + (size_t)(I < a.N - 1 ? I + 1 : 0) * L,
+                      W + (size_t)(I == 0 ? a.istar : 0) * L,
+                      I == 0 || I == a.N - 1 || I == a.istar,
+                      a.L,
+                      (I + colour) & 1,
+                      (uint32_t)I * (uint32_t)a.L,
+                      a.t_lo,
+                      a.t_hi,
+                      1u << 3,
+                      a.k0,
+                      a.k1,
+                      n_live == 21};
+    LatticeRule<MEASURE> rule{a, I, kSpinBits & (~0ull << (3 * (21 - n_live)))};
+    update_row_words<WPT>(r, w0, table, rule);
     if (MEASURE) {
-        anti = wave_sum_u32(anti);
-        ups = wave_sum_u32(ups);
-        const uint32_t wave = ((blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
-        if (lane_id() == 0) partials[wave] = {anti, ups};
+        const uint32_t anti = wave_sum_u32(rule.anti), ups = wave_sum_u32(rule.ups);
+        if (lane_id() == 0) *partial = {anti, ups};
     }
+}
+
+template <int WPT, bool MEASURE>
+__global__ void __launch_bounds__(kTiledMaxBlock)
+    k_halfsweep_single(uint64_t* __restrict__ W, SweepArgs a, int colour, int band, Partial* __restrict__ partials) {
+    __shared__ uint32_t table[(kTiledMaxBlock / 64) * row_table_words<WPT>()];
+    // one word row per workgroup: the row, its wrap cases, live slots and
+    // counter base are wave-uniform (scalar unit)
+    const RowBlock b = row_block(band);
+    if (b.row >= a.N) return;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int waves = (int)(blockDim.x >> 6);
+    const int x = b.x * waves + wv;  // wavefront of the row
+    const int per_row = (int)(band > 0 ? gridDim.y : gridDim.x) * waves;
+    update_lattice_row<WPT, MEASURE>(W, a, b.row, 64 * WPT * x, colour, table + wv * row_table_words<WPT>(),
+                                     MEASURE ? partials + (size_t)b.row * per_row + x : nullptr);
 }
 
 // E = 2 A - 2 L^2 (A antiparallel bonds out of 2 L^2), M = 2 U - L^2.
@@ -159,11 +186,12 @@ __device__ __forceinline__ void finalize_lattice(const LatticeDesc& d, LatticeSt
 // lattice's measured sweep fin_off from the partials that an earlier launch
 // left (the launch boundary orders them), which saves a launch per sample.
 // ---------------------------------------------------------------------------
-template <int WPT, bool MEASURE, bool OFF32>
+template <int WPT, bool MEASURE>
 __global__ void __launch_bounds__(kTiledMaxBlock)
     k_halfsweep_multi(const LatticeDesc* __restrict__ descs, LatticeState* __restrict__ states,
                       const WaveItem* __restrict__ waves, uint32_t n_waves, int colour, uint32_t sweep_off,
                       Partial* __restrict__ partials, const Partial* __restrict__ fin_partials, uint32_t fin_off) {
+    __shared__ uint32_t table[(kTiledMaxBlock / 64) * row_table_words<WPT>()];
     const uint32_t wave = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     if (wave >= n_waves) return;
     const WaveItem item = waves[wave];
@@ -175,22 +203,10 @@ __global__ void __launch_bounds__(kTiledMaxBlock)
         if (MEASURE && lane_id() == 0) partials[wave] = {0u, 0u};
         return;
     }
-    const SweepArgs a = {d.L, d.N, d.istar, d.sh_star, (uint32_t)t, (uint32_t)(t >> 32), d.k0, d.k1, d.t4, d.t8};
-    const int I = item.row;
-    const int seg = item.seg0 + (int)lane_id();
-    uint32_t anti = 0, ups = 0;
-    if (seg < d.segs) {
-        const int J0 = seg * 2 * WPT + ((I + colour) & 1);
-        const WordPtr<OFF32> p{d.W, (uint32_t)a.L};
-        auto ld = [&](int i, int j) { return *p.at(i, j); };
-        auto st = [&](int i, int j, uint64_t v) { *p.at(i, j) = v; };
-        update_segment<WPT, MEASURE>(ld, st, I, J0, a, anti, ups);
-    }
-    if (MEASURE) {
-        anti = wave_sum_u32(anti);
-        ups = wave_sum_u32(ups);
-        if (lane_id() == 0) partials[wave] = {anti, ups};
-    }
+    const SweepArgs a = {d.L, d.N, d.istar, d.sh_star, d.pstar, (uint32_t)t, (uint32_t)(t >> 32), d.k0, d.k1, d.t4, d.t8};
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    update_lattice_row<WPT, MEASURE>(d.W, a, item.row, item.w0, colour, table + wv * row_table_words<WPT>(),
+                                     MEASURE ? partials + wave : nullptr);
 }
 
 __device__ __forceinline__ void block_sum2(uint64_t& x, uint64_t& y, uint64_t* red /* 2 * 16 */) {
@@ -335,7 +351,7 @@ __global__ void __launch_bounds__(kResidentMaxBlock)
     }
     for (int s = 0; s < n_sweeps; ++s) {
         const uint64_t t = t0 + (uint64_t)s;
-        const SweepArgs a = {L, N, d.istar, d.sh_star, (uint32_t)t, (uint32_t)(t >> 32), d.k0, d.k1, d.t4, d.t8};
+        const SweepArgs a = {L, N, d.istar, d.sh_star, d.pstar, (uint32_t)t, (uint32_t)(t >> 32), d.k0, d.k1, d.t4, d.t8};
         const bool meas = every > 0 && ((s + 1) % every) == 0;
         for (int colour = 0; colour < 2; ++colour) {
             uint32_t anti = 0, ups = 0;
@@ -494,20 +510,14 @@ int64_t halfsweep_single_waves(const Geometry& g, int wpt, int block) {
 hipError_t launch_halfsweep_single(int wpt, int block, uint64_t* W, const SweepArgs& a, int colour,
                                    Partial* partials, int64_t* n_waves, hipStream_t s) {
     const Geometry g = {a.L, a.N, a.istar, a.sh_star};
-    const int32_t segs = segments_per_row(a.L, wpt);
-    const dim3 grid(grid_for((uint64_t)segs, block), (unsigned)a.N), blk(block);
+    int band = 0;
+    const dim3 grid = row_grid(a.N, grid_for((uint64_t)segments_per_row(a.L, wpt), block), (size_t)a.L * 8, &band);
+    const dim3 blk(block);
     if (n_waves) *n_waves = halfsweep_single_waves(g, wpt, block);
     const bool m = partials != nullptr;
-    const bool off32 = (uint64_t)g.N * (uint64_t)g.L * 8u < (1ull << 32);
-#define ISING_LAUNCH_HS2(WPT_, O_)                                                                                \
-    if (m) hipLaunchKernelGGL((k_halfsweep_single<WPT_, true, O_>), grid, blk, 0, s, W, a, segs, colour, partials); \
-    else hipLaunchKernelGGL((k_halfsweep_single<WPT_, false, O_>), grid, blk, 0, s, W, a, segs, colour, partials);
-#define ISING_LAUNCH_HS(WPT_)            \
-    if (off32) {                         \
-        ISING_LAUNCH_HS2(WPT_, true)     \
-    } else {                             \
-        ISING_LAUNCH_HS2(WPT_, false)    \
-    }
+#define ISING_LAUNCH_HS(WPT_)                                                                                    \
+    if (m) hipLaunchKernelGGL((k_halfsweep_single<WPT_, true>), grid, blk, 0, s, W, a, colour, band, partials);        \
+    else hipLaunchKernelGGL((k_halfsweep_single<WPT_, false>), grid, blk, 0, s, W, a, colour, band, partials);
     switch (wpt) {
         case 1: ISING_LAUNCH_HS(1) break;
         case 2: ISING_LAUNCH_HS(2) break;
@@ -515,7 +525,6 @@ hipError_t launch_halfsweep_single(int wpt, int block, uint64_t* W, const SweepA
         default: return hipErrorInvalidValue;
     }
 #undef ISING_LAUNCH_HS
-#undef ISING_LAUNCH_HS2
     return hipGetLastError();
 }
 
@@ -560,23 +569,16 @@ hipError_t launch_pack_rows(const uint8_t* in, const Geometry& g, int32_t r0, in
 
 hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, LatticeState* states,
                                   const WaveItem* waves, int64_t n_waves, int colour, uint32_t sweep_off,
-                                  Partial* partials, const Partial* fin_partials, uint32_t fin_off, bool off32,
-                                  hipStream_t s) {
+                                  Partial* partials, const Partial* fin_partials, uint32_t fin_off, hipStream_t s) {
     if (n_waves <= 0) return hipSuccess;
     const dim3 grid(grid_for((uint64_t)n_waves * 64, block)), blk(block);
     const bool m = partials != nullptr;
     const uint32_t nw = (uint32_t)n_waves;
-#define ISING_LAUNCH_HM2(WPT_, O_)                                                                                  \
-    if (m) hipLaunchKernelGGL((k_halfsweep_multi<WPT_, true, O_>), grid, blk, 0, s, descs, states, waves, nw,       \
-                              colour, sweep_off, partials, fin_partials, fin_off);                                  \
-    else hipLaunchKernelGGL((k_halfsweep_multi<WPT_, false, O_>), grid, blk, 0, s, descs, states, waves, nw,        \
-                            colour, sweep_off, partials, fin_partials, fin_off);
-#define ISING_LAUNCH_HM(WPT_)           \
-    if (off32) {                        \
-        ISING_LAUNCH_HM2(WPT_, true)    \
-    } else {                            \
-        ISING_LAUNCH_HM2(WPT_, false)   \
-    }
+#define ISING_LAUNCH_HM(WPT_)                                                                                       \
+    if (m) hipLaunchKernelGGL((k_halfsweep_multi<WPT_, true>), grid, blk, 0, s, descs, states, waves, nw, colour,   \
+                              sweep_off, partials, fin_partials, fin_off);                                          \
+    else hipLaunchKernelGGL((k_halfsweep_multi<WPT_, false>), grid, blk, 0, s, descs, states, waves, nw, colour,    \
+                            sweep_off, partials, fin_partials, fin_off);
     switch (wpt) {
         case 1: ISING_LAUNCH_HM(1) break;
         case 2: ISING_LAUNCH_HM(2) break;
@@ -584,7 +586,6 @@ hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, 
         default: return hipErrorInvalidValue;
     }
 #undef ISING_LAUNCH_HM
-#undef ISING_LAUNCH_HM2
     return hipGetLastError();
 }
 

@@ -192,16 +192,7 @@ static int create_impl(int32_t L, uint64_t seed, int32_t init, void* dev_words, 
         release(h);
         return fail(ISING_ENOMEM, "ising_create: scratch allocation failed: %s", hipGetErrorString(e));
     }
-    // default plan (measured on gfx950): from 64 Ki to 1 Mi words per colour
-    // (L from about 1200 to 4600) one word per thread in 64-thread
-    // workgroups is fastest (L = 4096: 1112 against 827 attempts/ns for two
-    // words in 256-thread workgroups); above it the plans are within a few
-    // per cent and two words per thread in 256-thread workgroups is kept;
-    // below it (a handful of workgroups) 256-thread workgroups with one word
-    // per thread
-    const int64_t words = units_per_colour(h->g, 1);
-    h->wpt = words < ((int64_t)1 << 20) ? 1 : 2;
-    h->block = (words >= ((int64_t)1 << 16) && words < ((int64_t)1 << 20)) ? 64 : 256;
+    default_halfsweep_plan(h->g, &h->wpt, &h->block);
     e = launch_init(h->W, h->g, seed, init, h->stream);
     if (e != hipSuccess) {
         release(h);
@@ -268,6 +259,7 @@ static SweepArgs sweep_args(const ising_lattice* h, uint64_t t, uint32_t t4, uin
     a.N = h->g.N;
     a.istar = h->g.istar;
     a.sh_star = h->g.sh_star;
+    a.pstar = (h->g.L - 1) / h->g.N;
     a.t_lo = (uint32_t)t;
     a.t_hi = (uint32_t)(t >> 32);
     a.k0 = (uint32_t)h->seed;
@@ -686,6 +678,7 @@ static int ensure_desc(ising_lattice* h) {
     d.N = h->g.N;
     d.istar = h->g.istar;
     d.sh_star = h->g.sh_star;
+    d.pstar = (h->g.L - 1) / h->g.N;
     d.sweep_limit = 0x7FFFFFFF;
     ISING_HIP(hipMalloc(&h->d_desc, sizeof(LatticeDesc)));
     ISING_HIP(hipMemcpy(h->d_desc, &d, sizeof d, hipMemcpyHostToDevice));

@@ -13,8 +13,18 @@ namespace ising {
 
 // Tiled work of one colour of a lattice: segments of 2*wpt columns per row.
 inline int32_t segments_per_row(int32_t L, int32_t wpt) { return (L + 2 * wpt - 1) / (2 * wpt); }
-inline int64_t units_per_colour(const Geometry& g, int32_t wpt) {
-    return (int64_t)g.N * segments_per_row(g.L, wpt);
+// Launch shape of one lattice's half-sweeps by its words of a colour (us per
+// half-sweep on gfx950).  From 3 Mi words (L from about 11,200) four words per
+// thread, whose position-20 blocks are shared best: L = 12288 30.7 against
+// 32.4 with one, 16384 49.4 / 52.0, 32768 190 / 201.  From 1 Mi words one
+// word per thread in 256-thread workgroups (L = 8000 17.1, 9998 23.8; the
+// shapes are within 3 per cent there); below it 64-thread workgroups, which
+// start faster (L = 2048 3.9 against 4.2), and below 64 Ki words, a handful of
+// workgroups, 256 threads again.
+inline void default_halfsweep_plan(const Geometry& g, int* wpt, int* block) {
+    const int64_t words = (int64_t)g.N * (g.L / 2);
+    *wpt = words < ((int64_t)3 << 20) ? 1 : 4;
+    *block = (words >= ((int64_t)1 << 16) && words < ((int64_t)1 << 20)) ? 64 : 256;
 }
 // Wavefronts of a tiled half-sweep of one lattice: every word row starts a
 // new wavefront.
@@ -89,9 +99,8 @@ hipError_t launch_pack_rows(const uint8_t* in, const Geometry& g, int32_t r0, in
 // offset took no part in that sweep and are skipped.
 hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, LatticeState* states,
                                   const WaveItem* waves, int64_t n_waves, int colour, uint32_t sweep_off,
-                                  Partial* partials, const Partial* fin_partials, uint32_t fin_off, bool off32,
+                                  Partial* partials, const Partial* fin_partials, uint32_t fin_off,
                                   hipStream_t s);
-inline bool fits_off32(const Geometry& g) { return (uint64_t)g.N * (uint64_t)g.L * 8u < (1ull << 32); }
 // End of a chunk of k sweeps: finalize the tiled lattices' measured sweep
 // fin_off (fin_partials non-null) and advance every lattice's sweep counter
 // by min(k, sweep_limit).

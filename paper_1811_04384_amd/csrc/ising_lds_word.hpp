@@ -62,55 +62,26 @@ __device__ __forceinline__ uint64_t down_of(const Nbhd& n, int I, int N, int ist
     return I == istar ? patched : d;
 }
 
-// The sums of measure_word with fewer counts: live has only the spin bit 3k
-// of each field, so the masked bond words for up and down shifted by one
-// and two bits fill the two free bits of every field, and one count covers
-// three of them (likewise for the two up-spin counts).
-__device__ __forceinline__ void measure_word_packed(uint64_t w, uint64_t up, uint64_t dn, uint64_t lf, uint64_t rt,
-                                                    uint64_t live, uint32_t& anti, uint32_t& ups) {
-    const uint64_t b3 = ((w ^ lf) & live) | (((w ^ up) & live) << 1) | (((w ^ dn) & live) << 2);
-    anti += __popcll(b3) + __popcll((w ^ rt) & live);
-    ups += __popcll((w & live) | ((lf & live) << 1));
-}
-
-// The acceptance codes of positions 0..19 of the word with Philox counter
+// The acceptance bits of positions 0..19 of the word with Philox counter
 // word c1 = I L + J at sweep t: blocks g = 0..4 of counter (t, c1), four
 // positions each (blocks past the last live position skipped on small
 // lattices, whose rows have at most 16 live positions).
-__device__ __forceinline__ void lds_word_codes19(const LdsSweep& s, const RoundKeys& rk, int n_live, uint32_t c1,
-                                                 Codes& codes) {
-    if (s.all_blocks) {
-#pragma unroll
-        for (int g = 0; g < 5; ++g) {
-            const U4 r = philox_lane_c1(s.t_lo, c1, s.t_hi, (uint32_t)g | (1u << 3), s.k0, s.k1, rk);
-            append_draw(codes, 4 * g + 0, r.x, s.t4, s.t8);
-            append_draw(codes, 4 * g + 1, r.y, s.t4, s.t8);
-            append_draw(codes, 4 * g + 2, r.z, s.t4, s.t8);
-            append_draw(codes, 4 * g + 3, r.w, s.t4, s.t8);
-        }
-    } else {
-#pragma unroll
-        for (int g = 0; g < 5; ++g) {
-            if (4 * g < n_live) {
-                const U4 r = philox_lane_c1(s.t_lo, c1, s.t_hi, (uint32_t)g | (1u << 3), s.k0, s.k1, rk);
-                append_draw(codes, 4 * g + 0, r.x, s.t4, s.t8);
-                append_draw(codes, 4 * g + 1, r.y, s.t4, s.t8);
-                append_draw(codes, 4 * g + 2, r.z, s.t4, s.t8);
-                append_draw(codes, 4 * g + 3, r.w, s.t4, s.t8);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) append_code(codes, 4 * g + k, 0u);
-            }
-        }
-    }
+template <class Accept>
+__device__ __forceinline__ void lds_word_accept19(const LdsSweep& s, const RoundKeys& rk, int n_live, uint32_t c1,
+                                                  Accept& acc) {
+    auto block = [&](int g) {
+        return philox_lane_c1(s.t_lo, c1, s.t_hi, (uint32_t)g | (1u << 3), s.k0, s.k1, rk);
+    };
+    if (s.all_blocks) accept_word(acc, block, 21, s.t4, s.t8);
+    else accept_word(acc, block, n_live, s.t4, s.t8);
 }
 
 // The bit-sliced flip of Table 1 and the Metropolis rule applied to the word
-// with the assembled codes of all its positions; with meas (wave-uniform),
+// with the acceptance bits a, b of all its positions; with meas (wave-uniform),
 // adds the word's antiparallel bonds and its and its left neighbour's up
 // spins when count (per lane) is set.
 __device__ __forceinline__ uint64_t lds_word_flip(const LdsSweep& s, const Nbhd& nb, int I, uint64_t live,
-                                                  uint64_t codes, bool meas, bool count, uint32_t& anti,
+                                                  uint64_t a, uint64_t b, bool meas, bool count, uint32_t& anti,
                                                   uint32_t& ups) {
     // only rows 0, N - 1 and I* wrap or take the patch: the selects run
     // only in the wavefronts that hold such a row
@@ -119,12 +90,12 @@ __device__ __forceinline__ uint64_t lds_word_flip(const LdsSweep& s, const Nbhd&
         up = up_of(nb, I, s.sh_star);
         dn = down_of(nb, I, s.N, s.istar, s.sh_star);
     }
-    const uint64_t nw = nb.w ^ flip_mask(nb.w, up, dn, nb.lf, nb.rt, codes, live);
+    const uint64_t nw = nb.w ^ flip_mask(nb.w, up, dn, nb.lf, nb.rt, a, b, live);
     if (meas) {
-        uint32_t a = 0, u = 0;
-        measure_word_packed(nw, up, dn, nb.lf, nb.rt, live, a, u);
-        anti += count ? a : 0u;
-        ups += count ? u : 0u;
+        uint32_t bonds = 0, up_spins = 0;
+        measure_word_packed(nw, up, dn, nb.lf, nb.rt, live, bonds, up_spins);
+        anti += count ? bonds : 0u;
+        ups += count ? up_spins : 0u;
     }
     return nw;
 }
@@ -141,19 +112,19 @@ __device__ __forceinline__ uint64_t live_mask(const LdsSweep& s, int I) {
 __device__ __forceinline__ uint64_t lds_word_update_c1(const LdsSweep& s, const RoundKeys& rk, const Nbhd& nb, int I,
                                                        uint32_t c1, uint32_t u20, bool meas, bool count,
                                                        uint32_t& anti, uint32_t& ups) {
-    Codes codes = {0u, 0u, 0u};
-    lds_word_codes19(s, rk, s.pstar + (I <= s.istar ? 1 : 0), c1, codes);
-    append_draw(codes, 20, u20, s.t4, s.t8);  // a dead slot when n_live < 21 (masked by live)
-    return lds_word_flip(s, nb, I, live_mask(s, I), assemble_codes(codes), meas, count, anti, ups);
+    AcceptSelect acc;
+    lds_word_accept19(s, rk, s.pstar + (I <= s.istar ? 1 : 0), c1, acc);
+    acc.add<20>(u20, s.t4, s.t8);  // a dead slot when n_live < 21 (masked by live)
+    return lds_word_flip(s, nb, I, live_mask(s, I), acc.word(), acc.word() >> 1, meas, count, anti, ups);
 }
 
-// The codes of positions 0..19 of a word, assembled, with field 0 (position
-// 20) left 0: drawn ahead of the word's update.
+// The codes of positions 0..19 of a word, with field 0 (position 20) left 0:
+// drawn ahead of the word's update.
 __device__ __forceinline__ uint64_t lds_word_codes(const LdsSweep& s, const RoundKeys& rk, int I, uint32_t c1) {
-    Codes codes = {0u, 0u, 0u};
-    lds_word_codes19(s, rk, s.pstar + (I <= s.istar ? 1 : 0), c1, codes);
-    append_code(codes, 20, 0u);
-    return assemble_codes(codes);
+    AcceptSelect acc;
+    lds_word_accept19(s, rk, s.pstar + (I <= s.istar ? 1 : 0), c1, acc);
+    acc.lo <<= 3;  // field 0
+    return acc.word();
 }
 
 // The update of a word whose codes of positions 0..19 were drawn ahead:
@@ -161,8 +132,10 @@ __device__ __forceinline__ uint64_t lds_word_codes(const LdsSweep& s, const Roun
 __device__ __forceinline__ uint64_t lds_word_apply(const LdsSweep& s, const Nbhd& nb, int I, uint64_t codes19,
                                                    uint32_t u20, bool meas, bool count, uint32_t& anti,
                                                    uint32_t& ups) {
-    const uint64_t codes = codes19 | first_accept(u20, s.t4, s.t8);  // a dead slot when n_live < 21
-    return lds_word_flip(s, nb, I, live_mask(s, I), codes, meas, count, anti, ups);
+    AcceptSelect last;
+    last.add<0>(u20, s.t4, s.t8);  // a dead slot when n_live < 21
+    const uint64_t codes = codes19 | last.hi;
+    return lds_word_flip(s, nb, I, live_mask(s, I), codes, codes >> 1, meas, count, anti, ups);
 }
 
 // The same, forming c1 from (I, J).

@@ -84,6 +84,10 @@ int ising_replicas_create(int32_t L, uint64_t seed, int32_t init, void* stream, 
     h->L = L;
     h->seed = seed;
     h->stream = static_cast<hipStream_t>(stream);
+    // words per thread (us per half-sweep with 1 / 2 / 4: L = 770 7.2 / 7.6 /
+    // 7.6, 1026 10.0 / 9.8 / 10.7, 1500 16.3 / 14.8 / 14.9, 2048 24.5 / 21.8 /
+    // 20.4, 8192 300 / 271 / 253)
+    h->wpt = L < 1024 ? 1 : L < 1536 ? 2 : 4;
     hipError_t e = hipMalloc(&h->W, sizeof(uint64_t) * (size_t)L * (size_t)L);
     if (e == hipSuccess) e = hipMalloc(&h->d_totals, sizeof(unsigned long long) * 2 * kReplicas);
     if (e == hipSuccess) e = hipMalloc(&h->d_EM, sizeof(int64_t) * 2 * kReplicas);

@@ -13,6 +13,7 @@
 #include "ising_device.hpp"
 #include "ising_moments.hpp"
 #include "ising_replicas.hpp"
+#include "ising_row_words.hpp"
 
 namespace ising {
 
@@ -20,6 +21,7 @@ namespace {
 
 constexpr uint32_t kStreamSweep = 6;  // Philox counter word 3 = g + 8 stream
 constexpr uint32_t kStreamInit = 7;
+constexpr int kHalfSweepBlock = 64;
 
 // Draw of replica k at site (r, c): block g = k div 4 (k < 20) keyed by the
 // site, output k mod 4; replica 20 shares block 5 among the four same-colour
@@ -46,58 +48,61 @@ __global__ void __launch_bounds__(256) k_replica_init(uint64_t* __restrict__ W, 
     W[i] = w;
 }
 
-// One colour of every replica: one thread per row segment of 2 WPT columns
-// (WPT same-colour words), as in the column-coded half-sweep.  The
-// position-20 block of the segment's words is drawn once.
-template <int WPT>
-__global__ void __launch_bounds__(256) k_replica_halfsweep(uint64_t* __restrict__ W, ReplicaArgs a, int colour) {
-    const int L = a.L;
-    const int segs = (L / 2 + WPT - 1) / WPT;
-    const uint64_t unit = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (unit >= (uint64_t)L * (uint64_t)segs) return;
-    const int r = (int)(unit / (uint64_t)segs);
-    const int seg = (int)(unit - (uint64_t)r * (uint64_t)segs);
-    const int J0 = seg * 2 * WPT + ((r + colour) & 1);
-    const int ru = r == 0 ? L - 1 : r - 1, rd = r == L - 1 ? 0 : r + 1;
-    const uint32_t row_base = (uint32_t)r * (uint32_t)L;
-    const uint32_t c3 = 8u * kStreamSweep;
-    uint64_t* __restrict__ row = W + (size_t)r * (size_t)L;
-    const uint64_t* __restrict__ row_up = W + (size_t)ru * (size_t)L;
-    const uint64_t* __restrict__ row_dn = W + (size_t)rd * (size_t)L;
+// The four replicas of Philox block G, each with its own thresholds.
+template <int G>
+__device__ __forceinline__ void replica_accept(AcceptPair& acc, const U4& o, const ReplicaArgs& a) {
+    acc.add<4 * G + 0>(o.x, a.t4[4 * G + 0], a.t8[4 * G + 0]);
+    acc.add<4 * G + 1>(o.y, a.t4[4 * G + 1], a.t8[4 * G + 1]);
+    acc.add<4 * G + 2>(o.z, a.t4[4 * G + 2], a.t8[4 * G + 2]);
+    acc.add<4 * G + 3>(o.w, a.t4[4 * G + 3], a.t8[4 * G + 3]);
+}
 
-    const RoundKeys rk = round_keys(a.k0, a.k1);
-    uint32_t u20[4] = {0u, 0u, 0u, 0u};
-    {
-        const uint32_t col = ((uint32_t)J0 & ~7u) | ((uint32_t)J0 & 1u);
-        const U4 o = philox_lane_c1(a.t_lo, row_base + col, a.t_hi, 5u + c3, a.k0, a.k1, rk);
-        const uint32_t q0 = ((uint32_t)J0 >> 1) & 3u;
-#pragma unroll
-        for (int k = 0; k < WPT; ++k) {
-            const uint32_t q = (q0 + (uint32_t)k) & 3u;
-            u20[k] = q == 0 ? o.x : q == 1 ? o.y : q == 2 ? o.z : o.w;
-        }
+// What a half-sweep of the replicas does with a run of words: a threshold
+// pair per field, all fields live, plain neighbours on the torus.
+struct ReplicaRule {
+    const ReplicaArgs& a;
+    uint64_t live = kSpinBits;
+    template <class Block>
+    __device__ __forceinline__ void accept(AcceptPair& acc, const Block& block) const {
+        replica_accept<0>(acc, block(0), a);
+        replica_accept<1>(acc, block(1), a);
+        replica_accept<2>(acc, block(2), a);
+        replica_accept<3>(acc, block(3), a);
+        replica_accept<4>(acc, block(4), a);
     }
-#pragma unroll
-    for (int k = 0; k < WPT; ++k) {
-        const int J = J0 + 2 * k;
-        if (J >= L) break;
-        const uint64_t w = row[J];
-        const uint64_t lf = row[J == 0 ? L - 1 : J - 1];
-        const uint64_t rt = row[J == L - 1 ? 0 : J + 1];
-        const uint64_t up = row_up[J];
-        const uint64_t dn = row_dn[J];
-        Codes codes = {0u, 0u, 0u};
-#pragma unroll
-        for (int g = 0; g < 5; ++g) {
-            const U4 o = philox_lane_c1(a.t_lo, row_base + (uint32_t)J, a.t_hi, (uint32_t)g + c3, a.k0, a.k1, rk);
-            append_draw(codes, 4 * g + 0, o.x, a.t4[4 * g + 0], a.t8[4 * g + 0]);
-            append_draw(codes, 4 * g + 1, o.y, a.t4[4 * g + 1], a.t8[4 * g + 1]);
-            append_draw(codes, 4 * g + 2, o.z, a.t4[4 * g + 2], a.t8[4 * g + 2]);
-            append_draw(codes, 4 * g + 3, o.w, a.t4[4 * g + 3], a.t8[4 * g + 3]);
-        }
-        append_draw(codes, 20, u20[k], a.t4[20], a.t8[20]);
-        row[J] = w ^ flip_mask(w, up, dn, lf, rt, assemble_codes(codes), kSpinBits);
-    }
+    __device__ __forceinline__ void accept20(AcceptPair& acc, uint32_t u) const { acc.add<20>(u, a.t4[20], a.t8[20]); }
+    __device__ __forceinline__ void vertical(uint64_t&, uint64_t&, uint64_t) const {}
+    __device__ __forceinline__ void after(uint64_t, uint64_t, uint64_t, uint64_t, uint64_t) const {}
+};
+
+// One colour of every replica: every wavefront updates 64 WPT words of the
+// colour of one row (row_block).
+template <int WPT>
+__global__ void __launch_bounds__(kHalfSweepBlock) k_replica_halfsweep(uint64_t* __restrict__ W, ReplicaArgs a, int colour,
+                                                                      int band) {
+    __shared__ uint32_t table[(kHalfSweepBlock / 64) * row_table_words<WPT>()];
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const RowBlock b = row_block(band);
+    const int row = b.row;
+    if (row >= a.L) return;
+    const int x = b.x * (int)(blockDim.x >> 6) + wv;  // wavefront of the row
+    const size_t L = (size_t)a.L;
+    uint64_t* const W_row = W + (size_t)row * L;
+    const RowRun r = {W_row,
+                      W + (size_t)(row == 0 ? a.L - 1 : row - 1) * L,
+                      W + (size_t)(row == a.L - 1 ? 0 : row + 1) * L,
+                      W_row,
+                      false,
+                      a.L,
+                      (row + colour) & 1,
+                      (uint32_t)row * (uint32_t)a.L,
+                      a.t_lo,
+                      a.t_hi,
+                      8u * kStreamSweep,
+                      a.k0,
+                      a.k1,
+                      true};
+    update_row_words<WPT>(r, 64 * WPT * x, table + wv * row_table_words<WPT>(), ReplicaRule{a});
 }
 
 // Per-replica antiparallel right+down bonds and up spins of all words.
@@ -199,12 +204,13 @@ hipError_t launch_replica_init(uint64_t* W, int L, uint64_t seed, int hot, hipSt
 }
 
 hipError_t launch_replica_halfsweep(int wpt, uint64_t* W, const ReplicaArgs& a, int colour, hipStream_t s) {
-    const uint64_t units = (uint64_t)a.L * (uint64_t)((a.L / 2 + wpt - 1) / wpt);
-    const dim3 grid(rgrid(units, 256)), blk(256);
+    int band = 0;
+    const dim3 grid = row_grid(a.L, rgrid((uint64_t)a.L / 2, kHalfSweepBlock * wpt), (size_t)a.L * 8, &band);
+    const dim3 blk(kHalfSweepBlock);
     switch (wpt) {
-        case 1: hipLaunchKernelGGL(k_replica_halfsweep<1>, grid, blk, 0, s, W, a, colour); break;
-        case 2: hipLaunchKernelGGL(k_replica_halfsweep<2>, grid, blk, 0, s, W, a, colour); break;
-        case 4: hipLaunchKernelGGL(k_replica_halfsweep<4>, grid, blk, 0, s, W, a, colour); break;
+        case 1: hipLaunchKernelGGL(k_replica_halfsweep<1>, grid, blk, 0, s, W, a, colour, band); break;
+        case 2: hipLaunchKernelGGL(k_replica_halfsweep<2>, grid, blk, 0, s, W, a, colour, band); break;
+        case 4: hipLaunchKernelGGL(k_replica_halfsweep<4>, grid, blk, 0, s, W, a, colour, band); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -206,7 +206,6 @@ int enqueue_quantum(ising_server* s) {
     if (rc != ISING_OK) return rc;
     int32_t n_res = 0, K = 0;
     size_t lds = 0;
-    bool off32 = true;
     n_waves = 0;
     for (int32_t i = 0; i < slots; ++i) {
         const Slot& sl = sc.slots()[i];
@@ -222,7 +221,7 @@ int enqueue_quantum(ising_server* s) {
         d.k0 = (uint32_t)sl.req.seed;
         d.k1 = (uint32_t)(sl.req.seed >> 32);
         thresholds_of(sl.req.T, &d.t4, &d.t8);
-        d.segs = segments_per_row(g.L, kServerWpt);
+        d.pstar = (g.L - 1) / g.N;
         d.sweep_limit = (int32_t)sl.planned;
         if (sl.planned <= 0) continue;
         K = std::max<int32_t>(K, (int32_t)sl.planned);
@@ -231,11 +230,9 @@ int enqueue_quantum(ising_server* s) {
             st.ids[n_res++] = i;
             lds = std::max(lds, (size_t)g.N * g.L * 8);
         } else {
-            d.units = units_per_colour(g, kServerWpt);
-            off32 = off32 && fits_off32(g);
             d.part_begin = (int32_t)n_waves;
             for (int32_t I = 0; I < g.N; ++I)
-                for (int32_t s0 = 0; s0 < d.segs; s0 += 64) st.waves[n_waves++] = {i, I, s0};
+                for (int32_t w0 = 0; w0 < g.L / 2; w0 += 64 * kServerWpt) st.waves[n_waves++] = {i, I, w0};
             d.part_count = (int32_t)(n_waves - d.part_begin);
         }
     }
@@ -256,9 +253,9 @@ int enqueue_quantum(ising_server* s) {
         }
         for (int32_t k = 0; k < K && n_waves; ++k) {
             ISING_HIP(launch_halfsweep_multi(kServerWpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 0,
-                                             (uint32_t)k, nullptr, nullptr, 0, off32, s->stream));
+                                             (uint32_t)k, nullptr, nullptr, 0, s->stream));
             ISING_HIP(launch_halfsweep_multi(kServerWpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 1,
-                                             (uint32_t)k, nullptr, nullptr, 0, off32, s->stream));
+                                             (uint32_t)k, nullptr, nullptr, 0, s->stream));
         }
         if (n_res) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));
         ISING_HIP(launch_chunk_end(s->d_desc, s->d_state, slots, nullptr, 0, (uint32_t)K, s->stream));

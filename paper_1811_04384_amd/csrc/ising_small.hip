@@ -35,7 +35,7 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 // One workgroup per listed lattice (ids), K sweeps (each lattice at most its
 // sweep limit); a sample after local sweep s when (s + 1) % every == 0
 // (every > 0).  LDS: the words [N][L], then the codes of `batch` sweeps
-// [batch][N][L] (bit 3k: code >= 1 at field k, bit 3k + 1: code = 2).
+// [batch][N][L] (bit 3k: A at field k, bit 3k + 1: B).
 __global__ void __launch_bounds__(kSmallMaxBlock) k_small(const LatticeDesc* __restrict__ descs,
                                                            LatticeState* __restrict__ states,
                                                            const int32_t* __restrict__ ids, int32_t K, int32_t every,
@@ -97,23 +97,16 @@ __global__ void __launch_bounds__(kSmallMaxBlock) k_small(const LatticeDesc* __r
             for (int m = 0; m < 4; ++m) {
                 const int J = 8 * grp + par + 2 * m;
                 if (J >= L) break;
-                Codes cd = {0u, 0u, 0u};
-#pragma unroll
-                for (int g = 0; g < 5; ++g) {
-                    if (4 * g < n_live) {
-                        const U4 rr = philox_lane_c1(t_lo, (uint32_t)I * (uint32_t)L + (uint32_t)J, t_hi,
-                                                     (uint32_t)g | (1u << 3), d.k0, d.k1, rk);
-                        append_draw(cd, 4 * g + 0, rr.x, d.t4, d.t8);
-                        append_draw(cd, 4 * g + 1, rr.y, d.t4, d.t8);
-                        append_draw(cd, 4 * g + 2, rr.z, d.t4, d.t8);
-                        append_draw(cd, 4 * g + 3, rr.w, d.t4, d.t8);
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) append_code(cd, 4 * g + k, 0u);
-                    }
-                }
-                append_draw(cd, 20, pick4(u5, (uint32_t)m), d.t4, d.t8);  // a dead slot when n_live < 21
-                codes[(size_t)j * NL + I * L + J] = assemble_codes(cd);
+                AcceptSelect acc;
+                accept_word(
+                    acc,
+                    [&](int g) {
+                        return philox_lane_c1(t_lo, (uint32_t)I * (uint32_t)L + (uint32_t)J, t_hi,
+                                              (uint32_t)g | (1u << 3), d.k0, d.k1, rk);
+                    },
+                    n_live, d.t4, d.t8);
+                acc.add<20>(pick4(u5, (uint32_t)m), d.t4, d.t8);  // a dead slot when n_live < 21
+                codes[(size_t)j * NL + I * L + J] = acc.word();
             }
         }
         __syncthreads();

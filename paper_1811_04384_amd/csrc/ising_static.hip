@@ -61,11 +61,11 @@ int ising_sweep_measure_static(void* dev_words, size_t bytes, int32_t L, uint64_
     if (n_sweeps < 0 || every < 1)
         return fail(ISING_EINVAL, "ising_sweep_measure_static: need n_sweeps >= 0 and every >= 1");
     // the launch shape of ising_create's default plan (one launch per
-    // half-sweep); its sampled half-sweeps must fit the partial sums
-    const int64_t words = units_per_colour(g, 1);
-    const int wpt = words < ((int64_t)1 << 20) ? 1 : 2;
-    const int block = (words >= ((int64_t)1 << 16) && words < ((int64_t)1 << 20)) ? 64 : 256;
-    const int64_t waves = halfsweep_single_waves(g, wpt, block);
+    // half-sweep); the sizes taken are those whose sampled half-sweeps fit
+    // the partial sums with at most two words per thread
+    int wpt = 1, block = 256;
+    default_halfsweep_plan(g, &wpt, &block);
+    const int64_t waves = halfsweep_single_waves(g, std::min(wpt, 2), block);
     if (waves > (int64_t)kStaticPartials)
         return fail(ISING_EINVAL,
                     "ising_sweep_measure_static: L = %d needs %lld partial sums, more than the %zu of the static "
@@ -88,6 +88,7 @@ int ising_sweep_measure_static(void* dev_words, size_t bytes, int32_t L, uint64_
     a.N = g.N;
     a.istar = g.istar;
     a.sh_star = g.sh_star;
+    a.pstar = (g.L - 1) / g.N;
     a.k0 = (uint32_t)seed;
     a.k1 = (uint32_t)(seed >> 32);
     a.t4 = t4;
