@@ -91,6 +91,7 @@ struct ising_batch {
     int32_t draw_max_items = 0;  // largest n_draw of the list
     int32_t draw_S = 0;          // sweeps per draw pass
     int32_t draw_wmax = 0;       // words of a colour per thread of an apply workgroup
+    int32_t draw_block = 64;     // threads of an apply workgroup
     size_t draw_lds = 0;
     uint64_t* d_codes = nullptr;
     uint8_t* d_stage = nullptr;  // spin output staging, spin_stage_bytes of the largest L
@@ -183,7 +184,8 @@ int32_t tile_width(const Geometry& g, const ising_batch_plan& p, size_t lds_limi
     return tile_lds_bytes(g.L, g.N, w, p.tile_sweeps) <= lds_limit ? w : 0;
 }
 
-// Threads per apply workgroup of the lattices whose codes are drawn chip-wide.
+// Most threads per apply workgroup of the lattices whose codes are drawn
+// chip-wide.
 int32_t apply_block(const ising_batch_plan& p) { return std::min(p.resident_block, 256); }
 
 size_t tile_launch_lds(const ising_batch* b, int32_t K) {
@@ -398,6 +400,12 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
             b->draw_max_items = std::max(b->draw_max_items, dl.back().n_draw);
             b->draw_wmax = std::max(b->draw_wmax, wave_apply_words_per_thread(g.L, g.N, apply_block(p)));
         }
+        // no more wavefronts than the largest lattice has words for: an idle one
+        // still takes part in every barrier (8 lattices of L = 16: 0.40 us a
+        // sweep with four wavefronts, 0.36 with one, which needs no barrier)
+        int32_t draw_words = 1;
+        for (int32_t i : ids_draw) draw_words = std::max(draw_words, b->geo[i].N * (b->geo[i].L / 2));
+        b->draw_block = ((draw_words + b->draw_wmax - 1) / b->draw_wmax + 63) / 64 * 64;
         b->draw_S = (int32_t)std::min<int64_t>(p.draw_sweeps, std::max<int64_t>(1, (int64_t)(kMaxDrawBytes / 8) / words));
         int64_t base = 0;
         for (auto& e : dl) {
@@ -444,7 +452,7 @@ int enqueue_chunk(ising_batch* b, int32_t k, int32_t every, hipStream_t s0, hipS
         const int32_t S = std::min(b->draw_S, k - done);
         ISING_HIP(launch_draw_codes(b->d_desc, b->d_state, b->d_draw, b->n_draw, b->draw_max_items, b->d_codes, done,
                                     S, rs));
-        ISING_HIP(launch_wave_apply(b->draw_wmax, apply_block(p), b->d_desc, b->d_state, b->d_draw, b->n_draw,
+        ISING_HIP(launch_wave_apply(b->draw_wmax, b->draw_block, b->d_desc, b->d_state, b->d_draw, b->n_draw,
                                     b->d_codes, done, S, every, b->draw_lds, rs));
     }
     // A measured sweep s is finalized by the next launch on s0: the colour-0

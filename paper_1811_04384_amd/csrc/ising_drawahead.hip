@@ -112,105 +112,174 @@ __device__ __forceinline__ void load_codes(uint64_t (&cr)[2][WMAX], const uint64
         for (int k = 0; k < WMAX; ++k) cr[c][k] = __builtin_nontemporal_load(p + c * words + min(tid + stride * k, words - 1));
 }
 
-}  // namespace
+// LDS addressed by 32-bit byte addresses kept in registers
+typedef __attribute__((address_space(3))) uint64_t lds_u64;
+__device__ __forceinline__ uint32_t lds_addr(const uint64_t* p) { return (uint32_t)(size_t)(const lds_u64*)p; }
+__device__ __forceinline__ uint64_t lds_load(uint32_t addr) { return *(const lds_u64*)(size_t)addr; }
+__device__ __forceinline__ void lds_store(uint32_t addr, uint64_t v) { *(lds_u64*)(size_t)addr = v; }
 
-// Apply pass: one workgroup of A = blockDim.x / 64 wavefronts (ONE_WAVE: A
-// = 1) per lattice entry, S sweeps of the pass (local sweep index s =
-// sweep_off + j of the chunk; a sample after it when (s + 1) % every == 0,
-// every > 0).  LDS: the lattice [N][L], then one (antiparallel bonds, up
-// spins) pair per sample of the pass.  Thread tid holds the word slots
-// tid + 64 A k (k < WMAX) of each colour, and the codes of its words are
-// loaded from the global buffer straight into registers, P sweeps ahead of
-// their use.  In a half-sweep no word read is written (all neighbours, the
-// wrap words and the patch word have the other colour), so every thread
-// loads all of its neighbourhoods first and then flips and stores;
-// half-sweeps are separated by a workgroup barrier, or, with one wavefront,
-// by the in-order completion of its LDS operations.  A sampled sweep only
-// adds its wavefront sums to its pair; after the sweeps the first wavefront
-// turns the pairs into E, M, the series and the moment sums.
+// A word slot of a thread, the same columns 2h and 2h + 1 of word row I in
+// both colours: own[c] is the LDS address of the word of colour c (and the
+// near neighbour of colour 1 - c), far[c] that of its other neighbour in the
+// row, up / dn / pt those of the rows above and below and of the patch word.
+// The wrap of rows 0, N - 1 and I* is formed by every lane with its own
+// constants, without selects: the word above is shifted down one field in row
+// 0 (su = 3), the one below up one field in row N - 1 (sd = 3; its bit 63 is
+// masked by live), bit 60 of the word above row 0 comes from the patch word
+// (mu), and bit sh_star of the word below row I* too (md).
+struct Slot {
+    uint32_t own[2], far[2], up[2], dn[2], pt[2];
+    uint32_t su, sd, mu;
+    uint64_t md, live;
+};
+
+__device__ __forceinline__ Slot make_slot(const uint64_t* T, int I, int h, int L, int N, int istar, int sh_star,
+                                          int pstar) {
+    Slot s;
+    const uint64_t* row = T + I * L;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int par = (I + c) & 1;
+        const int J = 2 * h + par;
+        const int f = par ? (J == L - 1 ? 0 : J + 1) : (J == 0 ? L - 1 : J - 1);
+        s.own[c] = lds_addr(row + J);
+        s.far[c] = lds_addr(row + f);
+        s.up[c] = lds_addr(T + (I > 0 ? I - 1 : N - 1) * L + J);
+        s.dn[c] = lds_addr(T + (I < N - 1 ? I + 1 : 0) * L + J);
+        // row I* for row 0; rows without a patch read row 0 and ignore it
+        s.pt[c] = lds_addr(T + (I == 0 ? istar : 0) * L + J);
+    }
+    s.su = I == 0 ? 3u : 0u;
+    s.sd = I == N - 1 ? 3u : 0u;
+    s.mu = I == 0 ? 1u << 28 : 0u;
+    s.md = I == istar ? 1ull << sh_star : 0ull;
+    const int n_live = pstar + (I <= istar ? 1 : 0);
+    s.live = kSpinBits & (~0ull << (3 * (21 - n_live)));
+    return s;
+}
+
+// What an apply pass of one lattice needs (wave-uniform): n sweeps with the
+// codes at `codes`, a sample after the local sweep j (from 0) when
+// (sweep_off + j + 1) % every == 0, every > 0.
+struct ApplyTask {
+    uint64_t* W;
+    int L, N, istar, sh_star;
+    const uint64_t* codes;
+    int n, sweep_off, every;
+};
+
+// The sweeps of an apply pass, the lattice in LDS (T, [N][L]) and the samples'
+// (antiparallel bonds, up spins) added to stage[2 k]; returns the number of
+// samples.  Thread tid holds the word slots tid + B k (k < WMAX) of each
+// colour (past the last slot, one more copy of it: the same loads and the same
+// store), and the codes of its words are loaded from the global buffer
+// straight into registers, P sweeps ahead of their use.  In a half-sweep no
+// word read is written (all neighbours, the wrap words and the patch word
+// have the other colour), so every thread loads all of its neighbourhoods
+// first and then flips and stores; half-sweeps are separated by a workgroup
+// barrier, or, with one wavefront, by the in-order completion of its LDS
+// operations.  A half-sweep is a chain -- LDS loads, about 30 vector
+// instructions per word, the store, the barrier -- with few wavefronts to fill
+// it, so everything that can be is taken off it: addresses and wrap constants
+// are formed once; with several wavefronts, whose loads queue for the LDS, a
+// slot's own two words stay in registers and only the four words of other
+// slots are loaded (with one wavefront the two extra loads cost nothing); a
+// sample's sum over the wavefront is formed while the loads of the next
+// half-sweep are in flight; and no wavefront without words takes part.
+// us per sweep, eight lattices, without samples / a sample each sweep, before
+// (selects per half-sweep, six loads, four wavefronts always) and now: L = 16
+// 0.41/0.57 and 0.30/0.43, 64 0.48/0.64 and 0.41/0.54, 128 0.94/1.18 and
+// 0.73/0.89, 168 1.36/1.63 and 1.04/1.21, 204 1.68/2.00 and 1.30/1.59; 512
+// lattices of L = 64 1.52/1.68 and 1.34/1.46, 2048 4.71/5.13 and 4.11/4.30
+// (the draws included, which the larger counts are bound by).
 template <int WMAX, int P, bool ONE_WAVE>
-__global__ void __launch_bounds__(kApplyMaxBlock) k_wave_apply(const LatticeDesc* __restrict__ descs,
-                                                               LatticeState* __restrict__ states,
-                                                               const DrawLat* __restrict__ lats,
-                                                               const uint64_t* __restrict__ codes, int32_t sweep_off,
-                                                               int32_t S, int32_t every) {
-    extern __shared__ uint64_t lds[];
-    const DrawLat dl = lats[blockIdx.x];
-    const LatticeDesc& d = descs[dl.lat];
-    LatticeState& state = states[dl.lat];
-    const int n = min(S, d.sweep_limit - sweep_off);
-    if (n <= 0) return;  // uniform over the workgroup
-    const int L = d.L, N = d.N, istar = d.istar, sh_star = d.sh_star;
-    const int NL = N * L;
-    const int pstar = (L - 1) / N;
-    const int half = L >> 1;
-    const int words = N * half;  // words of one colour
+__device__ __forceinline__ int apply_sweeps(const ApplyTask& a, uint64_t* __restrict__ T, uint32_t* __restrict__ stage) {
+    const int L = a.L, N = a.N;
+    const int NL = N * L, half = L >> 1, words = N * half;  // words of one colour
     const int tid = threadIdx.x, B = blockDim.x;
-    uint64_t* __restrict__ T = lds;
-    uint32_t* __restrict__ stage = reinterpret_cast<uint32_t*>(lds + NL);  // [samples][2]
-    const int n_samples = every > 0 ? (sweep_off + n) / every - sweep_off / every : 0;
-    const uint64_t* __restrict__ cg = codes + dl.base;
-    uint64_t* __restrict__ G = d.W;
-    for (int i = tid; i < NL; i += B) T[i] = G[i];
+    const int n = a.n, every = a.every, pstar = (L - 1) / N;
+    const int n_samples = every > 0 ? (a.sweep_off + n) / every - a.sweep_off / every : 0;
+    for (int i = tid; i < NL; i += B) T[i] = a.W[i];
     for (int i = tid; i < 2 * n_samples; i += B) stage[i] = 0u;
-    int Iw[WMAX], Hw[WMAX];
-    uint64_t live[WMAX];
+    Slot slot[WMAX];
 #pragma unroll
     for (int k = 0; k < WMAX; ++k) {
         const int f = min(tid + B * k, words - 1);
-        Iw[k] = f / half;
-        Hw[k] = f - Iw[k] * half;
-        const int n_live = pstar + (Iw[k] <= istar ? 1 : 0);
-        live[k] = kSpinBits & (~0ull << (3 * (21 - n_live)));
+        const int I = f / half;
+        slot[k] = make_slot(T, I, f - I * half, L, N, a.istar, a.sh_star, pstar);
     }
+    const int sh_up = 60 - a.sh_star;  // between the patch bits of rows L - 1 and 0
     uint64_t ring[P][2][WMAX];
 #pragma unroll
-    for (int r = 0; r < P; ++r) load_codes<WMAX>(ring[r], cg, (size_t)NL, words, tid, B, min(r, n - 1));
+    for (int r = 0; r < P; ++r) load_codes<WMAX>(ring[r], a.codes, (size_t)NL, words, tid, B, min(r, n - 1));
     __syncthreads();
-    // sweeps left before the next sample, and the index of that sample
-    int until = every > 0 ? every - 1 - sweep_off % every : 0x7FFFFFFF;
-    int ks = 0;
+    // both words of every slot stay in registers; LDS holds them for the others
+    uint64_t held[WMAX][2];
+#pragma unroll
+    for (int k = 0; k < WMAX; ++k)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) held[k][c] = lds_load(slot[k].own[c]);
+    __syncthreads();
+    // sweeps left before the next sample, the LDS address of that sample, and
+    // the thread's counts of the last one while they are not yet summed
+    int until = every > 0 ? every - 1 - a.sweep_off % every : 0x7FFFFFFF;
+    uint32_t at = lds_addr(reinterpret_cast<uint64_t*>(stage));
+    bool open = false;
+    uint32_t counts = 0;
+    auto close_sample = [&] {
+        // one wavefront sum of both counts: a wavefront's words (at most 256)
+        // have fewer than 2^16 antiparallel bonds (84 per word) and up spins
+        // (42 per word, with the near neighbour's)
+        const uint32_t both = wave_sum_u32(counts);
+        if ((tid & 63) == 0) {
+            // one 64-bit LDS add (ups in the high half); the address is kept
+            // opaque so that the compiler emits the add alone, not a loop over
+            // the lanes in front of it
+            asm("" : "+v"(at));
+            __hip_atomic_fetch_add((lds_u64*)(size_t)at, ((uint64_t)(both & 0xFFFFu) << 32) | (both >> 16),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        at += 8;
+        open = false;
+    };
     // the next sweep, with its codes cc
     auto sweep = [&](const uint64_t (&cc)[2][WMAX]) {
         const bool meas = until == 0;
         until = meas ? every - 1 : until - 1;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            Nbhd nb[WMAX];
+            uint64_t w[WMAX], near[WMAX], far[WMAX], up[WMAX], dn[WMAX], pt[WMAX];
 #pragma unroll
             for (int k = 0; k < WMAX; ++k) {
-                if (tid + B * k < words) {
-                    const int I = Iw[k], J = 2 * Hw[k] + ((I + c) & 1);
-                    nb[k] = lds_nbhd(T, L, N, istar, I, J, J == 0 ? L - 1 : J - 1, J == L - 1 ? 0 : J + 1);
-                }
+                const Slot& s = slot[k];
+                w[k] = ONE_WAVE ? lds_load(s.own[c]) : held[k][c];
+                near[k] = ONE_WAVE ? lds_load(s.own[1 - c]) : held[k][1 - c];
+                far[k] = lds_load(s.far[c]);
+                up[k] = lds_load(s.up[c]);
+                dn[k] = lds_load(s.dn[c]);
+                pt[k] = lds_load(s.pt[c]);
             }
+            if (c == 0 && open) close_sample();
             uint32_t anti = 0, ups = 0;
 #pragma unroll
             for (int k = 0; k < WMAX; ++k) {
-                if (tid + B * k < words) {
-                    const int I = Iw[k], J = 2 * Hw[k] + ((I + c) & 1);
-                    const uint64_t up = up_of(nb[k], I, sh_star);
-                    const uint64_t dn = down_of(nb[k], I, N, istar, sh_star);
-                    const uint64_t nw = nb[k].w ^ flip_mask(nb[k].w, up, dn, nb[k].lf, nb[k].rt, cc[c][k], live[k]);
-                    T[I * L + J] = nw;
-                    if (c == 1 && meas) measure_word(nw, up, dn, nb[k].lf, nb[k].rt, live[k], anti, ups);
-                }
+                const Slot& s = slot[k];
+                const uint32_t pu = (uint32_t)((pt[k] << sh_up) >> 32);  // bit sh_star -> 60
+                const uint64_t pd = pt[k] >> sh_up;                     // bit 60 -> sh_star
+                uint64_t u = up[k] >> s.su, d = dn[k] << s.sd;
+                u |= (uint64_t)(pu & s.mu) << 32;
+                d = (d & ~s.md) | (pd & s.md);
+                const uint64_t nw = w[k] ^ flip_mask(w[k], u, d, near[k], far[k], cc[c][k], s.live);
+                if (!ONE_WAVE) held[k][c] = nw;
+                lds_store(s.own[c], nw);  // a slot past the last word holds and stores that word
+                // (near in the place of the left neighbour: the pair of
+                // columns holds one word of each colour)
+                if (c == 1 && meas && tid + B * k < words)
+                    measure_word_packed(nw, u, d, near[k], far[k], s.live, anti, ups);
             }
             if (c == 1 && meas) {
-                // one wavefront sum of both counts: a wavefront's words (at
-                // most 256) have fewer than 2^16 antiparallel bonds (84 per
-                // word) and up spins (42 per word, with the left neighbour's)
-                const uint32_t both = wave_sum_u32((anti << 16) | ups);
-                if ((tid & 63) == 0) {
-                    if (ONE_WAVE) {
-                        stage[2 * ks] = both >> 16;
-                        stage[2 * ks + 1] = both & 0xFFFFu;
-                    } else {
-                        atomicAdd(&stage[2 * ks], both >> 16);
-                        atomicAdd(&stage[2 * ks + 1], both & 0xFFFFu);
-                    }
-                }
-                ks += 1;
+                counts = (anti << 16) | ups;
+                open = true;
             }
             if (ONE_WAVE)
                 wave_lds_order();
@@ -225,42 +294,78 @@ __global__ void __launch_bounds__(kApplyMaxBlock) k_wave_apply(const LatticeDesc
 #pragma unroll
         for (int r = 0; r < P; ++r) {
             sweep(ring[r]);
-            load_codes<WMAX>(ring[r], cg, (size_t)NL, words, tid, B, min(j0 + r + P, n - 1));
+            load_codes<WMAX>(ring[r], a.codes, (size_t)NL, words, tid, B, min(j0 + r + P, n - 1));
         }
     }
 #pragma unroll
     for (int r = 0; r < P; ++r)
         if (j0 + r < n) sweep(ring[r]);
+    if (open) close_sample();
     __syncthreads();
-    // the samples of the pass, in the first wavefront: lane l takes samples
-    // l, l + 64, ...; the moment sums are merged across lanes exactly
-    if (tid < 64 && n_samples > 0) {
-        const int64_t nn = (int64_t)L * (int64_t)L;
+    for (int i = tid; i < NL; i += B) a.W[i] = T[i];
+    return n_samples;
+}
+
+// The samples of an apply pass, in the first wavefront: lane l takes samples
+// l, l + 64, ...; E, M to the series (each optional), the moment sums merged
+// exactly over the lanes into lane 0's result.
+__device__ __forceinline__ Moments finish_samples(const uint32_t* __restrict__ stage, int n_samples, int L,
+                                                  int64_t* series_E, int64_t* series_M) {
+    const int64_t nn = (int64_t)L * (int64_t)L;
+    Moments part = {};
+    for (int k = (int)threadIdx.x; k < n_samples; k += 64) {
+        const int64_t E = 2 * (int64_t)stage[2 * k] - 2 * nn, M = 2 * (int64_t)stage[2 * k + 1] - nn;
+        if (series_E) series_E[k] = E;
+        if (series_M) series_M[k] = M;
+        add_sample(part, E, M);
+    }
+    wave_merge_moments(part);
+    return part;
+}
+
+}  // namespace
+
+// Apply pass: one workgroup of A = blockDim.x / 64 wavefronts (ONE_WAVE: A
+// = 1) per lattice entry, S sweeps of the pass (local sweep index s =
+// sweep_off + j of the chunk; a sample after it when (s + 1) % every == 0,
+// every > 0).  LDS: the lattice [N][L], then one (antiparallel bonds, up
+// spins) pair per sample of the pass.
+template <int WMAX, int P, bool ONE_WAVE>
+__global__ void __launch_bounds__(kApplyMaxBlock) k_wave_apply(const LatticeDesc* __restrict__ descs,
+                                                               LatticeState* __restrict__ states,
+                                                               const DrawLat* __restrict__ lats,
+                                                               const uint64_t* __restrict__ codes, int32_t sweep_off,
+                                                               int32_t S, int32_t every) {
+    extern __shared__ uint64_t lds[];
+    const DrawLat dl = lats[blockIdx.x];
+    const LatticeDesc& d = descs[dl.lat];
+    LatticeState& state = states[dl.lat];
+    const int n = min(S, d.sweep_limit - sweep_off);
+    if (n <= 0) return;  // uniform over the workgroup
+    const int L = d.L;
+    uint32_t* __restrict__ stage = reinterpret_cast<uint32_t*>(lds + d.N * L);  // [samples][2]
+    const ApplyTask task = {d.W, L, d.N, d.istar, d.sh_star, codes + dl.base, n, sweep_off, every};
+    const int n_samples = apply_sweeps<WMAX, P, ONE_WAVE>(task, lds, stage);
+    if (threadIdx.x < 64 && n_samples > 0) {
         const int64_t idx = state.series_idx;
-        Moments part = {};
-        for (int k = tid; k < n_samples; k += 64) {
-            const int64_t E = 2 * (int64_t)stage[2 * k] - 2 * nn, M = 2 * (int64_t)stage[2 * k + 1] - nn;
-            if (d.series_E) d.series_E[idx + k] = E;
-            if (d.series_M) d.series_M[idx + k] = M;
-            add_sample(part, E, M);
-        }
-        wave_merge_moments(part);
-        if (tid == 0) {
+        const Moments part = finish_samples(stage, n_samples, L, d.series_E ? d.series_E + idx : nullptr,
+                                            d.series_M ? d.series_M + idx : nullptr);
+        if (threadIdx.x == 0) {
             Moments m = state.mom;
             merge_moments(m, part);
             state.mom = m;
+            const int64_t nn = (int64_t)L * (int64_t)L;
             const int k = n_samples - 1;
             state.last_E = 2 * (int64_t)stage[2 * k] - 2 * nn;
             state.last_M = 2 * (int64_t)stage[2 * k + 1] - nn;
             state.series_idx = idx + n_samples;
         }
     }
-    for (int i = tid; i < NL; i += B) G[i] = T[i];
 }
 
 int32_t wave_apply_words_per_thread(int32_t L, int32_t N, int32_t block) {
     const int32_t w = (N * (L / 2) + block - 1) / block;
-    return w <= 1 ? 1 : w <= 2 ? 2 : w <= 4 ? 4 : 0;
+    return w <= 1 ? 1 : w <= 4 ? w : 0;
 }
 
 size_t wave_apply_lds_bytes(int32_t NL, int32_t max_samples) { return (size_t)NL * 8 + (size_t)max_samples * 8; }
@@ -269,9 +374,11 @@ hipError_t allow_wave_apply_lds(int device) {
     const int lim = (int)resident_lds_limit(device);
     const void* fs[] = {reinterpret_cast<const void*>(&k_wave_apply<1, 8, true>),
                         reinterpret_cast<const void*>(&k_wave_apply<2, 8, true>),
+                        reinterpret_cast<const void*>(&k_wave_apply<3, 4, true>),
                         reinterpret_cast<const void*>(&k_wave_apply<4, 4, true>),
                         reinterpret_cast<const void*>(&k_wave_apply<1, 8, false>),
                         reinterpret_cast<const void*>(&k_wave_apply<2, 8, false>),
+                        reinterpret_cast<const void*>(&k_wave_apply<3, 4, false>),
                         reinterpret_cast<const void*>(&k_wave_apply<4, 4, false>)};
     for (const void* f : fs) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
@@ -306,6 +413,7 @@ hipError_t launch_wave_apply(int wmax, int block, const LatticeDesc* descs, Latt
     switch (wmax) {
         case 1: ISING_WAVE_APPLY(1, 8) break;
         case 2: ISING_WAVE_APPLY(2, 8) break;
+        case 3: ISING_WAVE_APPLY(3, 4) break;
         case 4: ISING_WAVE_APPLY(4, 4) break;
         default: return hipErrorInvalidValue;
     }

@@ -210,8 +210,8 @@ hipError_t launch_small(int block, const LatticeDesc* descs, LatticeState* state
 // max_n_draw = the largest n_draw of the list.
 hipError_t launch_draw_codes(const LatticeDesc* descs, const LatticeState* states, const DrawLat* lats, int32_t n_lats,
                              int32_t max_n_draw, uint64_t* codes, int32_t sweep_off, int32_t S, hipStream_t s);
-// Apply pass over the same sweeps: one workgroup of `block` threads (64,
-// 128 or 256) per listed lattice, wmax (1, 2 or 4:
+// Apply pass over the same sweeps: one workgroup of `block` threads (a
+// multiple of 64, at most 256) per listed lattice, wmax (1 to 4:
 // wave_apply_words_per_thread) words of a colour per thread, codes loaded
 // from the buffer into registers ahead of use; lds_bytes =
 // wave_apply_lds_bytes(largest N L, S).  Samples as launch_resident.
