@@ -297,7 +297,11 @@ int ising_get_tiling(ising_lattice* h, int32_t* sweeps_per_launch, int32_t* tile
    L = 192 the whole lattice in one workgroup of one thread per word of a
    colour, a power of two from 64 to 1024; below L = 1024 bands of 8
    columns, 512 threads; from there bands of 2 ceil(L / 512) columns, 1024
-   threads; 1000 sweeps per launch) when those fit. */
+   threads; 1000 sweeps per launch) when those fit.  Until the caller sets a
+   shape (or ising_set_tiling), lattices with at most 2048 words of a colour
+   (L <= 292) run in one workgroup with their draws spread over the chip
+   instead, a launch drawing the next sweeps beside the workgroup that applies
+   the last ones; these launches wait for nothing. */
 int ising_set_resident_tiles(ising_lattice* h, int32_t tile_cols, int32_t block, int32_t max_sweeps);
 /* Bound of every wait of the resident-tile launches for their neighbour
    tiles, in ticks of the GPU's 100 MHz constant clock; 0 restores the
@@ -387,8 +391,9 @@ int ising_batch_get_sweep_count(ising_batch* b, int32_t i, uint64_t* t);
    acceptance codes (which do not depend on the spins, Table 1) drawn by a
    launch spread over the whole chip, draw_sweeps sweeps at a time (a
    device buffer of draw_sweeps x 8 x their words bytes, capped at
-   256 MiB), and applied by one workgroup of min(resident_block, 256)
-   threads per lattice.  Results never depend on the plan. */
+   256 MiB), and applied by one workgroup of at most min(resident_block, 256)
+   threads per lattice (at most 1024 where that is 256 and there are no more
+   such lattices than compute units).  Results never depend on the plan. */
 typedef struct {
     int32_t resident_max_L;   /* 0 = no resident lattices                    */
     int32_t resident_block;   /* threads per resident workgroup (64..1024)   */

@@ -400,12 +400,17 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
             b->draw_max_items = std::max(b->draw_max_items, dl.back().n_draw);
             b->draw_wmax = std::max(b->draw_wmax, wave_apply_words_per_thread(g.L, g.N, apply_block(p)));
         }
-        // no more wavefronts than the largest lattice has words for: an idle one
-        // still takes part in every barrier (8 lattices of L = 16: 0.40 us a
-        // sweep with four wavefronts, 0.36 with one, which needs no barrier)
         int32_t draw_words = 1;
         for (int32_t i : ids_draw) draw_words = std::max(draw_words, b->geo[i].N * (b->geo[i].L / 2));
-        b->draw_block = ((draw_words + b->draw_wmax - 1) / b->draw_wmax + 63) / 64 * 64;
+        // No more lattices than compute units: a word per thread, so that all four
+        // SIMDs of the unit share the lattice's words (8 lattices, us per sweep
+        // with at most 256 threads / a word per thread: L = 100 0.67 / 0.58, 128
+        // 0.73 / 0.61, 168 1.04 / 0.74, 204 1.30 / 0.89).  With more lattices the
+        // units are shared anyway (512 lattices of L = 128: 4.1 with 256 threads).
+        int cus = 0;
+        ISING_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device));
+        if (apply_block(p) == 256 && (int)ids_draw.size() <= cus) b->draw_wmax = 1;
+        b->draw_block = wave_apply_block(draw_words, b->draw_wmax);
         b->draw_S = (int32_t)std::min<int64_t>(p.draw_sweeps, std::max<int64_t>(1, (int64_t)(kMaxDrawBytes / 8) / words));
         int64_t base = 0;
         for (auto& e : dl) {

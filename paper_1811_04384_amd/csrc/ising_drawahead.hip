@@ -8,9 +8,11 @@
 // leaves all but a few compute units idle when each lattice's workgroup
 // draws its own codes; here a draw pass spreads the codes of many sweeps of
 // every such lattice over the whole chip into a global buffer, and an apply
-// pass then runs the sweeps: one workgroup of one to four wavefronts per
+// pass then runs the sweeps: one workgroup of one to sixteen wavefronts per
 // lattice, the lattice in LDS, each thread's codes loaded into registers
-// several sweeps ahead of their use.  What is left per half-sweep is one
+// several sweeps ahead of their use.  A batch runs the two passes as two
+// launches; a single lattice's launches draw the next chunk of sweeps beside
+// the workgroup that applies the last one.  What is left per half-sweep is one
 // word update per thread and word -- a chain of a few hundred cycles -- and
 // a workgroup barrier; with one wavefront not even that, as a wavefront's
 // LDS operations complete in issue order, so one half-sweep's stores are
@@ -29,7 +31,7 @@ namespace ising {
 namespace {
 
 constexpr int kDrawBlock = 256;
-constexpr int kApplyMaxBlock = 256;
+constexpr int kApplyMaxBlock = 1024;
 
 // Order a lone wavefront's LDS stores of one half-sweep before the loads of
 // the next (the hardware completes them in issue order; this keeps the
@@ -308,30 +310,30 @@ __device__ __forceinline__ int apply_sweeps(const ApplyTask& a, uint64_t* __rest
 
 // The samples of an apply pass, in the first wavefront: lane l takes samples
 // l, l + 64, ...; E, M to the series (each optional), the moment sums merged
-// exactly over the lanes into lane 0's result.
+// exactly over the lanes into lane 0's result (when wanted: moments).
 __device__ __forceinline__ Moments finish_samples(const uint32_t* __restrict__ stage, int n_samples, int L,
-                                                  int64_t* series_E, int64_t* series_M) {
+                                                  int64_t* series_E, int64_t* series_M, bool moments) {
     const int64_t nn = (int64_t)L * (int64_t)L;
     Moments part = {};
     for (int k = (int)threadIdx.x; k < n_samples; k += 64) {
         const int64_t E = 2 * (int64_t)stage[2 * k] - 2 * nn, M = 2 * (int64_t)stage[2 * k + 1] - nn;
         if (series_E) series_E[k] = E;
         if (series_M) series_M[k] = M;
-        add_sample(part, E, M);
+        if (moments) add_sample(part, E, M);
     }
-    wave_merge_moments(part);
+    if (moments) wave_merge_moments(part);
     return part;
 }
 
 }  // namespace
 
-// Apply pass: one workgroup of A = blockDim.x / 64 wavefronts (ONE_WAVE: A
-// = 1) per lattice entry, S sweeps of the pass (local sweep index s =
+// Apply pass: one workgroup of at most BLOCK threads (64: one wavefront) per
+// lattice entry, S sweeps of the pass (local sweep index s =
 // sweep_off + j of the chunk; a sample after it when (s + 1) % every == 0,
 // every > 0).  LDS: the lattice [N][L], then one (antiparallel bonds, up
 // spins) pair per sample of the pass.
-template <int WMAX, int P, bool ONE_WAVE>
-__global__ void __launch_bounds__(kApplyMaxBlock) k_wave_apply(const LatticeDesc* __restrict__ descs,
+template <int WMAX, int P, int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_wave_apply(const LatticeDesc* __restrict__ descs,
                                                                LatticeState* __restrict__ states,
                                                                const DrawLat* __restrict__ lats,
                                                                const uint64_t* __restrict__ codes, int32_t sweep_off,
@@ -345,11 +347,11 @@ __global__ void __launch_bounds__(kApplyMaxBlock) k_wave_apply(const LatticeDesc
     const int L = d.L;
     uint32_t* __restrict__ stage = reinterpret_cast<uint32_t*>(lds + d.N * L);  // [samples][2]
     const ApplyTask task = {d.W, L, d.N, d.istar, d.sh_star, codes + dl.base, n, sweep_off, every};
-    const int n_samples = apply_sweeps<WMAX, P, ONE_WAVE>(task, lds, stage);
+    const int n_samples = apply_sweeps<WMAX, P, BLOCK == 64>(task, lds, stage);
     if (threadIdx.x < 64 && n_samples > 0) {
         const int64_t idx = state.series_idx;
         const Moments part = finish_samples(stage, n_samples, L, d.series_E ? d.series_E + idx : nullptr,
-                                            d.series_M ? d.series_M + idx : nullptr);
+                                            d.series_M ? d.series_M + idx : nullptr, true);
         if (threadIdx.x == 0) {
             Moments m = state.mom;
             merge_moments(m, part);
@@ -363,23 +365,80 @@ __global__ void __launch_bounds__(kApplyMaxBlock) k_wave_apply(const LatticeDesc
     }
 }
 
+// One lattice of a handle: workgroup 0 applies the sweeps drawn by the launch
+// before, the others draw those of the next one, a word of one sweep per
+// thread (the chip is otherwise idle, so the draws' latency is what counts:
+// a thread's four words one after another would take four times as long).
+// us per call with a sample each sweep, before (one resident workgroup that
+// draws its own codes; from L = 194 bands of eight columns that exchange their
+// boundary words) and now, 20 and 1000 sweeps: L = 16 70/2160 and 27/380, 64
+// 82/2754 and 30/476, 128 97/3442 and 33/629, 192 137/5346 and 44/1029, 204
+// 83/2745 and 43/1019, 256 82/2616 and 58/1766, 292 84/2770 and 59/1779.
+template <int WMAX, int P, int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_drawn(DrawnLaunch a) {
+    extern __shared__ uint64_t lds[];
+    const int L = a.L, N = a.N, NL = N * L;
+    if (blockIdx.x > 0) {
+        const int f = (int)(blockIdx.x - 1) * (int)blockDim.x + (int)threadIdx.x;
+        const int j = f / NL, r = f - j * NL;
+        if (j >= a.n_draw) return;
+        const int half = L >> 1;
+        const int c = r >= N * half ? 1 : 0;
+        const int I = (r - c * N * half) / half, h = r - (c * N + I) * half;
+        const int par = (I + c) & 1;
+        const int J = 2 * h + par;
+        const int n_live = (L - 1) / N + (I <= a.istar ? 1 : 0);
+        const uint64_t t = a.t_draw + (uint64_t)j;
+        const uint32_t t_lo = (uint32_t)t, t_hi = (uint32_t)(t >> 32);
+        const RoundKeys rk = round_keys(a.k0, a.k1);
+        auto block = [&](uint32_t c1, int g) {
+            return philox_lane_c1(t_lo, c1, t_hi, (uint32_t)g | (1u << 3), a.k0, a.k1, rk);
+        };
+        AcceptWord acc;
+        accept_word(acc, [&](int g) { return block((uint32_t)I * (uint32_t)L + (uint32_t)J, g); }, n_live, a.t4, a.t8);
+        uint32_t u20 = 0;  // a dead slot when n_live < 21
+        if (n_live == 21) {
+            const U4 r5 = block((uint32_t)I * (uint32_t)L + (uint32_t)((J & ~7) | par), 5);
+            u20 = pick4(make_uint4(r5.x, r5.y, r5.z, r5.w), (uint32_t)h & 3u);
+        }
+        acc.add<20>(u20, a.t4, a.t8);
+        a.drawn[(size_t)j * (size_t)NL + r] = acc.word();
+        return;
+    }
+    if (a.n_apply <= 0) return;
+    uint32_t* __restrict__ stage = reinterpret_cast<uint32_t*>(lds + NL);  // [samples][2]
+    const ApplyTask task = {a.W, L, N, a.istar, a.sh_star, a.codes, a.n_apply, a.sweep_off, a.every};
+    const int n_samples = apply_sweeps<WMAX, P, BLOCK == 64>(task, lds, stage);
+    if (threadIdx.x < 64 && n_samples > 0) {
+        const Moments part = finish_samples(stage, n_samples, L, a.series_E, a.series_M, a.mom != nullptr);
+        if (threadIdx.x == 0 && a.mom) {
+            Moments m = *a.mom;
+            merge_moments(m, part);
+            *a.mom = m;
+        }
+    }
+}
+
 int32_t wave_apply_words_per_thread(int32_t L, int32_t N, int32_t block) {
     const int32_t w = (N * (L / 2) + block - 1) / block;
     return w <= 1 ? 1 : w <= 4 ? w : 0;
 }
 
+int32_t wave_apply_block(int32_t words, int32_t wmax) { return ((words + wmax - 1) / wmax + 63) / 64 * 64; }
+
 size_t wave_apply_lds_bytes(int32_t NL, int32_t max_samples) { return (size_t)NL * 8 + (size_t)max_samples * 8; }
 
 hipError_t allow_wave_apply_lds(int device) {
     const int lim = (int)resident_lds_limit(device);
-    const void* fs[] = {reinterpret_cast<const void*>(&k_wave_apply<1, 8, true>),
-                        reinterpret_cast<const void*>(&k_wave_apply<2, 8, true>),
-                        reinterpret_cast<const void*>(&k_wave_apply<3, 4, true>),
-                        reinterpret_cast<const void*>(&k_wave_apply<4, 4, true>),
-                        reinterpret_cast<const void*>(&k_wave_apply<1, 8, false>),
-                        reinterpret_cast<const void*>(&k_wave_apply<2, 8, false>),
-                        reinterpret_cast<const void*>(&k_wave_apply<3, 4, false>),
-                        reinterpret_cast<const void*>(&k_wave_apply<4, 4, false>)};
+    const void* fs[] = {reinterpret_cast<const void*>(&k_wave_apply<1, 8, 64>),
+                        reinterpret_cast<const void*>(&k_wave_apply<2, 8, 64>),
+                        reinterpret_cast<const void*>(&k_wave_apply<3, 4, 64>),
+                        reinterpret_cast<const void*>(&k_wave_apply<4, 4, 64>),
+                        reinterpret_cast<const void*>(&k_wave_apply<1, 8, 256>),
+                        reinterpret_cast<const void*>(&k_wave_apply<2, 8, 256>),
+                        reinterpret_cast<const void*>(&k_wave_apply<3, 4, 256>),
+                        reinterpret_cast<const void*>(&k_wave_apply<4, 4, 256>),
+                        reinterpret_cast<const void*>(&k_wave_apply<1, 4, 1024>)};
     for (const void* f : fs) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
         if (e != hipSuccess) return e;
@@ -403,21 +462,56 @@ hipError_t launch_wave_apply(int wmax, int block, const LatticeDesc* descs, Latt
     if (n_lats <= 0 || S <= 0) return hipSuccess;
     if (block < 64 || block > kApplyMaxBlock || block % 64) return hipErrorInvalidValue;
     const dim3 grid(n_lats), blk(block);
-#define ISING_WAVE_APPLY(W_, P_)                                                                                 \
-    if (block == 64)                                                                                             \
-        hipLaunchKernelGGL((k_wave_apply<W_, P_, true>), grid, blk, lds_bytes, s, descs, states, lats, codes,   \
-                           sweep_off, S, every);                                                                 \
-    else                                                                                                         \
-        hipLaunchKernelGGL((k_wave_apply<W_, P_, false>), grid, blk, lds_bytes, s, descs, states, lats, codes,  \
-                           sweep_off, S, every);
-    switch (wmax) {
-        case 1: ISING_WAVE_APPLY(1, 8) break;
-        case 2: ISING_WAVE_APPLY(2, 8) break;
-        case 3: ISING_WAVE_APPLY(3, 4) break;
-        case 4: ISING_WAVE_APPLY(4, 4) break;
-        default: return hipErrorInvalidValue;
+#define ISING_WAVE_APPLY(W_, P_, B_)                                                                              \
+    hipLaunchKernelGGL((k_wave_apply<W_, P_, B_>), grid, blk, lds_bytes, s, descs, states, lats, codes, sweep_off, \
+                       S, every)
+    if (block == 64) {
+        switch (wmax) {
+            case 1: ISING_WAVE_APPLY(1, 8, 64); break;
+            case 2: ISING_WAVE_APPLY(2, 8, 64); break;
+            case 3: ISING_WAVE_APPLY(3, 4, 64); break;
+            case 4: ISING_WAVE_APPLY(4, 4, 64); break;
+            default: return hipErrorInvalidValue;
+        }
+    } else if (block <= 256) {
+        switch (wmax) {
+            case 1: ISING_WAVE_APPLY(1, 8, 256); break;
+            case 2: ISING_WAVE_APPLY(2, 8, 256); break;
+            case 3: ISING_WAVE_APPLY(3, 4, 256); break;
+            case 4: ISING_WAVE_APPLY(4, 4, 256); break;
+            default: return hipErrorInvalidValue;
+        }
+    } else if (wmax == 1) {
+        ISING_WAVE_APPLY(1, 4, 1024);
+    } else {
+        return hipErrorInvalidValue;
     }
 #undef ISING_WAVE_APPLY
+    return hipGetLastError();
+}
+
+// Two words per thread at the most: a third leaves the 1024 threads without
+// registers for codes loaded ahead (L = 320, 1000 sweeps with a sample each: 2699 us
+// against 2662 by bands of columns; L = 292 with two words 1779 against 2770).
+int32_t drawn_max_words() { return 2 * kApplyMaxBlock; }
+
+size_t drawn_lds_bytes(int32_t L, int32_t N) { return wave_apply_lds_bytes(N * L, kDrawnMaxSweeps); }
+
+hipError_t launch_drawn(const DrawnLaunch& a, hipStream_t s) {
+    const int64_t NL = (int64_t)a.N * a.L;
+    const int32_t words = a.N * (a.L / 2);
+    if (words > drawn_max_words() || a.n_apply > kDrawnMaxSweeps || a.n_draw > kDrawnMaxSweeps)
+        return hipErrorInvalidValue;
+    const int32_t wmax = wave_apply_words_per_thread(a.L, a.N, kApplyMaxBlock);
+    const int block = wave_apply_block(words, wmax);
+    const dim3 grid((unsigned)(1 + (a.n_draw * NL + block - 1) / block)), blk(block);
+    const size_t lds_bytes = drawn_lds_bytes(a.L, a.N);
+#define ISING_DRAWN(W_, P_, B_) hipLaunchKernelGGL((k_drawn<W_, P_, B_>), grid, blk, lds_bytes, s, a)
+    if (wmax == 2) ISING_DRAWN(2, 2, 1024);
+    else if (block > 256) ISING_DRAWN(1, 4, 1024);
+    else if (block > 64) ISING_DRAWN(1, 8, 256);
+    else ISING_DRAWN(1, 8, 64);
+#undef ISING_DRAWN
     return hipGetLastError();
 }
 

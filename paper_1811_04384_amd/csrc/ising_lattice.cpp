@@ -51,6 +51,12 @@ struct ising_lattice {
     uint64_t res_wait = 0;          // bound of each wait, 100 MHz clock ticks
     Partial* d_rpart = nullptr;     // res_sweeps x n_res partial sums
     int64_t* d_rEM = nullptr;       // 2 x res_sweeps sample scratch (moments without a series)
+    // sweeps applied from codes drawn chip-wide (drawn_sweeps = 0: off), two
+    // buffers of drawn_sweeps sweeps' codes in turn
+    int32_t drawn_sweeps = 0;
+    uint64_t* d_codes = nullptr;
+    int drawn_buf = 0;              // the buffer the next launch draws into
+    DrawnLaunch drawn = {};         // its n_apply sweeps are drawn and not yet applied
 };
 
 // Temperatures of a scan whose moment sums are read back together.
@@ -58,6 +64,7 @@ constexpr int32_t kScanBlock = 256;
 
 static int ensure_desc(ising_lattice* h);
 static void free_resident(ising_lattice* h);
+static bool enable_drawn(ising_lattice* h, int32_t tile_cols, int32_t block, int32_t max_sweeps);
 
 namespace ising {
 std::string& last_error_ref() {
@@ -146,6 +153,7 @@ static void release(ising_lattice* h) {
     if (h->h_err) (void)hipHostFree(h->h_err);
     if (h->d_rpart) (void)hipFree(h->d_rpart);
     if (h->d_rEM) (void)hipFree(h->d_rEM);
+    if (h->d_codes) (void)hipFree(h->d_codes);
     delete h;
 }
 
@@ -199,10 +207,10 @@ static int create_impl(int32_t L, uint64_t seed, int32_t init, void* dev_words, 
         return hip_fail(e, "init kernel launch");
     }
     // Up to 7680 columns resident tiles are faster than one launch per
-    // half-sweep at every size measured (attempts/ns, resident against
-    // half-sweep launches, E/M every 10 sweeps: L = 64 1.7 / 0.7, 128
-    // 5.2 / 2.9, 256 11.6 / 10.2, 512 47.6 / 45.0, 1024 190 / 152, 2048
-    // 743 / 525, 4096 2182 / 1120, 5120 1687 / 1311, 7680 1815 / 1611).
+    // half-sweep at every size measured (us per sweep, resident against
+    // half-sweep launches, E/M every 10 sweeps: L = 294 2.7 / 8.9, 512 2.6 /
+    // 8.5, 1024 3.0 / 9.4, 2048 4.0 / 9.8, 4096 8.1 / 14.8, 5120 14.8 /
+    // 19.3, 7680 31.7 / 33.0).
     // Shapes: up to L = 192 the whole lattice in one workgroup, a thread per
     // word of a colour (a power of two, 64 to 1024); below L = 1024 bands
     // of 8 columns, 512 threads; from there bands of 2 ceil(L / 512)
@@ -220,7 +228,8 @@ static int create_impl(int32_t L, uint64_t seed, int32_t init, void* dev_words, 
             w = 8;
             block = 512;
         }
-        if (ising_set_resident_tiles(h, w, block, 1000) != ISING_OK) last_error_ref().clear();
+        if (!enable_drawn(h, w, block, 1000) && ising_set_resident_tiles(h, w, block, 1000) != ISING_OK)
+            last_error_ref().clear();
     }
     *out = h;
     return ISING_OK;
@@ -365,6 +374,49 @@ static int enqueue_resident_sweeps(ising_lattice* h, uint64_t t0, double T, int6
     return ISING_OK;
 }
 
+// One launch: the pending sweeps applied, the n sweeps from t on drawn (0: none)
+// to be pending next.
+static int drawn_launch(ising_lattice* h, uint64_t t, int32_t n) {
+    DrawnLaunch& a = h->drawn;
+    const size_t sweep_words = (size_t)h->g.N * (size_t)h->g.L;
+    uint64_t* const next = h->d_codes + (size_t)h->drawn_buf * (size_t)h->drawn_sweeps * sweep_words;
+    a.W = h->W;
+    a.L = h->g.L;
+    a.N = h->g.N;
+    a.istar = h->g.istar;
+    a.sh_star = h->g.sh_star;
+    a.k0 = (uint32_t)h->seed;
+    a.k1 = (uint32_t)(h->seed >> 32);
+    a.t_draw = t;
+    a.n_draw = n;
+    a.drawn = next;
+    const hipError_t e = a.n_apply > 0 || n > 0 ? launch_drawn(a, h->stream) : hipSuccess;
+    a.n_apply = e == hipSuccess ? n : 0;
+    a.codes = next;
+    h->drawn_buf ^= 1;
+    return e == hipSuccess ? ISING_OK : hip_fail(e, "launch_drawn");
+}
+
+// Enqueue n sweeps by drawn codes.  The last of them are left pending: the
+// caller follows with drawn_launch(h, 0, 0), or with the next sweeps.
+static int enqueue_drawn_sweeps(ising_lattice* h, uint64_t t0, double T, int64_t n, int32_t every, int64_t* dev_E,
+                                int64_t* dev_M, Moments* mom) {
+    DrawnLaunch& a = h->drawn;
+    for (int64_t done = 0; done < n;) {
+        const int32_t kb = (int32_t)std::min<int64_t>(h->drawn_sweeps, n - done);
+        thresholds_of(T, &a.t4, &a.t8);
+        const int rc = drawn_launch(h, t0 + (uint64_t)done, kb);
+        if (rc != ISING_OK) return rc;
+        a.every = every;
+        a.sweep_off = every > 0 ? (int32_t)(done % every) : 0;
+        a.series_E = dev_E ? dev_E + done / every : nullptr;
+        a.series_M = dev_M ? dev_M + done / every : nullptr;
+        a.mom = mom;
+        done += kb;
+    }
+    return ISING_OK;
+}
+
 // Enqueue n sweeps of lattice words W (the handle's or a scratch copy)
 // starting at absolute sweep t0.
 static int enqueue_sweeps(const ising_lattice* h, uint64_t* W, uint64_t t0, double T, int64_t n, int32_t every,
@@ -387,14 +439,20 @@ static int enqueue_sweeps(const ising_lattice* h, uint64_t* W, uint64_t t0, doub
     return ISING_OK;
 }
 
+// defer: the last sweeps may stay pending (drawn codes); the caller applies them.
 static int sweep_impl(ising_lattice* h, double T, int64_t n, int32_t every, int64_t* dev_E, int64_t* dev_M,
-                      Moments* mom = nullptr) {
+                      Moments* mom = nullptr, bool defer = false) {
     if (!h) return fail(ISING_EINVAL, "ising_sweep: null handle");
     if (!valid_T(T)) return fail(ISING_EINVAL, "ising_sweep: T must be finite and > 0 (got %g)", T);
     if (n < 0) return fail(ISING_EINVAL, "ising_sweep: n_sweeps must be >= 0");
     int rc = resident_error(h);
     if (rc != ISING_OK) return rc;
-    rc = enqueue_sweeps(h, h->W, h->t, T, n, every, dev_E, dev_M, mom, h->wpt, h->block);
+    if (h->drawn_sweeps > 0) {
+        rc = enqueue_drawn_sweeps(h, h->t, T, n, every, dev_E, dev_M, mom);
+        if (rc == ISING_OK && !defer) rc = drawn_launch(h, 0, 0);
+    } else {
+        rc = enqueue_sweeps(h, h->W, h->t, T, n, every, dev_E, dev_M, mom, h->wpt, h->block);
+    }
     if (rc != ISING_OK) return rc;
     h->t += (uint64_t)n;
     return ISING_OK;
@@ -430,9 +488,11 @@ int ising_scan(ising_lattice* h, int32_t n_T, const double* T, int64_t therm, in
         const int32_t nb = std::min(kScanBlock, n_T - j0);
         ISING_HIP(hipMemsetAsync(h->d_scan, 0, sizeof(Moments) * (size_t)nb, h->stream));
         for (int32_t i = 0; i < nb; ++i) {
-            int rc = sweep_impl(h, T[j0 + i], therm, 0, nullptr, nullptr);
-            if (rc == ISING_OK) rc = sweep_impl(h, T[j0 + i], meas, every, nullptr, nullptr, h->d_scan + i);
+            int rc = sweep_impl(h, T[j0 + i], therm, 0, nullptr, nullptr, nullptr, true);
+            if (rc == ISING_OK) rc = sweep_impl(h, T[j0 + i], meas, every, nullptr, nullptr, h->d_scan + i, true);
+            if (rc == ISING_OK && i + 1 == nb && h->drawn_sweeps > 0) rc = drawn_launch(h, 0, 0);
             if (rc != ISING_OK) {
+                h->drawn.n_apply = 0;
                 (void)hipStreamSynchronize(h->stream);
                 return rc;
             }
@@ -691,6 +751,9 @@ static void free_resident(ising_lattice* h) {
     if (h->d_flags) (void)hipFree(h->d_flags);
     if (h->d_rpart) (void)hipFree(h->d_rpart);
     if (h->d_rEM) (void)hipFree(h->d_rEM);
+    if (h->d_codes) (void)hipFree(h->d_codes);
+    h->d_codes = nullptr;
+    h->drawn_sweeps = 0;
     h->d_res = nullptr;
     h->d_exch = nullptr;
     h->d_flags = nullptr;
@@ -724,15 +787,15 @@ static std::vector<PersistTile> resident_tile_table(int32_t lattice, int32_t L, 
 // Largest number of sweeps of one resident-tile launch.
 constexpr int32_t kResidentMaxSweeps = 4096;
 
-int ising_set_resident_tiles(ising_lattice* h, int32_t tile_cols, int32_t block, int32_t max_sweeps) {
-    if (!h) return fail(ISING_EINVAL, "ising_set_resident_tiles: null handle");
-    ISING_HIP(hipStreamSynchronize(h->stream));  // earlier launches may still read the old tables
-    int rc = resident_error(h);
-    if (rc != ISING_OK) return rc;
-    if (tile_cols == 0) {
-        free_resident(h);
-        return ISING_OK;
-    }
+// A shape of resident tiles that this device can run.
+struct PersistShape {
+    std::vector<PersistTile> tiles;
+    int32_t cols = 0, block = 0, sweeps = 0;
+    size_t lds = 0;
+};
+
+static int resident_shape(const ising_lattice* h, int32_t tile_cols, int32_t block, int32_t max_sweeps,
+                          PersistShape* sh) {
     const int32_t L = h->g.L, N = h->g.N;
     if (tile_cols < 2 || tile_cols % 2) return fail(ISING_EINVAL, "ising_set_resident_tiles: tile_cols must be even and >= 2");
     if (!valid_block(block, 1024))
@@ -745,19 +808,47 @@ int ising_set_resident_tiles(ising_lattice* h, int32_t tile_cols, int32_t block,
         return fail(ISING_EINVAL, "ising_set_resident_tiles: a tile needs %zu bytes of LDS, %zu available", lds,
                     persist_lds_limit(h->device));
     ISING_HIP(allow_persist_lds(h->device));
-    std::vector<PersistTile> tiles = resident_tile_table(0, L, w, 0);
-    const int32_t n = (int32_t)tiles.size();
+    sh->tiles = resident_tile_table(0, L, w, 0);
+    const int32_t n = (int32_t)sh->tiles.size();
     int64_t capacity = 0;
     ISING_HIP(persist_capacity(block, lds, h->device, &capacity));
     if (n > capacity)
         return fail(ISING_EINVAL, "ising_set_resident_tiles: %d tiles of %d threads and %zu bytes of LDS exceed the %lld "
                     "the device holds at once", n, block, lds, (long long)capacity);
+    sh->cols = w;
+    sh->block = block;
+    sh->sweeps = max_sweeps;
+    sh->lds = lds;
+    return ISING_OK;
+}
+
+static void keep_resident_shape(ising_lattice* h, const PersistShape& sh) {
+    h->n_res = (int32_t)sh.tiles.size();
+    h->res_cols = sh.cols;
+    h->res_block = sh.block;
+    h->res_sweeps = sh.sweeps;
+    h->res_lds = sh.lds;
+}
+
+int ising_set_resident_tiles(ising_lattice* h, int32_t tile_cols, int32_t block, int32_t max_sweeps) {
+    if (!h) return fail(ISING_EINVAL, "ising_set_resident_tiles: null handle");
+    ISING_HIP(hipStreamSynchronize(h->stream));  // earlier launches may still read the old tables
+    int rc = resident_error(h);
+    if (rc != ISING_OK) return rc;
+    if (tile_cols == 0) {
+        free_resident(h);
+        return ISING_OK;
+    }
+    PersistShape sh;
+    rc = resident_shape(h, tile_cols, block, max_sweeps, &sh);
+    if (rc != ISING_OK) return rc;
+    const int32_t N = h->g.N, n = (int32_t)sh.tiles.size();
     free_resident(h);
     h->tile_k = 0;  // multi-sweep halo tiles off
     rc = ensure_desc(h);
     if (rc != ISING_OK) return rc;
     hipError_t e = hipMalloc(&h->d_res, sizeof(PersistTile) * n);
-    if (e == hipSuccess) e = hipMemcpy(h->d_res, tiles.data(), sizeof(PersistTile) * n, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(h->d_res, sh.tiles.data(), sizeof(PersistTile) * n, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc(&h->d_exch, sizeof(uint64_t) * 4 * (size_t)N * n);
     if (e == hipSuccess) e = hipMemset(h->d_exch, 0, sizeof(uint64_t) * 4 * (size_t)N * n);
     if (e == hipSuccess) e = hipMalloc(&h->d_flags, sizeof(uint64_t) * n);
@@ -772,12 +863,37 @@ int ising_set_resident_tiles(ising_lattice* h, int32_t tile_cols, int32_t block,
         return hip_fail(e, "ising_set_resident_tiles");
     }
     *h->h_err = 0;
-    h->n_res = n;
-    h->res_cols = w;
-    h->res_block = block;
-    h->res_sweeps = max_sweeps;
-    h->res_lds = lds;
+    keep_resident_shape(h, sh);
     return ISING_OK;
+}
+
+// Sweeps by drawn codes, for a lattice that one workgroup updates with at most
+// two words of a colour per thread (L <= 292), until the caller sets a shape of
+// its own: resident tiles of any shape are slower there (k_drawn's figures).
+// The shape that resident tiles would have is kept for the caller to read.
+// The buffers hold 256 sweeps where that is no more than 4 MiB each: a launch
+// starts in 4 us and applies 256 sweeps in 60 us or more, and larger buffers
+// would only make creation slower (an allocation above 1 MiB takes 30 us).
+constexpr size_t kDrawnBytes = size_t(4) << 20;  // codes of one launch
+static bool enable_drawn(ising_lattice* h, int32_t tile_cols, int32_t block, int32_t max_sweeps) {
+    const size_t sweep_bytes = ising_required_bytes(h->g.L);
+    PersistShape sh;
+    if (h->g.N * (h->g.L / 2) > drawn_max_words() ||
+        drawn_lds_bytes(h->g.L, h->g.N) > resident_lds_limit(h->device))
+        return false;
+    if (resident_shape(h, tile_cols, block, max_sweeps, &sh) != ISING_OK) {
+        last_error_ref().clear();
+        return false;
+    }
+    const int32_t S = (int32_t)std::min<size_t>(kDrawnMaxSweeps, kDrawnBytes / sweep_bytes);
+    if (hipMalloc(&h->d_codes, 2 * sweep_bytes * (size_t)S) != hipSuccess) {
+        (void)hipGetLastError();
+        h->d_codes = nullptr;
+        return false;
+    }
+    h->drawn_sweeps = S;
+    keep_resident_shape(h, sh);
+    return true;
 }
 
 int ising_set_resident_wait(ising_lattice* h, uint64_t ticks) {

@@ -211,18 +211,48 @@ hipError_t launch_small(int block, const LatticeDesc* descs, LatticeState* state
 hipError_t launch_draw_codes(const LatticeDesc* descs, const LatticeState* states, const DrawLat* lats, int32_t n_lats,
                              int32_t max_n_draw, uint64_t* codes, int32_t sweep_off, int32_t S, hipStream_t s);
 // Apply pass over the same sweeps: one workgroup of `block` threads (a
-// multiple of 64, at most 256) per listed lattice, wmax (1 to 4:
-// wave_apply_words_per_thread) words of a colour per thread, codes loaded
+// multiple of 64; at most 256, or 1024 with one word per thread) per listed
+// lattice, wmax (1 to 4: wave_apply_words_per_thread) words of a colour per thread, codes loaded
 // from the buffer into registers ahead of use; lds_bytes =
 // wave_apply_lds_bytes(largest N L, S).  Samples as launch_resident.
 hipError_t launch_wave_apply(int wmax, int block, const LatticeDesc* descs, LatticeState* states, const DrawLat* lats,
                              int32_t n_lats, const uint64_t* codes, int32_t sweep_off, int32_t S, int32_t every,
                              size_t lds_bytes, hipStream_t s);
 size_t wave_apply_lds_bytes(int32_t NL, int32_t max_samples);
+// Threads of an apply workgroup of lattices of up to `words` words of a colour,
+// wmax of them per thread: no wavefront without words, as an idle one still takes
+// part in every barrier (8 lattices of L = 16: 0.40 us a sweep with four
+// wavefronts, 0.30 with one, which needs no barrier).
+int32_t wave_apply_block(int32_t words, int32_t wmax);
 // Words of one colour per thread of a `block`-thread apply workgroup (0:
 // more than 4).
 int32_t wave_apply_words_per_thread(int32_t L, int32_t N, int32_t block);
 hipError_t allow_wave_apply_lds(int device);
+
+// One lattice of a handle with its draws spread over the chip: a launch applies
+// the n_apply sweeps whose codes the launch before drew, and draws the n_draw
+// sweeps from t_draw on for the next one (either may be 0).
+constexpr int32_t kDrawnMaxSweeps = 256;  // of one launch
+struct DrawnLaunch {
+    uint64_t* W;
+    int32_t L, N, istar, sh_star;
+    uint32_t k0, k1;
+    uint64_t t_draw;
+    uint64_t* drawn;        // n_draw x N L codes
+    const uint64_t* codes;  // n_apply x N L codes
+    uint32_t t4, t8;        // of the sweeps drawn
+    int32_t n_draw, n_apply;
+    // a sample after the applied sweep j when (sweep_off + j + 1) % every == 0
+    // (every > 0); each output may be null
+    int32_t sweep_off, every;
+    int64_t* series_E;
+    int64_t* series_M;
+    Moments* mom;
+};
+int32_t drawn_max_words();  // most words of a colour of such a lattice
+hipError_t launch_drawn(const DrawnLaunch& a, hipStream_t s);
+// LDS of such a launch, to be compared with resident_lds_limit.
+size_t drawn_lds_bytes(int32_t L, int32_t N);
 
 // Largest dynamic LDS a resident workgroup may use on this device.
 size_t resident_lds_limit(int device);
