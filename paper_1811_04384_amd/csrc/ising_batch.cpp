@@ -814,7 +814,11 @@ static int resident_error(ising_batch* b) {
 int ising_batch_results(ising_batch* b, int64_t* E, int64_t* M, int64_t* sum_E, int64_t* sum_absM,
                         int64_t* n_samples) {
     if (!b) return fail(ISING_EINVAL, "ising_batch_results: null handle");
-    if (E || M) ISING_HIP(launch_observe_multi(b->d_desc, b->d_state, nullptr, b->n, nullptr, b->stream));
+    if (E || M) {
+        int64_t max_words = 0;
+        for (const Geometry& g : b->geo) max_words = std::max(max_words, (int64_t)g.N * g.L);
+        ISING_HIP(launch_observe_multi(b->d_desc, b->d_state, nullptr, b->n, max_words, nullptr, b->stream));
+    }
     std::vector<LatticeState> st(b->n);
     ISING_HIP(hipMemcpyAsync(st.data(), b->d_state, sizeof(LatticeState) * b->n, hipMemcpyDeviceToHost, b->stream));
     ISING_HIP(hipStreamSynchronize(b->stream));

@@ -84,6 +84,7 @@ struct LatticeState {
     int64_t series_idx;       // next sample slot of the current call
     Moments mom;              // sums over the samples since the last reset
     int64_t last_E, last_M;   // most recent sample or observation
+    unsigned long long obs_anti, obs_ups;  // sums of an observation's workgroups (zero between observations)
 };
 
 // One wavefront of a tiled half-sweep launch: up to 64 words_per_thread

@@ -189,10 +189,17 @@ __device__ __forceinline__ void finalize_lattice(const LatticeDesc& d, LatticeSt
 template <int WPT, bool MEASURE>
 __global__ void __launch_bounds__(kTiledMaxBlock)
     k_halfsweep_multi(const LatticeDesc* __restrict__ descs, LatticeState* __restrict__ states,
-                      const WaveItem* __restrict__ waves, uint32_t n_waves, int colour, uint32_t sweep_off,
-                      Partial* __restrict__ partials, const Partial* __restrict__ fin_partials, uint32_t fin_off) {
+                      const WaveItem* __restrict__ waves, uint32_t n_waves, uint32_t group, int colour,
+                      uint32_t sweep_off, Partial* __restrict__ partials, const Partial* __restrict__ fin_partials,
+                      uint32_t fin_off) {
     __shared__ uint32_t table[(kTiledMaxBlock / 64) * row_table_words<WPT>()];
-    const uint32_t wave = __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+    // groups of consecutive workgroups of the table to one XCD (see launch)
+    uint32_t b = blockIdx.x;
+    if (b < gridDim.x / (8 * group) * (8 * group)) {
+        const uint32_t seq = b >> 3, g = seq / group;
+        b = (8 * g + (b & 7u)) * group + (seq - g * group);
+    }
+    const uint32_t wave = __builtin_amdgcn_readfirstlane((b * blockDim.x + threadIdx.x) >> 6);
     if (wave >= n_waves) return;
     const WaveItem item = waves[wave];
     const LatticeDesc& d = descs[item.lattice];
@@ -390,62 +397,96 @@ __global__ void __launch_bounds__(kResidentMaxBlock)
     }
 }
 
-// Observables of every lattice of a table, one workgroup per lattice:
-// antiparallel right and down bonds (Section 5.3) and up spins.
-__global__ void __launch_bounds__(256) k_observe_multi(const LatticeDesc* __restrict__ descs,
-                                                       LatticeState* __restrict__ states,
-                                                       const int32_t* __restrict__ ids, int64_t* __restrict__ out_EM) {
-    __shared__ uint64_t red[32];
-    const int32_t lat = ids ? ids[blockIdx.x] : (int32_t)blockIdx.x;
-    const LatticeDesc& d = descs[lat];
-    const int L = d.L, N = d.N;
-    const uint64_t* __restrict__ W = d.W;
+// Antiparallel right and down bonds (Section 5.3) and up spins of the words
+// idx, idx + 256, ... below end of one lattice, a thread's share of a
+// workgroup's consecutive words.
+__device__ __forceinline__ void observe_words(const uint64_t* __restrict__ W, int L, int N, int istar, int sh_star,
+                                              uint32_t idx, uint32_t end, uint32_t& anti, uint32_t& ups) {
     auto ld = [&](int i, int j) { return W[(size_t)i * L + j]; };
-    uint64_t anti = 0, ups = 0;
-    const uint32_t n_words = (uint32_t)N * (uint32_t)L;
-    for (uint32_t idx = threadIdx.x; idx < n_words; idx += blockDim.x) {
-        const int I = (int)(idx / (uint32_t)L);
-        const int J = (int)(idx - (uint32_t)I * (uint32_t)L);
+    int I = (int)(idx / (uint32_t)L);
+    int J = (int)(idx - (uint32_t)I * (uint32_t)L);
+    for (; idx < end; idx += 256) {
         const uint64_t live = live_mask(I, L, N);
         const uint64_t w = ld(I, J);
         const uint64_t rt = ld(I, J == L - 1 ? 0 : J + 1);
-        const uint64_t dn = down_word(ld, I, J, N, d.istar, d.sh_star);
+        const uint64_t dn = down_word(ld, I, J, N, istar, sh_star);
         anti += __popcll((w ^ rt) & live) + __popcll((w ^ dn) & live);
         ups += __popcll(w & live);
-    }
-    block_sum2(anti, ups, red);
-    if (threadIdx.x == 0) {
-        int64_t E, M;
-        energy_magnetisation(anti, ups, L, E, M);
-        states[lat].last_E = E;
-        states[lat].last_M = M;
-        if (out_EM) {
-            out_EM[2 * blockIdx.x] = E;
-            out_EM[2 * blockIdx.x + 1] = M;
+        J += 256;
+        while (J >= L) {
+            J -= L;
+            I += 1;
         }
     }
 }
 
-__global__ void __launch_bounds__(256) k_observe_single(const uint64_t* __restrict__ W, Geometry g,
-                                                        Partial* __restrict__ partials) {
-    const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t n_words = (uint32_t)g.N * (uint32_t)g.L;
-    uint32_t anti = 0, ups = 0;
-    if (idx < n_words) {
-        const int L = g.L;
-        auto ld = [&](int i, int j) { return W[(size_t)i * L + j]; };
-        const int I = (int)(idx / (uint32_t)L);
-        const int J = (int)(idx - (uint32_t)I * (uint32_t)L);
-        const uint64_t live = live_mask(I, L, g.N);
-        const uint64_t w = ld(I, J);
-        const uint64_t rt = ld(I, J == L - 1 ? 0 : J + 1);
-        const uint64_t dn = down_word(ld, I, J, g.N, g.istar, g.sh_star);
-        anti = __popcll((w ^ rt) & live) + __popcll((w ^ dn) & live);
-        ups = __popcll(w & live);
+// Words of a lattice per workgroup of k_observe_multi.
+constexpr uint32_t kObserveWords = 2048;
+
+// Observables of every lattice of a table: workgroup part of `parts` of a
+// lattice takes every parts-th run of kObserveWords words and adds its sums to the
+// lattice's in device memory (a workgroup without words, of a smaller lattice of
+// the table, does not take part); k_observed, launched behind it, forms E and M.
+// Bound by the words' bytes: 256 lattices of L = 256 ... 2048 (137 MB) 74 us,
+// against 379 with one workgroup per lattice; one of L = 4096 12 us against 790.
+// A count of arrived workgroups in this kernel instead of the second launch took
+// 287 us, for its acquire and release by each of them.
+__global__ void __launch_bounds__(256) k_observe_multi(const LatticeDesc* __restrict__ descs,
+                                                       LatticeState* __restrict__ states,
+                                                       const int32_t* __restrict__ ids, int32_t parts) {
+    __shared__ uint64_t red[32];
+    const uint32_t k = blockIdx.x / (uint32_t)parts, part = blockIdx.x - k * (uint32_t)parts;
+    const int32_t lat = ids ? ids[k] : (int32_t)k;
+    const LatticeDesc& d = descs[lat];
+    const int L = d.L, N = d.N;
+    const uint32_t n_words = (uint32_t)N * (uint32_t)L;
+    if ((uint64_t)part * kObserveWords >= n_words) return;
+    uint64_t anti = 0, ups = 0;
+    for (uint64_t w0 = (uint64_t)part * kObserveWords; w0 < n_words; w0 += (uint64_t)parts * kObserveWords) {
+        uint32_t a = 0, u = 0;
+        observe_words(d.W, L, N, d.istar, d.sh_star, (uint32_t)w0 + threadIdx.x,
+                      (uint32_t)min((uint64_t)n_words, w0 + kObserveWords), a, u);
+        anti += a;
+        ups += u;
     }
+    block_sum2(anti, ups, red);
+    if (threadIdx.x == 0) {
+        atomicAdd(&states[lat].obs_anti, (unsigned long long)anti);
+        atomicAdd(&states[lat].obs_ups, (unsigned long long)ups);
+    }
+}
+
+// E and M of the k-th listed lattice from its sums, which are left zero.
+__global__ void __launch_bounds__(256) k_observed(const LatticeDesc* __restrict__ descs,
+                                                  LatticeState* __restrict__ states, const int32_t* __restrict__ ids,
+                                                  int32_t n_lat, int64_t* __restrict__ out_EM) {
+    const int32_t k = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (k >= n_lat) return;
+    const int32_t lat = ids ? ids[k] : k;
+    LatticeState& st = states[lat];
+    int64_t E, M;
+    energy_magnetisation(st.obs_anti, st.obs_ups, descs[lat].L, E, M);
+    st.obs_anti = 0;
+    st.obs_ups = 0;
+    st.last_E = E;
+    st.last_M = M;
+    if (out_EM) {
+        out_EM[2 * k] = E;
+        out_EM[2 * k + 1] = M;
+    }
+}
+
+// The same of one lattice, `run` words (a multiple of 256) per workgroup, as
+// wavefront partial sums.
+__global__ void __launch_bounds__(256) k_observe_single(const uint64_t* __restrict__ W, Geometry g, uint32_t run,
+                                                        Partial* __restrict__ partials) {
+    const uint32_t n_words = (uint32_t)g.N * (uint32_t)g.L;
+    const uint32_t w0 = blockIdx.x * run;
+    uint32_t anti = 0, ups = 0;
+    observe_words(W, g.L, g.N, g.istar, g.sh_star, w0 + threadIdx.x, min(n_words, w0 + run), anti, ups);
     anti = wave_sum_u32(anti);
     ups = wave_sum_u32(ups);
-    if (lane_id() == 0) partials[idx >> 6] = {anti, ups};
+    if (lane_id() == 0) partials[blockIdx.x * 4 + (threadIdx.x >> 6)] = {anti, ups};
 }
 
 __global__ void __launch_bounds__(256) k_unpack(const uint64_t* __restrict__ W, Geometry g, int32_t r0, int32_t c0,
@@ -542,13 +583,23 @@ hipError_t launch_finalize_single(const Partial* partials, int64_t n_partials, i
     return hipGetLastError();
 }
 
-int64_t observe_single_waves(const Geometry& g) { return (int64_t)grid_for((uint64_t)g.N * g.L, 256) * 4; }
+namespace {
+
+// Words per workgroup of k_observe_single: with 2048 L = 32768 takes 119 us (156
+// with 256, and eight times the partial sums to add up), below 2^20 words that
+// would leave compute units without a workgroup (L = 2016: 95).
+uint32_t observe_run(const Geometry& g) { return (uint64_t)g.N * g.L >= (1u << 20) ? 2048 : 256; }
+
+}  // namespace
+
+int64_t observe_single_waves(const Geometry& g) { return (int64_t)grid_for((uint64_t)g.N * g.L, observe_run(g)) * 4; }
 
 hipError_t launch_observe_single(const uint64_t* W, const Geometry& g, Partial* partials, int64_t* n_waves,
                                  hipStream_t s) {
-    const uint64_t n = (uint64_t)g.N * (uint64_t)g.L;
-    if (n_waves) *n_waves = (int64_t)grid_for(n, 256) * 4;
-    hipLaunchKernelGGL(k_observe_single, dim3(grid_for(n, 256)), dim3(256), 0, s, W, g, partials);
+    const uint64_t n = (uint64_t)g.N * g.L;
+    const uint32_t run = observe_run(g);
+    if (n_waves) *n_waves = observe_single_waves(g);
+    hipLaunchKernelGGL(k_observe_single, dim3(grid_for(n, run)), dim3(256), 0, s, W, g, run, partials);
     return hipGetLastError();
 }
 
@@ -574,10 +625,19 @@ hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, 
     const dim3 grid(grid_for((uint64_t)n_waves * 64, block)), blk(block);
     const bool m = partials != nullptr;
     const uint32_t nw = (uint32_t)n_waves;
+    // Consecutive workgroups are dealt to the 8 XCDs in turn; runs of 256
+    // wavefronts of the table (a few rows at least) go to one XCD, so that the rows
+    // above and below are mostly in its L2, and the runs to the XCDs in turn, at
+    // least eight each, so that lattices that have finished their sweeps leave
+    // none of them idle.  us per half-sweep without and with, 256 lattices of L = 256
+    // ... 2048: 101 / 68 with two words per thread and 256 threads, 92 / 67 with four
+    // words; 64 of 64 ... 512: 5.8 / 4.9 with a word and 64 threads; where a row is 8
+    // workgroups the same either way (68).
+    const uint32_t group = std::max(1u, std::min(grid.x / 64, 16384u / (unsigned)block));
 #define ISING_LAUNCH_HM(WPT_)                                                                                       \
-    if (m) hipLaunchKernelGGL((k_halfsweep_multi<WPT_, true>), grid, blk, 0, s, descs, states, waves, nw, colour,   \
+    if (m) hipLaunchKernelGGL((k_halfsweep_multi<WPT_, true>), grid, blk, 0, s, descs, states, waves, nw, group, colour, \
                               sweep_off, partials, fin_partials, fin_off);                                          \
-    else hipLaunchKernelGGL((k_halfsweep_multi<WPT_, false>), grid, blk, 0, s, descs, states, waves, nw, colour,    \
+    else hipLaunchKernelGGL((k_halfsweep_multi<WPT_, false>), grid, blk, 0, s, descs, states, waves, nw, group, colour, \
                             sweep_off, partials, fin_partials, fin_off);
     switch (wpt) {
         case 1: ISING_LAUNCH_HM(1) break;
@@ -609,9 +669,15 @@ hipError_t launch_begin_call(LatticeState* states, int32_t n_lat, hipStream_t s)
 }
 
 hipError_t launch_observe_multi(const LatticeDesc* descs, LatticeState* states, const int32_t* ids, int32_t n_lat,
-                                int64_t* out_EM, hipStream_t s) {
+                                int64_t max_words, int64_t* out_EM, hipStream_t s) {
     if (n_lat <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_observe_multi, dim3(n_lat), dim3(256), 0, s, descs, states, ids, out_EM);
+    // workgroups for every run of the largest lattice, up to 1024 per lattice and
+    // 16384 in all (beyond, a workgroup takes several runs)
+    const int64_t runs = (max_words + kObserveWords - 1) / kObserveWords;
+    const int64_t parts = std::max<int64_t>(1, std::min({runs, (int64_t)1024, (int64_t)16384 / n_lat}));
+    hipLaunchKernelGGL(k_observe_multi, dim3((unsigned)(parts * n_lat)), dim3(256), 0, s, descs, states, ids,
+                       (int32_t)parts);
+    hipLaunchKernelGGL(k_observed, dim3(grid_for(n_lat, 256)), dim3(256), 0, s, descs, states, ids, n_lat, out_EM);
     return hipGetLastError();
 }
 

@@ -276,9 +276,11 @@ int enqueue_retirements(ising_server* s) {
     if (rc != ISING_OK) return rc;
     s->next_ring = (s->next_ring + 1) % kRing;
     const int32_t nf = (int32_t)fin.size();
+    int64_t max_words = 0;
     for (int32_t k = 0; k < nf; ++k) {
         const Slot& sl = s->sched.slots()[fin[k]];
         r.ids[k] = fin[k];
+        max_words = std::max<int64_t>(max_words, (int64_t)(ising_required_bytes(sl.req.L) / 8));
         ising_result m;
         m.req_id = sl.req.id;
         m.L = sl.req.L;
@@ -292,7 +294,7 @@ int enqueue_retirements(ising_server* s) {
         r.meta.push_back(m);
     }
     ISING_HIP(hipMemcpyAsync(s->d_fin, r.ids, sizeof(int32_t) * nf, hipMemcpyHostToDevice, s->stream));
-    ISING_HIP(launch_observe_multi(s->d_desc, s->d_state, s->d_fin, nf, s->d_em, s->stream));
+    ISING_HIP(launch_observe_multi(s->d_desc, s->d_state, s->d_fin, nf, max_words, s->d_em, s->stream));
     ISING_HIP(hipMemcpyAsync(r.em, s->d_em, sizeof(int64_t) * 2 * nf, hipMemcpyDeviceToHost, s->stream));
     ISING_HIP(hipEventRecord(r.done, s->stream));
     r.pending = true;

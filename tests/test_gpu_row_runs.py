@@ -89,3 +89,23 @@ def test_thresholds_at_both_ends(T):
             assert (lat.spins() == s).all(), resident
         finally:
             lat.close()
+
+
+@pytest.mark.parametrize("wpt,block", [(1, 64), (1, 256), (2, 64), (4, 256)])
+def test_batch_table_in_runs_per_xcd(wpt, block):
+    """A batch's table of wavefronts dealt to the XCDs in runs, with workgroups left over behind the last whole
+    round of runs."""
+    print(f"batch table words_per_thread={wpt} block={block}", flush=True)
+    Ls = [1008, 256, 2048, 130, 514]
+    seeds, Ts = [3, 4, 5, 6, 7], [2.0, 2.3, 2.6, 1.8, 3.0]
+    b = ising.Batch(Ls, seeds, hot=True)
+    try:
+        b.set_plan(resident_max_L=0, resident_block=256, words_per_thread=wpt, tiled_block=block, sweeps_per_graph=3)
+        E, M = (x.cpu().numpy() for x in b.sweep(Ts, 6, every=3, series=True))
+        for i, (L, seed, T) in enumerate(zip(Ls, seeds, Ts)):
+            s = oracle.init(L, seed, True)
+            Es, Ms = oracle.sweep(s, seed, 0, 6, T, every=3)
+            assert E[i].tolist() == Es.tolist() and M[i].tolist() == Ms.tolist(), L
+            assert (b.spins(i) == s).all(), L
+    finally:
+        b.close()
