@@ -78,6 +78,7 @@ struct ising_batch {
     PersistTile* d_res = nullptr;
     int32_t n_res = 0;
     size_t res_lds = 0;
+    int res_form = -1;  // of the resident tiles (persist_form)
     uint64_t* d_exch = nullptr;
     int64_t exch_tile_words = 0;
     uint64_t* d_flags = nullptr;
@@ -251,6 +252,7 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
     b->n_res = 0;
     b->n_res_lat = 0;
     b->res_lds = 0;
+    b->res_form = -1;
     b->tile_shapes.clear();
     b->plan = p;
     const size_t res_limit = persist_lds_limit(b->device);
@@ -304,6 +306,8 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
                                          base + t});
                 }
                 b->res_lds = std::max(b->res_lds, lds);
+                const int form = persist_form(g.L, g.N, w, p.tile_block);
+                b->res_form = b->res_form < 0 || b->res_form == form ? form : persist_form_any();
                 res_max_N = std::max(res_max_N, g.N);
                 continue;
             }
@@ -482,7 +486,7 @@ int enqueue_chunk(ising_batch* b, int32_t k, int32_t every, hipStream_t s0, hipS
         a.flags = b->d_flags;
         a.error = b->d_err;
         a.wait_ticks = 100000000ull;  // one second of the 100 MHz clock
-        ISING_HIP(launch_persist(a, b->n_res, p.tile_block, b->res_lds, rs));
+        ISING_HIP(launch_persist(a, b->res_form, b->n_res, p.tile_block, b->res_lds, rs));
         if (every > 0)
             ISING_HIP(launch_finalize_resident(b->d_desc, b->d_state, b->d_ids_res, b->n_res_lat, b->d_res_part,
                                                b->n_res, k / every, rs));

@@ -244,6 +244,7 @@ struct AcceptWord {
     }
     template <int G>
     __device__ __forceinline__ void skip() {}
+    __device__ __forceinline__ void end19() {}
     __device__ __forceinline__ uint64_t word() const { return ((uint64_t)hi << 32) | lo; }
 };
 
@@ -251,8 +252,7 @@ struct AcceptWord {
 // (the LDS forms, whose half-sweep waits for its slowest wavefront): compares
 // into lane masks, selects and a shift-or, one instruction more per position
 // but no wait for the execution mask between them (L = 64 in one workgroup of
-// two wavefronts 1.18 us per half-sweep, 1.42 with the form above; L = 4096 in
-// resident tiles 3.79 / 3.83).  Positions are added in order.  The s_nop gives
+// two wavefronts 1.18 us per half-sweep, 1.42 with the form above).  Positions are added in order.  The s_nop gives
 // the lane masks the wait states that a vector instruction's read of a
 // vector-written scalar register needs.
 struct AcceptSelect {
@@ -280,6 +280,7 @@ struct AcceptSelect {
         else if (G == 2) hi <<= 6;
         else lo <<= 12;
     }
+    __device__ __forceinline__ void end19() { lo <<= 3; }  // after positions 0..19: field 0 empty
     __device__ __forceinline__ uint64_t word() const {
         return ((uint64_t)((hi << 1) | (mid >> 2)) << 32) | (mid << 30) | lo;
     }

@@ -354,13 +354,14 @@ static int enqueue_resident_sweeps(ising_lattice* h, uint64_t t0, double T, int6
     a.flags = h->d_flags;
     a.error = h->d_err;
     a.wait_ticks = h->res_wait ? h->res_wait : kResidentWaitTicks;
+    const int form = persist_form(h->g.L, h->g.N, h->res_cols, h->res_block);
     for (int64_t done = 0; done < n;) {
         const int32_t kb = (int32_t)std::min<int64_t>(h->res_sweeps, n - done);
         a.t0 = t0 + (uint64_t)done;
         a.K = kb;
         a.sample_base = done;
         ISING_HIP(resident_gate(h->device, h->stream,
-                                [&] { return launch_persist(a, h->n_res, h->res_block, h->res_lds, h->stream); }));
+                                [&] { return launch_persist(a, form, h->n_res, h->res_block, h->res_lds, h->stream); }));
         const int64_t n_samples = every > 0 ? (done + kb) / every - done / every : 0;
         if (n_samples > 0) {
             const int64_t idx0 = done / every;  // series index of the launch's first sample

@@ -172,7 +172,12 @@ hipError_t allow_persist_lds(int device);
 // How many resident tiles of `block` threads and lds_bytes of LDS the device
 // holds at once (a launch must not exceed it).
 hipError_t persist_capacity(int block, size_t lds_bytes, int device, int64_t* tiles);
-hipError_t launch_persist(const PersistLaunch& a, int32_t n_tiles, int block, size_t lds_bytes, hipStream_t s);
+// form: persist_form of the tiles of the launch (of the widest one of a lattice), or
+// persist_form_any where its lattices' differ.
+int persist_form(int32_t L, int32_t N, int32_t w, int block);
+int persist_form_any();
+hipError_t launch_persist(const PersistLaunch& a, int form, int32_t n_tiles, int block, size_t lds_bytes,
+                          hipStream_t s);
 // Runs launch(), which enqueues work holding resident tiles on stream s of
 // `device`, ordered after the previous such work of this process on that
 // device (a stream wait on its completion event), and makes it the previous

@@ -120,10 +120,11 @@ __device__ __forceinline__ uint64_t lds_word_update_c1(const LdsSweep& s, const 
 
 // The codes of positions 0..19 of a word, with field 0 (position 20) left 0:
 // drawn ahead of the word's update.
+template <class Accept>
 __device__ __forceinline__ uint64_t lds_word_codes(const LdsSweep& s, const RoundKeys& rk, int I, uint32_t c1) {
-    AcceptSelect acc;
+    Accept acc;
     lds_word_accept19(s, rk, s.pstar + (I <= s.istar ? 1 : 0), c1, acc);
-    acc.lo <<= 3;  // field 0
+    acc.end19();
     return acc.word();
 }
 

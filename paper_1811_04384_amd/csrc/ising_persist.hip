@@ -27,10 +27,10 @@
 // it waits for, so that one store and one load are all that lies between the
 // update of a boundary word and its use next door; no flag is raised behind
 // the data and no store is waited for.  Small bands are bound by that path:
-// 126 bands of 8 columns of L = 1008 take 1.35 us per half-sweep, against 2.69
+// 126 bands of 8 columns of L = 1008 take 1.26 us per half-sweep, against 2.69
 // with a flag per tile, raised after every publisher's store had completed
 // and polled before the barrier (three memory round trips after each other);
-// bands of 16 columns (L = 4096: 3.90 against 3.97 us) are bound by the
+// bands of 16 columns (L = 4096: 3.80 against 3.97 us) are bound by the
 // vector unit.
 // Only colour-c words are exchanged, because the next half-sweep only reads
 // those from a ghost column.  The exchange buffer alternates between two
@@ -50,6 +50,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "ising_device.hpp"
@@ -105,10 +106,15 @@ __device__ __forceinline__ uint64_t spread_next(uint64_t tag) {
 
 // How a tile's threads hold its word items: formed in every half-sweep, or
 // once per launch with one or two items per thread and colour.
-enum Items { kFormed, kOne, kTwo };
+// kAny: a kernel whose tiles choose.
+enum Items { kFormed, kOne, kTwo, kAny };
+
+__host__ __device__ constexpr Items items_mode(int n_w, int block) {
+    return n_w <= block ? kOne : n_w <= 2 * block ? kTwo : kFormed;
+}
 
 // Word items of a colour of a tile.
-__device__ __forceinline__ int tile_items(int L, int N, int tile_w) {
+__host__ __device__ __forceinline__ int tile_items(int L, int N, int tile_w) {
     return tile_w >= L ? N * (L >> 1) : N + N * ((tile_w - 2) >> 1);
 }
 
@@ -263,11 +269,14 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
     WordItem cur0{}, cur1{}, oth0{}, oth1{};  // word items, this colour and the other
     DrawItem dcur0{}, dcur1{}, doth0{}, doth1{};  // the items whose codes this thread draws
     const int f0 = split ? B - 1 - tid : tid, f1 = tid + B;
+    // two words per thread keep the vector unit busy: the form with fewer
+    // instructions (those 16 lattices 2670 us with selects, 2600 with it)
+    typedef std::conditional_t<ITEMS == kTwo, AcceptWord, AcceptSelect> Accept;
     auto draw_codes = [&](const DrawItem& it, int f, const LdsSweep& swc, uint32_t table) {
         // the sweep index made opaque to the compiler (see the words below)
         LdsSweep swi = swc;
         asm volatile("" : "+s"(swi.t_lo), "+s"(swi.t_hi));
-        lds_store64(table + 8u * (uint32_t)f, lds_word_codes(swi, rk, it.I, it.c1));
+        lds_store64(table + 8u * (uint32_t)f, lds_word_codes<Accept>(swi, rk, it.I, it.c1));
     };
     if (pre) {
         // a thread without an item holds the last one's addresses: its loads
@@ -323,9 +332,36 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
     // `want`.  Bounded twice, by the clock (a failed poll counts for at least
     // 100 ns) and by the number of polls; when a bound is reached, or another
     // tile has set the error word, the launch is abandoned after this
-    // half-sweep.
+    // half-sweep.  In small bands (kOne), whose half-sweep waits for these words
+    // alone, two more reads follow the first at 0.1 us distance, so that a word
+    // that just missed one is not seen a whole round trip later (us per
+    // half-sweep with one read at a time / three: L = 300 1.31 / 1.16, 1008 1.34 /
+    // 1.29; wider bands gain nothing, L = 4096 3.74 / 3.80).
     auto ghost = [&](const uint64_t* p, uint64_t v, uint64_t want) -> uint64_t {
-        if ((v & ~kSpinBits) != want) {
+        if constexpr (split) {
+            __builtin_amdgcn_s_sleep(4);  // 256 cycles
+            uint64_t v1 = fetch(p);
+            __builtin_amdgcn_s_sleep(4);
+            uint64_t v2 = fetch(p);
+            if ((v & ~kSpinBits) != want) {
+                const uint64_t start = clock_ticks() - 10;
+                uint32_t err = 0;  // read behind the words, checked a round later
+                for (uint32_t polls = 0;; ++polls) {
+                    v = v1;
+                    if ((v & ~kSpinBits) == want) break;
+                    v1 = fetch(p);
+                    v = v2;
+                    if ((v & ~kSpinBits) == want) break;
+                    v2 = fetch(p);
+                    if (err != 0u || clock_ticks() - start > a.wait_ticks || polls > kMaxPolls) {
+                        __hip_atomic_store(a.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        stop = 1;
+                        break;
+                    }
+                    err = __hip_atomic_load(a.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+        } else if ((v & ~kSpinBits) != want) {
             const uint64_t start = clock_ticks() - 10;
             for (uint32_t polls = 0;; ++polls) {
                 if (__hip_atomic_load(a.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
@@ -511,24 +547,49 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
 
 }  // namespace
 
+// ITEMS: how the tiles of the launch hold their items (kAny: lattices of the
+// launch differ, and each tile chooses).  A kernel of each form by itself has the
+// registers it needs and no others' (all three in one kernel against each alone,
+// us per sweep: L = 300 2.33 / 2.28, 512 2.41 / 2.34, 1024 2.64 / 2.58, 4096 7.66 /
+// 7.61; 16 lattices of L = 1008 in bands of 64 columns, 300 sampled sweeps 2590 /
+// 2560).
+template <int ITEMS>
 __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
     extern __shared__ uint64_t lds[];
     __shared__ uint32_t red[2 * (kPersistMaxBlock / 64)];
     __shared__ int stop;
     const PersistTile tp = a.tiles[blockIdx.x];
     const LatticeDesc& d = a.descs[tp.lattice];
-    const int n_w = tile_items(d.L, d.N, tp.w), B = blockDim.x;
-    const int items = n_w <= B ? kOne : n_w <= 2 * B ? kTwo : kFormed;
-    if (tp.w >= d.L) {
-        if (items == kOne) persist_tile<kOne, true>(a, tp, lds, red, stop);
-        else if (items == kTwo) persist_tile<kTwo, true>(a, tp, lds, red, stop);
-        else persist_tile<kFormed, true>(a, tp, lds, red, stop);
-    } else {
-        if (items == kOne) persist_tile<kOne, false>(a, tp, lds, red, stop);
-        else if (items == kTwo) persist_tile<kTwo, false>(a, tp, lds, red, stop);
+    const bool whole = tp.w >= d.L;
+    const int items = ITEMS == kAny ? items_mode(tile_items(d.L, d.N, tp.w), blockDim.x) : ITEMS;
+    if (items == kOne && (ITEMS == kOne || ITEMS == kAny)) {
+        if (whole) persist_tile<kOne, true>(a, tp, lds, red, stop);
+        else persist_tile<kOne, false>(a, tp, lds, red, stop);
+    } else if (items == kTwo && (ITEMS == kTwo || ITEMS == kAny)) {
+        if (whole) persist_tile<kTwo, true>(a, tp, lds, red, stop);
+        else persist_tile<kTwo, false>(a, tp, lds, red, stop);
+    } else if (ITEMS == kFormed || ITEMS == kAny) {
+        if (whole) persist_tile<kFormed, true>(a, tp, lds, red, stop);
         else persist_tile<kFormed, false>(a, tp, lds, red, stop);
     }
 }
+
+namespace {
+
+typedef void (*PersistKernel)(PersistLaunch);
+PersistKernel persist_kernel(int form) {
+    switch (form) {
+        case kOne: return &k_persist<kOne>;
+        case kTwo: return &k_persist<kTwo>;
+        case kFormed: return &k_persist<kFormed>;
+        default: return &k_persist<kAny>;
+    }
+}
+
+}  // namespace
+
+int persist_form(int32_t L, int32_t N, int32_t w, int block) { return items_mode(tile_items(L, N, w), block); }
+int persist_form_any() { return kAny; }
 
 size_t persist_lds_bytes(int32_t L, int32_t N, int32_t w, int32_t block) {
     // a tile of width wi: its band with the ghost columns, two position-20
@@ -556,24 +617,31 @@ size_t persist_lds_limit(int device) {
 }
 
 hipError_t allow_persist_lds(int device) {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_persist), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)persist_lds_limit(device));
+    const int limit = (int)persist_lds_limit(device);
+    hipError_t e = hipSuccess;
+    for (int form : {kFormed, kOne, kTwo, kAny})
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(persist_kernel(form)),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, limit);
+    return e;
 }
 
 hipError_t persist_capacity(int block, size_t lds_bytes, int device, int64_t* tiles) {
+    // of the kernel that holds every form: the others need no more
     int per_cu = 0, cus = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_persist),
-                                                                block, lds_bytes);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &per_cu, reinterpret_cast<const void*>(persist_kernel(kAny)), block, lds_bytes);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (e != hipSuccess) return e;
     *tiles = (int64_t)per_cu * cus;
     return hipSuccess;
 }
 
-hipError_t launch_persist(const PersistLaunch& a, int32_t n_tiles, int block, size_t lds_bytes, hipStream_t s) {
+hipError_t launch_persist(const PersistLaunch& a, int form, int32_t n_tiles, int block, size_t lds_bytes,
+                          hipStream_t s) {
     if (n_tiles <= 0 || a.K <= 0) return hipSuccess;
     if (block < 64 || block > kPersistMaxBlock || block % 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_persist, dim3(n_tiles), dim3(block), lds_bytes, s, a);
+    hipLaunchKernelGGL(persist_kernel(form), dim3(n_tiles), dim3(block), lds_bytes, s, a);
     return hipGetLastError();
 }
 
