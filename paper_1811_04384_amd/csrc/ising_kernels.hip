@@ -518,6 +518,22 @@ __global__ void __launch_bounds__(256) k_pack_rows(const uint8_t* __restrict__ i
     *w = in[idx] ? (*w | bit) : (*w & ~bit);
 }
 
+// The words of a whole lattice from its L x L bytes, a thread per word: word
+// (I, J) holds the rows I + p N of column J.
+__global__ void __launch_bounds__(256) k_pack_words(const uint8_t* __restrict__ in, Geometry g,
+                                                    uint64_t* __restrict__ W) {
+    const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= (uint32_t)g.N * (uint32_t)g.L) return;
+    const int I = (int)(idx / (uint32_t)g.L);
+    const int n_live = (g.L - 1 - I) / g.N + 1;
+    const size_t step = (size_t)g.N * (size_t)g.L;  // bytes from one position's row to the next one's
+    uint64_t w = 0;
+#pragma unroll
+    for (int p = 0; p < 21; ++p)
+        if (p < n_live) w |= (in[idx + p * step] ? 1ull : 0ull) << (3 * (20 - p));
+    W[idx] = w;
+}
+
 __global__ void __launch_bounds__(256) k_zero_words(uint64_t* __restrict__ p, uint64_t n) {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
@@ -615,6 +631,11 @@ hipError_t launch_pack_rows(const uint8_t* in, const Geometry& g, int32_t r0, in
     if (nrows < 1 || nrows > g.N || r0 < 0 || r0 + nrows > g.L) return hipErrorInvalidValue;
     const uint64_t n = (uint64_t)nrows * (uint64_t)g.L;
     hipLaunchKernelGGL(k_pack_rows, dim3(grid_for(n, 256)), dim3(256), 0, s, in, g, r0, nrows, W);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_words(const uint8_t* in, const Geometry& g, uint64_t* W, hipStream_t s) {
+    hipLaunchKernelGGL(k_pack_words, dim3(grid_for((uint64_t)g.N * g.L, 256)), dim3(256), 0, s, in, g, W);
     return hipGetLastError();
 }
 

@@ -87,6 +87,8 @@ hipError_t launch_unpack(const uint64_t* W, const Geometry& g, int32_t r0, int32
                          int32_t ncols, uint8_t* out, hipStream_t s);
 hipError_t launch_pack_rows(const uint8_t* in, const Geometry& g, int32_t r0, int32_t nrows, uint64_t* W,
                             hipStream_t s);
+// Every word from the bytes of the whole lattice (row major, nonzero = up).
+hipError_t launch_pack_words(const uint8_t* in, const Geometry& g, uint64_t* W, hipStream_t s);
 
 // ---- batches --------------------------------------------------------------
 
