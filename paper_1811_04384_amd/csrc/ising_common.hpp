@@ -50,6 +50,17 @@ struct StripArgs {
     uint32_t t4, t8;      // acceptance thresholds
 };
 
+// The picks [k0, k0 + n_k) of one phase of every strip, listed by word (column
+// of the phase, word row) and in pick order for each: strip p's word s has the
+// entries first[p (N width + 1) + s] .. first[... + s + 1] of the strip's n_k, a
+// pick's number after k0 and its acceptance codes.  k0 and n_k are even.
+struct StripLists {
+    uint16_t* first;  // strips x (N width + 1)
+    uint16_t* k;      // strips x n_k
+    uint64_t* codes;  // strips x n_k
+    uint32_t k0, n_k;
+};
+
 // Per-lattice parameters of a batch, written by the host before each call
 // and read-only for every kernel.
 struct LatticeDesc {

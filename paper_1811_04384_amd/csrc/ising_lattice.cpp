@@ -29,6 +29,7 @@ struct ising_lattice {
     void* d_fin = nullptr;    // device scratch of the partial-sum reduction
     uint32_t* strip_pos = nullptr;    // drawn picks of the strip dynamics (allocated on first use)
     uint64_t* strip_codes = nullptr;  // their acceptance codes
+    char* strip_lists = nullptr;      // two sets of pick lists (allocated on first use)
     uint8_t* d_stage = nullptr;       // spin input/output staging, spin_stage_bytes(L)
     Moments* d_scan = nullptr;        // moment sums of up to kScanBlock temperatures of a scan
     // multi-sweep LDS tiles (tile_k = 0: one launch per half-sweep)
@@ -148,6 +149,7 @@ static void release(ising_lattice* h) {
     if (h->d_fin) (void)hipFree(h->d_fin);
     if (h->strip_pos) (void)hipFree(h->strip_pos);
     if (h->strip_codes) (void)hipFree(h->strip_codes);
+    if (h->strip_lists) (void)hipFree(h->strip_lists);
     if (h->d_stage) (void)hipFree(h->d_stage);
     if (h->d_scan) (void)hipFree(h->d_scan);
     if (h->d_tiles) (void)hipFree(h->d_tiles);
@@ -521,6 +523,57 @@ constexpr int64_t kStripPickLimit = int64_t(1) << 22;
 constexpr int64_t kStripBufEntries = int64_t(1) << 22;
 constexpr size_t kStripChainLdsMax = 16 * 1024;
 
+// Picks and words' first entries of one set of lists (10 and 2 bytes each): every
+// strip shape of at most 512 words per phase has at most 2.76 million words.
+constexpr int64_t kStripListEntries = int64_t(1) << 21;
+constexpr int64_t kStripListFirst = 2816 * 1024;
+constexpr size_t kStripListBytes = (size_t)(10 * kStripListEntries + 2 * kStripListFirst);
+
+// Iterations by lists of picks: phase args(t, ph); observe(k) after iteration k.
+// A launch draws the next chunk of picks beside the one that it applies.
+extern "C++" {
+template <class Args, class Observe>
+static int strip_list_iterations(ising_lattice* h, int64_t n, const Args& args, const Observe& observe) {
+    if (!h->strip_lists) {
+        ISING_HIP(allow_strip_list_lds());
+        ISING_HIP(hipMalloc(&h->strip_lists, 2 * kStripListBytes));
+    }
+    StripArgs a = {};
+    StripLists l = {};  // drawn and not yet applied
+    int64_t sample = 0;  // the iteration that ends with it (0: none does)
+    int set = 0;
+    for (int64_t k = 1; k <= n; ++k) {
+        for (uint32_t ph = 0; ph < 2; ++ph) {
+            const StripArgs b = args(k, ph);
+            // chunks of about the same size, even
+            uint32_t most = strip_list_picks(b, kStripListEntries);
+            const uint32_t chunks = (b.picks + most - 1) / most;
+            most = ((b.picks + chunks - 1) / chunks + 1) & ~1u;
+            for (uint32_t k0 = 0; k0 < b.picks; k0 += most) {
+                char* const at = h->strip_lists + (size_t)set * kStripListBytes;
+                StripLists lb;
+                lb.codes = reinterpret_cast<uint64_t*>(at);
+                lb.k = reinterpret_cast<uint16_t*>(at + 8 * kStripListEntries);
+                lb.first = lb.k + kStripListEntries;
+                lb.k0 = k0;
+                lb.n_k = std::min(most, b.picks - k0);
+                ISING_HIP(launch_strip_lists(h->W, a, l, b, lb, h->stream));
+                if (sample) {
+                    const int rc = observe(sample);
+                    if (rc != ISING_OK) return rc;
+                }
+                a = b;
+                l = lb;
+                set ^= 1;
+                sample = ph == 1 && k0 + most >= b.picks ? k : 0;
+            }
+        }
+    }
+    ISING_HIP(launch_strip_lists(h->W, a, l, a, StripLists{}, h->stream));
+    return sample ? observe(sample) : ISING_OK;
+}
+}  // extern "C++"
+
 static int strip_phase(ising_lattice* h, const StripArgs& a) {
     if (strip_chain_lds_bytes(a) > kStripChainLdsMax || strip_apply_lds_bytes(a, 1) > kStripLdsBytes) {
         ISING_HIP(launch_strip_phase(h->W, a, h->stream));
@@ -574,23 +627,37 @@ int ising_random_iterations(ising_lattice* h, double T, int32_t strip_cols, int6
     a.k1 = (uint32_t)(h->seed >> 32);
     a.t4 = t4;
     a.t8 = t8;
-    for (int64_t k = 1; k <= n_iterations; ++k) {
+    auto phase = [&](int64_t k, uint32_t ph) {
         const uint64_t t = h->t + (uint64_t)(k - 1);
         a.t_lo = (uint32_t)t;
         a.t_hi = (uint32_t)(t >> 32);
-        for (uint32_t ph = 0; ph < 2; ++ph) {
-            a.phase = ph;
-            a.off = ph == 0 ? 0 : strip_cols / 2;
-            a.width = ph == 0 ? strip_cols / 2 : strip_cols - strip_cols / 2;
-            a.picks = (uint32_t)(10 * (int64_t)N * a.width);
-            const int rc = strip_phase(h, a);
+        a.phase = ph;
+        a.off = ph == 0 ? 0 : strip_cols / 2;
+        a.width = ph == 0 ? strip_cols / 2 : strip_cols - strip_cols / 2;
+        a.picks = (uint32_t)(10 * (int64_t)N * a.width);
+        return a;
+    };
+    auto observe = [&](int64_t k) -> int {
+        if (every == 0 || k % every != 0) return ISING_OK;
+        int64_t nw = 0;
+        ISING_HIP(launch_observe_single(h->W, h->g, h->partials, &nw, h->stream));
+        ISING_HIP(launch_finalize_single(h->partials, nw, L, dev_E, dev_M, k / every - 1, nullptr,
+                                         reinterpret_cast<Moments*>(dev_acc), h->d_fin, h->stream));
+        return ISING_OK;
+    };
+    // the right half of a strip is at least as wide as the left one
+    if (n_iterations > 0 && strip_list_picks(phase(1, 1), kStripListEntries) > 0 &&
+        (int64_t)a.strips * ((int64_t)N * a.width + 1) <= kStripListFirst) {
+        const int rc = strip_list_iterations(h, n_iterations, phase, observe);
+        if (rc != ISING_OK) return rc;
+    } else {
+        for (int64_t k = 1; k <= n_iterations; ++k) {
+            for (uint32_t ph = 0; ph < 2; ++ph) {
+                const int rc = strip_phase(h, phase(k, ph));
+                if (rc != ISING_OK) return rc;
+            }
+            const int rc = observe(k);
             if (rc != ISING_OK) return rc;
-        }
-        if (every > 0 && k % every == 0) {
-            int64_t nw = 0;
-            ISING_HIP(launch_observe_single(h->W, h->g, h->partials, &nw, h->stream));
-            ISING_HIP(launch_finalize_single(h->partials, nw, L, dev_E, dev_M, k / every - 1, nullptr,
-                                             reinterpret_cast<Moments*>(dev_acc), h->d_fin, h->stream));
         }
     }
     h->t += (uint64_t)n_iterations;

@@ -75,6 +75,17 @@ hipError_t launch_strip_draws(const StripArgs& a, uint32_t k0, uint32_t n_k, uin
 hipError_t launch_strip_apply(uint64_t* W, const StripArgs& a, uint32_t n_k, const uint32_t* pos,
                               const uint64_t* codes, hipStream_t s);
 
+// The same phase by lists of picks per word, for strips of at most 512 words of a
+// phase: a launch applies the lists `l` of phase a (l.n_k = 0: none) and draws
+// those of phase n (ln, in other buffers) for the next one.  strip_list_picks:
+// how many picks of a phase a list may hold (even; 0: not usable) when a buffer
+// holds max_entries of them; allow_strip_list_lds once before the first launch.
+constexpr size_t kStripListLds = 80 * 1024;
+uint32_t strip_list_picks(const StripArgs& a, int64_t max_entries);
+hipError_t allow_strip_list_lds();
+hipError_t launch_strip_lists(uint64_t* W, const StripArgs& a, const StripLists& l, const StripArgs& n,
+                              const StripLists& ln, hipStream_t s);
+
 // Observables of one lattice: per-wavefront partials of right+down
 // antiparallel bonds and up spins over all words.
 hipError_t launch_observe_single(const uint64_t* W, const Geometry& g, Partial* partials, int64_t* n_waves,

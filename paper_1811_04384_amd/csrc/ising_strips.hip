@@ -295,6 +295,308 @@ __global__ void __launch_bounds__(64) k_strip_apply(uint64_t* __restrict__ W, St
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same phase from lists per word.  A word's picks are applied in order,
+// and a pick commutes with every other one whose word it neither is nor reads;
+// so the state is that of applying the picks one by one if a word's next pick is
+// applied only when it is earlier than the next picks of the words it reads
+// (its phase neighbours: left, right, up, down, the wrap rows' patch word; the
+// relation is symmetric).  One to four wavefronts take a strip, a word of the
+// phase (at most two) per lane: in every step the lanes whose next pick is the
+// earliest of its neighbourhood apply it, all loads of a step before its stores,
+// and put their word's next pick in its place.  That takes as many steps as the
+// longest chain of dependent picks is long (46 on average and about 60 in the
+// worst of 1008 strips, for the ten picks per word of a phase), with nothing
+// claimed, deferred or looked up in between; what is left is the chain of a
+// step, 0.4 us.  The lists are made by the launch before (in its other
+// workgroups, a strip each, beside the strips that this one applies): the draws
+// do not depend on the state.  us per phase with E and M after every second
+// one, windows of picks with claims above / lists: L = 84 in strips of 2 columns
+// 29 / 16, 1008 of 2 47 / 24, of 6 71 / 34, 2016 of 2 73 / 36 (28 of the 30 us of
+// a launch are the application, 20 the draws beside it), of 4 90 / 37, of 6 110 / 59,
+// 4200 of 2 182 / 138.  With more than 512 words per phase the windows stay.
+// ---------------------------------------------------------------------------
+constexpr int kListBlock = 256;
+constexpr uint32_t kNoPick = 0xFFFFFFFFu;
+
+// Order a wavefront's LDS stores of one step before the loads of the next (the
+// hardware completes them in issue order; this keeps the compiler from moving
+// them).
+__device__ __forceinline__ void strip_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// LDS of one applied strip: the words and the numbers of the next picks of its phase
+// columns and of the two frozen columns beside them ([width + 2][N]), the codes
+// and the pick numbers of its list (with an entry more of each, read and not
+// used).
+__host__ __device__ inline size_t list_strip_bytes(int cells, uint32_t n_k) {
+    return ((size_t)cells * 12 + (size_t)(n_k + 1) * 10 + 15) / 16 * 16;
+}
+
+// LDS of drawing one strip's list: first entry and fill count per word, then word
+// and bucket entry per pick.
+__host__ __device__ inline size_t list_draw_bytes(int sites, uint32_t n_k) {
+    return (size_t)(2 * sites + 2) * 4 + (size_t)n_k * 4;
+}
+
+// The list of strip p: its picks [k0, k0 + n_k) by word (column of the phase,
+// row), in pick order for each word.
+__device__ void draw_strip_list(const StripArgs& a, const StripLists& l, uint32_t p, uint64_t* lds) {
+    const int N = a.N, sites = N * a.width, tid = threadIdx.x;
+    const uint32_t n_k = l.n_k;
+    uint32_t* __restrict__ first = reinterpret_cast<uint32_t*>(lds);  // [sites + 1]: counts, then their sums
+    uint32_t* __restrict__ fill = first + sites + 1;                  // [sites + 1]
+    uint16_t* __restrict__ site = reinterpret_cast<uint16_t*>(fill + sites + 1);
+    uint16_t* __restrict__ bucket = site + n_k;
+    const uint32_t c3_pick = 8u * (2u + a.phase) + (a.t_hi << 8);
+    const uint32_t c3_word = 8u * (4u + a.phase) + (a.t_hi << 8);
+    const RoundKeys rk = round_keys(a.k0, a.k1);
+    for (int s = tid; s <= sites; s += kListBlock) first[s] = fill[s] = 0u;
+    __syncthreads();
+    // a Philox block holds two picks; k0 and n_k are even
+    for (uint32_t h = tid; h < n_k / 2; h += kListBlock) {
+        const U4 r = philox_lane_c1(a.t_lo, p, l.k0 / 2 + h, c3_pick, a.k0, a.k1, rk);
+        const uint32_t x[2] = {r.x, r.z}, y[2] = {r.y, r.w};
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t I = (uint32_t)(((uint64_t)x[e] * (uint64_t)(uint32_t)N) >> 32);
+            const uint32_t jl = (uint32_t)(((uint64_t)y[e] * (uint64_t)(uint32_t)a.width) >> 32);
+            const uint32_t s = jl * (uint32_t)N + I;
+            site[2 * h + e] = (uint16_t)s;
+            atomicAdd(&first[s], 1u);
+        }
+    }
+    __syncthreads();
+    // sums over the words before each (at most 512 words: eight per lane)
+    if (tid < 64) {
+        uint32_t c[8], sum = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int s = 8 * tid + e;
+            c[e] = sum;
+            sum += s < sites ? first[s] : 0u;
+        }
+        uint32_t before = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(before, off, 64);
+            before += tid >= off ? o : 0u;
+        }
+        before -= sum;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int s = 8 * tid + e;
+            if (s < sites) first[s] = before + c[e];
+        }
+        if (tid == 0) first[sites] = n_k;
+    }
+    __syncthreads();
+    uint16_t* __restrict__ out_first = l.first + (size_t)p * (size_t)(sites + 1);
+    for (int s = tid; s <= sites; s += kListBlock) out_first[s] = (uint16_t)first[s];
+    for (uint32_t k = tid; k < n_k; k += kListBlock) {
+        const uint32_t s = site[k];
+        bucket[first[s] + atomicAdd(&fill[s], 1u)] = (uint16_t)k;
+    }
+    __syncthreads();
+    uint16_t* __restrict__ out_k = l.k + (size_t)p * n_k;
+    uint64_t* __restrict__ out_codes = l.codes + (size_t)p * n_k;
+    for (uint32_t i = tid; i < n_k; i += kListBlock) {
+        const uint32_t k = bucket[i], s = site[k];
+        uint32_t at = first[s], before = 0;
+        const uint32_t end = first[s + 1];
+        for (uint32_t j = at; j < end; j += 4) {
+            // four reads in flight; those past the word's own entries count for nothing
+            const uint32_t b0 = bucket[j], b1 = bucket[min(j + 1, n_k - 1)], b2 = bucket[min(j + 2, n_k - 1)],
+                           b3 = bucket[min(j + 3, n_k - 1)];
+            before += (b0 < k ? 1u : 0u) + (j + 1 < end && b1 < k ? 1u : 0u) + (j + 2 < end && b2 < k ? 1u : 0u) +
+                      (j + 3 < end && b3 < k ? 1u : 0u);
+        }
+        at += before;
+        AcceptWord acc;
+        accept_word(
+            acc,
+            [&](int g) { return philox_lane_c1(a.t_lo, p, l.k0 + k, (uint32_t)g + c3_word, a.k0, a.k1, rk); }, 21, a.t4,
+            a.t8);
+        const U4 r5 = philox_lane_c1(a.t_lo, p, l.k0 + k, 5u + c3_word, a.k0, a.k1, rk);
+        acc.add<20>(r5.x, a.t4, a.t8);
+        out_k[at] = (uint16_t)k;
+        out_codes[at] = acc.word();
+    }
+}
+
+// The picks of strip p's list applied by V wavefronts, R words per lane.  With one
+// wavefront its LDS operations keep the steps in order; with more a barrier of
+// the workgroup follows the loads of a step and another its stores, and the
+// workgroup's strips (p past the last one: none) step together; busy: two words
+// of LDS, for the last step in which a wavefront of it had picks left.
+template <int R, int V, bool ONE_COLUMN>
+__device__ __forceinline__ void apply_strip_list(uint64_t* __restrict__ W, const StripArgs& a, const StripLists& l,
+                                                 int p, uint64_t* lds, uint32_t* busy) {
+    const bool strip = p < a.strips;
+    p = min(p, a.strips - 1);
+    const int L = a.L, N = a.N, width = ONE_COLUMN ? 1 : a.width, cells = (width + 2) * N, sites = N * width;
+    constexpr int T = 64 * V;
+    const int tid = (int)threadIdx.x & (T - 1);
+    const uint32_t n_k = l.n_k;
+    uint64_t* __restrict__ word = lds;
+    uint64_t* __restrict__ codes = word + cells;
+    uint32_t* __restrict__ next = reinterpret_cast<uint32_t*>(codes + n_k + 1);
+    uint16_t* __restrict__ ks = reinterpret_cast<uint16_t*>(next + cells);
+    const uint64_t* __restrict__ in_codes = l.codes + (size_t)p * n_k;
+    const uint32_t* __restrict__ in_k = reinterpret_cast<const uint32_t*>(l.k + (size_t)p * n_k);  // n_k is even
+    const uint16_t* __restrict__ in_first = l.first + (size_t)p * (size_t)(sites + 1);
+    const int col0 = p * a.S + a.off - 1;  // column of cell 0
+    auto order = [&] {
+        if (V == 1) strip_lds_order();
+        else __syncthreads();
+    };
+#pragma unroll 4
+    for (uint32_t e = tid; e < n_k; e += T) codes[e] = in_codes[e];
+#pragma unroll 4
+    for (uint32_t e = tid; e < n_k / 2; e += T) reinterpret_cast<uint32_t*>(ks)[e] = in_k[e];
+#pragma unroll 4
+    for (int e = tid; e < cells; e += T) {
+        // neighbouring lanes take neighbouring columns
+        const int I = e / (width + 2), cc = e - I * (width + 2);
+        int J = col0 + cc;
+        J = J < 0 ? J + L : J >= L ? J - L : J;
+        word[cc * N + I] = W[(size_t)I * (size_t)L + (size_t)J];
+        next[cc * N + I] = kNoPick;
+    }
+    order();
+    // LDS indexes of the words and their patch words, and the step to the column
+    // to the right; the frozen words beside a single column stay in registers
+    int at[R], up[R], dn[R], pt[R];
+    uint32_t own[R], ptr[R], end[R], su[R], sd[R], mu[R];
+    uint64_t code[R], w[R], live[R], md[R], fl[R], fr[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int s = tid + T * r, sc = min(s, sites - 1);
+        const int cc = sc / N + 1, I = sc - (cc - 1) * N;
+        at[r] = cc * N + I;
+        up[r] = cc * N + (I > 0 ? I - 1 : N - 1);
+        dn[r] = cc * N + (I < N - 1 ? I + 1 : 0);
+        pt[r] = I == 0 ? cc * N + a.istar : I == a.istar ? cc * N : -1;
+        su[r] = I == 0 ? 3u : 0u;
+        sd[r] = I == N - 1 ? 3u : 0u;
+        mu[r] = I == 0 ? 1u << 28 : 0u;
+        md[r] = I == a.istar ? 1ull << a.sh_star : 0ull;
+        live[r] = live_mask(I, L, N);
+        w[r] = word[at[r]];
+        fl[r] = word[at[r] - N];
+        fr[r] = word[at[r] + N];
+        const uint32_t first = in_first[sc];
+        end[r] = in_first[sc + 1];
+        own[r] = strip && s < sites && first < end[r] ? (uint32_t)ks[first] : kNoPick;
+        code[r] = codes[first];
+        ptr[r] = min(first + 1, n_k);
+    }
+    order();
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (tid + T * r < sites) next[at[r]] = own[r];
+    order();
+    const int sh_up = 60 - a.sh_star;  // between the patch bits of rows L - 1 and 0
+    // Every step applies at least the strip's earliest pick left.  A step's loads
+    // are all in flight together (the word's next entry of the list too), and
+    // no more of them than a step needs: with eight wavefronts in a compute unit
+    // the LDS is soon what bounds it (with all six words and numbers of every lane
+    // by 128-bit loads a launch took 37 us instead of 30).
+    for (uint32_t step = 1;; ++step) {
+        bool left = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) left |= own[r] != kNoPick;
+        const bool wave_left = __ballot(left) != 0ull;
+        if (V == 1 && !wave_left) break;
+        if (V > 1 && wave_left) busy[step & 1u] = step;
+        uint64_t wu[R], wd[R], wl[R], wr[R], wp[R], ncode[R];
+        uint32_t m[R], nk[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            uint32_t n_up = next[up[r]], n_dn = next[dn[r]], n_lf = kNoPick, n_rt = kNoPick, n_pt = kNoPick;
+            wu[r] = word[up[r]];
+            wd[r] = word[dn[r]];
+            wl[r] = fl[r];
+            wr[r] = fr[r];
+            wp[r] = 0;
+            if (!ONE_COLUMN) {
+                n_lf = next[at[r] - N];
+                n_rt = next[at[r] + N];
+                wl[r] = word[at[r] - N];
+                wr[r] = word[at[r] + N];
+            }
+            if (pt[r] >= 0) {
+                n_pt = next[pt[r]];
+                wp[r] = word[pt[r]];
+            }
+            nk[r] = ks[ptr[r]];
+            ncode[r] = codes[ptr[r]];
+            m[r] = min(min(n_up, n_dn), min(min(n_lf, n_rt), n_pt));
+        }
+        uint64_t nw[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t pu = (uint32_t)((wp[r] << sh_up) >> 32);  // bit sh_star -> 60
+            const uint64_t pd = wp[r] >> sh_up;                     // bit 60 -> sh_star
+            uint64_t u = wu[r] >> su[r], d = wd[r] << sd[r];
+            u |= (uint64_t)(pu & mu[r]) << 32;
+            d = (d & ~md[r]) | (pd & md[r]);
+            nw[r] = w[r] ^ flip_mask(w[r], u, d, wl[r], wr[r], code[r], live[r]);
+            nk[r] = ptr[r] < end[r] ? nk[r] : kNoPick;
+        }
+        if (V > 1) __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (own[r] < m[r]) {
+                word[at[r]] = nw[r];
+                next[at[r]] = nk[r];
+                w[r] = nw[r];
+                own[r] = nk[r];
+                code[r] = ncode[r];
+                ptr[r] = min(ptr[r] + 1, n_k);
+            }
+        }
+        if (V > 1 && busy[step & 1u] != step) break;  // the same in every wavefront
+        order();
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int s = tid + T * r;
+        if (strip && s < sites) {
+            const int c = s / N, I = s - c * N;
+            W[(size_t)I * (size_t)L + (size_t)(col0 + 1 + c)] = w[r];
+        }
+    }
+}
+
+// Workgroups [0, apply_blocks) apply the lists `l` of phase a, 4 / V strips each; the
+// others draw the lists `ln` of phase n, a strip each.
+template <int R, int V, bool ONE_COLUMN>
+__global__ void __launch_bounds__(kListBlock) k_strip_lists(uint64_t* __restrict__ W, StripArgs a, StripLists l,
+                                                            int apply_blocks, StripArgs n, StripLists ln) {
+    extern __shared__ uint64_t list_lds[];
+    __shared__ uint32_t busy[2];
+    if ((int)blockIdx.x >= apply_blocks) {
+        draw_strip_list(n, ln, blockIdx.x - (uint32_t)apply_blocks, list_lds);
+        return;
+    }
+    if (threadIdx.x < 2) busy[threadIdx.x] = 0u;  // (steps count from 1; barriers follow)
+    const int group = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / (64 * V)));
+    const int p = (int)blockIdx.x * (4 / V) + group;
+    if (V == 1 && p >= a.strips) return;
+    apply_strip_list<R, V, ONE_COLUMN>(
+        W, a, l, p, list_lds + (size_t)group * (list_strip_bytes((a.width + 2) * a.N, l.n_k) / sizeof(uint64_t)), busy);
+}
+
+// Wavefronts of a strip of `sites` words per phase: a word per lane as far as four
+// go (L = 2016 in strips of two columns, 96 words: two wavefronts 30 us per launch,
+// one with two words per lane 33).
+inline int list_waves(int sites) { return sites <= 64 ? 1 : sites <= 128 ? 2 : 4; }
+inline int list_strips(const StripArgs& a) { return 4 / list_waves(a.N * a.width); }
+
 inline unsigned strip_grid(uint64_t n, int block) { return (unsigned)((n + block - 1) / block); }
 
 }  // namespace
@@ -330,6 +632,61 @@ hipError_t launch_strip_apply(uint64_t* W, const StripArgs& a, uint32_t n_k, con
     if (lds > kStripLdsBytes) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_strip_apply, dim3(strip_grid((uint64_t)a.strips, chains)), dim3(64), lds, s, W, a, chains,
                        n_k, pos, codes);
+    return hipGetLastError();
+}
+
+uint32_t strip_list_picks(const StripArgs& a, int64_t max_entries) {
+    const int64_t sites = (int64_t)a.N * a.width;
+    if (sites > 512) return 0;
+    const int64_t room = (int64_t)(kStripListLds / list_strips(a)) - (int64_t)list_strip_bytes((a.width + 2) * a.N, 1);
+    int64_t n = std::min<int64_t>({room / 10, max_entries / a.strips, 65534, (int64_t)a.picks});
+    n &= ~int64_t(1);
+    return n < 2 || list_draw_bytes((int)sites, (uint32_t)n) > kStripListLds ? 0u : (uint32_t)n;
+}
+
+hipError_t allow_strip_list_lds() {
+    const void* fs[] = {reinterpret_cast<const void*>(&k_strip_lists<1, 1, true>),
+                        reinterpret_cast<const void*>(&k_strip_lists<1, 1, false>),
+                        reinterpret_cast<const void*>(&k_strip_lists<1, 2, true>),
+                        reinterpret_cast<const void*>(&k_strip_lists<1, 2, false>),
+                        reinterpret_cast<const void*>(&k_strip_lists<1, 4, true>),
+                        reinterpret_cast<const void*>(&k_strip_lists<1, 4, false>),
+                        reinterpret_cast<const void*>(&k_strip_lists<2, 4, true>),
+                        reinterpret_cast<const void*>(&k_strip_lists<2, 4, false>)};
+    for (const void* f : fs) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripListLds);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_strip_lists(uint64_t* W, const StripArgs& a, const StripLists& l, const StripArgs& n,
+                              const StripLists& ln, hipStream_t s) {
+    const int per = l.n_k ? list_strips(a) : 1;
+    const int apply_blocks = l.n_k ? (a.strips + per - 1) / per : 0;
+    const int draw_blocks = ln.n_k ? n.strips : 0;
+    if (apply_blocks + draw_blocks == 0) return hipSuccess;
+    const int sites = l.n_k ? a.N * a.width : 1;
+    size_t lds = l.n_k ? per * list_strip_bytes((a.width + 2) * a.N, l.n_k) : 0;
+    if (ln.n_k) lds = std::max(lds, list_draw_bytes(n.N * n.width, ln.n_k));
+    if (sites > 512 || (ln.n_k && n.N * n.width > 512) || lds > kStripListLds || l.n_k % 2 || ln.n_k % 2 || ln.k0 % 2)
+        return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(apply_blocks + draw_blocks)), blk(kListBlock);
+#define ISING_STRIP_LISTS(R_, V_)                                                                        \
+    if (a.width == 1)                                                                                    \
+        hipLaunchKernelGGL((k_strip_lists<R_, V_, true>), grid, blk, lds, s, W, a, l, apply_blocks, n, ln); \
+    else                                                                                                 \
+        hipLaunchKernelGGL((k_strip_lists<R_, V_, false>), grid, blk, lds, s, W, a, l, apply_blocks, n, ln)
+    if (sites <= 64) {
+        ISING_STRIP_LISTS(1, 1);
+    } else if (sites <= 128) {
+        ISING_STRIP_LISTS(1, 2);
+    } else if (sites <= 256) {
+        ISING_STRIP_LISTS(1, 4);
+    } else {
+        ISING_STRIP_LISTS(2, 4);
+    }
+#undef ISING_STRIP_LISTS
     return hipGetLastError();
 }
 
