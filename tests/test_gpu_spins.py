@@ -33,3 +33,15 @@ def test_set_spins_roundtrip(L):
         assert (lat.spins() == s).all()
     finally:
         lat.close()
+
+
+# rows that fill, just miss and just exceed a wavefront's and a workgroup's run
+@pytest.mark.parametrize("L", [4, 62, 64, 66, 254, 256, 258, 1022, 1024, 1026, 2058])
+@pytest.mark.parametrize("hot", [True, False])
+def test_initial_state_matches_oracle(L, hot):
+    print(f"initial state L={L} hot={hot}", flush=True)
+    lat = ising.Lattice(L, 77 + (3 << 32), hot=hot)
+    try:
+        assert (lat.spins() == oracle.init(L, 77 + (3 << 32), hot)).all()
+    finally:
+        lat.close()
