@@ -17,7 +17,7 @@ struct ising_replicas {
     uint64_t* W = nullptr;
     hipStream_t stream = nullptr;
     int wpt = 2;
-    unsigned long long* d_totals = nullptr;  // 42 counters of the observables reduction
+    unsigned long long* d_totals = nullptr;  // counters of the observables reduction
     int64_t* d_EM = nullptr;                 // E[21], M[21] of ising_replicas_observables
     uint8_t* d_stage = nullptr;              // spin output staging, spin_stage_bytes(L)
 };
@@ -89,10 +89,10 @@ int ising_replicas_create(int32_t L, uint64_t seed, int32_t init, void* stream, 
     // 20.4, 8192 300 / 271 / 253)
     h->wpt = L < 1024 ? 1 : L < 1536 ? 2 : 4;
     hipError_t e = hipMalloc(&h->W, sizeof(uint64_t) * (size_t)L * (size_t)L);
-    if (e == hipSuccess) e = hipMalloc(&h->d_totals, sizeof(unsigned long long) * 2 * kReplicas);
+    if (e == hipSuccess) e = hipMalloc(&h->d_totals, sizeof(unsigned long long) * kTotalCopies * kTotalStride);
     if (e == hipSuccess) e = hipMalloc(&h->d_EM, sizeof(int64_t) * 2 * kReplicas);
     if (e == hipSuccess) e = hipMalloc(&h->d_stage, spin_stage_bytes(L));
-    if (e == hipSuccess) e = hipMemsetAsync(h->d_totals, 0, sizeof(unsigned long long) * 2 * kReplicas, h->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(h->d_totals, 0, sizeof(unsigned long long) * kTotalCopies * kTotalStride, h->stream);
     if (e == hipSuccess) e = launch_replica_init(h->W, L, seed, init == ISING_HOT, h->stream);
     if (e != hipSuccess) {
         release(h);

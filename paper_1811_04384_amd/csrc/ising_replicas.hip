@@ -110,7 +110,11 @@ __global__ void __launch_bounds__(kHalfSweepBlock) k_replica_halfsweep(uint64_t*
 // fields shifted down by 3), at most 2 per word, flushing to per-replica
 // counters every 31 words; field 20 (bit 60, whose lane would have only 4
 // bits) is counted directly.  The workgroup then sums the counters in LDS
-// and adds them to totals[0..20] (bonds) and totals[21..41] (up spins).
+// and adds them to one of kTotalCopies copies of the totals, [0..20] (bonds) and
+// [21..41] (up spins).  A thread loads four words at a time: one by one, each
+// waits for its loads in turn.  us per sample, before (one by one, 32 words per
+// thread, one copy of the totals) and now: L = 256 22/9, 1024 29/13, 2048
+// 32/17, 4096 68/42; with one copy of the totals 10, 17, 26, 48.
 constexpr uint64_t kLaneFields = 0x0041041041041041ull;  // bits 0, 6, ..., 54
 
 __device__ __forceinline__ void flush_lanes(uint64_t& even, uint64_t& odd, uint32_t* cnt) {
@@ -123,7 +127,7 @@ __device__ __forceinline__ void flush_lanes(uint64_t& even, uint64_t& odd, uint3
     odd = 0;
 }
 
-__global__ void __launch_bounds__(256) k_replica_observe(const uint64_t* __restrict__ W, int L,
+__global__ void __launch_bounds__(256) k_replica_observe(const uint64_t* __restrict__ W, int L, uint32_t run,
                                                         unsigned long long* __restrict__ totals) {
     __shared__ uint32_t sums[2 * kReplicas];
     for (int i = threadIdx.x; i < 2 * kReplicas; i += blockDim.x) sums[i] = 0;
@@ -133,19 +137,42 @@ __global__ void __launch_bounds__(256) k_replica_observe(const uint64_t* __restr
     for (int k = 0; k < kReplicas; ++k) anti[k] = ups[k] = 0;
     uint64_t ae = 0, ao = 0, ue = 0, uo = 0;
     int pending = 0;
+    // a run of consecutive words per workgroup, four of them in flight per thread
     const uint64_t n = (uint64_t)L * (uint64_t)L;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(i / (uint64_t)L), c = (int)(i - (uint64_t)r * (uint64_t)L);
-        const uint64_t w = W[i];
-        const uint64_t xr = w ^ W[(size_t)r * L + (c == L - 1 ? 0 : c + 1)];
-        const uint64_t xd = w ^ W[(size_t)(r == L - 1 ? 0 : r + 1) * L + c];
-        ae += (xr & kLaneFields) + (xd & kLaneFields);
-        ao += ((xr >> 3) & kLaneFields) + ((xd >> 3) & kLaneFields);
-        ue += w & kLaneFields;
-        uo += (w >> 3) & kLaneFields;
-        anti[0] += (uint32_t)(xr >> 60) + (uint32_t)(xd >> 60);  // field 20 = replica 0
-        ups[0] += (uint32_t)(w >> 60);
-        if (++pending == 31) {
+    const uint64_t end = min(n, (uint64_t)(blockIdx.x + 1) * run);
+    uint64_t i = (uint64_t)blockIdx.x * run + threadIdx.x;
+    int r = (int)(i / (uint64_t)L), c = (int)(i - (uint64_t)r * (uint64_t)L);
+    while (i < end) {
+        uint64_t w[4], rt[4], dn[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool in = i < end;
+            const uint64_t* row = W + (in ? (size_t)r * L : 0);
+            const uint64_t* below = W + (in && r < L - 1 ? (size_t)(r + 1) * L : 0);
+            const int cc = in ? c : 0;
+            w[k] = row[cc];
+            rt[k] = row[cc == L - 1 ? 0 : cc + 1];
+            dn[k] = below[cc];
+            if (!in) w[k] = rt[k] = dn[k] = 0;
+            i += 256;
+            c += 256;
+            while (c >= L) {
+                c -= L;
+                r += 1;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint64_t xr = w[k] ^ rt[k], xd = w[k] ^ dn[k];
+            ae += (xr & kLaneFields) + (xd & kLaneFields);
+            ao += ((xr >> 3) & kLaneFields) + ((xd >> 3) & kLaneFields);
+            ue += w[k] & kLaneFields;
+            uo += (w[k] >> 3) & kLaneFields;
+            anti[0] += (uint32_t)(xr >> 60) + (uint32_t)(xd >> 60);  // field 20 = replica 0
+            ups[0] += (uint32_t)(w[k] >> 60);
+        }
+        pending += 4;
+        if (pending > 27) {
             flush_lanes(ae, ao, anti);
             flush_lanes(ue, uo, ups);
             pending = 0;
@@ -162,6 +189,7 @@ __global__ void __launch_bounds__(256) k_replica_observe(const uint64_t* __restr
         }
     }
     __syncthreads();
+    totals += (blockIdx.x % kTotalCopies) * kTotalStride;
     for (int i = threadIdx.x; i < 2 * kReplicas; i += blockDim.x) atomicAdd(&totals[i], (unsigned long long)sums[i]);
 }
 
@@ -172,8 +200,14 @@ __global__ void k_replica_finalize(unsigned long long* __restrict__ totals, int 
     const int k = threadIdx.x;
     if (k >= kReplicas) return;
     const int64_t n = (int64_t)L * (int64_t)L;
-    const int64_t E = 2 * (int64_t)totals[k] - 2 * n;
-    const int64_t M = 2 * (int64_t)totals[kReplicas + k] - n;
+    int64_t bonds = 0, up = 0;
+#pragma unroll
+    for (int x = 0; x < kTotalCopies; ++x) {
+        bonds += (int64_t)totals[x * kTotalStride + k];
+        up += (int64_t)totals[x * kTotalStride + kReplicas + k];
+    }
+    const int64_t E = 2 * bonds - 2 * n;
+    const int64_t M = 2 * up - n;
     if (series_E) series_E[idx * kReplicas + k] = E;
     if (series_M) series_M[idx * kReplicas + k] = M;
     if (mom) add_sample(mom[k], E, M);
@@ -181,8 +215,11 @@ __global__ void k_replica_finalize(unsigned long long* __restrict__ totals, int 
         out_EM[k] = E;
         out_EM[kReplicas + k] = M;
     }
-    totals[k] = 0;
-    totals[kReplicas + k] = 0;
+#pragma unroll
+    for (int x = 0; x < kTotalCopies; ++x) {
+        totals[x * kTotalStride + k] = 0;
+        totals[x * kTotalStride + kReplicas + k] = 0;
+    }
 }
 
 // Spins of replica k in rows r0 .. r0 + nrows - 1, row major.
@@ -219,8 +256,11 @@ hipError_t launch_replica_halfsweep(int wpt, uint64_t* W, const ReplicaArgs& a, 
 hipError_t launch_replica_observe(const uint64_t* W, int L, unsigned long long* totals, int64_t* series_E,
                                   int64_t* series_M, int64_t idx, Moments* mom, int64_t* out_EM, hipStream_t s) {
     const uint64_t n = (uint64_t)L * (uint64_t)L;
-    const unsigned blocks = std::max(1u, std::min(rgrid(n, 256 * 32), 2048u));
-    hipLaunchKernelGGL(k_replica_observe, dim3(blocks), dim3(256), 0, s, W, L, totals);
+    // about 512 workgroups (more add more counts than they save in loads: L = 4096
+    // 42 us with 512, 43 with 1024), of at least eight words per thread
+    const uint32_t run = (uint32_t)std::max<uint64_t>(256 * 8, (n + 512 * 256 - 1) / (512 * 256) * 256);
+    const unsigned blocks = rgrid(n, run);
+    hipLaunchKernelGGL(k_replica_observe, dim3(blocks), dim3(256), 0, s, W, L, run, totals);
     hipLaunchKernelGGL(k_replica_finalize, dim3(1), dim3(64), 0, s, totals, L, series_E, series_M, idx, mom, out_EM);
     return hipGetLastError();
 }

@@ -25,7 +25,8 @@ hipError_t launch_replica_init(uint64_t* W, int L, uint64_t seed, int hot, hipSt
 hipError_t launch_replica_halfsweep(int wpt, uint64_t* W, const ReplicaArgs& a, int colour, hipStream_t s);
 // Per-replica E, M of the current words: series slot idx (21 entries each),
 // moment sums mom[21], out_EM[0..41] (E then M), each optional.  `totals` is
-// 42 zeroed unsigned 64-bit counters, left zeroed.
+// kTotalCopies x kTotalStride zeroed unsigned 64-bit counters, left zeroed.
+constexpr int kTotalCopies = 8, kTotalStride = 64;  // counters apart
 hipError_t launch_replica_observe(const uint64_t* W, int L, unsigned long long* totals, int64_t* series_E,
                                   int64_t* series_M, int64_t idx, Moments* mom, int64_t* out_EM, hipStream_t s);
 // Spins of replica k in rows r0 .. r0 + nrows - 1 as bytes (row major).
