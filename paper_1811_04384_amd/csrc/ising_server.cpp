@@ -28,7 +28,7 @@ using namespace ising;
 
 namespace {
 
-constexpr int kServerWpt = 1;  // words per thread of the server's kernels
+constexpr int kServerWpt = 1;  // words per thread of the server's resident lattices
 constexpr int kStages = 2;     // quanta in flight = staging buffer sets
 constexpr int kRing = 4;       // read-back ring entries
 
@@ -200,8 +200,13 @@ int enqueue_quantum(ising_server* s) {
         const Slot& sl = sc.slots()[i];
         if (!sl.active || sl.planned <= 0) continue;
         const Geometry g = make_geometry(sl.req.L);
-        if (!is_resident(s, g)) n_waves += waves_per_colour(g, kServerWpt);
+        if (!is_resident(s, g)) n_waves += waves_per_colour(g, 1);
     }
+    // two words per thread where one would be more wavefronts than the device holds
+    // at once (bursts of 16 requests of L = 128 ... 4096, six seeds: 16.3 / 17.1, 20.1
+    // / 21.1, 12.7 / 13.3 ms and three within 1 %; the line at 12288 or 16384
+    // wavefronts is no better); below, more wavefronts fill it better
+    const int wpt = n_waves > 8192 ? 2 : 1;
     int rc = grow_waves(s, st, std::max<int64_t>(n_waves, 1));
     if (rc != ISING_OK) return rc;
     int32_t n_res = 0, K = 0;
@@ -232,7 +237,7 @@ int enqueue_quantum(ising_server* s) {
         } else {
             d.part_begin = (int32_t)n_waves;
             for (int32_t I = 0; I < g.N; ++I)
-                for (int32_t w0 = 0; w0 < g.L / 2; w0 += 64 * kServerWpt) st.waves[n_waves++] = {i, I, w0};
+                for (int32_t w0 = 0; w0 < g.L / 2; w0 += 64 * wpt) st.waves[n_waves++] = {i, I, w0};
             d.part_count = (int32_t)(n_waves - d.part_begin);
         }
     }
@@ -252,9 +257,9 @@ int enqueue_quantum(ising_server* s) {
             ISING_HIP(hipEventRecord(s->join_ev, s->side));
         }
         for (int32_t k = 0; k < K && n_waves; ++k) {
-            ISING_HIP(launch_halfsweep_multi(kServerWpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 0,
+            ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 0,
                                              (uint32_t)k, nullptr, nullptr, 0, s->stream));
-            ISING_HIP(launch_halfsweep_multi(kServerWpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 1,
+            ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 1,
                                              (uint32_t)k, nullptr, nullptr, 0, s->stream));
         }
         if (n_res) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));
