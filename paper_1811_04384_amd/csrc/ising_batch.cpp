@@ -422,7 +422,6 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
             base += (int64_t)b->draw_S * b->geo[e.lat].N * b->geo[e.lat].L;
         }
         b->draw_lds = wave_apply_lds_bytes(max_NL, b->draw_S);
-        ISING_HIP(allow_wave_apply_lds(b->device));
         ISING_HIP(hipMalloc(&b->d_draw, sizeof(DrawLat) * dl.size()));
         ISING_HIP(hipMemcpy(b->d_draw, dl.data(), sizeof(DrawLat) * dl.size(), hipMemcpyHostToDevice));
         ISING_HIP(hipMalloc(&b->d_codes, sizeof(uint64_t) * (size_t)base));

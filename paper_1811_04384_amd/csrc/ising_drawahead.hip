@@ -428,24 +428,6 @@ int32_t wave_apply_block(int32_t words, int32_t wmax) { return ((words + wmax - 
 
 size_t wave_apply_lds_bytes(int32_t NL, int32_t max_samples) { return (size_t)NL * 8 + (size_t)max_samples * 8; }
 
-hipError_t allow_wave_apply_lds(int device) {
-    const int lim = (int)resident_lds_limit(device);
-    const void* fs[] = {reinterpret_cast<const void*>(&k_wave_apply<1, 8, 64>),
-                        reinterpret_cast<const void*>(&k_wave_apply<2, 8, 64>),
-                        reinterpret_cast<const void*>(&k_wave_apply<3, 4, 64>),
-                        reinterpret_cast<const void*>(&k_wave_apply<4, 4, 64>),
-                        reinterpret_cast<const void*>(&k_wave_apply<1, 8, 256>),
-                        reinterpret_cast<const void*>(&k_wave_apply<2, 8, 256>),
-                        reinterpret_cast<const void*>(&k_wave_apply<3, 4, 256>),
-                        reinterpret_cast<const void*>(&k_wave_apply<4, 4, 256>),
-                        reinterpret_cast<const void*>(&k_wave_apply<1, 4, 1024>)};
-    for (const void* f : fs) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
 hipError_t launch_draw_codes(const LatticeDesc* descs, const LatticeState* states, const DrawLat* lats, int32_t n_lats,
                              int32_t max_n_draw, uint64_t* codes, int32_t sweep_off, int32_t S, hipStream_t s) {
     if (n_lats <= 0 || S <= 0) return hipSuccess;
@@ -483,6 +465,8 @@ hipError_t launch_wave_apply(int wmax, int block, const LatticeDesc* descs, Latt
         }
     } else if (wmax == 1) {
         ISING_WAVE_APPLY(1, 4, 1024);
+    } else if (wmax == 2) {
+        ISING_WAVE_APPLY(2, 2, 1024);
     } else {
         return hipErrorInvalidValue;
     }

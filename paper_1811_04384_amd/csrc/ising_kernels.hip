@@ -22,25 +22,23 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 // ---------------------------------------------------------------------------
 // Initial state.  Hot start: a site is up iff its stream-0 draw at t = 0 is below
 // 2^31 (the random initialisation of Section 5.1 with a reproducible
-// generator).  A wavefront takes 256 words of a word row, four per lane, so that
-// the block of position 20, which eight columns share in two, is drawn once for
-// four words; what is left is five Philox blocks and two instructions per
+// generator).  A wavefront takes 64 `runs` words of a word row, one to four per lane:
+// with four the block of position 20, which eight columns share in two, is drawn
+// once for four words; what is left is five Philox blocks and two instructions per
 // position (the draw's upper bit shifted to its field, collected inverted).  L =
-// 32768: 329 us, 462 with a word per thread that draws all six blocks.
+// 32768: 296 us, 419 with a word per thread that draws all six blocks.
 // ---------------------------------------------------------------------------
-constexpr int kInitRun = 256;  // words per wavefront
-
-__global__ void __launch_bounds__(256) k_init(uint64_t* __restrict__ W, Geometry g, uint32_t k0, uint32_t k1,
-                                              int hot) {
+__global__ void __launch_bounds__(256) k_init(uint64_t* __restrict__ W, Geometry g, uint32_t k0, uint32_t k1, int hot,
+                                              int runs) {
     __shared__ uint4 last[4][64];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = lane_id();
     const int I = (int)blockIdx.y;
-    const int w0 = ((int)blockIdx.x * 4 + wv) * kInitRun;
+    const int w0 = ((int)blockIdx.x * 4 + wv) * 64 * runs;
     if (w0 >= g.L) return;
     const uint64_t live = live_mask(I, g.L, g.N);
     uint64_t* __restrict__ row = W + (size_t)I * (size_t)g.L;
     if (!hot) {
-        for (int J = w0 + lane; J < min(g.L, w0 + kInitRun); J += 64) row[J] = live;
+        for (int J = w0 + lane; J < min(g.L, w0 + 64 * runs); J += 64) row[J] = live;
         return;
     }
     const uint32_t row_base = (uint32_t)I * (uint32_t)g.L;
@@ -56,7 +54,7 @@ __global__ void __launch_bounds__(256) k_init(uint64_t* __restrict__ W, Geometry
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 #pragma unroll 1
-    for (int k = 0; k < kInitRun / 64; ++k) {
+    for (int k = 0; k < runs; ++k) {
         const int x = 64 * k + lane, J = w0 + x;
         if (J >= g.L) break;
         uint32_t lo = 0, hi = 0;  // bits set where the draw is 2^31 or above
@@ -575,8 +573,12 @@ hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t s) {
 }
 
 hipError_t launch_init(uint64_t* W, const Geometry& g, uint64_t seed, int hot, hipStream_t s) {
-    hipLaunchKernelGGL(k_init, dim3(grid_for((uint64_t)g.L, 4 * kInitRun), g.N), dim3(256), 0, s, W, g, (uint32_t)seed,
-                       (uint32_t)(seed >> 32), hot);
+    // four words per lane only where there are wavefronts enough without (us per
+    // launch with one / four: L = 2500 4.7 / 5.7, 4096 8.7 / 8.8, 5120 12.2 / 11.1,
+    // 9998 42 / 36, 32768 362 / 296)
+    const int runs = (int64_t)g.N * g.L >= (1 << 20) ? 4 : 1;
+    hipLaunchKernelGGL(k_init, dim3(grid_for((uint64_t)g.L, 4 * 64 * runs), g.N), dim3(256), 0, s, W, g,
+                       (uint32_t)seed, (uint32_t)(seed >> 32), hot, runs);
     return hipGetLastError();
 }
 

@@ -229,13 +229,15 @@ hipError_t launch_small(int block, const LatticeDesc* descs, LatticeState* state
 hipError_t launch_draw_codes(const LatticeDesc* descs, const LatticeState* states, const DrawLat* lats, int32_t n_lats,
                              int32_t max_n_draw, uint64_t* codes, int32_t sweep_off, int32_t S, hipStream_t s);
 // Apply pass over the same sweeps: one workgroup of `block` threads (a
-// multiple of 64; at most 256, or 1024 with one word per thread) per listed
+// multiple of 64; at most 256, or 1024 with one or two words per thread) per listed
 // lattice, wmax (1 to 4: wave_apply_words_per_thread) words of a colour per thread, codes loaded
 // from the buffer into registers ahead of use; lds_bytes =
 // wave_apply_lds_bytes(largest N L, S).  Samples as launch_resident.
 hipError_t launch_wave_apply(int wmax, int block, const LatticeDesc* descs, LatticeState* states, const DrawLat* lats,
                              int32_t n_lats, const uint64_t* codes, int32_t sweep_off, int32_t S, int32_t every,
                              size_t lds_bytes, hipStream_t s);
+// (at most 48 KB: 2040 words and 4096 samples, so that no kernel needs leave for
+// more than the 64 KB that every launch may use)
 size_t wave_apply_lds_bytes(int32_t NL, int32_t max_samples);
 // Threads of an apply workgroup of lattices of up to `words` words of a colour,
 // wmax of them per thread: no wavefront without words, as an idle one still takes
@@ -245,7 +247,6 @@ int32_t wave_apply_block(int32_t words, int32_t wmax);
 // Words of one colour per thread of a `block`-thread apply workgroup (0:
 // more than 4).
 int32_t wave_apply_words_per_thread(int32_t L, int32_t N, int32_t block);
-hipError_t allow_wave_apply_lds(int device);
 
 // One lattice of a handle with its draws spread over the chip: a launch applies
 // the n_apply sweeps whose codes the launch before drew, and draws the n_draw

@@ -2,7 +2,7 @@
 // share the GPU.  Their packed lattices and sweep counters stay resident in
 // one device arena; every quantum advances all resident lattices together
 // (tiled lattices in shared half-sweep launches, small ones one workgroup
-// each), and requests join and leave between quanta.  Admission is by
+// each from codes drawn by the whole chip), and requests join and leave between quanta.  Admission is by
 // memory footprint (first-fit in the arena) and free slots, in arrival order.
 //
 // Pipelining: the host plans, uploads and enqueues quantum q+1 while quantum
@@ -28,7 +28,18 @@ using namespace ising;
 
 namespace {
 
-constexpr int kServerWpt = 1;  // words per thread of the server's resident lattices
+// Acceptance codes of the small lattices held at once (a device buffer): small
+// lattices go in groups of which it holds at least eight sweeps (about 300 of L =
+// 256, and 157 sweeps of 16 of them).
+constexpr int64_t kServerCodeWords = int64_t(8) << 20;
+constexpr int64_t kServerGroupWords = kServerCodeWords / 8;
+
+// A group: entries [begin, end) of the quantum's table of small lattices.
+struct SmallGroup {
+    int32_t begin, end;
+    int64_t words;       // of its lattices
+    int32_t max_NL, max_words, max_draws, K;  // the largest lattice's words, words of a colour, draw items; sweeps
+};
 constexpr int kStages = 2;     // quanta in flight = staging buffer sets
 constexpr int kRing = 4;       // read-back ring entries
 
@@ -41,7 +52,7 @@ struct Stage {
     LatticeDesc* desc = nullptr;
     WaveItem* waves = nullptr;
     int64_t waves_cap = 0;
-    int32_t* ids = nullptr;
+    DrawLat* draw = nullptr;
     hipEvent_t done = nullptr;  // recorded after the quantum's kernels
     bool used = false;
 };
@@ -68,7 +79,9 @@ struct ising_server {
     LatticeState* d_state = nullptr;
     WaveItem* d_waves = nullptr;
     int64_t d_waves_cap = 0;
-    int32_t* d_ids = nullptr;  // resident ids of the current quantum
+    DrawLat* d_draw = nullptr;  // small lattices of the current quantum
+    uint64_t* d_codes = nullptr;  // their acceptance codes, kServerCodeWords
+    int cus = 0;
     int32_t* d_fin = nullptr;  // ids of a read-back batch
     int64_t* d_em = nullptr;   // (E, M) of a read-back batch
     Stage stage[kStages];
@@ -91,13 +104,14 @@ void release(ising_server* s) {
     if (s->d_desc) (void)hipFree(s->d_desc);
     if (s->d_state) (void)hipFree(s->d_state);
     if (s->d_waves) (void)hipFree(s->d_waves);
-    if (s->d_ids) (void)hipFree(s->d_ids);
+    if (s->d_draw) (void)hipFree(s->d_draw);
+    if (s->d_codes) (void)hipFree(s->d_codes);
     if (s->d_fin) (void)hipFree(s->d_fin);
     if (s->d_em) (void)hipFree(s->d_em);
     for (Stage& st : s->stage) {
         if (st.desc) (void)hipHostFree(st.desc);
         if (st.waves) (void)hipHostFree(st.waves);
-        if (st.ids) (void)hipHostFree(st.ids);
+        if (st.draw) (void)hipHostFree(st.draw);
         if (st.done) (void)hipEventDestroy(st.done);
     }
     for (Readback& r : s->ring) {
@@ -181,9 +195,13 @@ int admit_queued(ising_server* s) {
     return ISING_OK;
 }
 
+// (at most 27 KB of LDS, which every launch may use)
 bool is_resident(const ising_server* s, const Geometry& g) {
     return g.L <= s->resident_max_L && (size_t)g.N * g.L * 8 <= s->lds_limit;
 }
+
+// Sweeps of a group whose codes are drawn together.
+int32_t group_sweeps(const SmallGroup& gr) { return (int32_t)std::min<int64_t>(gr.K, kServerCodeWords / gr.words); }
 
 // Plan the next quantum, upload its tables through a staging set and enqueue
 // its kernels.  Descriptors cover every active slot (those already done with
@@ -210,7 +228,7 @@ int enqueue_quantum(ising_server* s) {
     int rc = grow_waves(s, st, std::max<int64_t>(n_waves, 1));
     if (rc != ISING_OK) return rc;
     int32_t n_res = 0, K = 0;
-    size_t lds = 0;
+    std::vector<SmallGroup> groups;
     n_waves = 0;
     for (int32_t i = 0; i < slots; ++i) {
         const Slot& sl = sc.slots()[i];
@@ -232,8 +250,18 @@ int enqueue_quantum(ising_server* s) {
         K = std::max<int32_t>(K, (int32_t)sl.planned);
         if (is_resident(s, g)) {
             d.resident = 1;
-            st.ids[n_res++] = i;
-            lds = std::max(lds, (size_t)g.N * g.L * 8);
+            st.draw[n_res] = {i, 2 * g.N * ((g.L + 7) / 8), 0};
+            const int64_t words = (int64_t)g.N * g.L;
+            if (groups.empty() || groups.back().words + words > kServerGroupWords)
+                groups.push_back({n_res, n_res, 0, 0, 0, 0, 0});
+            SmallGroup& gr = groups.back();
+            gr.end = n_res + 1;
+            gr.words += words;
+            gr.max_NL = std::max(gr.max_NL, g.N * g.L);
+            gr.max_words = std::max(gr.max_words, g.N * (g.L / 2));
+            gr.max_draws = std::max(gr.max_draws, st.draw[n_res].n_draw);
+            gr.K = std::max<int32_t>(gr.K, (int32_t)sl.planned);
+            ++n_res;
         } else {
             d.part_begin = (int32_t)n_waves;
             for (int32_t I = 0; I < g.N; ++I)
@@ -244,17 +272,46 @@ int enqueue_quantum(ising_server* s) {
     ISING_HIP(hipMemcpyAsync(s->d_desc, st.desc, sizeof(LatticeDesc) * slots, hipMemcpyHostToDevice, s->stream));
     if (n_waves)
         ISING_HIP(hipMemcpyAsync(s->d_waves, st.waves, sizeof(WaveItem) * n_waves, hipMemcpyHostToDevice, s->stream));
-    if (n_res) ISING_HIP(hipMemcpyAsync(s->d_ids, st.ids, sizeof(int32_t) * n_res, hipMemcpyHostToDevice, s->stream));
+    for (const SmallGroup& gr : groups) {
+        int64_t base = 0;
+        const int64_t S = group_sweeps(gr);
+        for (int32_t k = gr.begin; k < gr.end; ++k) {
+            const LatticeDesc& d = st.desc[st.draw[k].lat];
+            st.draw[k].base = base;
+            base += S * d.N * d.L;
+        }
+    }
+    if (n_res) ISING_HIP(hipMemcpyAsync(s->d_draw, st.draw, sizeof(DrawLat) * n_res, hipMemcpyHostToDevice, s->stream));
     if (K > 0) {
-        const int block = 64, rblock = 256;
+        const int block = 64;
         if (n_res) {
-            // the resident lattices (one workgroup each) run on the side
-            // stream, overlapping the tiled launches of the other lattices
-            ISING_HIP(set_resident_lds(kServerWpt, lds));
-            ISING_HIP(hipEventRecord(s->fork_ev, s->stream));
-            ISING_HIP(hipStreamWaitEvent(s->side, s->fork_ev, 0));
-            ISING_HIP(launch_resident(kServerWpt, rblock, s->d_desc, s->d_state, s->d_ids, n_res, K, 0, lds, s->side));
-            ISING_HIP(hipEventRecord(s->join_ev, s->side));
+            // The small lattices (one workgroup each) run on the side stream,
+            // beside the tiled launches of the other lattices if there are any; as in
+            // a batch, a word per thread where each has a compute unit to itself.  us
+            // for requests of 300 to 500 sweeps in quanta of 100, with workgroups that
+            // draw their own codes / these: 8 of L = 64 1379/775, 16 of L = 256
+            // 5261/836, 300 of L = 128 and 256 8519/3663; 100 of L = 16 in quanta of
+            // one sweep, where launches and the join of two streams are all there is,
+            // 1852/1369.
+            if (n_waves) {
+                ISING_HIP(hipEventRecord(s->fork_ev, s->stream));
+                ISING_HIP(hipStreamWaitEvent(s->side, s->fork_ev, 0));
+            }
+            const hipStream_t on = n_waves ? s->side : s->stream;
+            for (const SmallGroup& gr : groups) {
+                const int32_t n = gr.end - gr.begin, S = group_sweeps(gr);
+                const int wmax = n <= s->cus || gr.max_words > 1024 ? (gr.max_words + 1023) / 1024
+                                                                    : (gr.max_words + 255) / 256;
+                for (int32_t done = 0; done < gr.K; done += S) {
+                    const int32_t k = std::min(S, gr.K - done);
+                    ISING_HIP(launch_draw_codes(s->d_desc, s->d_state, s->d_draw + gr.begin, n, gr.max_draws,
+                                                s->d_codes, done, k, on));
+                    ISING_HIP(launch_wave_apply(wmax, wave_apply_block(gr.max_words, wmax), s->d_desc, s->d_state,
+                                                s->d_draw + gr.begin, n, s->d_codes, done, k, 0,
+                                                wave_apply_lds_bytes(gr.max_NL, 0), on));
+                }
+            }
+            if (n_waves) ISING_HIP(hipEventRecord(s->join_ev, s->side));
         }
         for (int32_t k = 0; k < K && n_waves; ++k) {
             ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 0,
@@ -262,7 +319,7 @@ int enqueue_quantum(ising_server* s) {
             ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 1,
                                              (uint32_t)k, nullptr, nullptr, 0, s->stream));
         }
-        if (n_res) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));
+        if (n_res && n_waves) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));
         ISING_HIP(launch_chunk_end(s->d_desc, s->d_state, slots, nullptr, 0, (uint32_t)K, s->stream));
     }
     ISING_HIP(hipEventRecord(st.done, s->stream));
@@ -342,12 +399,14 @@ int ising_server_create(size_t hbm_budget, int32_t max_slots, int32_t quantum_sw
     }
     e = hipMalloc(&s->d_desc, sizeof(LatticeDesc) * max_slots);
     if (e == hipSuccess) e = hipMalloc(&s->d_state, sizeof(LatticeState) * max_slots);
-    if (e == hipSuccess) e = hipMalloc(&s->d_ids, sizeof(int32_t) * max_slots);
+    if (e == hipSuccess) e = hipMalloc(&s->d_draw, sizeof(DrawLat) * max_slots);
+    if (e == hipSuccess) e = hipMalloc(&s->d_codes, sizeof(uint64_t) * kServerCodeWords);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device);
     if (e == hipSuccess) e = hipMalloc(&s->d_fin, sizeof(int32_t) * max_slots);
     if (e == hipSuccess) e = hipMalloc(&s->d_em, sizeof(int64_t) * 2 * max_slots);
     for (Stage& st : s->stage) {
         if (e == hipSuccess) e = hipHostMalloc(&st.desc, sizeof(LatticeDesc) * max_slots, hipHostMallocDefault);
-        if (e == hipSuccess) e = hipHostMalloc(&st.ids, sizeof(int32_t) * max_slots, hipHostMallocDefault);
+        if (e == hipSuccess) e = hipHostMalloc(&st.draw, sizeof(DrawLat) * max_slots, hipHostMallocDefault);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&st.done, hipEventDisableTiming);
     }
     for (Readback& r : s->ring) {
