@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <string>
+#include <vector>
 
 #include "../../include/ising.h"
 #include "ising_common.hpp"
@@ -79,5 +80,44 @@ int read_spin_window(const uint64_t* W, const Geometry& g, int32_t r0, int32_t c
 // Replace every spin by the host bytes (L x L, nonzero = up), staged through
 // `stage` (cap bytes >= L); synchronises the stream.
 int write_spins(uint64_t* W, const Geometry& g, const uint8_t* host, uint8_t* stage, size_t cap, hipStream_t s);
+
+// Resident tiles of a lattice of up to 7680 columns: up to L = 192 the whole
+// lattice in one workgroup, a thread per word of a colour (a power of two, 64 to
+// 1024); below L = 1024 bands of 8 columns, 512 threads; from there bands of
+// 2 ceil(L / 512) columns (at most 256, one per compute unit), 1024 threads.
+inline void default_resident_shape(const Geometry& g, int32_t* w, int32_t* block) {
+    *w = 2 * ((g.L + 511) / 512);
+    *block = 1024;
+    if (g.L <= 192) {
+        const int64_t items = (int64_t)g.N * g.L / 2;
+        *w = g.L;
+        *block = 64;
+        while (*block < 1024 && *block < items) *block *= 2;
+    } else if (g.L < 1024) {
+        *w = 8;
+        *block = 512;
+    }
+}
+
+// The resident tiles of one lattice (interior width w, the last one
+// narrower), indexed by workgroup: consecutive workgroups are dealt to the
+// 8 XCDs in turn, so when the tile count is a multiple of 8 tile t goes to
+// workgroup 8 (t mod m) + t div m (m = count / 8) and every XCD holds a run
+// of neighbouring tiles, which then trade their boundary words inside one
+// XCD except at the ends of the runs.  part_base offsets the partial slots.
+inline std::vector<PersistTile> resident_tile_table(int32_t lattice, int32_t L, int32_t w, int32_t part_base) {
+    int32_t n = 0;
+    for (int32_t c0 = 0; c0 < L; c0 += w) ++n;
+    const bool spread = n % 8 == 0;
+    const int32_t m = n / 8;
+    auto block_of = [&](int32_t t) { return spread ? 8 * (t % m) + t / m : t; };
+    std::vector<PersistTile> tiles(n);
+    for (int32_t t = 0; t < n; ++t) {
+        const int32_t c0 = t * w;
+        tiles[block_of(t)] = {lattice, c0, std::min(w, L - c0), block_of((t + n - 1) % n), block_of((t + 1) % n),
+                              part_base + t};
+    }
+    return tiles;
+}
 
 }  // namespace ising

@@ -221,23 +221,11 @@ static int create_impl(int32_t L, uint64_t seed, int32_t init, void* dev_words, 
     // half-sweep launches, E/M every 10 sweeps: L = 294 2.7 / 8.9, 512 2.6 /
     // 8.5, 1024 3.0 / 9.4, 2048 4.0 / 9.8, 4096 8.1 / 14.8, 5120 14.8 /
     // 19.3, 7680 31.7 / 33.0).
-    // Shapes: up to L = 192 the whole lattice in one workgroup, a thread per
-    // word of a colour (a power of two, 64 to 1024); below L = 1024 bands
-    // of 8 columns, 512 threads; from there bands of 2 ceil(L / 512)
-    // columns (at most 256, one per compute unit), 1024 threads.  Above
-    // 7680 a band no longer fits in LDS; where the tiles do not fit the
+    // Above 7680 a band no longer fits in LDS; where the tiles do not fit the
     // lattice keeps the half-sweep launches.
     if (L <= 7680) {
-        int32_t w = 2 * ((L + 511) / 512), block = 1024;
-        if (L <= 192) {
-            const int64_t items = (int64_t)h->g.N * L / 2;
-            w = L;
-            block = 64;
-            while (block < 1024 && block < items) block *= 2;
-        } else if (L < 1024) {
-            w = 8;
-            block = 512;
-        }
+        int32_t w, block;
+        default_resident_shape(h->g, &w, &block);
         if (!enable_drawn(h, w, block, 1000) && ising_set_resident_tiles(h, w, block, 1000) != ISING_OK)
             last_error_ref().clear();
     }
@@ -837,27 +825,6 @@ static void free_resident(ising_lattice* h) {
     h->d_rEM = nullptr;
     h->res_cols = 0;
     h->n_res = 0;
-}
-
-// The resident tiles of one lattice (interior width w, the last one
-// narrower), indexed by workgroup: consecutive workgroups are dealt to the
-// 8 XCDs in turn, so when the tile count is a multiple of 8 tile t goes to
-// workgroup 8 (t mod m) + t div m (m = count / 8) and every XCD holds a run
-// of neighbouring tiles, which then trade their boundary words inside one
-// XCD except at the ends of the runs.  part_base offsets the partial slots.
-static std::vector<PersistTile> resident_tile_table(int32_t lattice, int32_t L, int32_t w, int32_t part_base) {
-    int32_t n = 0;
-    for (int32_t c0 = 0; c0 < L; c0 += w) ++n;
-    const bool spread = n % 8 == 0;
-    const int32_t m = n / 8;
-    auto block_of = [&](int32_t t) { return spread ? 8 * (t % m) + t / m : t; };
-    std::vector<PersistTile> tiles(n);
-    for (int32_t t = 0; t < n; ++t) {
-        const int32_t c0 = t * w;
-        tiles[block_of(t)] = {lattice, c0, std::min(w, L - c0), block_of((t + n - 1) % n), block_of((t + 1) % n),
-                              part_base + t};
-    }
-    return tiles;
 }
 
 // Largest number of sweeps of one resident-tile launch.

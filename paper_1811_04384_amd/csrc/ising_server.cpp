@@ -1,8 +1,9 @@
 // Continuous-batching server: requests of different L, T and sweep counts
 // share the GPU.  Their packed lattices and sweep counters stay resident in
 // one device arena; every quantum advances all resident lattices together
-// (tiled lattices in shared half-sweep launches, small ones one workgroup
-// each from codes drawn by the whole chip), and requests join and leave between quanta.  Admission is by
+// (large lattices in shared half-sweep launches, or one after the other in
+// resident tiles where they are few; small ones one workgroup each from codes
+// drawn by the whole chip), and requests join and leave between quanta.  Admission is by
 // memory footprint (first-fit in the arena) and free slots, in arrival order.
 //
 // Pipelining: the host plans, uploads and enqueues quantum q+1 while quantum
@@ -34,6 +35,22 @@ namespace {
 constexpr int64_t kServerCodeWords = int64_t(8) << 20;
 constexpr int64_t kServerGroupWords = kServerCodeWords / 8;
 
+// Large lattices in resident tiles, one after the other, in a quantum: at most so
+// many, of so many columns, and the tiles of each.
+constexpr int32_t kServerTiled = 8;
+constexpr int32_t kServerTiledMaxL = 4096;
+constexpr int32_t kServerTiles = 256;
+constexpr int32_t kServerTileSweeps = 4096;  // of one launch
+
+// us of `sweeps` sweeps of a lattice in resident tiles (2.3 a sweep at L = 300, 2.6 at
+// 1024, 3.5 at 2048, 5.6 at 3072, 7.6 at 4096, and 50 to set a launch up), and of
+// a half-sweep launch of n wavefronts of one word per thread (3.3 with 100, 3.7
+// with 392, 4.7 with 1568, 8.6 with 6272, 17 with 24232 in half as many of two).
+double tiled_us(int32_t L, int64_t sweeps) { return 50.0 + (double)sweeps * (2.2 + (double)L * L / 3.1e6); }
+double halfsweep_us(int64_t n) {
+    return 3.3 + 0.0008 * (double)std::min<int64_t>(n, 8192) + 0.0005 * (double)std::max<int64_t>(n - 8192, 0);
+}
+
 // A group: entries [begin, end) of the quantum's table of small lattices.
 struct SmallGroup {
     int32_t begin, end;
@@ -53,6 +70,7 @@ struct Stage {
     WaveItem* waves = nullptr;
     int64_t waves_cap = 0;
     DrawLat* draw = nullptr;
+    PersistTile* tiles = nullptr;  // behind draw
     hipEvent_t done = nullptr;  // recorded after the quantum's kernels
     bool used = false;
 };
@@ -61,6 +79,7 @@ struct Stage {
 struct Readback {
     int32_t* ids = nullptr;  // pinned: slot ids uploaded for the reduction
     int64_t* em = nullptr;   // pinned: (E, M) per listed slot
+    uint32_t* err = nullptr;  // the tiles' error word, behind em
     hipEvent_t done = nullptr;
     bool pending = false;
     std::vector<ising_result> meta;  // request data; E, M and t_done filled at harvest
@@ -82,6 +101,12 @@ struct ising_server {
     DrawLat* d_draw = nullptr;  // small lattices of the current quantum
     uint64_t* d_codes = nullptr;  // their acceptance codes, kServerCodeWords
     int cus = 0;
+    // resident tiles (set up when first wanted): the quantum's tables; one word
+    // per tile and the exchange buffer; the error word
+    enum { kTilesUnknown, kTilesUsable, kTilesNot } tiles = kTilesUnknown;
+    PersistTile* d_tiles = nullptr;
+    uint64_t* d_exch = nullptr;
+    uint32_t* d_err = nullptr;
     int32_t* d_fin = nullptr;  // ids of a read-back batch
     int64_t* d_em = nullptr;   // (E, M) of a read-back batch
     Stage stage[kStages];
@@ -106,6 +131,9 @@ void release(ising_server* s) {
     if (s->d_waves) (void)hipFree(s->d_waves);
     if (s->d_draw) (void)hipFree(s->d_draw);
     if (s->d_codes) (void)hipFree(s->d_codes);
+    if (s->d_tiles) (void)hipFree(s->d_tiles);
+    if (s->d_exch) (void)hipFree(s->d_exch);
+    if (s->d_err) (void)hipFree(s->d_err);
     if (s->d_fin) (void)hipFree(s->d_fin);
     if (s->d_em) (void)hipFree(s->d_em);
     for (Stage& st : s->stage) {
@@ -136,6 +164,14 @@ int harvest(ising_server* s, Readback& r, bool wait) {
         const hipError_t e = hipEventQuery(r.done);
         if (e == hipErrorNotReady) return ISING_OK;
         if (e != hipSuccess) return hip_fail(e, "hipEventQuery");
+    }
+    if (*r.err) {  // a launch of resident tiles was abandoned: these results are not valid
+        *r.err = 0;
+        r.meta.clear();
+        r.pending = false;
+        ISING_HIP(launch_zero_words(reinterpret_cast<uint64_t*>(s->d_err), 1, s->stream));
+        return fail(ISING_EHIP, "server: a resident-tile launch waited too long for a neighbour tile and was abandoned; "
+                                "the states of its lattices are undefined");
     }
     const double t = now_s();
     for (size_t k = 0; k < r.meta.size(); ++k) {
@@ -200,6 +236,31 @@ bool is_resident(const ising_server* s, const Geometry& g) {
     return g.L <= s->resident_max_L && (size_t)g.N * g.L * 8 <= s->lds_limit;
 }
 
+// Whether resident tiles can be used: the device holds those of the largest
+// lattice at once and the buffers could be had.
+bool tiles_usable(ising_server* s) {
+    if (s->tiles != ising_server::kTilesUnknown) return s->tiles == ising_server::kTilesUsable;
+    s->tiles = ising_server::kTilesNot;
+    const Geometry big = make_geometry(kServerTiledMaxL);
+    int32_t w, block;
+    default_resident_shape(big, &w, &block);
+    const size_t lds = persist_lds_bytes(big.L, big.N, w, block);
+    int64_t capacity = 0;
+    if (lds > persist_lds_limit(s->device)) return false;
+    hipError_t e = allow_persist_lds(s->device);
+    if (e == hipSuccess) e = persist_capacity(block, lds, s->device, &capacity);
+    if (e == hipSuccess && capacity >= kServerTiles) {
+        e = hipMalloc(&s->d_tiles, sizeof(PersistTile) * kServerTiled * kServerTiles);
+        if (e == hipSuccess)
+            e = hipMalloc(&s->d_exch, sizeof(uint64_t) * (kServerTiles + (size_t)kServerTiles * 4 * (size_t)big.N));
+        if (e == hipSuccess) e = hipMalloc(&s->d_err, sizeof(uint64_t));
+        if (e == hipSuccess) e = launch_zero_words(reinterpret_cast<uint64_t*>(s->d_err), 1, s->stream);
+        if (e == hipSuccess) s->tiles = ising_server::kTilesUsable;
+    }
+    if (e != hipSuccess) (void)hipGetLastError();
+    return s->tiles == ising_server::kTilesUsable;
+}
+
 // Sweeps of a group whose codes are drawn together.
 int32_t group_sweeps(const SmallGroup& gr) { return (int32_t)std::min<int64_t>(gr.K, kServerCodeWords / gr.words); }
 
@@ -220,6 +281,28 @@ int enqueue_quantum(ising_server* s) {
         const Geometry g = make_geometry(sl.req.L);
         if (!is_resident(s, g)) n_waves += waves_per_colour(g, 1);
     }
+    // Few large lattices leave a launch per half-sweep mostly waiting for the next:
+    // then they go through the quantum one after the other in resident tiles.  The
+    // estimates above say which is less; us for 300 sweeps in quanta of 100, half-sweeps /
+    // tiles: L = 512 2001/878, 2048 2813/1317, 4096 5181/2665, 2048 and 1024 and 512
+    // 3091/2776; three of 1024 2544/2633, four of 512 2171/2156.
+    double tiled = 0.0, swept = 0.0;
+    int32_t n_large = 0;
+    for (int32_t i = 0; i < slots; ++i) {
+        const Slot& sl = sc.slots()[i];
+        if (!sl.active || sl.planned <= 0) continue;
+        const Geometry g = make_geometry(sl.req.L);
+        if (is_resident(s, g)) continue;
+        n_large += 1;
+        tiled += g.L <= kServerTiledMaxL ? tiled_us(g.L, sl.planned) : 1e300;
+        swept = std::max(swept, 2.0 * (double)sl.planned * halfsweep_us(n_waves));
+    }
+    const bool tiles = n_large > 0 && n_large <= kServerTiled && tiled < swept && tiles_usable(s);
+    if (tiles) n_waves = 0;
+    struct Tiled {
+        int32_t lattice, first, count, w, block, K;
+    };
+    std::vector<Tiled> large;
     // two words per thread where one would be more wavefronts than the device holds
     // at once (bursts of 16 requests of L = 128 ... 4096, six seeds: 16.3 / 17.1, 20.1
     // / 21.1, 12.7 / 13.3 ms and three within 1 %; the line at 12288 or 16384
@@ -262,6 +345,13 @@ int enqueue_quantum(ising_server* s) {
             gr.max_draws = std::max(gr.max_draws, st.draw[n_res].n_draw);
             gr.K = std::max<int32_t>(gr.K, (int32_t)sl.planned);
             ++n_res;
+        } else if (tiles) {
+            Tiled t = {i, large.empty() ? 0 : large.back().first + large.back().count, 0, 0, 0, (int32_t)sl.planned};
+            default_resident_shape(g, &t.w, &t.block);
+            const std::vector<PersistTile> table = resident_tile_table(i, g.L, t.w, 0);
+            t.count = (int32_t)table.size();
+            std::copy(table.begin(), table.end(), st.tiles + t.first);
+            large.push_back(t);
         } else {
             d.part_begin = (int32_t)n_waves;
             for (int32_t I = 0; I < g.N; ++I)
@@ -272,6 +362,10 @@ int enqueue_quantum(ising_server* s) {
     ISING_HIP(hipMemcpyAsync(s->d_desc, st.desc, sizeof(LatticeDesc) * slots, hipMemcpyHostToDevice, s->stream));
     if (n_waves)
         ISING_HIP(hipMemcpyAsync(s->d_waves, st.waves, sizeof(WaveItem) * n_waves, hipMemcpyHostToDevice, s->stream));
+    if (!large.empty())
+        ISING_HIP(hipMemcpyAsync(s->d_tiles, st.tiles,
+                                 sizeof(PersistTile) * (size_t)(large.back().first + large.back().count),
+                                 hipMemcpyHostToDevice, s->stream));
     for (const SmallGroup& gr : groups) {
         int64_t base = 0;
         const int64_t S = group_sweeps(gr);
@@ -293,11 +387,11 @@ int enqueue_quantum(ising_server* s) {
             // 5261/836, 300 of L = 128 and 256 8519/3663; 100 of L = 16 in quanta of
             // one sweep, where launches and the join of two streams are all there is,
             // 1852/1369.
-            if (n_waves) {
+            if (n_large) {
                 ISING_HIP(hipEventRecord(s->fork_ev, s->stream));
                 ISING_HIP(hipStreamWaitEvent(s->side, s->fork_ev, 0));
             }
-            const hipStream_t on = n_waves ? s->side : s->stream;
+            const hipStream_t on = n_large ? s->side : s->stream;
             for (const SmallGroup& gr : groups) {
                 const int32_t n = gr.end - gr.begin, S = group_sweeps(gr);
                 const int wmax = n <= s->cus || gr.max_words > 1024 ? (gr.max_words + 1023) / 1024
@@ -311,7 +405,30 @@ int enqueue_quantum(ising_server* s) {
                                                 wave_apply_lds_bytes(gr.max_NL, 0), on));
                 }
             }
-            if (n_waves) ISING_HIP(hipEventRecord(s->join_ev, s->side));
+            if (n_large) ISING_HIP(hipEventRecord(s->join_ev, s->side));
+        }
+        for (const Tiled& t : large) {
+            const Geometry g = make_geometry(sc.slots()[t.lattice].req.L);
+            // the tags of the lattice before
+            ISING_HIP(launch_zero_words(s->d_exch, kServerTiles + (uint64_t)t.count * 4 * g.N, s->stream));
+            PersistLaunch a = {};
+            a.tiles = s->d_tiles + t.first;
+            a.descs = s->d_desc;
+            a.states = s->d_state;
+            a.n_tiles = t.count;
+            a.flags = s->d_exch;
+            a.exch = s->d_exch + kServerTiles;
+            a.exch_tile_words = 4 * (int64_t)g.N;
+            a.error = s->d_err;
+            a.wait_ticks = 100000000ull;  // one second of the 100 MHz clock
+            for (int32_t done = 0; done < t.K; done += kServerTileSweeps) {
+                a.sweep_off = (uint32_t)done;
+                a.K = std::min(kServerTileSweeps, t.K - done);
+                ISING_HIP(resident_gate(s->device, s->stream, [&] {
+                    return launch_persist(a, persist_form(g.L, g.N, t.w, t.block), t.count, t.block,
+                                          persist_lds_bytes(g.L, g.N, t.w, t.block), s->stream);
+                }));
+            }
         }
         for (int32_t k = 0; k < K && n_waves; ++k) {
             ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 0,
@@ -319,7 +436,7 @@ int enqueue_quantum(ising_server* s) {
             ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 1,
                                              (uint32_t)k, nullptr, nullptr, 0, s->stream));
         }
-        if (n_res && n_waves) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));
+        if (n_res && n_large) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));
         ISING_HIP(launch_chunk_end(s->d_desc, s->d_state, slots, nullptr, 0, (uint32_t)K, s->stream));
     }
     ISING_HIP(hipEventRecord(st.done, s->stream));
@@ -358,6 +475,8 @@ int enqueue_retirements(ising_server* s) {
     ISING_HIP(hipMemcpyAsync(s->d_fin, r.ids, sizeof(int32_t) * nf, hipMemcpyHostToDevice, s->stream));
     ISING_HIP(launch_observe_multi(s->d_desc, s->d_state, s->d_fin, nf, max_words, s->d_em, s->stream));
     ISING_HIP(hipMemcpyAsync(r.em, s->d_em, sizeof(int64_t) * 2 * nf, hipMemcpyDeviceToHost, s->stream));
+    if (s->tiles == ising_server::kTilesUsable)
+        ISING_HIP(hipMemcpyAsync(r.err, s->d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, s->stream));
     ISING_HIP(hipEventRecord(r.done, s->stream));
     r.pending = true;
     for (int32_t i : fin) s->sched.retire(i);
@@ -406,12 +525,19 @@ int ising_server_create(size_t hbm_budget, int32_t max_slots, int32_t quantum_sw
     if (e == hipSuccess) e = hipMalloc(&s->d_em, sizeof(int64_t) * 2 * max_slots);
     for (Stage& st : s->stage) {
         if (e == hipSuccess) e = hipHostMalloc(&st.desc, sizeof(LatticeDesc) * max_slots, hipHostMallocDefault);
-        if (e == hipSuccess) e = hipHostMalloc(&st.draw, sizeof(DrawLat) * max_slots, hipHostMallocDefault);
+        if (e == hipSuccess)
+            e = hipHostMalloc(&st.draw, sizeof(DrawLat) * max_slots + sizeof(PersistTile) * kServerTiled * kServerTiles,
+                              hipHostMallocDefault);
+        if (e == hipSuccess) st.tiles = reinterpret_cast<PersistTile*>(st.draw + max_slots);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&st.done, hipEventDisableTiming);
     }
     for (Readback& r : s->ring) {
         if (e == hipSuccess) e = hipHostMalloc(&r.ids, sizeof(int32_t) * max_slots, hipHostMallocDefault);
-        if (e == hipSuccess) e = hipHostMalloc(&r.em, sizeof(int64_t) * 2 * max_slots, hipHostMallocDefault);
+        if (e == hipSuccess) e = hipHostMalloc(&r.em, sizeof(int64_t) * (2 * (size_t)max_slots + 1), hipHostMallocDefault);
+        if (e == hipSuccess) {
+            r.err = reinterpret_cast<uint32_t*>(r.em + 2 * (size_t)max_slots);
+            *r.err = 0;
+        }
         if (e == hipSuccess) e = hipEventCreateWithFlags(&r.done, hipEventDisableTiming);
     }
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking);

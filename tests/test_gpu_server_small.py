@@ -55,3 +55,17 @@ def test_served_many_small(L, n):
     print(f"served {n} of L={L}", flush=True)
     reqs = [(L, 2.0 + 0.001 * i, 20 - i % 3) for i in range(n)]
     _check(_serve(reqs, 20), reqs, [0, 1, 255, 256, 299, n - 27, n - 26, n - 25, n - 24, n - 1])
+
+
+@pytest.mark.parametrize("Ls,quantum", [
+    ([294], 30),                 # bands of 8 columns
+    ([1024], 40), ([1026], 40),  # bands of 4 columns; of 6, the last one narrower
+    ([2048, 64], 40),            # beside a small lattice
+    ([700, 2048, 1008], 100),    # one after the other, with different numbers of sweeps left
+])
+def test_served_few_large(Ls, quantum):
+    """Few large lattices: they go through a quantum in resident tiles, and results, retired in turn, are those of
+    half-sweep launches."""
+    print(f"served few large {Ls}", flush=True)
+    reqs = [(L, 2.1 + 0.1 * i, 130 + 17 * i) for i, L in enumerate(Ls)]
+    _check(_serve(reqs, quantum), reqs, range(len(reqs)))
