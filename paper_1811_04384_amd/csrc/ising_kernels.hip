@@ -662,7 +662,7 @@ hipError_t launch_pack_words(const uint8_t* in, const Geometry& g, uint64_t* W, 
 }
 
 hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, LatticeState* states,
-                                  const WaveItem* waves, int64_t n_waves, int colour, uint32_t sweep_off,
+                                  const WaveItem* waves, int64_t n_waves, bool runs, int colour, uint32_t sweep_off,
                                   Partial* partials, const Partial* fin_partials, uint32_t fin_off, hipStream_t s) {
     if (n_waves <= 0) return hipSuccess;
     const dim3 grid(grid_for((uint64_t)n_waves * 64, block)), blk(block);
@@ -674,9 +674,11 @@ hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, 
     // least eight each, so that lattices that have finished their sweeps leave
     // none of them idle.  us per half-sweep without and with, 256 lattices of L = 256
     // ... 2048: 101 / 68 with two words per thread and 256 threads, 92 / 67 with four
-    // words; 64 of 64 ... 512: 5.8 / 4.9 with a word and 64 threads; where a row is 8
-    // workgroups the same either way (68).
-    const uint32_t group = std::max(1u, std::min(grid.x / 64, 16384u / (unsigned)block));
+    // words; 64 of 64 ... 512: 5.8 / 4.9 with a word and 64 threads.  Not where most
+    // rows are a multiple of 8 workgroups (runs = false), which keeps the rows above
+    // and below on the XCD anyway: one L = 4096 with a word and 64 threads 8.1, in
+    // runs 9.1.
+    const uint32_t group = runs ? std::max(1u, std::min(grid.x / 64, 16384u / (unsigned)block)) : grid.x;
 #define ISING_LAUNCH_HM(WPT_)                                                                                       \
     if (m) hipLaunchKernelGGL((k_halfsweep_multi<WPT_, true>), grid, blk, 0, s, descs, states, waves, nw, group, colour, \
                               sweep_off, partials, fin_partials, fin_off);                                          \

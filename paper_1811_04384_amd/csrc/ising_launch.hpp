@@ -32,6 +32,13 @@ inline int64_t waves_per_colour(const Geometry& g, int32_t wpt) {
     return (int64_t)g.N * ((segments_per_row(g.L, wpt) + 63) / 64);
 }
 
+// Whether the rows of a lattice in a table of wavefronts are a multiple of 8
+// workgroups each, so that workgroups dealt to the 8 XCDs in turn put a column
+// of words of all its rows on one XCD.
+inline bool rows_fill_xcds(const Geometry& g, int32_t wpt, int block) {
+    return (waves_per_colour(g, wpt) / g.N) % (8 * (block / 64)) == 0;
+}
+
 // Zero n 64-bit words with a kernel (usable inside a captured graph).
 hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t s);
 
@@ -103,15 +110,15 @@ hipError_t launch_pack_words(const uint8_t* in, const Geometry& g, uint64_t* W, 
 
 // ---- batches --------------------------------------------------------------
 
-// Tiled half-sweep over a wave table covering many lattices.  off32: every
-// listed lattice is smaller than 4 GiB (32-bit word offsets).  partials
+// Tiled half-sweep over a wave table covering many lattices.  partials
 // (colour 1 of a measured sweep): each wavefront stores its sums there.
 // fin_partials: before its own work, the launch finalizes every tiled
 // lattice's measured sweep fin_off from those partials (written by an
 // earlier launch on the same stream).  Lattices whose sweep_limit is <= an
-// offset took no part in that sweep and are skipped.
+// offset took no part in that sweep and are skipped.  runs: the table is dealt
+// to the XCDs in runs of wavefronts, not workgroup by workgroup.
 hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, LatticeState* states,
-                                  const WaveItem* waves, int64_t n_waves, int colour, uint32_t sweep_off,
+                                  const WaveItem* waves, int64_t n_waves, bool runs, int colour, uint32_t sweep_off,
                                   Partial* partials, const Partial* fin_partials, uint32_t fin_off,
                                   hipStream_t s);
 // End of a chunk of k sweeps: finalize the tiled lattices' measured sweep

@@ -57,6 +57,7 @@ struct SmallGroup {
     int64_t words;       // of its lattices
     int32_t max_NL, max_words, max_draws, K;  // the largest lattice's words, words of a colour, draw items; sweeps
 };
+constexpr int kServerTiledBlock = 64;  // threads of a half-sweep workgroup
 constexpr int kStages = 2;     // quanta in flight = staging buffer sets
 constexpr int kRing = 4;       // read-back ring entries
 
@@ -312,6 +313,7 @@ int enqueue_quantum(ising_server* s) {
     if (rc != ISING_OK) return rc;
     int32_t n_res = 0, K = 0;
     std::vector<SmallGroup> groups;
+    int64_t filling = 0;  // wavefronts of rows that fill the XCDs evenly
     n_waves = 0;
     for (int32_t i = 0; i < slots; ++i) {
         const Slot& sl = sc.slots()[i];
@@ -357,8 +359,10 @@ int enqueue_quantum(ising_server* s) {
             for (int32_t I = 0; I < g.N; ++I)
                 for (int32_t w0 = 0; w0 < g.L / 2; w0 += 64 * wpt) st.waves[n_waves++] = {i, I, w0};
             d.part_count = (int32_t)(n_waves - d.part_begin);
+            if (rows_fill_xcds(g, wpt, kServerTiledBlock)) filling += d.part_count;
         }
     }
+    const bool wave_runs = 2 * filling <= n_waves;
     ISING_HIP(hipMemcpyAsync(s->d_desc, st.desc, sizeof(LatticeDesc) * slots, hipMemcpyHostToDevice, s->stream));
     if (n_waves)
         ISING_HIP(hipMemcpyAsync(s->d_waves, st.waves, sizeof(WaveItem) * n_waves, hipMemcpyHostToDevice, s->stream));
@@ -377,7 +381,7 @@ int enqueue_quantum(ising_server* s) {
     }
     if (n_res) ISING_HIP(hipMemcpyAsync(s->d_draw, st.draw, sizeof(DrawLat) * n_res, hipMemcpyHostToDevice, s->stream));
     if (K > 0) {
-        const int block = 64;
+        const int block = kServerTiledBlock;
         if (n_res) {
             // The small lattices (one workgroup each) run on the side stream,
             // beside the tiled launches of the other lattices if there are any; as in
@@ -431,9 +435,9 @@ int enqueue_quantum(ising_server* s) {
             }
         }
         for (int32_t k = 0; k < K && n_waves; ++k) {
-            ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 0,
+            ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, 0,
                                              (uint32_t)k, nullptr, nullptr, 0, s->stream));
-            ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, 1,
+            ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, 1,
                                              (uint32_t)k, nullptr, nullptr, 0, s->stream));
         }
         if (n_res && n_large) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));
