@@ -190,9 +190,10 @@ def load_traffic(plan):
             d = json.load(f)
         if d.get("kernel_source_sha256_16") != kernel_source_hash():
             return None
-        if f"<{plan['words_per_thread']}," not in d["kernel"]:
-            return None
-        return d["bytes_per_launch"]
+        for e in [d] + d.get("plans", []):
+            if f"<{plan['words_per_thread']}," in e["kernel"]:
+                return e["bytes_per_launch"]
+        return None
     except (OSError, KeyError, ValueError):
         return None
 
