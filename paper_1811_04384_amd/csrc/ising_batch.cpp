@@ -377,7 +377,7 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
             }
             res_tiles.swap(by_block);
         }
-        ISING_HIP(allow_persist_lds(b->device));
+        ISING_HIP(allow_persist_lds(b->device, b->res_form, b->res_lds));
         b->exch_tile_words = 4 * (int64_t)res_max_N;
         ISING_HIP(hipMalloc(&b->d_res, sizeof(PersistTile) * res_tiles.size()));
         ISING_HIP(hipMemcpy(b->d_res, res_tiles.data(), sizeof(PersistTile) * res_tiles.size(), hipMemcpyHostToDevice));

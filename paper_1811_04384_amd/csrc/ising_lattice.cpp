@@ -850,7 +850,7 @@ static int resident_shape(const ising_lattice* h, int32_t tile_cols, int32_t blo
     if (lds > persist_lds_limit(h->device))
         return fail(ISING_EINVAL, "ising_set_resident_tiles: a tile needs %zu bytes of LDS, %zu available", lds,
                     persist_lds_limit(h->device));
-    ISING_HIP(allow_persist_lds(h->device));
+    ISING_HIP(allow_persist_lds(h->device, persist_form(L, N, w, block), lds));
     sh->tiles = resident_tile_table(0, L, w, 0);
     const int32_t n = (int32_t)sh->tiles.size();
     int64_t capacity = 0;

@@ -188,7 +188,8 @@ hipError_t launch_finalize_tiles(const LatticeDesc* descs, LatticeState* states,
 // the limit and the one-time attribute as for the tiles above.
 size_t persist_lds_bytes(int32_t L, int32_t N, int32_t w, int32_t block);
 size_t persist_lds_limit(int device);
-hipError_t allow_persist_lds(int device);
+// (of a form, below, and of the kernel that holds all of them)
+hipError_t allow_persist_lds(int device, int form, size_t lds_bytes);
 // How many resident tiles of `block` threads and lds_bytes of LDS the device
 // holds at once (a launch must not exceed it).
 hipError_t persist_capacity(int block, size_t lds_bytes, int device, int64_t* tiles);

@@ -27,10 +27,10 @@
 // it waits for, so that one store and one load are all that lies between the
 // update of a boundary word and its use next door; no flag is raised behind
 // the data and no store is waited for.  Small bands are bound by that path:
-// 126 bands of 8 columns of L = 1008 take 1.26 us per half-sweep, against 2.69
+// 126 bands of 8 columns of L = 1008 take 1.25 us per half-sweep, against 2.69
 // with a flag per tile, raised after every publisher's store had completed
 // and polled before the barrier (three memory round trips after each other);
-// bands of 16 columns (L = 4096: 3.80 against 3.97 us) are bound by the
+// bands of 16 columns (L = 4096: 3.79 against 3.97 us) are bound by the
 // vector unit.
 // Only colour-c words are exchanged, because the next half-sweep only reads
 // those from a ghost column.  The exchange buffer alternates between two
@@ -547,48 +547,61 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
 
 }  // namespace
 
-// ITEMS: how the tiles of the launch hold their items (kAny: lattices of the
-// launch differ, and each tile chooses).  A kernel of each form by itself has the
-// registers it needs and no others' (all three in one kernel against each alone,
-// us per sweep: L = 300 2.33 / 2.28, 512 2.41 / 2.34, 1024 2.64 / 2.58, 4096 7.66 /
-// 7.61; 16 lattices of L = 1008 in bands of 64 columns, 300 sampled sweeps 2590 /
-// 2560).
-template <int ITEMS>
+// ITEMS: how the tiles of the launch hold their items, WHOLE: whether they are whole
+// lattices (kAny: the lattices of the launch differ, and each tile chooses).  A kernel of each form by itself has the
+// registers it needs and no others' (us per sweep, all of them in one kernel / each
+// alone: L = 300 2.33 / 2.25, 512 2.41 / 2.32, 1024 2.64 / 2.53, 2048 3.48 / 3.38, 3072
+// 5.60 / 5.42, 4096 7.66 / 7.58, 5120 14.5 / 14.8; 16 lattices of L = 512 in bands of 64
+// columns, 300 sampled sweeps 1830 / 1800).
+template <int ITEMS, bool WHOLE>
 __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
     extern __shared__ uint64_t lds[];
     __shared__ uint32_t red[2 * (kPersistMaxBlock / 64)];
     __shared__ int stop;
     const PersistTile tp = a.tiles[blockIdx.x];
-    const LatticeDesc& d = a.descs[tp.lattice];
-    const bool whole = tp.w >= d.L;
-    const int items = ITEMS == kAny ? items_mode(tile_items(d.L, d.N, tp.w), blockDim.x) : ITEMS;
-    if (items == kOne && (ITEMS == kOne || ITEMS == kAny)) {
-        if (whole) persist_tile<kOne, true>(a, tp, lds, red, stop);
-        else persist_tile<kOne, false>(a, tp, lds, red, stop);
-    } else if (items == kTwo && (ITEMS == kTwo || ITEMS == kAny)) {
-        if (whole) persist_tile<kTwo, true>(a, tp, lds, red, stop);
-        else persist_tile<kTwo, false>(a, tp, lds, red, stop);
-    } else if (ITEMS == kFormed || ITEMS == kAny) {
-        if (whole) persist_tile<kFormed, true>(a, tp, lds, red, stop);
-        else persist_tile<kFormed, false>(a, tp, lds, red, stop);
+    if constexpr (ITEMS != kAny) {
+        persist_tile<ITEMS, WHOLE>(a, tp, lds, red, stop);
+    } else {
+        const LatticeDesc& d = a.descs[tp.lattice];
+        const bool whole = tp.w >= d.L;
+        switch (items_mode(tile_items(d.L, d.N, tp.w), blockDim.x)) {
+            case kOne:
+                if (whole) persist_tile<kOne, true>(a, tp, lds, red, stop);
+                else persist_tile<kOne, false>(a, tp, lds, red, stop);
+                break;
+            case kTwo:
+                if (whole) persist_tile<kTwo, true>(a, tp, lds, red, stop);
+                else persist_tile<kTwo, false>(a, tp, lds, red, stop);
+                break;
+            default:
+                if (whole) persist_tile<kFormed, true>(a, tp, lds, red, stop);
+                else persist_tile<kFormed, false>(a, tp, lds, red, stop);
+        }
     }
 }
 
 namespace {
 
+constexpr int kWhole = 4;  // added to the items of a form
+
 typedef void (*PersistKernel)(PersistLaunch);
 PersistKernel persist_kernel(int form) {
     switch (form) {
-        case kOne: return &k_persist<kOne>;
-        case kTwo: return &k_persist<kTwo>;
-        case kFormed: return &k_persist<kFormed>;
-        default: return &k_persist<kAny>;
+        case kOne: return &k_persist<kOne, false>;
+        case kTwo: return &k_persist<kTwo, false>;
+        case kFormed: return &k_persist<kFormed, false>;
+        case kOne + kWhole: return &k_persist<kOne, true>;
+        case kTwo + kWhole: return &k_persist<kTwo, true>;
+        case kFormed + kWhole: return &k_persist<kFormed, true>;
+        default: return &k_persist<kAny, false>;
     }
 }
 
 }  // namespace
 
-int persist_form(int32_t L, int32_t N, int32_t w, int block) { return items_mode(tile_items(L, N, w), block); }
+int persist_form(int32_t L, int32_t N, int32_t w, int block) {
+    return items_mode(tile_items(L, N, w), block) + (w >= L ? kWhole : 0);
+}
 int persist_form_any() { return kAny; }
 
 size_t persist_lds_bytes(int32_t L, int32_t N, int32_t w, int32_t block) {
@@ -616,12 +629,14 @@ size_t persist_lds_limit(int device) {
     return v > (int)static_bytes ? (size_t)v - static_bytes : 0;
 }
 
-hipError_t allow_persist_lds(int device) {
+hipError_t allow_persist_lds(int device, int form, size_t lds_bytes) {
+    // up to 64 KB, static part included, need no leave (setting it takes 10 us)
+    if (lds_bytes <= 60 * 1024) return hipSuccess;
     const int limit = (int)persist_lds_limit(device);
     hipError_t e = hipSuccess;
-    for (int form : {kFormed, kOne, kTwo, kAny})
+    for (int f : {form, (int)kAny})
         if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(persist_kernel(form)),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(persist_kernel(f)),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, limit);
     return e;
 }

@@ -71,7 +71,7 @@ struct Stage {
     WaveItem* waves = nullptr;
     int64_t waves_cap = 0;
     DrawLat* draw = nullptr;
-    PersistTile* tiles = nullptr;  // behind draw
+    PersistTile* tiles = nullptr;
     hipEvent_t done = nullptr;  // recorded after the quantum's kernels
     bool used = false;
 };
@@ -100,7 +100,7 @@ struct ising_server {
     WaveItem* d_waves = nullptr;
     int64_t d_waves_cap = 0;
     DrawLat* d_draw = nullptr;  // small lattices of the current quantum
-    uint64_t* d_codes = nullptr;  // their acceptance codes, kServerCodeWords
+    uint64_t* d_codes = nullptr;  // their acceptance codes, kServerCodeWords (allocated when first needed)
     int cus = 0;
     // resident tiles (set up when first wanted): the quantum's tables; one word
     // per tile and the exchange buffer; the error word
@@ -141,6 +141,7 @@ void release(ising_server* s) {
         if (st.desc) (void)hipHostFree(st.desc);
         if (st.waves) (void)hipHostFree(st.waves);
         if (st.draw) (void)hipHostFree(st.draw);
+        if (st.tiles) (void)hipHostFree(st.tiles);
         if (st.done) (void)hipEventDestroy(st.done);
     }
     for (Readback& r : s->ring) {
@@ -248,13 +249,17 @@ bool tiles_usable(ising_server* s) {
     const size_t lds = persist_lds_bytes(big.L, big.N, w, block);
     int64_t capacity = 0;
     if (lds > persist_lds_limit(s->device)) return false;
-    hipError_t e = allow_persist_lds(s->device);
+    // (smaller lattices need less than the largest one, and no leave)
+    hipError_t e = allow_persist_lds(s->device, persist_form(big.L, big.N, w, block), lds);
     if (e == hipSuccess) e = persist_capacity(block, lds, s->device, &capacity);
     if (e == hipSuccess && capacity >= kServerTiles) {
         e = hipMalloc(&s->d_tiles, sizeof(PersistTile) * kServerTiled * kServerTiles);
         if (e == hipSuccess)
             e = hipMalloc(&s->d_exch, sizeof(uint64_t) * (kServerTiles + (size_t)kServerTiles * 4 * (size_t)big.N));
         if (e == hipSuccess) e = hipMalloc(&s->d_err, sizeof(uint64_t));
+        for (Stage& st : s->stage)
+            if (e == hipSuccess)
+                e = hipHostMalloc(&st.tiles, sizeof(PersistTile) * kServerTiled * kServerTiles, hipHostMallocDefault);
         if (e == hipSuccess) e = launch_zero_words(reinterpret_cast<uint64_t*>(s->d_err), 1, s->stream);
         if (e == hipSuccess) s->tiles = ising_server::kTilesUsable;
     }
@@ -379,6 +384,7 @@ int enqueue_quantum(ising_server* s) {
             base += S * d.N * d.L;
         }
     }
+    if (n_res && !s->d_codes) ISING_HIP(hipMalloc(&s->d_codes, sizeof(uint64_t) * kServerCodeWords));
     if (n_res) ISING_HIP(hipMemcpyAsync(s->d_draw, st.draw, sizeof(DrawLat) * n_res, hipMemcpyHostToDevice, s->stream));
     if (K > 0) {
         const int block = kServerTiledBlock;
@@ -523,16 +529,12 @@ int ising_server_create(size_t hbm_budget, int32_t max_slots, int32_t quantum_sw
     e = hipMalloc(&s->d_desc, sizeof(LatticeDesc) * max_slots);
     if (e == hipSuccess) e = hipMalloc(&s->d_state, sizeof(LatticeState) * max_slots);
     if (e == hipSuccess) e = hipMalloc(&s->d_draw, sizeof(DrawLat) * max_slots);
-    if (e == hipSuccess) e = hipMalloc(&s->d_codes, sizeof(uint64_t) * kServerCodeWords);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device);
     if (e == hipSuccess) e = hipMalloc(&s->d_fin, sizeof(int32_t) * max_slots);
     if (e == hipSuccess) e = hipMalloc(&s->d_em, sizeof(int64_t) * 2 * max_slots);
     for (Stage& st : s->stage) {
         if (e == hipSuccess) e = hipHostMalloc(&st.desc, sizeof(LatticeDesc) * max_slots, hipHostMallocDefault);
-        if (e == hipSuccess)
-            e = hipHostMalloc(&st.draw, sizeof(DrawLat) * max_slots + sizeof(PersistTile) * kServerTiled * kServerTiles,
-                              hipHostMallocDefault);
-        if (e == hipSuccess) st.tiles = reinterpret_cast<PersistTile*>(st.draw + max_slots);
+        if (e == hipSuccess) e = hipHostMalloc(&st.draw, sizeof(DrawLat) * max_slots, hipHostMallocDefault);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&st.done, hipEventDisableTiming);
     }
     for (Readback& r : s->ring) {
