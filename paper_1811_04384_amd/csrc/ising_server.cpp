@@ -100,7 +100,10 @@ struct ising_server {
     WaveItem* d_waves = nullptr;
     int64_t d_waves_cap = 0;
     DrawLat* d_draw = nullptr;  // small lattices of the current quantum
-    uint64_t* d_codes = nullptr;  // their acceptance codes, kServerCodeWords (allocated when first needed)
+    // their acceptance codes, allocated when first needed: kServerCodeWords, or less,
+    // but room for a sweep of any group, where the device has no more left
+    uint64_t* d_codes = nullptr;
+    int64_t code_words = 0;
     int cus = 0;
     // resident tiles (set up when first wanted): the quantum's tables; one word
     // per tile and the exchange buffer; the error word
@@ -268,7 +271,24 @@ bool tiles_usable(ising_server* s) {
 }
 
 // Sweeps of a group whose codes are drawn together.
-int32_t group_sweeps(const SmallGroup& gr) { return (int32_t)std::min<int64_t>(gr.K, kServerCodeWords / gr.words); }
+int32_t group_sweeps(const ising_server* s, const SmallGroup& gr) {
+    return (int32_t)std::min<int64_t>(gr.K, s->code_words / gr.words);
+}
+
+hipError_t code_buffer(ising_server* s) {
+    if (s->d_codes) return hipSuccess;
+    hipError_t e = hipErrorOutOfMemory;
+    for (int64_t words = kServerCodeWords; e != hipSuccess && words >= kServerGroupWords; words /= 2) {
+        e = hipMalloc(&s->d_codes, sizeof(uint64_t) * (size_t)words);
+        if (e == hipSuccess) {
+            s->code_words = words;
+        } else {
+            s->d_codes = nullptr;
+            (void)hipGetLastError();
+        }
+    }
+    return e;
+}
 
 // Plan the next quantum, upload its tables through a staging set and enqueue
 // its kernels.  Descriptors cover every active slot (those already done with
@@ -375,16 +395,16 @@ int enqueue_quantum(ising_server* s) {
         ISING_HIP(hipMemcpyAsync(s->d_tiles, st.tiles,
                                  sizeof(PersistTile) * (size_t)(large.back().first + large.back().count),
                                  hipMemcpyHostToDevice, s->stream));
+    if (n_res) ISING_HIP(code_buffer(s));
     for (const SmallGroup& gr : groups) {
         int64_t base = 0;
-        const int64_t S = group_sweeps(gr);
+        const int64_t S = group_sweeps(s, gr);
         for (int32_t k = gr.begin; k < gr.end; ++k) {
             const LatticeDesc& d = st.desc[st.draw[k].lat];
             st.draw[k].base = base;
             base += S * d.N * d.L;
         }
     }
-    if (n_res && !s->d_codes) ISING_HIP(hipMalloc(&s->d_codes, sizeof(uint64_t) * kServerCodeWords));
     if (n_res) ISING_HIP(hipMemcpyAsync(s->d_draw, st.draw, sizeof(DrawLat) * n_res, hipMemcpyHostToDevice, s->stream));
     if (K > 0) {
         const int block = kServerTiledBlock;
@@ -403,7 +423,7 @@ int enqueue_quantum(ising_server* s) {
             }
             const hipStream_t on = n_large ? s->side : s->stream;
             for (const SmallGroup& gr : groups) {
-                const int32_t n = gr.end - gr.begin, S = group_sweeps(gr);
+                const int32_t n = gr.end - gr.begin, S = group_sweeps(s, gr);
                 const int wmax = n <= s->cus || gr.max_words > 1024 ? (gr.max_words + 1023) / 1024
                                                                     : (gr.max_words + 255) / 256;
                 for (int32_t done = 0; done < gr.K; done += S) {
