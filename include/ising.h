@@ -461,6 +461,14 @@ int ising_server_submit(ising_server* s, uint64_t req_id, int32_t L, double T, i
    lattices after the call.  Synchronises the previous quantum. */
 int ising_server_step(ising_server* s, int32_t* active);
 
+/* Bound of every wait of the server's resident-tile launches for a neighbour
+   tile, as ising_set_resident_wait (0: the default of one second).  A server
+   advances a few large lattices in resident tiles; a launch that cannot have the
+   device for longer than the bound is abandoned, and its request is then run
+   again from its start, without tiles: results never depend on it, only when
+   they come (t_admit_s is the last admission). */
+int ising_server_set_resident_wait(ising_server* s, uint64_t ticks);
+
 /* Move up to cap finished results into out (host array); *n receives how
    many.  Returns ISING_OK even when *n == 0. */
 int ising_server_poll(ising_server* s, ising_result* out, int32_t cap, int32_t* n);

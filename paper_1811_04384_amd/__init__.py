@@ -461,6 +461,10 @@ def ising_server_step(h):
     return int(a.value)
 
 
+def ising_server_set_resident_wait(h, ticks):
+    _check(_lib.load().ising_server_set_resident_wait(h, int(ticks)))
+
+
 def ising_server_poll(h, cap=4096):
     buf = (Result * cap)()
     n = ctypes.c_int32()
@@ -767,6 +771,9 @@ class Server:
 
     def step(self):
         return ising_server_step(self.handle)
+
+    def set_resident_wait(self, ticks):
+        ising_server_set_resident_wait(self.handle, ticks)
 
     def poll(self, cap=4096):
         return ising_server_poll(self.handle, cap)

@@ -107,6 +107,7 @@ SIGNATURES = {
     "ising_server_create": (c_int, [c_sz, c_i32, c_i32, c_vp, P(c_vp)]),
     "ising_server_submit": (c_int, [c_vp, c_u64, c_i32, c_dbl, c_i64, c_u64, c_i32]),
     "ising_server_step": (c_int, [c_vp, P(c_i32)]),
+    "ising_server_set_resident_wait": (c_int, [c_vp, ctypes.c_uint64]),
     "ising_server_poll": (c_int, [c_vp, P(Result), c_i32, P(c_i32)]),
     "ising_server_stats": (c_int, [c_vp, P(c_i32), P(c_i32), P(c_i32), P(c_sz)]),
     "ising_server_destroy": (c_int, [c_vp]),

@@ -96,6 +96,8 @@ struct LatticeState {
     Moments mom;              // sums over the samples since the last reset
     int64_t last_E, last_M;   // most recent sample or observation
     unsigned long long obs_anti, obs_ups;  // sums of an observation's workgroups (zero between observations)
+    uint32_t abandoned;       // a resident-tile launch of a server gave up on this lattice (until its slot is admitted to again)
+    uint32_t pad_;
 };
 
 // One wavefront of a tiled half-sweep launch: up to 64 words_per_thread

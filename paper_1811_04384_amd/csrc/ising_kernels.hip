@@ -478,7 +478,7 @@ __global__ void __launch_bounds__(256) k_observe_multi(const LatticeDesc* __rest
 // E and M of the k-th listed lattice from its sums, which are left zero.
 __global__ void __launch_bounds__(256) k_observed(const LatticeDesc* __restrict__ descs,
                                                   LatticeState* __restrict__ states, const int32_t* __restrict__ ids,
-                                                  int32_t n_lat, int64_t* __restrict__ out_EM) {
+                                                  int32_t n_lat, int64_t* __restrict__ out) {
     const int32_t k = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
     if (k >= n_lat) return;
     const int32_t lat = ids ? ids[k] : k;
@@ -489,9 +489,10 @@ __global__ void __launch_bounds__(256) k_observed(const LatticeDesc* __restrict_
     st.obs_ups = 0;
     st.last_E = E;
     st.last_M = M;
-    if (out_EM) {
-        out_EM[2 * k] = E;
-        out_EM[2 * k + 1] = M;
+    if (out) {
+        out[kObservedWords * k] = E;
+        out[kObservedWords * k + 1] = M;
+        out[kObservedWords * k + 2] = st.abandoned;
     }
 }
 
@@ -714,7 +715,7 @@ hipError_t launch_begin_call(LatticeState* states, int32_t n_lat, hipStream_t s)
 }
 
 hipError_t launch_observe_multi(const LatticeDesc* descs, LatticeState* states, const int32_t* ids, int32_t n_lat,
-                                int64_t max_words, int64_t* out_EM, hipStream_t s) {
+                                int64_t max_words, int64_t* out, hipStream_t s) {
     if (n_lat <= 0) return hipSuccess;
     // workgroups for every run of the largest lattice, up to 1024 per lattice and
     // 16384 in all (beyond, a workgroup takes several runs)
@@ -722,7 +723,7 @@ hipError_t launch_observe_multi(const LatticeDesc* descs, LatticeState* states, 
     const int64_t parts = std::max<int64_t>(1, std::min({runs, (int64_t)1024, (int64_t)16384 / n_lat}));
     hipLaunchKernelGGL(k_observe_multi, dim3((unsigned)(parts * n_lat)), dim3(256), 0, s, descs, states, ids,
                        (int32_t)parts);
-    hipLaunchKernelGGL(k_observed, dim3(grid_for(n_lat, 256)), dim3(256), 0, s, descs, states, ids, n_lat, out_EM);
+    hipLaunchKernelGGL(k_observed, dim3(grid_for(n_lat, 256)), dim3(256), 0, s, descs, states, ids, n_lat, out);
     return hipGetLastError();
 }
 

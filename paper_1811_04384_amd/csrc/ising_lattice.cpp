@@ -63,10 +63,6 @@ struct ising_lattice {
 // Temperatures of a scan whose moment sums are read back together.
 constexpr int32_t kScanBlock = 256;
 
-static int ensure_desc(ising_lattice* h);
-static void free_resident(ising_lattice* h);
-static bool enable_drawn(ising_lattice* h, int32_t tile_cols, int32_t block, int32_t max_sweeps);
-
 namespace ising {
 std::string& last_error_ref() {
     thread_local std::string s;
@@ -110,6 +106,10 @@ int write_spins(uint64_t* W, const Geometry& g, const uint8_t* host, uint8_t* st
 }  // namespace ising
 
 extern "C" {
+
+static int ensure_desc(ising_lattice* h);
+static void free_resident(ising_lattice* h);
+static bool enable_drawn(ising_lattice* h, int32_t tile_cols, int32_t block, int32_t max_sweeps);
 
 const char* ising_last_error(void) { return last_error_ref().c_str(); }
 

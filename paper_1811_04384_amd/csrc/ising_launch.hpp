@@ -134,10 +134,12 @@ hipError_t set_resident_lds(int wpt, size_t lds_bytes);
 hipError_t launch_resident(int wpt, int block, const LatticeDesc* descs, LatticeState* states, const int32_t* ids,
                            int32_t n_ids, int32_t K, int32_t every, size_t lds_bytes, hipStream_t s);
 // Current E and M into states[i].last_E / last_M for the lattices ids[0..n)
-// (ids null: lattices 0..n), and into out_EM[2k], out_EM[2k+1] for the k-th
-// listed lattice when out_EM is non-null; max_words: the words of the largest.
+// (ids null: lattices 0..n), and E, M and the state's `abandoned` into the
+// kObservedWords words out[kObservedWords k ...] for the k-th listed lattice when out
+// is non-null; max_words: the words of the largest.
+constexpr int kObservedWords = 3;
 hipError_t launch_observe_multi(const LatticeDesc* descs, LatticeState* states, const int32_t* ids, int32_t n_lat,
-                                int64_t max_words, int64_t* out_EM, hipStream_t s);
+                                int64_t max_words, int64_t* out, hipStream_t s);
 // Zero the sample accumulators of every lattice; start a call (series_idx = 0).
 hipError_t launch_reset_sums(LatticeState* states, int32_t n_lat, hipStream_t s);
 hipError_t launch_begin_call(LatticeState* states, int32_t n_lat, hipStream_t s);

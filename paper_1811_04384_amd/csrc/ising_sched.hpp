@@ -87,6 +87,7 @@ struct Request {
     int32_t init = 0;
     size_t bytes = 0;       // packed words
     double t_submit = 0;
+    bool no_tiles = false;  // a resident-tile launch of it was abandoned: not again
 };
 
 struct Slot {
@@ -149,6 +150,10 @@ class Scheduler {
         }
         return out;
     }
+
+    // Put admitted requests back at the head of the queue, in the order given: they
+    // start anew.
+    void requeue(const std::vector<Request>& rs) { queue_.insert(queue_.begin(), rs.begin(), rs.end()); }
 
     // Sweeps of every active slot in the next quantum: min(quantum, left).
     void plan_quantum() {

@@ -13,6 +13,12 @@
 // and its slot and arena range are reused at once (stream order puts any
 // later use after the read-back).  Results are harvested when their event
 // has completed.
+//
+// A resident-tile launch can be abandoned (its tiles wait for each other, at
+// most a second, and something else may hold the device for longer).  It then
+// marks its own lattice's state, and nothing else; the mark comes back with the
+// lattice's E and M, and its request goes through the queue once more, from its
+// start and without tiles.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -58,6 +64,7 @@ struct SmallGroup {
     int32_t max_NL, max_words, max_draws, K;  // the largest lattice's words, words of a colour, draw items; sweeps
 };
 constexpr int kServerTiledBlock = 64;  // threads of a half-sweep workgroup
+constexpr uint64_t kWaitTicks = 100000000;  // one second of the 100 MHz clock
 constexpr int kStages = 2;     // quanta in flight = staging buffer sets
 constexpr int kRing = 4;       // read-back ring entries
 
@@ -76,14 +83,19 @@ struct Stage {
     bool used = false;
 };
 
+// A finished request, and when it was admitted.
+struct Finished {
+    Request req;
+    double t_admit;
+};
+
 // One batch of finished requests whose E/M read-back is in flight.
 struct Readback {
     int32_t* ids = nullptr;  // pinned: slot ids uploaded for the reduction
-    int64_t* em = nullptr;   // pinned: (E, M) per listed slot
-    uint32_t* err = nullptr;  // the tiles' error word, behind em
+    int64_t* em = nullptr;   // pinned: kObservedWords per listed slot
     hipEvent_t done = nullptr;
     bool pending = false;
-    std::vector<ising_result> meta;  // request data; E, M and t_done filled at harvest
+    std::vector<Finished> requests;
 };
 
 }  // namespace
@@ -106,13 +118,13 @@ struct ising_server {
     int64_t code_words = 0;
     int cus = 0;
     // resident tiles (set up when first wanted): the quantum's tables; one word
-    // per tile and the exchange buffer; the error word
+    // per tile and the exchange buffer
     enum { kTilesUnknown, kTilesUsable, kTilesNot } tiles = kTilesUnknown;
     PersistTile* d_tiles = nullptr;
     uint64_t* d_exch = nullptr;
-    uint32_t* d_err = nullptr;
+    uint64_t wait_ticks = kWaitTicks;  // bound of each wait of the tiles, 100 MHz clock ticks
     int32_t* d_fin = nullptr;  // ids of a read-back batch
-    int64_t* d_em = nullptr;   // (E, M) of a read-back batch
+    int64_t* d_em = nullptr;   // kObservedWords per lattice of a read-back batch
     Stage stage[kStages];
     int next_stage = 0;
     std::deque<hipEvent_t> inflight;  // quantum events, oldest first
@@ -137,7 +149,6 @@ void release(ising_server* s) {
     if (s->d_codes) (void)hipFree(s->d_codes);
     if (s->d_tiles) (void)hipFree(s->d_tiles);
     if (s->d_exch) (void)hipFree(s->d_exch);
-    if (s->d_err) (void)hipFree(s->d_err);
     if (s->d_fin) (void)hipFree(s->d_fin);
     if (s->d_em) (void)hipFree(s->d_em);
     for (Stage& st : s->stage) {
@@ -159,8 +170,9 @@ void release(ising_server* s) {
     delete s;
 }
 
-// Move a completed read-back batch into the finished list.  wait: block on
-// its event; otherwise only if it has already completed.
+// Move a completed read-back batch into the finished list (an abandoned request
+// back into the queue).  wait: block on its event; otherwise only if it has
+// already completed.
 int harvest(ising_server* s, Readback& r, bool wait) {
     if (!r.pending) return ISING_OK;
     if (wait) {
@@ -170,23 +182,31 @@ int harvest(ising_server* s, Readback& r, bool wait) {
         if (e == hipErrorNotReady) return ISING_OK;
         if (e != hipSuccess) return hip_fail(e, "hipEventQuery");
     }
-    if (*r.err) {  // a launch of resident tiles was abandoned: these results are not valid
-        *r.err = 0;
-        r.meta.clear();
-        r.pending = false;
-        ISING_HIP(launch_zero_words(reinterpret_cast<uint64_t*>(s->d_err), 1, s->stream));
-        return fail(ISING_EHIP, "server: a resident-tile launch waited too long for a neighbour tile and was abandoned; "
-                                "the states of its lattices are undefined");
-    }
     const double t = now_s();
-    for (size_t k = 0; k < r.meta.size(); ++k) {
-        ising_result res = r.meta[k];
-        res.E = r.em[2 * k];
-        res.M = r.em[2 * k + 1];
+    std::vector<Request> again;
+    for (size_t k = 0; k < r.requests.size(); ++k) {
+        const Request& q = r.requests[k].req;
+        const int64_t* em = r.em + kObservedWords * k;
+        if (em[2]) {
+            again.push_back(q);
+            again.back().no_tiles = true;
+            continue;
+        }
+        ising_result res;
+        res.req_id = q.id;
+        res.L = q.L;
+        res.status = ISING_OK;
+        res.T = q.T;
+        res.sweeps = q.sweeps;
+        res.E = em[0];
+        res.M = em[1];
+        res.t_submit_s = q.t_submit;
+        res.t_admit_s = r.requests[k].t_admit;
         res.t_done_s = t;
         s->done.push_back(res);
     }
-    r.meta.clear();
+    s->sched.requeue(again);
+    r.requests.clear();
     r.pending = false;
     return ISING_OK;
 }
@@ -259,11 +279,9 @@ bool tiles_usable(ising_server* s) {
         e = hipMalloc(&s->d_tiles, sizeof(PersistTile) * kServerTiled * kServerTiles);
         if (e == hipSuccess)
             e = hipMalloc(&s->d_exch, sizeof(uint64_t) * (kServerTiles + (size_t)kServerTiles * 4 * (size_t)big.N));
-        if (e == hipSuccess) e = hipMalloc(&s->d_err, sizeof(uint64_t));
         for (Stage& st : s->stage)
             if (e == hipSuccess)
                 e = hipHostMalloc(&st.tiles, sizeof(PersistTile) * kServerTiled * kServerTiles, hipHostMallocDefault);
-        if (e == hipSuccess) e = launch_zero_words(reinterpret_cast<uint64_t*>(s->d_err), 1, s->stream);
         if (e == hipSuccess) s->tiles = ising_server::kTilesUsable;
     }
     if (e != hipSuccess) (void)hipGetLastError();
@@ -320,7 +338,7 @@ int enqueue_quantum(ising_server* s) {
         const Geometry g = make_geometry(sl.req.L);
         if (is_resident(s, g)) continue;
         n_large += 1;
-        tiled += g.L <= kServerTiledMaxL ? tiled_us(g.L, sl.planned) : 1e300;
+        tiled += g.L <= kServerTiledMaxL && !sl.req.no_tiles ? tiled_us(g.L, sl.planned) : 1e300;
         swept = std::max(swept, 2.0 * (double)sl.planned * halfsweep_us(n_waves));
     }
     const bool tiles = n_large > 0 && n_large <= kServerTiled && tiled < swept && tiles_usable(s);
@@ -449,8 +467,8 @@ int enqueue_quantum(ising_server* s) {
             a.flags = s->d_exch;
             a.exch = s->d_exch + kServerTiles;
             a.exch_tile_words = 4 * (int64_t)g.N;
-            a.error = s->d_err;
-            a.wait_ticks = 100000000ull;  // one second of the 100 MHz clock
+            a.error = &s->d_state[t.lattice].abandoned;
+            a.wait_ticks = s->wait_ticks;
             for (int32_t done = 0; done < t.K; done += kServerTileSweeps) {
                 a.sweep_off = (uint32_t)done;
                 a.K = std::min(kServerTileSweeps, t.K - done);
@@ -490,26 +508,33 @@ int enqueue_retirements(ising_server* s) {
         const Slot& sl = s->sched.slots()[fin[k]];
         r.ids[k] = fin[k];
         max_words = std::max<int64_t>(max_words, (int64_t)(ising_required_bytes(sl.req.L) / 8));
-        ising_result m;
-        m.req_id = sl.req.id;
-        m.L = sl.req.L;
-        m.status = ISING_OK;
-        m.T = sl.req.T;
-        m.sweeps = sl.req.sweeps;
-        m.E = m.M = 0;
-        m.t_submit_s = sl.req.t_submit;
-        m.t_admit_s = sl.t_admit;
-        m.t_done_s = 0;
-        r.meta.push_back(m);
+        r.requests.push_back({sl.req, sl.t_admit});
     }
     ISING_HIP(hipMemcpyAsync(s->d_fin, r.ids, sizeof(int32_t) * nf, hipMemcpyHostToDevice, s->stream));
     ISING_HIP(launch_observe_multi(s->d_desc, s->d_state, s->d_fin, nf, max_words, s->d_em, s->stream));
-    ISING_HIP(hipMemcpyAsync(r.em, s->d_em, sizeof(int64_t) * 2 * nf, hipMemcpyDeviceToHost, s->stream));
-    if (s->tiles == ising_server::kTilesUsable)
-        ISING_HIP(hipMemcpyAsync(r.err, s->d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, s->stream));
+    ISING_HIP(hipMemcpyAsync(r.em, s->d_em, sizeof(int64_t) * kObservedWords * nf, hipMemcpyDeviceToHost, s->stream));
     ISING_HIP(hipEventRecord(r.done, s->stream));
     r.pending = true;
     for (int32_t i : fin) s->sched.retire(i);
+    return ISING_OK;
+}
+
+// Admit what fits and enqueue a quantum of all resident lattices, the read-back
+// of those that it finishes behind it.
+int run_quantum(ising_server* s) {
+    int rc = admit_queued(s);
+    if (rc != ISING_OK || s->sched.active() == 0) return rc;
+    rc = enqueue_quantum(s);
+    if (rc == ISING_OK) rc = enqueue_retirements(s);
+    if (rc != ISING_OK) return rc;
+    hipEvent_t e = nullptr;
+    hipError_t he = hipEventCreateWithFlags(&e, hipEventDisableTiming);
+    if (he == hipSuccess) he = hipEventRecord(e, s->stream);
+    if (he != hipSuccess) {
+        if (e) (void)hipEventDestroy(e);
+        return hip_fail(he, "quantum event");
+    }
+    s->inflight.push_back(e);
     return ISING_OK;
 }
 
@@ -551,7 +576,7 @@ int ising_server_create(size_t hbm_budget, int32_t max_slots, int32_t quantum_sw
     if (e == hipSuccess) e = hipMalloc(&s->d_draw, sizeof(DrawLat) * max_slots);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device);
     if (e == hipSuccess) e = hipMalloc(&s->d_fin, sizeof(int32_t) * max_slots);
-    if (e == hipSuccess) e = hipMalloc(&s->d_em, sizeof(int64_t) * 2 * max_slots);
+    if (e == hipSuccess) e = hipMalloc(&s->d_em, sizeof(int64_t) * kObservedWords * max_slots);
     for (Stage& st : s->stage) {
         if (e == hipSuccess) e = hipHostMalloc(&st.desc, sizeof(LatticeDesc) * max_slots, hipHostMallocDefault);
         if (e == hipSuccess) e = hipHostMalloc(&st.draw, sizeof(DrawLat) * max_slots, hipHostMallocDefault);
@@ -559,11 +584,7 @@ int ising_server_create(size_t hbm_budget, int32_t max_slots, int32_t quantum_sw
     }
     for (Readback& r : s->ring) {
         if (e == hipSuccess) e = hipHostMalloc(&r.ids, sizeof(int32_t) * max_slots, hipHostMallocDefault);
-        if (e == hipSuccess) e = hipHostMalloc(&r.em, sizeof(int64_t) * (2 * (size_t)max_slots + 1), hipHostMallocDefault);
-        if (e == hipSuccess) {
-            r.err = reinterpret_cast<uint32_t*>(r.em + 2 * (size_t)max_slots);
-            *r.err = 0;
-        }
+        if (e == hipSuccess) e = hipHostMalloc(&r.em, sizeof(int64_t) * kObservedWords * max_slots, hipHostMallocDefault);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&r.done, hipEventDisableTiming);
     }
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking);
@@ -612,26 +633,26 @@ int ising_server_step(ising_server* s, int32_t* active) {
         if (he != hipSuccess) rc = hip_fail(he, "hipEventSynchronize");
         if (rc == ISING_OK) rc = harvest_all(s, false);
     }
-    if (rc == ISING_OK) rc = admit_queued(s);
-    if (rc == ISING_OK && s->sched.active() > 0) {
-        rc = enqueue_quantum(s);
-        if (rc == ISING_OK) rc = enqueue_retirements(s);
-        if (rc == ISING_OK) {
-            hipEvent_t e = nullptr;
-            hipError_t he = hipEventCreateWithFlags(&e, hipEventDisableTiming);
-            if (he == hipSuccess) he = hipEventRecord(e, s->stream);
-            if (he != hipSuccess) {
-                if (e) (void)hipEventDestroy(e);
-                rc = hip_fail(he, "quantum event");
-            } else {
-                s->inflight.push_back(e);
-            }
-        }
+    if (rc == ISING_OK) rc = run_quantum(s);
+    // nothing resident or queued: let every pending read-back land; one that brings
+    // an abandoned request back to the queue has the next quantum follow, so that a
+    // caller who stops when nothing is resident or queued has every result
+    while (rc == ISING_OK && s->sched.active() == 0 && s->sched.queued() == 0) {
+        rc = wait_idle(s);
+        if (s->sched.queued() == 0) break;
+        if (rc == ISING_OK) rc = run_quantum(s);
     }
-    // nothing resident or queued: let every pending read-back land
-    if (rc == ISING_OK && s->sched.active() == 0 && s->sched.queued() == 0) rc = wait_idle(s);
     if (active) *active = s->sched.active();
     return rc;
+}
+
+int ising_server_set_resident_wait(ising_server* s, uint64_t ticks) {
+    if (!s) return fail(ISING_EINVAL, "ising_server_set_resident_wait: null handle");
+    if (ticks > kWaitTicks * 60)
+        return fail(ISING_EINVAL, "ising_server_set_resident_wait: at most %llu ticks (one minute)",
+                    (unsigned long long)(kWaitTicks * 60));
+    s->wait_ticks = ticks ? ticks : kWaitTicks;
+    return ISING_OK;
 }
 
 int ising_server_poll(ising_server* s, ising_result* out, int32_t cap, int32_t* n) {

@@ -1,0 +1,332 @@
+// The library's host code (ising_server.cpp, ising_lattice.cpp) without a GPU, for
+// the paths that only a failure reaches: a stand-in HIP runtime that runs enqueued
+// work late, in the order of the calls and only when the host waits for it, whose
+// allocations can be made to fail, and stand-ins of the kernels' launchers that
+// can be made to fail and that keep, in a lattice's first word, a number which
+// depends on its seed and on every sweep applied to it, in order.
+//   host_stub <scenario> [number ...]   prints one line per finding; see main()
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <deque>
+#include <functional>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../include/ising.h"
+#include "../paper_1811_04384_amd/csrc/ising_launch.hpp"
+#include "../paper_1811_04384_amd/csrc/ising_replicas.hpp"
+
+using namespace ising;
+
+// ---- runtime ----------------------------------------------------------------
+
+namespace {
+
+std::deque<std::function<void()>> work;
+uint64_t enqueued = 0, executed = 0;
+size_t fail_above = ~size_t(0);  // allocations of more bytes fail
+int allocations = 0;
+int fail_launch = 0;   // the n-th launch from now fails (0: none)
+bool rewritten = false;  // a host buffer changed between a copy's enqueueing and its execution
+bool wrong = false;      // a launcher was given something that does not fit
+bool captured = false;   // a resident launch has been captured by a caller
+int n_persist = 0, n_swept = 0, n_strip_phase = 0, n_strip_lists = 0, n_strip_draws = 0;
+
+void enqueue(std::function<void()> f) {
+    work.push_back(std::move(f));
+    ++enqueued;
+}
+void run_until(uint64_t seq) {
+    while (executed < seq && !work.empty()) {
+        work.front()();
+        work.pop_front();
+        ++executed;
+    }
+}
+void run_all() { run_until(enqueued); }
+
+struct Event {
+    uint64_t seq = 0;
+};
+
+hipError_t launch(std::function<void()> f) {
+    if (fail_launch > 0 && --fail_launch == 0) return hipErrorLaunchFailure;
+    enqueue(std::move(f));
+    return hipSuccess;
+}
+
+}  // namespace
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+    if (n > fail_above) return hipErrorOutOfMemory;
+    ++allocations;
+    *p = std::malloc(n ? n : 1);
+    return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+    run_all();
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+    *p = std::malloc(n ? n : 1);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+    run_all();
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) {
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
+    *v = 256;
+    return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "stand-in error"; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+    *s = reinterpret_cast<hipStream_t>(std::malloc(1));
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t s) {
+    std::free(s);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) {
+    run_all();
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+    *e = reinterpret_cast<hipEvent_t>(new Event);
+    return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t e) {
+    delete reinterpret_cast<Event*>(e);
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+    reinterpret_cast<Event*>(e)->seq = enqueued;
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) {
+    run_until(reinterpret_cast<Event*>(e)->seq);
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) {
+    return executed >= reinterpret_cast<Event*>(e)->seq ? hipSuccess : hipErrorNotReady;
+}
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind kind, hipStream_t) {
+    if (kind == hipMemcpyHostToDevice) {
+        std::vector<char> was((const char*)src, (const char*)src + n);
+        enqueue([=] {
+            if (std::memcmp(was.data(), src, n) != 0) rewritten = true;
+            std::memcpy(dst, src, n);
+        });
+    } else {
+        enqueue([=] { std::memcpy(dst, src, n); });
+    }
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind) {
+    run_all();
+    std::memcpy(dst, src, n);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* p, int v, size_t n, hipStream_t) {
+    enqueue([=] { std::memset(p, v, n); });
+    return hipSuccess;
+}
+hipError_t hipMemset(void* p, int v, size_t n) {
+    run_all();
+    std::memset(p, v, n);
+    return hipSuccess;
+}
+}  // extern "C"
+
+// ---- launchers ----------------------------------------------------------------
+
+namespace ising {
+
+// The number in a lattice's first word: its start, and a sweep t.
+static uint64_t start_of(uint64_t seed, int hot) { return 2 * seed + (uint64_t)hot + 1; }
+static uint64_t swept(uint64_t v, uint64_t t) { return v * 6364136223846793005ull + t + 1442695040888963407ull; }
+
+hipError_t launch_init(uint64_t* W, const Geometry&, uint64_t seed, int hot, hipStream_t) {
+    return launch([=] { *W = start_of(seed, hot); });
+}
+hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t) {
+    return launch([=] { std::memset(p, 0, 8 * n); });
+}
+hipError_t launch_halfsweep_multi(int, int, const LatticeDesc* descs, LatticeState* states, const WaveItem* waves,
+                                  int64_t n_waves, bool, int colour, uint32_t sweep_off, Partial*, const Partial*,
+                                  uint32_t, hipStream_t) {
+    ++n_swept;
+    return launch([=] {
+        if (colour == 1)
+            for (int64_t w = 0; w < n_waves; ++w) {
+                const int32_t i = waves[w].lattice;
+                if (waves[w].row == 0 && waves[w].w0 == 0 && (int32_t)sweep_off < descs[i].sweep_limit)
+                    *descs[i].W = swept(*descs[i].W, states[i].t + sweep_off);
+            }
+    });
+}
+hipError_t launch_chunk_end(const LatticeDesc* descs, LatticeState* states, int32_t n, const Partial*, uint32_t, uint32_t k,
+                            hipStream_t) {
+    return launch([=] {
+        for (int32_t i = 0; i < n; ++i) states[i].t += std::min(k, (uint32_t)descs[i].sweep_limit);
+    });
+}
+hipError_t launch_observe_multi(const LatticeDesc* descs, LatticeState* states, const int32_t* ids, int32_t n, int64_t,
+                                int64_t* out, hipStream_t) {
+    return launch([=] {
+        for (int32_t k = 0; k < n; ++k) {
+            out[kObservedWords * k] = (int64_t)*descs[ids[k]].W;
+            out[kObservedWords * k + 1] = (int64_t)states[ids[k]].t;
+            out[kObservedWords * k + 2] = states[ids[k]].abandoned;
+        }
+    });
+}
+// Drawn codes: the first and last word of a sweep's codes hold its index.
+hipError_t launch_draw_codes(const LatticeDesc* descs, const LatticeState* states, const DrawLat* lats, int32_t n, int32_t,
+                             uint64_t* codes, int32_t off, int32_t S, hipStream_t) {
+    return launch([=] {
+        for (int32_t e = 0; e < n; ++e) {
+            const LatticeDesc& d = descs[lats[e].lat];
+            const int64_t NL = (int64_t)d.N * d.L;
+            for (int32_t j = 0; j < S && off + j < d.sweep_limit; ++j) {
+                uint64_t* c = codes + lats[e].base + j * NL;
+                c[0] = c[NL - 1] = states[lats[e].lat].t + off + j;
+            }
+        }
+    });
+}
+hipError_t launch_wave_apply(int wmax, int block, const LatticeDesc* descs, LatticeState* states, const DrawLat* lats,
+                             int32_t n, const uint64_t* codes, int32_t off, int32_t S, int32_t, size_t, hipStream_t) {
+    return launch([=] {
+        for (int32_t e = 0; e < n; ++e) {
+            const LatticeDesc& d = descs[lats[e].lat];
+            const int64_t NL = (int64_t)d.N * d.L;
+            if (NL / 2 > (int64_t)wmax * block || block > 1024) wrong = true;
+            for (int32_t j = 0; j < S && off + j < d.sweep_limit; ++j) {
+                const uint64_t* c = codes + lats[e].base + j * NL;
+                const uint64_t t = states[lats[e].lat].t + off + j;
+                if (c[0] != t || c[NL - 1] != t) wrong = true;
+                *d.W = swept(*d.W, t);
+            }
+        }
+    });
+}
+int32_t wave_apply_block(int32_t words, int32_t wmax) { return ((words + wmax - 1) / wmax + 63) / 64 * 64; }
+int32_t wave_apply_words_per_thread(int32_t L, int32_t N, int32_t block) { return (N * (L / 2) + block - 1) / block; }
+size_t wave_apply_lds_bytes(int32_t NL, int32_t) { return (size_t)NL * 8; }
+size_t resident_lds_limit(int) { return 160 * 1024; }
+
+// A wait bound of one tick expires at once: the launch leaves a state that is not the lattice's.
+hipError_t launch_persist(const PersistLaunch& a, int, int32_t, int, size_t, hipStream_t) {
+    ++n_persist;
+    return launch([=] {
+        const int32_t i = a.tiles[0].lattice;
+        uint64_t& w = *a.descs[i].W;
+        if (a.wait_ticks == 1) *a.error = 1;
+        if (*a.error) w ^= 0xDEADull;
+        else
+            for (int32_t j = 0; j < a.K; ++j) w = swept(w, a.states[i].t + a.sweep_off + j);
+    });
+}
+int persist_form(int32_t, int32_t, int32_t, int) { return 0; }
+size_t persist_lds_bytes(int32_t, int32_t, int32_t, int32_t) { return 1000; }
+size_t persist_lds_limit(int) { return 160 * 1024; }
+hipError_t allow_persist_lds(int, int, size_t) { return hipSuccess; }
+hipError_t persist_capacity(int, size_t, int, int64_t* tiles) {
+    *tiles = 256;
+    return hipSuccess;
+}
+hipError_t resident_gate(int, hipStream_t, const std::function<hipError_t()>& f) { return f(); }
+}  // namespace ising
+
+// ---- scenarios ----------------------------------------------------------------
+
+namespace {
+
+struct Req {
+    uint64_t id;
+    int32_t L;
+    int64_t sweeps;
+};
+
+uint64_t expected(const Req& r) {
+    uint64_t v = ising::start_of(r.id, 1);
+    for (int64_t t = 0; t < r.sweeps; ++t) v = ising::swept(v, (uint64_t)t);
+    return v;
+}
+
+// Serve the requests as a program does that stops when nothing is resident or queued;
+// prints each result and the launches of either kind.
+void serve(ising_server* s, const std::vector<Req>& reqs, bool tolerate = false) {
+    for (const Req& r : reqs)
+        if (ising_server_submit(s, r.id, r.L, 2.0, r.sweeps, r.id, ISING_HOT) != ISING_OK) std::printf("refused %d\n", (int)r.id);
+    int32_t active = 0, queued = 0;
+    for (int step = 0; step < 1000; ++step) {
+        const int rc = ising_server_step(s, &active);
+        if (rc != ISING_OK) {
+            std::printf("step error %d: %s\n", rc, ising_last_error());
+            if (!tolerate) break;
+        }
+        (void)ising_server_stats(s, &queued, nullptr, nullptr, nullptr);
+        if (active == 0 && queued == 0) break;
+    }
+    std::map<uint64_t, ising_result> got;
+    std::vector<ising_result> out(reqs.size() + 1);
+    int32_t n = 0;
+    (void)ising_server_poll(s, out.data(), (int32_t)out.size(), &n);
+    for (int32_t k = 0; k < n; ++k) got[out[k].req_id] = out[k];
+    if (n != (int32_t)got.size()) std::printf("a result twice\n");
+    double done_first = 1e300, admit_last = 0;
+    for (const Req& r : reqs) {
+        if (!got.count(r.id)) {
+            std::printf("missing %d\n", (int)r.id);
+            continue;
+        }
+        const ising_result& g = got[r.id];
+        const bool right = g.status == ISING_OK && (uint64_t)g.E == expected(r) && g.M == r.sweeps;
+        std::printf("%s %d\n", right ? "right" : g.status != ISING_OK ? "failed" : "WRONG", (int)r.id);
+        done_first = std::min(done_first, g.t_done_s);
+        admit_last = std::max(admit_last, g.t_admit_s);
+    }
+    std::printf("again %d persist %d halfsweeps %d\n", admit_last > done_first, n_persist, n_swept);
+}
+
+ising_server* server(size_t budget, int32_t slots, int32_t quantum) {
+    ising_server* s = nullptr;
+    if (ising_server_create(budget, slots, quantum, nullptr, &s) != ISING_OK) {
+        std::printf("create: %s\n", ising_last_error());
+        std::exit(1);
+    }
+    return s;
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    std::vector<int64_t> num;
+    for (int i = 2; i < argc; ++i) num.push_back(std::atoll(argv[i]));
+    if (what == "abandon") {
+        // sweeps of the large requests and of the small one, and whether waits expire
+        ising_server* s = server(64 << 20, 16, 100);
+        if (num[3]) (void)ising_server_set_resident_wait(s, 1);
+        serve(s, {{1, 1024, num[0]}, {2, 64, num[1]}, {3, 512, num[2]}});
+        ising_server_destroy(s);
+    }
+    std::printf("rewritten %d wrong %d\n", rewritten, wrong);
+    return 0;
+}

@@ -1,0 +1,43 @@
+"""What the library's host code does when something fails, without a GPU: its
+sources are compiled with a stand-in HIP runtime (host_stub.cpp) that runs work
+late and whose allocations and launches can be made to fail."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1811_04384_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("stub") / "host_stub")
+    subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-w",
+                    "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+                    os.path.join(ROOT, "tests", "host_stub.cpp"), os.path.join(CSRC, "ising_server.cpp"),
+                    os.path.join(CSRC, "ising_lattice.cpp"), "-Wl,--unresolved-symbols=ignore-all", "-o", exe], check=True)
+
+    def run(*args):
+        out = subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True, timeout=60)
+        assert out.returncode == 0, out.stdout + out.stderr
+        return out.stdout.split("\n")[:-1]
+
+    return run
+
+
+@pytest.mark.parametrize("sweeps", [
+    (400, 50, 250),   # the small request, valid, is read back before either abandoned one
+    (100, 100, 100),  # all of one quantum: valid and abandoned in one read-back, nothing left afterwards
+    (400, 0, 0),
+])
+def test_server_runs_abandoned_requests_again(stub, sweeps):
+    """A resident-tile launch whose waits expire leaves a state that is not its lattice's: that request, and no
+    other, is run again without tiles, and a caller who stops when nothing is resident or queued has every result."""
+    got = stub("abandon", *sweeps, 1)
+    assert got[:3] == ["right 1", "right 2", "right 3"], got
+    assert got[3].startswith("again 1 persist ") and not got[3].startswith("again 1 persist 0 "), got
+    assert got[4] == "rewritten 0 wrong 0"
+    # with the default bound nothing expires and nothing is run again
+    plain = stub("abandon", *sweeps, 0)
+    assert plain[:3] == ["right 1", "right 2", "right 3"] and plain[3].startswith("again 0 "), plain
