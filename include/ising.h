@@ -446,7 +446,11 @@ typedef struct {
    (ising_required_bytes) sum to at most hbm_budget bytes.  Work proceeds in
    quanta of `quantum_sweeps` sweeps over all resident lattices; requests are
    admitted in arrival order as slots and budget free up and leave as soon as
-   their sweeps are done. */
+   their sweeps are done.  The budget is that of the words alone: beside it the
+   server holds its tables, and from the first quantum on that needs them the
+   acceptance codes of small lattices (L <= 256; 64 MB, less where the device has
+   less left) and, for a few large lattices at a time, 1.7 MB of resident-tile
+   buffers. */
 int ising_server_create(size_t hbm_budget, int32_t max_slots, int32_t quantum_sweeps, void* stream,
                         ising_server** out);
 

@@ -35,10 +35,14 @@ using namespace ising;
 
 namespace {
 
-// Acceptance codes of the small lattices held at once (a device buffer): small
-// lattices go in groups of which it holds at least eight sweeps (about 300 of L =
-// 256, and 157 sweeps of 16 of them).
+// Acceptance codes of the small lattices held at once (a device buffer, made when
+// first needed): small lattices go in groups of which it holds at least eight
+// sweeps (about 300 of L = 256, and 157 sweeps of 16 of them).  Where the device has
+// no 64 MB left the buffer and the groups are smaller, down to a sweep of one
+// lattice (3584 words at L = 256), whose room a server has from its creation on: a
+// quantum never fails for want of it.
 constexpr int64_t kServerCodeWords = int64_t(8) << 20;
+constexpr int64_t kServerCodeWordsLeast = 4096;
 constexpr int64_t kServerGroupWords = kServerCodeWords / 8;
 
 // Large lattices in resident tiles, one after the other, in a quantum: at most so
@@ -112,8 +116,8 @@ struct ising_server {
     WaveItem* d_waves = nullptr;
     int64_t d_waves_cap = 0;
     DrawLat* d_draw = nullptr;  // small lattices of the current quantum
-    // their acceptance codes, allocated when first needed: kServerCodeWords, or less,
-    // but room for a sweep of any group, where the device has no more left
+    // their acceptance codes: the buffer of kServerCodeWordsLeast words, and the one in use
+    uint64_t* d_codes_least = nullptr;
     uint64_t* d_codes = nullptr;
     int64_t code_words = 0;
     int cus = 0;
@@ -146,7 +150,8 @@ void release(ising_server* s) {
     if (s->d_state) (void)hipFree(s->d_state);
     if (s->d_waves) (void)hipFree(s->d_waves);
     if (s->d_draw) (void)hipFree(s->d_draw);
-    if (s->d_codes) (void)hipFree(s->d_codes);
+    if (s->d_codes && s->d_codes != s->d_codes_least) (void)hipFree(s->d_codes);
+    if (s->d_codes_least) (void)hipFree(s->d_codes_least);
     if (s->d_tiles) (void)hipFree(s->d_tiles);
     if (s->d_exch) (void)hipFree(s->d_exch);
     if (s->d_fin) (void)hipFree(s->d_fin);
@@ -293,19 +298,23 @@ int32_t group_sweeps(const ising_server* s, const SmallGroup& gr) {
     return (int32_t)std::min<int64_t>(gr.K, s->code_words / gr.words);
 }
 
-hipError_t code_buffer(ising_server* s) {
-    if (s->d_codes) return hipSuccess;
-    hipError_t e = hipErrorOutOfMemory;
-    for (int64_t words = kServerCodeWords; e != hipSuccess && words >= kServerGroupWords; words /= 2) {
-        e = hipMalloc(&s->d_codes, sizeof(uint64_t) * (size_t)words);
-        if (e == hipSuccess) {
+// The buffer of the small lattices' codes, once: the largest that can be had.
+void code_buffer(ising_server* s) {
+    if (s->d_codes) return;
+    for (int64_t words = kServerCodeWords; words > kServerCodeWordsLeast; words /= 2) {
+        if (hipMalloc(&s->d_codes, sizeof(uint64_t) * (size_t)words) == hipSuccess) {
             s->code_words = words;
-        } else {
-            s->d_codes = nullptr;
-            (void)hipGetLastError();
+            return;
         }
+        (void)hipGetLastError();
     }
-    return e;
+    s->d_codes = s->d_codes_least;
+    s->code_words = kServerCodeWordsLeast;
+}
+
+// Words of a group of small lattices, at most (of more than one lattice).
+int64_t group_words(const ising_server* s) {
+    return std::min(kServerGroupWords, std::max(s->code_words / 8, kServerCodeWordsLeast));
 }
 
 // Plan the next quantum, upload its tables through a staging set and enqueue
@@ -377,10 +386,11 @@ int enqueue_quantum(ising_server* s) {
         if (sl.planned <= 0) continue;
         K = std::max<int32_t>(K, (int32_t)sl.planned);
         if (is_resident(s, g)) {
+            code_buffer(s);
             d.resident = 1;
             st.draw[n_res] = {i, 2 * g.N * ((g.L + 7) / 8), 0};
             const int64_t words = (int64_t)g.N * g.L;
-            if (groups.empty() || groups.back().words + words > kServerGroupWords)
+            if (groups.empty() || groups.back().words + words > group_words(s))
                 groups.push_back({n_res, n_res, 0, 0, 0, 0, 0});
             SmallGroup& gr = groups.back();
             gr.end = n_res + 1;
@@ -413,7 +423,6 @@ int enqueue_quantum(ising_server* s) {
         ISING_HIP(hipMemcpyAsync(s->d_tiles, st.tiles,
                                  sizeof(PersistTile) * (size_t)(large.back().first + large.back().count),
                                  hipMemcpyHostToDevice, s->stream));
-    if (n_res) ISING_HIP(code_buffer(s));
     for (const SmallGroup& gr : groups) {
         int64_t base = 0;
         const int64_t S = group_sweeps(s, gr);
@@ -574,6 +583,7 @@ int ising_server_create(size_t hbm_budget, int32_t max_slots, int32_t quantum_sw
     e = hipMalloc(&s->d_desc, sizeof(LatticeDesc) * max_slots);
     if (e == hipSuccess) e = hipMalloc(&s->d_state, sizeof(LatticeState) * max_slots);
     if (e == hipSuccess) e = hipMalloc(&s->d_draw, sizeof(DrawLat) * max_slots);
+    if (e == hipSuccess) e = hipMalloc(&s->d_codes_least, sizeof(uint64_t) * kServerCodeWordsLeast);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device);
     if (e == hipSuccess) e = hipMalloc(&s->d_fin, sizeof(int32_t) * max_slots);
     if (e == hipSuccess) e = hipMalloc(&s->d_em, sizeof(int64_t) * kObservedWords * max_slots);

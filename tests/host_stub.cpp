@@ -326,6 +326,15 @@ int main(int argc, char** argv) {
         if (num[3]) (void)ising_server_set_resident_wait(s, 1);
         serve(s, {{1, 1024, num[0]}, {2, 64, num[1]}, {3, 512, num[2]}});
         ising_server_destroy(s);
+    } else if (what == "tight") {
+        // once the server is made, allocations of more than num[0] bytes fail
+        ising_server* s = server(64 << 20, 400, 90);
+        fail_above = (size_t)num[0];
+        std::vector<Req> reqs;
+        for (int k = 0; k < 60; ++k) reqs.push_back({(uint64_t)k, (int32_t)(4 + (k * 38) % 254 / 2 * 2), 20 + 37 * k % 230});
+        reqs.push_back({60, 256, 130});
+        serve(s, reqs);
+        ising_server_destroy(s);
     }
     std::printf("rewritten %d wrong %d\n", rewritten, wrong);
     return 0;

@@ -41,3 +41,12 @@ def test_server_runs_abandoned_requests_again(stub, sweeps):
     # with the default bound nothing expires and nothing is run again
     plain = stub("abandon", *sweeps, 0)
     assert plain[:3] == ["right 1", "right 2", "right 3"] and plain[3].startswith("again 0 "), plain
+
+
+@pytest.mark.parametrize("most", [1 << 30, (64 << 20) - 1, 1 << 20, 100000, 65536, 32768, 1024])
+def test_server_serves_small_lattices_with_little_memory_left(stub, most):
+    """However little memory is left for the codes of small lattices, no quantum fails, no group draws past the
+    buffer (an address sanitizer watches) and every sweep is applied from its own codes."""
+    got = stub("tight", most)
+    assert got[:61] == [f"right {k}" for k in range(61)], got
+    assert got[62] == "rewritten 0 wrong 0"
