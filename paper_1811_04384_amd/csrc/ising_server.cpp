@@ -416,13 +416,6 @@ int enqueue_quantum(ising_server* s) {
         }
     }
     const bool wave_runs = 2 * filling <= n_waves;
-    ISING_HIP(hipMemcpyAsync(s->d_desc, st.desc, sizeof(LatticeDesc) * slots, hipMemcpyHostToDevice, s->stream));
-    if (n_waves)
-        ISING_HIP(hipMemcpyAsync(s->d_waves, st.waves, sizeof(WaveItem) * n_waves, hipMemcpyHostToDevice, s->stream));
-    if (!large.empty())
-        ISING_HIP(hipMemcpyAsync(s->d_tiles, st.tiles,
-                                 sizeof(PersistTile) * (size_t)(large.back().first + large.back().count),
-                                 hipMemcpyHostToDevice, s->stream));
     for (const SmallGroup& gr : groups) {
         int64_t base = 0;
         const int64_t S = group_sweeps(s, gr);
@@ -432,72 +425,92 @@ int enqueue_quantum(ising_server* s) {
             base += S * d.N * d.L;
         }
     }
-    if (n_res) ISING_HIP(hipMemcpyAsync(s->d_draw, st.draw, sizeof(DrawLat) * n_res, hipMemcpyHostToDevice, s->stream));
-    if (K > 0) {
-        const int block = kServerTiledBlock;
-        if (n_res) {
-            // The small lattices (one workgroup each) run on the side stream,
-            // beside the tiled launches of the other lattices if there are any; as in
-            // a batch, a word per thread where each has a compute unit to itself.  us
-            // for requests of 300 to 500 sweeps in quanta of 100, with workgroups that
-            // draw their own codes / these: 8 of L = 64 1379/775, 16 of L = 256
-            // 5261/836, 300 of L = 128 and 256 8519/3663; 100 of L = 16 in quanta of
-            // one sweep, where launches and the join of two streams are all there is,
-            // 1852/1369.
-            if (n_large) {
-                ISING_HIP(hipEventRecord(s->fork_ev, s->stream));
-                ISING_HIP(hipStreamWaitEvent(s->side, s->fork_ev, 0));
+    bool forked = false;
+    auto enqueue = [&]() -> int {
+        ISING_HIP(hipMemcpyAsync(s->d_desc, st.desc, sizeof(LatticeDesc) * slots, hipMemcpyHostToDevice, s->stream));
+        if (n_waves)
+            ISING_HIP(hipMemcpyAsync(s->d_waves, st.waves, sizeof(WaveItem) * n_waves, hipMemcpyHostToDevice, s->stream));
+        if (!large.empty())
+            ISING_HIP(hipMemcpyAsync(s->d_tiles, st.tiles,
+                                     sizeof(PersistTile) * (size_t)(large.back().first + large.back().count),
+                                     hipMemcpyHostToDevice, s->stream));
+        if (n_res) ISING_HIP(hipMemcpyAsync(s->d_draw, st.draw, sizeof(DrawLat) * n_res, hipMemcpyHostToDevice, s->stream));
+        if (K > 0) {
+            const int block = kServerTiledBlock;
+            if (n_res) {
+                // The small lattices (one workgroup each) run on the side stream,
+                // beside the tiled launches of the other lattices if there are any; as in
+                // a batch, a word per thread where each has a compute unit to itself.  us
+                // for requests of 300 to 500 sweeps in quanta of 100, with workgroups that
+                // draw their own codes / these: 8 of L = 64 1379/775, 16 of L = 256
+                // 5261/836, 300 of L = 128 and 256 8519/3663; 100 of L = 16 in quanta of
+                // one sweep, where launches and the join of two streams are all there is,
+                // 1852/1369.
+                if (n_large) {
+                    ISING_HIP(hipEventRecord(s->fork_ev, s->stream));
+                    ISING_HIP(hipStreamWaitEvent(s->side, s->fork_ev, 0));
+                    forked = true;
+                }
+                const hipStream_t on = n_large ? s->side : s->stream;
+                for (const SmallGroup& gr : groups) {
+                    const int32_t n = gr.end - gr.begin, S = group_sweeps(s, gr);
+                    const int wmax = n <= s->cus || gr.max_words > 1024 ? (gr.max_words + 1023) / 1024
+                                                                        : (gr.max_words + 255) / 256;
+                    for (int32_t done = 0; done < gr.K; done += S) {
+                        const int32_t k = std::min(S, gr.K - done);
+                        ISING_HIP(launch_draw_codes(s->d_desc, s->d_state, s->d_draw + gr.begin, n, gr.max_draws,
+                                                    s->d_codes, done, k, on));
+                        ISING_HIP(launch_wave_apply(wmax, wave_apply_block(gr.max_words, wmax), s->d_desc, s->d_state,
+                                                    s->d_draw + gr.begin, n, s->d_codes, done, k, 0,
+                                                    wave_apply_lds_bytes(gr.max_NL, 0), on));
+                    }
+                }
+                if (n_large) ISING_HIP(hipEventRecord(s->join_ev, s->side));
             }
-            const hipStream_t on = n_large ? s->side : s->stream;
-            for (const SmallGroup& gr : groups) {
-                const int32_t n = gr.end - gr.begin, S = group_sweeps(s, gr);
-                const int wmax = n <= s->cus || gr.max_words > 1024 ? (gr.max_words + 1023) / 1024
-                                                                    : (gr.max_words + 255) / 256;
-                for (int32_t done = 0; done < gr.K; done += S) {
-                    const int32_t k = std::min(S, gr.K - done);
-                    ISING_HIP(launch_draw_codes(s->d_desc, s->d_state, s->d_draw + gr.begin, n, gr.max_draws,
-                                                s->d_codes, done, k, on));
-                    ISING_HIP(launch_wave_apply(wmax, wave_apply_block(gr.max_words, wmax), s->d_desc, s->d_state,
-                                                s->d_draw + gr.begin, n, s->d_codes, done, k, 0,
-                                                wave_apply_lds_bytes(gr.max_NL, 0), on));
+            for (const Tiled& t : large) {
+                const Geometry g = make_geometry(sc.slots()[t.lattice].req.L);
+                // the tags of the lattice before
+                ISING_HIP(launch_zero_words(s->d_exch, kServerTiles + (uint64_t)t.count * 4 * g.N, s->stream));
+                PersistLaunch a = {};
+                a.tiles = s->d_tiles + t.first;
+                a.descs = s->d_desc;
+                a.states = s->d_state;
+                a.n_tiles = t.count;
+                a.flags = s->d_exch;
+                a.exch = s->d_exch + kServerTiles;
+                a.exch_tile_words = 4 * (int64_t)g.N;
+                a.error = &s->d_state[t.lattice].abandoned;
+                a.wait_ticks = s->wait_ticks;
+                for (int32_t done = 0; done < t.K; done += kServerTileSweeps) {
+                    a.sweep_off = (uint32_t)done;
+                    a.K = std::min(kServerTileSweeps, t.K - done);
+                    ISING_HIP(resident_gate(s->device, s->stream, [&] {
+                        return launch_persist(a, persist_form(g.L, g.N, t.w, t.block), t.count, t.block,
+                                              persist_lds_bytes(g.L, g.N, t.w, t.block), s->stream);
+                    }));
                 }
             }
-            if (n_large) ISING_HIP(hipEventRecord(s->join_ev, s->side));
-        }
-        for (const Tiled& t : large) {
-            const Geometry g = make_geometry(sc.slots()[t.lattice].req.L);
-            // the tags of the lattice before
-            ISING_HIP(launch_zero_words(s->d_exch, kServerTiles + (uint64_t)t.count * 4 * g.N, s->stream));
-            PersistLaunch a = {};
-            a.tiles = s->d_tiles + t.first;
-            a.descs = s->d_desc;
-            a.states = s->d_state;
-            a.n_tiles = t.count;
-            a.flags = s->d_exch;
-            a.exch = s->d_exch + kServerTiles;
-            a.exch_tile_words = 4 * (int64_t)g.N;
-            a.error = &s->d_state[t.lattice].abandoned;
-            a.wait_ticks = s->wait_ticks;
-            for (int32_t done = 0; done < t.K; done += kServerTileSweeps) {
-                a.sweep_off = (uint32_t)done;
-                a.K = std::min(kServerTileSweeps, t.K - done);
-                ISING_HIP(resident_gate(s->device, s->stream, [&] {
-                    return launch_persist(a, persist_form(g.L, g.N, t.w, t.block), t.count, t.block,
-                                          persist_lds_bytes(g.L, g.N, t.w, t.block), s->stream);
-                }));
+            for (int32_t k = 0; k < K && n_waves; ++k) {
+                ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, 0,
+                                                 (uint32_t)k, nullptr, nullptr, 0, s->stream));
+                ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, 1,
+                                                 (uint32_t)k, nullptr, nullptr, 0, s->stream));
             }
+            if (n_res && n_large) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));
+            ISING_HIP(launch_chunk_end(s->d_desc, s->d_state, slots, nullptr, 0, (uint32_t)K, s->stream));
         }
-        for (int32_t k = 0; k < K && n_waves; ++k) {
-            ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, 0,
-                                             (uint32_t)k, nullptr, nullptr, 0, s->stream));
-            ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, 1,
-                                             (uint32_t)k, nullptr, nullptr, 0, s->stream));
-        }
-        if (n_res && n_large) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));
-        ISING_HIP(launch_chunk_end(s->d_desc, s->d_state, slots, nullptr, 0, (uint32_t)K, s->stream));
+        return ISING_OK;
+    };
+    rc = enqueue();
+    // also after a failure half way: what was enqueued still reads this set and the device's tables
+    if (rc != ISING_OK && forked) {
+        (void)hipEventRecord(s->join_ev, s->side);
+        (void)hipStreamWaitEvent(s->stream, s->join_ev, 0);
     }
-    ISING_HIP(hipEventRecord(st.done, s->stream));
+    const hipError_t e = hipEventRecord(st.done, s->stream);
     st.used = true;
+    if (rc == ISING_OK && e != hipSuccess) rc = hip_fail(e, "hipEventRecord");
+    if (rc != ISING_OK) return rc;
     sc.complete_quantum();
     return ISING_OK;
 }
@@ -519,11 +532,20 @@ int enqueue_retirements(ising_server* s) {
         max_words = std::max<int64_t>(max_words, (int64_t)(ising_required_bytes(sl.req.L) / 8));
         r.requests.push_back({sl.req, sl.t_admit});
     }
-    ISING_HIP(hipMemcpyAsync(s->d_fin, r.ids, sizeof(int32_t) * nf, hipMemcpyHostToDevice, s->stream));
-    ISING_HIP(launch_observe_multi(s->d_desc, s->d_state, s->d_fin, nf, max_words, s->d_em, s->stream));
-    ISING_HIP(hipMemcpyAsync(r.em, s->d_em, sizeof(int64_t) * kObservedWords * nf, hipMemcpyDeviceToHost, s->stream));
-    ISING_HIP(hipEventRecord(r.done, s->stream));
-    r.pending = true;
+    auto enqueue = [&]() -> int {
+        ISING_HIP(hipMemcpyAsync(s->d_fin, r.ids, sizeof(int32_t) * nf, hipMemcpyHostToDevice, s->stream));
+        ISING_HIP(launch_observe_multi(s->d_desc, s->d_state, s->d_fin, nf, max_words, s->d_em, s->stream));
+        ISING_HIP(hipMemcpyAsync(r.em, s->d_em, sizeof(int64_t) * kObservedWords * nf, hipMemcpyDeviceToHost, s->stream));
+        return ISING_OK;
+    };
+    rc = enqueue();
+    const hipError_t e = hipEventRecord(r.done, s->stream);
+    if (rc == ISING_OK && e != hipSuccess) rc = hip_fail(e, "hipEventRecord");
+    r.pending = true;  // also after a failure half way: what was enqueued still uses the entry
+    if (rc != ISING_OK) {
+        r.requests.clear();  // read back with the next step's
+        return rc;
+    }
     for (int32_t i : fin) s->sched.retire(i);
     return ISING_OK;
 }

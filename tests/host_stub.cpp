@@ -335,6 +335,13 @@ int main(int argc, char** argv) {
         reqs.push_back({60, 256, 130});
         serve(s, reqs);
         ising_server_destroy(s);
+    } else if (what == "halfway") {
+        // the num[0]-th launch from the first step on fails, in quanta of num[1] sweeps; the caller steps on
+        ising_server* s = server(64 << 20, 16, (int32_t)num[1]);
+        fail_launch = (int)num[0];
+        serve(s, {{1, 64, 350}, {2, 2048, 320}, {3, 100, 80}, {4, 300, 700}}, true);
+        std::printf("failed %d\n", fail_launch == 0);
+        ising_server_destroy(s);
     }
     std::printf("rewritten %d wrong %d\n", rewritten, wrong);
     return 0;

@@ -50,3 +50,12 @@ def test_server_serves_small_lattices_with_little_memory_left(stub, most):
     got = stub("tight", most)
     assert got[:61] == [f"right {k}" for k in range(61)], got
     assert got[62] == "rewritten 0 wrong 0"
+
+
+@pytest.mark.parametrize("quantum,first", [(100, 40), (20, 100)])  # large lattices in tiles; in half-sweep launches
+def test_server_step_that_fails_half_way_leaves_no_staging_in_use(stub, quantum, first):
+    """After a launch that fails anywhere in a step, copies enqueued before it have not run yet: the caller's next
+    steps must not rewrite the host buffers they read, nor report a request twice."""
+    for n in range(1, first):
+        got = stub("halfway", n, quantum)
+        assert got[-1] == "rewritten 0 wrong 0" and got[-2] == "failed 1" and "a result twice" not in got, (n, got)
