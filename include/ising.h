@@ -290,8 +290,9 @@ int ising_get_tiling(ising_lattice* h, int32_t* sweeps_per_launch, int32_t* tile
    device at once.  A launch whose tiles wait for a neighbour longer than
    about a second is abandoned: the next call on the handle returns
    ISING_EHIP, and the lattice state is undefined.  Launches of resident
-   tiles on different streams of one device (of this or other handles and
-   batches) run one after another.  Synchronises.  Results never depend on
+   tiles on different streams of one device (of this or other handles,
+   batches and servers) run one after another; those that a caller captures into
+   a graph do not, and are not to be replayed beside others.  Synchronises.  Results never depend on
    it.  ising_get_resident_tiles returns zeros when off.
    ising_create and ising_create_in switch it on for L <= 7680 (up to
    L = 192 the whole lattice in one workgroup of one thread per word of a
@@ -470,7 +471,9 @@ int ising_server_step(ising_server* s, int32_t* active);
    advances a few large lattices in resident tiles; a launch that cannot have the
    device for longer than the bound is abandoned, and its request is then run
    again from its start, without tiles: results never depend on it, only when
-   they come (t_admit_s is the last admission). */
+   they come (t_admit_s is the last admission).  While a lattice handle holds
+   resident tiles whose sweeps a caller has captured into a graph, no further
+   quantum is run in tiles. */
 int ising_server_set_resident_wait(ising_server* s, uint64_t ticks);
 
 /* Move up to cap finished results into out (host array); *n receives how

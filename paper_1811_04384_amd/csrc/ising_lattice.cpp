@@ -49,6 +49,7 @@ struct ising_lattice {
     uint64_t* d_flags = nullptr;
     uint32_t* d_err = nullptr;      // 8 bytes: the error word and padding, cleared by a kernel
     uint32_t* h_err = nullptr;      // pinned copy of d_err, refreshed after every launch
+    bool res_captured = false;      // a caller's graph holds launches of these tiles
     uint64_t res_wait = 0;          // bound of each wait, 100 MHz clock ticks
     Partial* d_rpart = nullptr;     // res_sweeps x n_res partial sums
     int64_t* d_rEM = nullptr;       // 2 x res_sweeps sample scratch (moments without a series)
@@ -161,6 +162,7 @@ static void release(ising_lattice* h) {
     if (h->d_flags) (void)hipFree(h->d_flags);
     if (h->d_err) (void)hipFree(h->d_err);
     if (h->h_err) (void)hipHostFree(h->h_err);
+    if (h->res_captured) (void)resident_captures(h->device, -1);
     if (h->d_rpart) (void)hipFree(h->d_rpart);
     if (h->d_rEM) (void)hipFree(h->d_rEM);
     if (h->d_codes) (void)hipFree(h->d_codes);
@@ -358,8 +360,14 @@ static int enqueue_resident_sweeps(ising_lattice* h, uint64_t t0, double T, int6
         a.t0 = t0 + (uint64_t)done;
         a.K = kb;
         a.sample_base = done;
+        bool captured = false;
         ISING_HIP(resident_gate(h->device, h->stream,
-                                [&] { return launch_persist(a, form, h->n_res, h->res_block, h->res_lds, h->stream); }));
+                                [&] { return launch_persist(a, form, h->n_res, h->res_block, h->res_lds, h->stream); },
+                                &captured));
+        if (captured && !h->res_captured) {
+            h->res_captured = true;
+            (void)resident_captures(h->device, 1);
+        }
         const int64_t n_samples = every > 0 ? (done + kb) / every - done / every : 0;
         if (n_samples > 0) {
             const int64_t idx0 = done / every;  // series index of the launch's first sample
@@ -825,6 +833,8 @@ static void free_resident(ising_lattice* h) {
     h->d_rEM = nullptr;
     h->res_cols = 0;
     h->n_res = 0;
+    if (h->res_captured) (void)resident_captures(h->device, -1);
+    h->res_captured = false;
 }
 
 // Largest number of sweeps of one resident-tile launch.

@@ -204,9 +204,13 @@ hipError_t launch_persist(const PersistLaunch& a, int form, int32_t n_tiles, int
 // Runs launch(), which enqueues work holding resident tiles on stream s of
 // `device`, ordered after the previous such work of this process on that
 // device (a stream wait on its completion event), and makes it the previous
-// one.  Inside a graph capture of s, or with another device current,
-// launch() runs unordered.
-hipError_t resident_gate(int device, hipStream_t s, const std::function<hipError_t()>& launch);
+// one.  Inside a graph capture of s (then *captured, if given, becomes true), or
+// with another device current, launch() runs unordered.
+hipError_t resident_gate(int device, hipStream_t s, const std::function<hipError_t()>& launch,
+                         bool* captured = nullptr);
+// How many handles of the device hold resident launches that a caller has captured
+// and may replay at any time beside others, after adding n.
+int resident_captures(int device, int n = 0);
 // The n_samples samples of one resident-tile launch of a batch (partials
 // [sample][tile], a lattice's tiles at part_begin .. + part_count) for the
 // listed lattices: series entries, moment sums, last E and M, in order.

@@ -668,9 +668,17 @@ hipError_t launch_persist(const PersistLaunch& a, int form, int32_t n_tiles, int
 namespace {
 std::mutex g_gate_mutex;
 std::vector<hipEvent_t> g_gate;
+std::vector<int> g_captures;
 }  // namespace
 
-hipError_t resident_gate(int device, hipStream_t s, const std::function<hipError_t()>& launch) {
+int resident_captures(int device, int n) {
+    std::lock_guard<std::mutex> lock(g_gate_mutex);
+    if (device < 0) return 0;
+    if ((size_t)device >= g_captures.size()) g_captures.resize((size_t)device + 1, 0);
+    return g_captures[device] += n;
+}
+
+hipError_t resident_gate(int device, hipStream_t s, const std::function<hipError_t()>& launch, bool* captured) {
     std::lock_guard<std::mutex> lock(g_gate_mutex);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     hipError_t e = hipStreamIsCapturing(s, &cs);
@@ -680,6 +688,7 @@ hipError_t resident_gate(int device, hipStream_t s, const std::function<hipError
     if (e != hipSuccess) return e;
     // inside a capture a dependency on work outside it is not allowed, and
     // the event belongs to the device current when it was made
+    if (cs != hipStreamCaptureStatusNone && captured) *captured = true;
     if (cs != hipStreamCaptureStatusNone || device < 0 || current != device) return launch();
     if ((size_t)device >= g_gate.size()) g_gate.resize((size_t)device + 1, nullptr);
     if (g_gate[device]) {

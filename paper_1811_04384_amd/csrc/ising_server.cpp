@@ -350,7 +350,10 @@ int enqueue_quantum(ising_server* s) {
         tiled += g.L <= kServerTiledMaxL && !sl.req.no_tiles ? tiled_us(g.L, sl.planned) : 1e300;
         swept = std::max(swept, 2.0 * (double)sl.planned * halfsweep_us(n_waves));
     }
-    const bool tiles = n_large > 0 && n_large <= kServerTiled && tiled < swept && tiles_usable(s);
+    // Not while a caller's graph may replay a lattice's resident tiles beside them, in
+    // no order with these: each could wait for compute units that the other holds.
+    const bool tiles = n_large > 0 && n_large <= kServerTiled && tiled < swept && resident_captures(s->device) == 0 &&
+                       tiles_usable(s);
     if (tiles) n_waves = 0;
     struct Tiled {
         int32_t lattice, first, count, w, block, K;

@@ -33,7 +33,8 @@ int allocations = 0;
 int fail_launch = 0;   // the n-th launch from now fails (0: none)
 bool rewritten = false;  // a host buffer changed between a copy's enqueueing and its execution
 bool wrong = false;      // a launcher was given something that does not fit
-bool captured = false;   // a resident launch has been captured by a caller
+int captures = 0;        // handles whose resident launches a caller has captured
+bool capturing = false;  // the stream is in a caller's capture
 int n_persist = 0, n_swept = 0, n_strip_phase = 0, n_strip_lists = 0, n_strip_draws = 0;
 
 void enqueue(std::function<void()> f) {
@@ -234,6 +235,7 @@ size_t resident_lds_limit(int) { return 160 * 1024; }
 hipError_t launch_persist(const PersistLaunch& a, int, int32_t, int, size_t, hipStream_t) {
     ++n_persist;
     return launch([=] {
+        if (!a.states) return;  // of a single lattice
         const int32_t i = a.tiles[0].lattice;
         uint64_t& w = *a.descs[i].W;
         if (a.wait_ticks == 1) *a.error = 1;
@@ -250,7 +252,19 @@ hipError_t persist_capacity(int, size_t, int, int64_t* tiles) {
     *tiles = 256;
     return hipSuccess;
 }
-hipError_t resident_gate(int, hipStream_t, const std::function<hipError_t()>& f) { return f(); }
+hipError_t resident_gate(int, hipStream_t, const std::function<hipError_t()>& f, bool* captured) {
+    if (capturing && captured) *captured = true;
+    return f();
+}
+int resident_captures(int, int n) { return captures += n; }
+hipError_t launch_samples(const Partial*, int32_t, int32_t, int32_t, int64_t*, int64_t*, Moments*, hipStream_t) {
+    return hipSuccess;
+}
+size_t finalize_scratch_bytes() { return 4096; }
+int64_t observe_single_waves(const Geometry&) { return 16; }
+int64_t halfsweep_single_waves(const Geometry&, int, int) { return 16; }
+int32_t drawn_max_words() { return 2048; }
+size_t drawn_lds_bytes(int32_t L, int32_t N) { return (size_t)L * N * 8; }
 }  // namespace ising
 
 // ---- scenarios ----------------------------------------------------------------
@@ -341,6 +355,24 @@ int main(int argc, char** argv) {
         fail_launch = (int)num[0];
         serve(s, {{1, 64, 350}, {2, 2048, 320}, {3, 100, 80}, {4, 300, 700}}, true);
         std::printf("failed %d\n", fail_launch == 0);
+        ising_server_destroy(s);
+    } else if (what == "captured") {
+        // a quantum of one large lattice while a handle's captured tiles may be replayed, and after it is gone
+        ising_server* s = server(64 << 20, 16, 100);
+        ising_lattice* h = nullptr;
+        if (ising_create(1024, 1, ISING_HOT, nullptr, &h) != ISING_OK) return 1;
+        const int tile_sets = (int)num[0];  // 1: the tiles are set anew before the server runs
+        n_persist = 0;
+        capturing = true;
+        (void)ising_sweep(h, 2.0, 2500);
+        capturing = false;
+        std::printf("captures %d\n", captures);
+        if (tile_sets) (void)ising_set_resident_tiles(h, 8, 512, 100);
+        n_persist = 0;
+        serve(s, {{1, 1024, 100}});
+        ising_destroy(h);
+        std::printf("captures %d\n", captures);
+        serve(s, {{2, 1024, 100}});
         ising_server_destroy(s);
     }
     std::printf("rewritten %d wrong %d\n", rewritten, wrong);

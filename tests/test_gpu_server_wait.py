@@ -52,3 +52,44 @@ def test_resident_wait_is_checked():
         srv.set_resident_wait(0)
     finally:
         srv.close()
+
+
+def test_served_beside_a_captured_lattice():
+    """A lattice's resident tiles, captured by the caller and replayed on one stream while a server advances a large
+    lattice on another: both give the oracle's results."""
+    import torch
+
+    L, seed, T = 1024, 9, 2.269
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(a):
+        lat = ising.Lattice(L, seed, hot=True, stream=a)
+        assert lat.resident_tiles()[0] > 0
+        lat.sweep(T, 2)
+        start = lat.spins()
+        graph = torch.cuda.CUDAGraph()
+        a.synchronize()
+        with torch.cuda.graph(graph, stream=a):
+            lat.sweep(T, 60)
+    srv = ising.Server(hbm_budget=1 << 28, max_slots=8, quantum_sweeps=40, stream=b)
+    got = {}
+    print("captured tiles beside a server", flush=True)
+    try:
+        s = start.copy()
+        oracle.sweep(s, seed, 2, 60, T)
+        for rid in range(3):
+            srv.submit(rid, 2048, 2.0 + 0.2 * rid, 80)
+            with torch.cuda.stream(a):
+                lat.set_spins(start)
+                graph.replay()
+            while len(got) <= rid:
+                srv.step()
+                got.update({r["req_id"]: r for r in srv.poll()})
+            assert (lat.spins() == s).all(), rid
+            lat.synchronize()
+        for rid in range(3):
+            s = oracle.init(2048, rid, True)
+            oracle.sweep(s, rid, 0, 80, 2.0 + 0.2 * rid)
+            assert (got[rid]["E"], got[rid]["M"]) == oracle.observables(s), rid
+    finally:
+        srv.close()
+        lat.close()

@@ -59,3 +59,12 @@ def test_server_step_that_fails_half_way_leaves_no_staging_in_use(stub, quantum,
     for n in range(1, first):
         got = stub("halfway", n, quantum)
         assert got[-1] == "rewritten 0 wrong 0" and got[-2] == "failed 1" and "a result twice" not in got, (n, got)
+
+
+def test_server_keeps_off_tiles_while_captured_ones_may_be_replayed(stub):
+    """Tiles in a caller's graph are replayed in no order with the server's: none are launched while a handle holds
+    such a graph's tiles, and they are again once it is gone or has set others."""
+    assert stub("captured", 0) == ["captures 1", "right 1", "again 0 persist 0 halfsweeps 200", "captures 0", "right 2",
+                                   "again 0 persist 1 halfsweeps 200", "rewritten 0 wrong 0"]
+    assert stub("captured", 1) == ["captures 1", "right 1", "again 0 persist 1 halfsweeps 0", "captures 0", "right 2",
+                                   "again 0 persist 2 halfsweeps 0", "rewritten 0 wrong 0"]
