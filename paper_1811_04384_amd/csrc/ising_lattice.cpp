@@ -58,7 +58,8 @@ struct ising_lattice {
     int32_t drawn_sweeps = 0;
     uint64_t* d_codes = nullptr;
     int drawn_buf = 0;              // the buffer the next launch draws into
-    DrawnLaunch drawn = {};         // its n_apply sweeps are drawn and not yet applied
+    DrawnLaunch drawn = {};         // its n_apply sweeps, from drawn_t on, are drawn and not yet applied
+    uint64_t drawn_t = 0;
 };
 
 // Temperatures of a scan whose moment sums are read back together.
@@ -382,7 +383,8 @@ static int enqueue_resident_sweeps(ising_lattice* h, uint64_t t0, double T, int6
 }
 
 // One launch: the pending sweeps applied, the n sweeps from t on drawn (0: none)
-// to be pending next.
+// to be pending next.  Where it fails the pending sweeps are given up, and the
+// handle's sweep counter goes to the first sweep that is not applied.
 static int drawn_launch(ising_lattice* h, uint64_t t, int32_t n) {
     DrawnLaunch& a = h->drawn;
     const size_t sweep_words = (size_t)h->g.N * (size_t)h->g.L;
@@ -398,10 +400,16 @@ static int drawn_launch(ising_lattice* h, uint64_t t, int32_t n) {
     a.n_draw = n;
     a.drawn = next;
     const hipError_t e = a.n_apply > 0 || n > 0 ? launch_drawn(a, h->stream) : hipSuccess;
-    a.n_apply = e == hipSuccess ? n : 0;
+    if (e != hipSuccess) {
+        h->t = a.n_apply > 0 ? h->drawn_t : t;
+        a.n_apply = 0;
+        return hip_fail(e, "launch_drawn");
+    }
+    a.n_apply = n;
     a.codes = next;
+    h->drawn_t = t;
     h->drawn_buf ^= 1;
-    return e == hipSuccess ? ISING_OK : hip_fail(e, "launch_drawn");
+    return ISING_OK;
 }
 
 // Enqueue n sweeps by drawn codes.  The last of them are left pending: the
@@ -499,7 +507,6 @@ int ising_scan(ising_lattice* h, int32_t n_T, const double* T, int64_t therm, in
             if (rc == ISING_OK) rc = sweep_impl(h, T[j0 + i], meas, every, nullptr, nullptr, h->d_scan + i, true);
             if (rc == ISING_OK && i + 1 == nb && h->drawn_sweeps > 0) rc = drawn_launch(h, 0, 0);
             if (rc != ISING_OK) {
-                h->drawn.n_apply = 0;
                 (void)hipStreamSynchronize(h->stream);
                 return rc;
             }

@@ -260,6 +260,17 @@ int resident_captures(int, int n) { return captures += n; }
 hipError_t launch_samples(const Partial*, int32_t, int32_t, int32_t, int64_t*, int64_t*, Moments*, hipStream_t) {
     return hipSuccess;
 }
+// The codes' first and last word hold the sweep index; a lattice's first word counts its sweeps, which have to come in order.
+hipError_t launch_drawn(const DrawnLaunch& a, hipStream_t) {
+    return launch([=] {
+        const int64_t NL = (int64_t)a.N * a.L;
+        for (int32_t j = 0; j < a.n_apply; ++j) {
+            if (a.codes[j * NL] != *a.W || a.codes[(j + 1) * NL - 1] != *a.W) wrong = true;
+            *a.W += 1;
+        }
+        for (int32_t j = 0; j < a.n_draw; ++j) a.drawn[j * NL] = a.drawn[(j + 1) * NL - 1] = a.t_draw + j;
+    });
+}
 size_t finalize_scratch_bytes() { return 4096; }
 int64_t observe_single_waves(const Geometry&) { return 16; }
 int64_t halfsweep_single_waves(const Geometry&, int, int) { return 16; }
@@ -374,6 +385,27 @@ int main(int argc, char** argv) {
         std::printf("captures %d\n", captures);
         serve(s, {{2, 1024, 100}});
         ising_server_destroy(s);
+    } else if (what == "drawn") {
+        // num[0] 0: a scan, 1: a plain run, whose num[1]-th launch fails; then the rest, and a scan once more
+        ising_lattice* h = nullptr;
+        if (ising_create(64, 1, ISING_HOT, nullptr, &h) != ISING_OK) return 1;
+        void* W = nullptr;
+        size_t bytes = 0;
+        (void)ising_words(h, &W, &bytes);
+        run_all();
+        uint64_t& applied = *static_cast<uint64_t*>(W);
+        applied = 0;
+        const double T[3] = {1.5, 2.0, 2.5};
+        ising_moments m[3];
+        uint64_t t = 0;
+        for (int call = 0; call < 3; ++call) {
+            fail_launch = call == 1 ? (int)num[1] : 0;
+            const int rc = num[0] == 0 || call == 2 ? ising_scan(h, 3, T, 300, 20, 1, m) : ising_sweep(h, 2.0, 900);
+            run_all();
+            (void)ising_get_sweep_count(h, &t);
+            std::printf("%s t %s\n", rc == ISING_OK ? "ok" : "failed", t == applied ? "right" : "WRONG");
+        }
+        ising_destroy(h);
     }
     std::printf("rewritten %d wrong %d\n", rewritten, wrong);
     return 0;

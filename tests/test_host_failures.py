@@ -68,3 +68,12 @@ def test_server_keeps_off_tiles_while_captured_ones_may_be_replayed(stub):
                                    "again 0 persist 1 halfsweeps 200", "rewritten 0 wrong 0"]
     assert stub("captured", 1) == ["captures 1", "right 1", "again 0 persist 1 halfsweeps 0", "captures 0", "right 2",
                                    "again 0 persist 2 halfsweeps 0", "rewritten 0 wrong 0"]
+
+
+@pytest.mark.parametrize("plain", [0, 1])
+def test_drawn_sweeps_that_fail_leave_the_counter_with_the_state(stub, plain):
+    """A launch of drawn sweeps that fails: the sweep counter names the first sweep that the state lacks, and the
+    calls after it go on from there."""
+    for n in range(1, 5 if plain else 8):
+        assert stub("drawn", plain, n) == ["ok t right", "failed t right", "ok t right", "rewritten 0 wrong 0"], n
+    assert stub("drawn", plain, 0) == ["ok t right"] * 3 + ["rewritten 0 wrong 0"]
