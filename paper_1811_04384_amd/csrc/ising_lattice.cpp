@@ -27,9 +27,7 @@ struct ising_lattice {
     int64_t partial_cap = 0;
     int64_t* d_EM = nullptr;  // device scratch: E, M of ising_observables
     void* d_fin = nullptr;    // device scratch of the partial-sum reduction
-    uint32_t* strip_pos = nullptr;    // drawn picks of the strip dynamics (allocated on first use)
-    uint64_t* strip_codes = nullptr;  // their acceptance codes
-    char* strip_lists = nullptr;      // two sets of pick lists (allocated on first use)
+    char* strip_picks = nullptr;      // drawn picks of the strip dynamics (allocated on first use)
     uint8_t* d_stage = nullptr;       // spin input/output staging, spin_stage_bytes(L)
     Moments* d_scan = nullptr;        // moment sums of up to kScanBlock temperatures of a scan
     // multi-sweep LDS tiles (tile_k = 0: one launch per half-sweep)
@@ -149,9 +147,7 @@ static void release(ising_lattice* h) {
     if (h->partials) (void)hipFree(h->partials);
     if (h->d_EM) (void)hipFree(h->d_EM);
     if (h->d_fin) (void)hipFree(h->d_fin);
-    if (h->strip_pos) (void)hipFree(h->strip_pos);
-    if (h->strip_codes) (void)hipFree(h->strip_codes);
-    if (h->strip_lists) (void)hipFree(h->strip_lists);
+    if (h->strip_picks) (void)hipFree(h->strip_picks);
     if (h->d_stage) (void)hipFree(h->d_stage);
     if (h->d_scan) (void)hipFree(h->d_scan);
     if (h->d_tiles) (void)hipFree(h->d_tiles);
@@ -525,22 +521,30 @@ constexpr int64_t kStripPickLimit = int64_t(1) << 22;
 // which that path is used.
 constexpr int64_t kStripBufEntries = int64_t(1) << 22;
 constexpr size_t kStripChainLdsMax = 16 * 1024;
+constexpr size_t kStripBytes = (sizeof(uint64_t) + sizeof(uint32_t)) * kStripBufEntries;
 
-// Picks and words' first entries of one set of lists (10 and 2 bytes each): every
-// strip shape of at most 512 words per phase has at most 2.76 million words.
-constexpr int64_t kStripListEntries = int64_t(1) << 21;
+// The two sets of lists share that buffer (a call uses one form).  Words' first
+// entries and picks of a set (2 and 10 bytes each): every strip shape of at most
+// 512 words per phase has at most 2.76 million words, which leaves 1.9 million picks.
+constexpr size_t kStripListBytes = kStripBytes / 2;
 constexpr int64_t kStripListFirst = 2816 * 1024;
-constexpr size_t kStripListBytes = (size_t)(10 * kStripListEntries + 2 * kStripListFirst);
+constexpr int64_t kStripListEntries = (int64_t)(kStripListBytes - 2 * kStripListFirst) / 20 * 2;
+
+// The buffer of the drawn picks, made when first needed; false where the device has
+// no room for it (then k_strip_phase, which draws for itself, runs every shape).
+static bool strip_buffer(ising_lattice* h) {
+    if (h->strip_picks) return true;
+    if (allow_strip_list_lds() == hipSuccess && hipMalloc(&h->strip_picks, kStripBytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    h->strip_picks = nullptr;
+    return false;
+}
 
 // Iterations by lists of picks: phase args(t, ph); observe(k) after iteration k.
 // A launch draws the next chunk of picks beside the one that it applies.
 extern "C++" {
 template <class Args, class Observe>
 static int strip_list_iterations(ising_lattice* h, int64_t n, const Args& args, const Observe& observe) {
-    if (!h->strip_lists) {
-        ISING_HIP(allow_strip_list_lds());
-        ISING_HIP(hipMalloc(&h->strip_lists, 2 * kStripListBytes));
-    }
     StripArgs a = {};
     StripLists l = {};  // drawn and not yet applied
     int64_t sample = 0;  // the iteration that ends with it (0: none does)
@@ -553,7 +557,7 @@ static int strip_list_iterations(ising_lattice* h, int64_t n, const Args& args, 
             const uint32_t chunks = (b.picks + most - 1) / most;
             most = ((b.picks + chunks - 1) / chunks + 1) & ~1u;
             for (uint32_t k0 = 0; k0 < b.picks; k0 += most) {
-                char* const at = h->strip_lists + (size_t)set * kStripListBytes;
+                char* const at = h->strip_picks + (size_t)set * kStripListBytes;
                 StripLists lb;
                 lb.codes = reinterpret_cast<uint64_t*>(at);
                 lb.k = reinterpret_cast<uint16_t*>(at + 8 * kStripListEntries);
@@ -578,24 +582,18 @@ static int strip_list_iterations(ising_lattice* h, int64_t n, const Args& args, 
 }  // extern "C++"
 
 static int strip_phase(ising_lattice* h, const StripArgs& a) {
-    if (strip_chain_lds_bytes(a) > kStripChainLdsMax || strip_apply_lds_bytes(a, 1) > kStripLdsBytes) {
+    if (strip_chain_lds_bytes(a) > kStripChainLdsMax || strip_apply_lds_bytes(a, 1) > kStripLdsBytes ||
+        !strip_buffer(h)) {
         ISING_HIP(launch_strip_phase(h->W, a, h->stream));
         return ISING_OK;
     }
-    if (!h->strip_pos) {
-        ISING_HIP(hipMalloc(&h->strip_pos, sizeof(uint32_t) * kStripBufEntries));
-        hipError_t e = hipMalloc(&h->strip_codes, sizeof(uint64_t) * kStripBufEntries);
-        if (e != hipSuccess) {
-            (void)hipFree(h->strip_pos);
-            h->strip_pos = nullptr;
-            return hip_fail(e, "hipMalloc");
-        }
-    }
+    uint64_t* const codes = reinterpret_cast<uint64_t*>(h->strip_picks);
+    uint32_t* const pos = reinterpret_cast<uint32_t*>(codes + kStripBufEntries);
     const uint32_t chunk = (uint32_t)std::max<int64_t>(1, kStripBufEntries / a.strips);
     for (uint32_t k0 = 0; k0 < a.picks; k0 += chunk) {
         const uint32_t n_k = std::min(chunk, a.picks - k0);
-        ISING_HIP(launch_strip_draws(a, k0, n_k, h->strip_pos, h->strip_codes, h->stream));
-        ISING_HIP(launch_strip_apply(h->W, a, n_k, h->strip_pos, h->strip_codes, h->stream));
+        ISING_HIP(launch_strip_draws(a, k0, n_k, pos, codes, h->stream));
+        ISING_HIP(launch_strip_apply(h->W, a, n_k, pos, codes, h->stream));
     }
     return ISING_OK;
 }
@@ -650,7 +648,7 @@ int ising_random_iterations(ising_lattice* h, double T, int32_t strip_cols, int6
     };
     // the right half of a strip is at least as wide as the left one
     if (n_iterations > 0 && strip_list_picks(phase(1, 1), kStripListEntries) > 0 &&
-        (int64_t)a.strips * ((int64_t)N * a.width + 1) <= kStripListFirst) {
+        (int64_t)a.strips * ((int64_t)N * a.width + 1) <= kStripListFirst && strip_buffer(h)) {
         const int rc = strip_list_iterations(h, n_iterations, phase, observe);
         if (rc != ISING_OK) return rc;
     } else {

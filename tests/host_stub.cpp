@@ -271,6 +271,46 @@ hipError_t launch_drawn(const DrawnLaunch& a, hipStream_t) {
         for (int32_t j = 0; j < a.n_draw; ++j) a.drawn[j * NL] = a.drawn[(j + 1) * NL - 1] = a.t_draw + j;
     });
 }
+// The strip dynamics: only that a phase's picks are all drawn, in order, and what is drawn lies within the buffers.
+static uint64_t strip_picks_done = 0;
+hipError_t launch_strip_phase(uint64_t*, const StripArgs& a, hipStream_t) {
+    ++n_strip_phase;
+    strip_picks_done += a.picks;
+    return hipSuccess;
+}
+size_t strip_chain_lds_bytes(const StripArgs& a) { return (size_t)(a.width + 2) * (size_t)a.N * 8; }
+size_t strip_apply_lds_bytes(const StripArgs&, int) { return 1024; }
+hipError_t launch_strip_draws(const StripArgs& a, uint32_t, uint32_t n_k, uint32_t* pos, uint64_t* codes, hipStream_t) {
+    ++n_strip_draws;
+    const size_t n = (size_t)n_k * (size_t)a.strips;
+    return launch([=] { pos[0] = pos[n - 1] = 7, codes[0] = codes[n - 1] = 7; });
+}
+hipError_t launch_strip_apply(uint64_t*, const StripArgs& a, uint32_t n_k, const uint32_t* pos, const uint64_t* codes, hipStream_t) {
+    strip_picks_done += n_k;
+    const size_t n = (size_t)n_k * (size_t)a.strips;
+    return launch([=] {
+        if (pos[0] != 7 || pos[n - 1] != 7 || codes[0] != 7 || codes[n - 1] != 7) wrong = true;
+    });
+}
+uint32_t strip_list_picks(const StripArgs& a, int64_t max_entries) {
+    return (int64_t)a.N * a.width > 512 ? 0u : (uint32_t)std::min<int64_t>(max_entries / a.strips, a.picks) & ~1u;
+}
+hipError_t allow_strip_list_lds() { return hipSuccess; }
+hipError_t launch_strip_lists(uint64_t*, const StripArgs& a, const StripLists& l, const StripArgs& n, const StripLists& ln, hipStream_t) {
+    ++n_strip_lists;
+    strip_picks_done += l.n_k;
+    return launch([=] {
+        auto mark = [](const StripArgs& p, const StripLists& x, bool set) {
+            const size_t e = (size_t)p.strips * x.n_k, f = (size_t)p.strips * (size_t)(p.N * p.width + 1);
+            if (set) x.codes[0] = x.codes[e - 1] = x.k0 + 1, x.k[0] = x.k[e - 1] = 3, x.first[0] = x.first[f - 1] = 5;
+            else if (x.codes[0] != x.k0 + 1 || x.codes[e - 1] != x.k0 + 1 || x.k[0] != 3 || x.k[e - 1] != 3 || x.first[0] != 5 ||
+                     x.first[f - 1] != 5)
+                wrong = true;
+        };
+        if (ln.n_k) mark(n, ln, true);
+        if (l.n_k) mark(a, l, false);
+    });
+}
 size_t finalize_scratch_bytes() { return 4096; }
 int64_t observe_single_waves(const Geometry&) { return 16; }
 int64_t halfsweep_single_waves(const Geometry&, int, int) { return 16; }
@@ -405,6 +445,22 @@ int main(int argc, char** argv) {
             (void)ising_get_sweep_count(h, &t);
             std::printf("%s t %s\n", rc == ISING_OK ? "ok" : "failed", t == applied ? "right" : "WRONG");
         }
+        ising_destroy(h);
+    } else if (what == "strips") {
+        // strips of num[1], then of num[2] columns of L = num[0]; allocations of more than num[3] bytes fail
+        ising_lattice* h = nullptr;
+        if (ising_create((int32_t)num[0], 1, ISING_HOT, nullptr, &h) != ISING_OK) return 1;
+        fail_above = (size_t)num[3];
+        const int before = allocations;
+        const uint64_t N = (uint64_t)ising_word_rows((int32_t)num[0]);
+        for (int call = 0; call < 4; ++call) {
+            const uint64_t cols = (uint64_t)num[1 + call % 2], want = ising::strip_picks_done + 3 * 10 * N * cols;
+            const int rc = ising_random_iterations(h, 2.0, (int32_t)cols, 3, 0, nullptr, nullptr, nullptr);
+            run_all();
+            if (rc != ISING_OK || ising::strip_picks_done != want) std::printf("error %d: %s\n", rc, ising_last_error());
+        }
+        std::printf("allocations %d phase %d draws %d lists %d\n", allocations - before, n_strip_phase > 0,
+                    n_strip_draws > 0, n_strip_lists > 0);
         ising_destroy(h);
     }
     std::printf("rewritten %d wrong %d\n", rewritten, wrong);

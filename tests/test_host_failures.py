@@ -77,3 +77,18 @@ def test_drawn_sweeps_that_fail_leave_the_counter_with_the_state(stub, plain):
     for n in range(1, 5 if plain else 8):
         assert stub("drawn", plain, n) == ["ok t right", "failed t right", "ok t right", "rewritten 0 wrong 0"], n
     assert stub("drawn", plain, 0) == ["ok t right"] * 3 + ["rewritten 0 wrong 0"]
+
+
+# L, strip columns of two kinds in turn: few words per phase (lists), more (windows), or too many for either
+@pytest.mark.parametrize("L,a,b,forms", [
+    (84, 2, 12, (0, 0, 1)), (1008, 2, 36, (0, 1, 1)), (1008, 36, 2, (0, 1, 1)), (4200, 2, 4, (0, 0, 1)),
+    (10752, 2, 2, (0, 0, 1)), (1008, 504, 2, (1, 0, 1)),
+])
+def test_strip_dynamics_with_little_memory_left(stub, L, a, b, forms):
+    """Both forms that draw picks ahead use one buffer (48 MiB, allocated once, within which all they draw lies); and
+    where the device has no room for it the form that needs none runs every shape."""
+    names = ("phase", "draws", "lists")
+    got = stub("strips", L, a, b, 1 << 30)
+    assert got == ["allocations 1 " + " ".join(f"{n} {f}" for n, f in zip(names, forms)), "rewritten 0 wrong 0"]
+    assert stub("strips", L, a, b, 48 << 20) == got
+    assert stub("strips", L, a, b, (48 << 20) - 1) == ["allocations 0 phase 1 draws 0 lists 0", "rewritten 0 wrong 0"]
