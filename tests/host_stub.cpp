@@ -462,6 +462,15 @@ int main(int argc, char** argv) {
         std::printf("allocations %d phase %d draws %d lists %d\n", allocations - before, n_strip_phase > 0,
                     n_strip_draws > 0, n_strip_lists > 0);
         ising_destroy(h);
+    } else if (what == "samples") {
+        int bad = 0;
+        for (int64_t every : {1, 2, 3, 7, 255, 256, 257, 1000, 2147483391, 2147483646, 2147483647})
+            for (int64_t back = 0; back < 600; ++back)
+                for (int64_t n : {1, 2, 7, 255, 256, 4096}) {
+                    const int64_t off = (every - 1 - back % every);
+                    bad += samples_in((int32_t)off, (int32_t)n, (int32_t)every) != (off + n) / every - off / every;
+                }
+        std::printf("bad %d none %d\n", bad, samples_in(5, 100, 0));
     }
     std::printf("rewritten %d wrong %d\n", rewritten, wrong);
     return 0;

@@ -92,3 +92,8 @@ def test_strip_dynamics_with_little_memory_left(stub, L, a, b, forms):
     assert got == ["allocations 1 " + " ".join(f"{n} {f}" for n, f in zip(names, forms)), "rewritten 0 wrong 0"]
     assert stub("strips", L, a, b, 48 << 20) == got
     assert stub("strips", L, a, b, (48 << 20) - 1) == ["allocations 0 phase 1 draws 0 lists 0", "rewritten 0 wrong 0"]
+
+
+def test_samples_of_a_launch_at_any_interval(stub):
+    """A sampling interval near 2^31 sweeps, and launches just before and over its end."""
+    assert stub("samples") == ["bad 0 none 0", "rewritten 0 wrong 0"]
