@@ -332,12 +332,14 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
     // `want`.  Bounded twice, by the clock (a failed poll counts for at least
     // 100 ns) and by the number of polls; when a bound is reached, or another
     // tile has set the error word, the launch is abandoned after this
-    // half-sweep.  In small bands (kOne), whose half-sweep waits for these words
+    // half-sweep, whose number `stop` holds: a wavefront that is already in the
+    // next one when another reads it puts that one's number there, and all of them
+    // leave after the same half-sweep.  In small bands (kOne), whose half-sweep waits for these words
     // alone, two more reads follow the first at 0.1 us distance, so that a word
     // that just missed one is not seen a whole round trip later (us per
     // half-sweep with one read at a time / three: L = 300 1.31 / 1.16, 1008 1.34 /
     // 1.29; wider bands gain nothing, L = 4096 3.74 / 3.80).
-    auto ghost = [&](const uint64_t* p, uint64_t v, uint64_t want) -> uint64_t {
+    auto ghost = [&](const uint64_t* p, uint64_t v, uint64_t want, int hs) -> uint64_t {
         if constexpr (split) {
             __builtin_amdgcn_s_sleep(4);  // 256 cycles
             uint64_t v1 = fetch(p);
@@ -355,7 +357,7 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
                     v2 = fetch(p);
                     if (err != 0u || clock_ticks() - start > a.wait_ticks || polls > kMaxPolls) {
                         __hip_atomic_store(a.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        stop = 1;
+                        stop = hs + 1;
                         break;
                     }
                     err = __hip_atomic_load(a.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -367,7 +369,7 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
                 if (__hip_atomic_load(a.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
                     clock_ticks() - start > a.wait_ticks || polls > kMaxPolls) {
                     __hip_atomic_store(a.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    stop = 1;
+                    stop = hs + 1;
                     break;
                 }
                 v = fetch(p);
@@ -414,7 +416,7 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
         // valid: whether the thread has this item.
         auto poll = [&](const WordItem& it) {
             const uint64_t* p = ghost_at(it, 1 - c);
-            return ghost(p, fetch(p), want);
+            return ghost(p, fetch(p), want, hs);
         };
         auto word = [&](const WordItem& it, bool valid, bool edge, auto ghost_of, auto early, auto between, auto update) {
             Nbhd nb;
@@ -484,7 +486,7 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
                 u5next[(size_t)k * N + I] = block5(sw_next, rk, I, g_lo + k, c ^ 1);
             }
         }
-        if (fetch0) ghost0 = ghost(ghost_at(oth0, c), ghost0, tag);
+        if (fetch0) ghost0 = ghost(ghost_at(oth0, c), ghost0, tag, hs);
         if (meas) {
             if (pre) {
                 // at most two words per thread: a wavefront's antiparallel
@@ -515,7 +517,7 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
             next_sample += a.every;
             ++n_taken;
         }
-        return stop != 0;
+        return stop == hs + 1;
     };
     if (pre) {
         // two half-sweeps per trip, so that the items of each colour stay in
