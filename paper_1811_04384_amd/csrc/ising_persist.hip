@@ -550,11 +550,15 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
 }  // namespace
 
 // ITEMS: how the tiles of the launch hold their items, WHOLE: whether they are whole
-// lattices (kAny: the lattices of the launch differ, and each tile chooses).  A kernel of each form by itself has the
-// registers it needs and no others' (us per sweep, all of them in one kernel / each
-// alone: L = 300 2.33 / 2.25, 512 2.41 / 2.32, 1024 2.64 / 2.53, 2048 3.48 / 3.38, 3072
-// 5.60 / 5.42, 4096 7.66 / 7.58, 5120 14.5 / 14.8; 16 lattices of L = 512 in bands of 64
-// columns, 300 sampled sweeps 1830 / 1800).
+// lattices (kAny: the lattices of the launch differ, and each tile chooses).  A kernel
+// of each form by itself has the registers it needs and no others' (us per sweep,
+// all of them in one kernel / each alone: L = 300 2.33 / 2.25, 512 2.41 / 2.32, 1024
+// 2.64 / 2.53, 2048 3.48 / 3.38, 3072 5.60 / 5.42, 4096 7.66 / 7.58; 16 lattices of L =
+// 512 in bands of 64 columns, 300 sampled sweeps 1830 / 1800; 256 whole lattices of L
+// = 256 by 1024 threads 7.76 / 7.58).  Bands whose items are formed in every half-sweep
+// have none of their own: with it they are the slower ones (L = 4610 13.3 / 13.8, 5120
+// 14.4 / 14.9, 6144 19.5 / 20.2, 7680 31.3 / 31.9; 16 of L = 1008 in bands of 64 columns
+// by 512 threads 10.6 / 10.9).
 template <int ITEMS, bool WHOLE>
 __global__ void __launch_bounds__(kPersistMaxBlock) k_persist(PersistLaunch a) {
     extern __shared__ uint64_t lds[];
@@ -591,7 +595,6 @@ PersistKernel persist_kernel(int form) {
     switch (form) {
         case kOne: return &k_persist<kOne, false>;
         case kTwo: return &k_persist<kTwo, false>;
-        case kFormed: return &k_persist<kFormed, false>;
         case kOne + kWhole: return &k_persist<kOne, true>;
         case kTwo + kWhole: return &k_persist<kTwo, true>;
         case kFormed + kWhole: return &k_persist<kFormed, true>;
