@@ -302,7 +302,12 @@ int ising_get_tiling(ising_lattice* h, int32_t* sweeps_per_launch, int32_t* tile
    shape (or ising_set_tiling), lattices with at most 2048 words of a colour
    (L <= 292) run in one workgroup with their draws spread over the chip
    instead, a launch drawing the next sweeps beside the workgroup that applies
-   the last ones; these launches wait for nothing. */
+   the last ones; these launches wait for nothing, and are faster than tiles of
+   any shape.  ising_get_resident_tiles then gives the shape that tiles would
+   have; setting a shape, this one too, runs tiles for the rest of the handle's
+   life.  Such a handle holds two buffers of acceptance codes from its creation
+   on: 256 sweeps of its words each, at most 4 MiB (L = 64 0.5 MiB, 128 2, from
+   204 on 4). */
 int ising_set_resident_tiles(ising_lattice* h, int32_t tile_cols, int32_t block, int32_t max_sweeps);
 /* Bound of every wait of the resident-tile launches for their neighbour
    tiles, in ticks of the GPU's 100 MHz constant clock; 0 restores the
