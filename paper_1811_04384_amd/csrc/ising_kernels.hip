@@ -137,7 +137,7 @@ __device__ __forceinline__ void update_lattice_row(uint64_t* __restrict__ W, con
 template <int WPT, bool MEASURE>
 __global__ void __launch_bounds__(kTiledMaxBlock)
     k_halfsweep_single(uint64_t* __restrict__ W, SweepArgs a, int colour, int band, Partial* __restrict__ partials) {
-    __shared__ uint32_t table[(kTiledMaxBlock / 64) * row_table_words<WPT>()];
+    __shared__ __align__(16) uint32_t table[(kTiledMaxBlock / 64) * row_table_words<WPT>()];
     // one word row per workgroup: the row, its wrap cases, live slots and
     // counter base are wave-uniform (scalar unit)
     const RowBlock b = row_block(band);
@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(kTiledMaxBlock)
                       const WaveItem* __restrict__ waves, uint32_t n_waves, uint32_t group, int colour,
                       uint32_t sweep_off, Partial* __restrict__ partials, const Partial* __restrict__ fin_partials,
                       uint32_t fin_off) {
-    __shared__ uint32_t table[(kTiledMaxBlock / 64) * row_table_words<WPT>()];
+    __shared__ __align__(16) uint32_t table[(kTiledMaxBlock / 64) * row_table_words<WPT>()];
     // groups of consecutive workgroups of the table to one XCD (see launch)
     uint32_t b = blockIdx.x;
     if (b < gridDim.x / (8 * group) * (8 * group)) {

@@ -80,7 +80,7 @@ struct ReplicaRule {
 template <int WPT>
 __global__ void __launch_bounds__(kHalfSweepBlock) k_replica_halfsweep(uint64_t* __restrict__ W, ReplicaArgs a, int colour,
                                                                       int band) {
-    __shared__ uint32_t table[(kHalfSweepBlock / 64) * row_table_words<WPT>()];
+    __shared__ __align__(16) uint32_t table[(kHalfSweepBlock / 64) * row_table_words<WPT>()];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const RowBlock b = row_block(band);
     const int row = b.row;

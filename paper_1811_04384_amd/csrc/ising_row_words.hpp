@@ -46,7 +46,8 @@ __device__ __forceinline__ RowBlock row_block(int band) {
     return {(int)blockIdx.y, (int)blockIdx.x};
 }
 
-// Words of the position-20 table of one wavefront.
+// Words of the position-20 table of one wavefront (the kernel's tables start at a
+// multiple of 16 bytes: a block is stored whole).
 template <int WPT>
 constexpr int row_table_words() {
     return 64 * WPT;
