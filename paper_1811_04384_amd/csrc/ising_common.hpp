@@ -94,17 +94,20 @@ struct Moments {
     uint64_t sum_M4[3];    // sum of M^4 (192 bits)
 };
 
-// Per-lattice state of a batch, written only by kernels (the host reads it
-// back and zeroes it at creation).
+// Per-lattice state of a batch or of a server's slot, written only by kernels (the
+// host reads it back and zeroes it at creation and admission).  128 bytes: with 136,
+// which straddle cache lines, 20 sweeps of 256 mixed lattices took 1 % longer.
 struct LatticeState {
     uint64_t t;               // absolute index of the next sweep
-    int64_t series_idx;       // next sample slot of the current call
+    union {
+        int64_t series_idx;   // next sample slot of the current call
+        uint32_t abandoned;   // of a server, which takes no samples: a resident-tile launch gave up on this lattice
+    };
     Moments mom;              // sums over the samples since the last reset
     int64_t last_E, last_M;   // most recent sample or observation
     unsigned long long obs_anti, obs_ups;  // sums of an observation's workgroups (zero between observations)
-    uint32_t abandoned;       // a resident-tile launch of a server gave up on this lattice (until its slot is admitted to again)
-    uint32_t pad_;
 };
+static_assert(sizeof(LatticeState) == 128, "one lattice's state fills cache lines of its own");
 
 // One wavefront of a tiled half-sweep launch: up to 64 words_per_thread
 // consecutive words of a colour of one word row of one lattice, so the
