@@ -28,12 +28,6 @@ inline Geometry make_geometry(int32_t L) {
     return g;
 }
 
-// Samples of the sweeps off .. off + n - 1 (n < 2^31) of a run that takes one after
-// every every-th sweep: off may be anything below every = 2^31 - 1.
-constexpr int32_t samples_in(int32_t off, int32_t n, int32_t every) {
-    return every > 0 ? (int32_t)(((uint32_t)off + (uint32_t)n) / (uint32_t)every - (uint32_t)off / (uint32_t)every) : 0;
-}
-
 // Everything a half-sweep of one lattice needs; wave-uniform.
 struct SweepArgs {
     int32_t L, N, istar, sh_star;

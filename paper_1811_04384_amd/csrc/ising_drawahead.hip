@@ -200,7 +200,7 @@ __device__ __forceinline__ int apply_sweeps(const ApplyTask& a, uint64_t* __rest
     const int NL = N * L, half = L >> 1, words = N * half;  // words of one colour
     const int tid = threadIdx.x, B = blockDim.x;
     const int n = a.n, every = a.every, pstar = (L - 1) / N;
-    const int n_samples = samples_in(a.sweep_off, n, every);
+    const int n_samples = every > 0 ? (a.sweep_off + n) / every - a.sweep_off / every : 0;
     for (int i = tid; i < NL; i += B) T[i] = a.W[i];
     for (int i = tid; i < 2 * n_samples; i += B) stage[i] = 0u;
     Slot slot[WMAX];

@@ -418,8 +418,7 @@ static int enqueue_drawn_sweeps(ising_lattice* h, uint64_t t0, double T, int64_t
         thresholds_of(T, &a.t4, &a.t8);
         const int rc = drawn_launch(h, t0 + (uint64_t)done, kb);
         if (rc != ISING_OK) return rc;
-        a.every = every;
-        a.sweep_off = every > 0 ? (int32_t)(done % every) : 0;
+        sampled_as(a, done, kb, every);
         a.series_E = dev_E ? dev_E + done / every : nullptr;
         a.series_M = dev_M ? dev_M + done / every : nullptr;
         a.mom = mom;

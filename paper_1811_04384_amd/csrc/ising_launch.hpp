@@ -276,12 +276,24 @@ struct DrawnLaunch {
     uint32_t t4, t8;        // of the sweeps drawn
     int32_t n_draw, n_apply;
     // a sample after the applied sweep j when (sweep_off + j + 1) % every == 0
-    // (every > 0); each output may be null
+    // (every > 0; sampled_as); each output may be null
     int32_t sweep_off, every;
     int64_t* series_E;
     int64_t* series_M;
     Moments* mom;
 };
+// sweep_off and every of a launch of n sweeps, `done` sweeps after the start of a
+// run sampled after every every-th: as they are, or, where the launch holds a
+// sample at most, smaller ones that say the same, so that their sum with n, which
+// the kernel divides, does not overflow at intervals near 2^31.
+inline void sampled_as(DrawnLaunch& a, int64_t done, int32_t n, int32_t every) {
+    a.every = every;
+    a.sweep_off = every > 0 ? (int32_t)(done % every) : 0;
+    if (every <= 2 * kDrawnMaxSweeps) return;
+    const int32_t left = every - a.sweep_off;  // sweeps to the next sample
+    a.every = left <= n ? 2 * kDrawnMaxSweeps : 0;
+    a.sweep_off = left <= n ? a.every - left : 0;
+}
 int32_t drawn_max_words();  // most words of a colour of such a lattice
 hipError_t launch_drawn(const DrawnLaunch& a, hipStream_t s);
 // LDS of such a launch, to be compared with resident_lds_limit.

@@ -463,14 +463,25 @@ int main(int argc, char** argv) {
                     n_strip_draws > 0, n_strip_lists > 0);
         ising_destroy(h);
     } else if (what == "samples") {
+        // the sweeps of a launch that are sampled, from what the kernel is given and from the run
         int bad = 0;
-        for (int64_t every : {1, 2, 3, 7, 255, 256, 257, 1000, 2147483391, 2147483646, 2147483647})
+        for (int64_t every : {1, 2, 3, 7, 255, 256, 257, 511, 512, 513, 1000, 2147483391, 2147483646, 2147483647})
             for (int64_t back = 0; back < 600; ++back)
-                for (int64_t n : {1, 2, 7, 255, 256, 4096}) {
-                    const int64_t off = (every - 1 - back % every);
-                    bad += samples_in((int32_t)off, (int32_t)n, (int32_t)every) != (off + n) / every - off / every;
+                for (int32_t n : {1, 2, 7, 255, 256}) {
+                    const int64_t done = 5 * every + (every - 1 - back % every);
+                    DrawnLaunch a = {};
+                    sampled_as(a, done, n, (int32_t)every);
+                    int32_t count = 0;
+                    for (int32_t j = 0; j < n; ++j) {
+                        const bool sampled = a.every > 0 && (a.sweep_off + j + 1) % a.every == 0;
+                        bad += sampled != ((done + j + 1) % every == 0);
+                        count += sampled;
+                    }
+                    bad += count != (a.every > 0 ? (a.sweep_off + n) / a.every - a.sweep_off / a.every : 0);
                 }
-        std::printf("bad %d none %d\n", bad, samples_in(5, 100, 0));
+        DrawnLaunch none = {};
+        sampled_as(none, 100, 5, 0);
+        std::printf("bad %d none %d %d\n", bad, none.every, none.sweep_off);
     }
     std::printf("rewritten %d wrong %d\n", rewritten, wrong);
     return 0;

@@ -96,4 +96,4 @@ def test_strip_dynamics_with_little_memory_left(stub, L, a, b, forms):
 
 def test_samples_of_a_launch_at_any_interval(stub):
     """A sampling interval near 2^31 sweeps, and launches just before and over its end."""
-    assert stub("samples") == ["bad 0 none 0", "rewritten 0 wrong 0"]
+    assert stub("samples") == ["bad 0 none 0 0", "rewritten 0 wrong 0"]
