@@ -14,7 +14,7 @@ namespace ising {
 // Tiled work of one colour of a lattice: segments of 2*wpt columns per row.
 inline int32_t segments_per_row(int32_t L, int32_t wpt) { return (L + 2 * wpt - 1) / (2 * wpt); }
 // Launch shape of one lattice's half-sweeps by its words of a colour (us per
-// half-sweep on gfx950).  From 3 Mi words (L from about 11,200) four words per
+// half-sweep on gfx950).  From 3 Mi words (L from about 11,500) four words per
 // thread, whose position-20 blocks are shared best: L = 12288 30.7 against
 // 32.4 with one, 16384 49.4 / 52.0, 32768 190 / 201.  From 1 Mi words one
 // word per thread in 256-thread workgroups (L = 8000 17.1, 9998 23.8; the
