@@ -34,6 +34,24 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
+// Order a wavefront's LDS stores before its loads behind them, without a barrier:
+// the hardware completes them in issue order; this keeps the compiler from moving
+// them.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// LDS seen as what it is (address space 3), so that 32-bit LDS addresses can be kept
+// in registers and loaded from with no base added.
+typedef __attribute__((address_space(3))) uint64_t lds_u64;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __forceinline__ uint32_t lds_addr(const lds_u64* p) { return (uint32_t)(size_t)p; }
+__device__ __forceinline__ uint64_t lds_load64(uint32_t addr) { return *(const lds_u64*)(size_t)addr; }
+__device__ __forceinline__ uint32_t lds_load32(uint32_t addr) { return *(const lds_u32*)(size_t)addr; }
+__device__ __forceinline__ void lds_store64(uint32_t addr, uint64_t v) { *(lds_u64*)(size_t)addr = v; }
+
 // A vector-register copy of a wave-uniform value.  On gfx950, simple 32-bit
 // vector instructions (add, xor, three-input bitwise) that read a scalar
 // register take about 4.4 cycles per wave64 instruction when they follow

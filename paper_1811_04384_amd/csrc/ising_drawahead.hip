@@ -33,15 +33,6 @@ namespace {
 constexpr int kDrawBlock = 256;
 constexpr int kApplyMaxBlock = 1024;
 
-// Order a lone wavefront's LDS stores of one half-sweep before the loads of
-// the next (the hardware completes them in issue order; this keeps the
-// compiler from moving them).
-__device__ __forceinline__ void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 }  // namespace
 
 // Draw pass: item f of lattice entry e (blockIdx.x div blocks_per_lat) is
@@ -114,12 +105,6 @@ __device__ __forceinline__ void load_codes(uint64_t (&cr)[2][WMAX], const uint64
         for (int k = 0; k < WMAX; ++k) cr[c][k] = __builtin_nontemporal_load(p + c * words + min(tid + stride * k, words - 1));
 }
 
-// LDS addressed by 32-bit byte addresses kept in registers
-typedef __attribute__((address_space(3))) uint64_t lds_u64;
-__device__ __forceinline__ uint32_t lds_addr(const uint64_t* p) { return (uint32_t)(size_t)(const lds_u64*)p; }
-__device__ __forceinline__ uint64_t lds_load(uint32_t addr) { return *(const lds_u64*)(size_t)addr; }
-__device__ __forceinline__ void lds_store(uint32_t addr, uint64_t v) { *(lds_u64*)(size_t)addr = v; }
-
 // A word slot of a thread, the same columns 2h and 2h + 1 of word row I in
 // both colours: own[c] is the LDS address of the word of colour c (and the
 // near neighbour of colour 1 - c), far[c] that of its other neighbour in the
@@ -135,10 +120,10 @@ struct Slot {
     uint64_t md, live;
 };
 
-__device__ __forceinline__ Slot make_slot(const uint64_t* T, int I, int h, int L, int N, int istar, int sh_star,
+__device__ __forceinline__ Slot make_slot(const lds_u64* T, int I, int h, int L, int N, int istar, int sh_star,
                                           int pstar) {
     Slot s;
-    const uint64_t* row = T + I * L;
+    const lds_u64* row = T + I * L;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         const int par = (I + c) & 1;
@@ -208,7 +193,7 @@ __device__ __forceinline__ int apply_sweeps(const ApplyTask& a, uint64_t* __rest
     for (int k = 0; k < WMAX; ++k) {
         const int f = min(tid + B * k, words - 1);
         const int I = f / half;
-        slot[k] = make_slot(T, I, f - I * half, L, N, a.istar, a.sh_star, pstar);
+        slot[k] = make_slot((const lds_u64*)T, I, f - I * half, L, N, a.istar, a.sh_star, pstar);
     }
     const int sh_up = 60 - a.sh_star;  // between the patch bits of rows L - 1 and 0
     uint64_t ring[P][2][WMAX];
@@ -220,12 +205,12 @@ __device__ __forceinline__ int apply_sweeps(const ApplyTask& a, uint64_t* __rest
 #pragma unroll
     for (int k = 0; k < WMAX; ++k)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) held[k][c] = lds_load(slot[k].own[c]);
+        for (int c = 0; c < 2; ++c) held[k][c] = lds_load64(slot[k].own[c]);
     __syncthreads();
     // sweeps left before the next sample, the LDS address of that sample, and
     // the thread's counts of the last one while they are not yet summed
     int until = every > 0 ? every - 1 - a.sweep_off % every : 0x7FFFFFFF;
-    uint32_t at = lds_addr(reinterpret_cast<uint64_t*>(stage));
+    uint32_t at = lds_addr((const lds_u64*)reinterpret_cast<uint64_t*>(stage));
     bool open = false;
     uint32_t counts = 0;
     auto close_sample = [&] {
@@ -254,12 +239,12 @@ __device__ __forceinline__ int apply_sweeps(const ApplyTask& a, uint64_t* __rest
 #pragma unroll
             for (int k = 0; k < WMAX; ++k) {
                 const Slot& s = slot[k];
-                w[k] = ONE_WAVE ? lds_load(s.own[c]) : held[k][c];
-                near[k] = ONE_WAVE ? lds_load(s.own[1 - c]) : held[k][1 - c];
-                far[k] = lds_load(s.far[c]);
-                up[k] = lds_load(s.up[c]);
-                dn[k] = lds_load(s.dn[c]);
-                pt[k] = lds_load(s.pt[c]);
+                w[k] = ONE_WAVE ? lds_load64(s.own[c]) : held[k][c];
+                near[k] = ONE_WAVE ? lds_load64(s.own[1 - c]) : held[k][1 - c];
+                far[k] = lds_load64(s.far[c]);
+                up[k] = lds_load64(s.up[c]);
+                dn[k] = lds_load64(s.dn[c]);
+                pt[k] = lds_load64(s.pt[c]);
             }
             if (c == 0 && open) close_sample();
             uint32_t anti = 0, ups = 0;
@@ -273,7 +258,7 @@ __device__ __forceinline__ int apply_sweeps(const ApplyTask& a, uint64_t* __rest
                 d = (d & ~s.md) | (pd & s.md);
                 const uint64_t nw = w[k] ^ flip_mask(w[k], u, d, near[k], far[k], cc[c][k], s.live);
                 if (!ONE_WAVE) held[k][c] = nw;
-                lds_store(s.own[c], nw);  // a slot past the last word holds and stores that word
+                lds_store64(s.own[c], nw);  // a slot past the last word holds and stores that word
                 // (near in the place of the left neighbour: the pair of
                 // columns holds one word of each colour)
                 if (c == 1 && meas && tid + B * k < words)

@@ -47,11 +47,7 @@ __global__ void __launch_bounds__(256) k_init(uint64_t* __restrict__ W, Geometry
     if (live & 1ull) {
         const U4 r = block((uint32_t)(w0 + 8 * (lane >> 1) + (lane & 1)), 5u);
         last[wv][lane] = make_uint4(r.x, r.y, r.z, r.w);
-        // one wavefront's LDS operations complete in order; this keeps the
-        // compiler from moving them
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_order();
     }
 #pragma unroll 1
     for (int k = 0; k < runs; ++k) {

@@ -69,15 +69,6 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 __device__ __forceinline__ uint64_t clock_ticks() { return __builtin_amdgcn_s_memrealtime(); }
 
-// LDS seen as what it is (address space 3), so that 32-bit LDS addresses
-// can be kept in registers and loaded from with no base added
-typedef __attribute__((address_space(3))) uint64_t lds_u64;
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-__device__ __forceinline__ uint32_t lds_addr(const lds_u64* p) { return (uint32_t)(size_t)p; }
-__device__ __forceinline__ uint64_t lds_load64(uint32_t addr) { return *(const lds_u64*)(size_t)addr; }
-__device__ __forceinline__ void lds_store64(uint32_t addr, uint64_t v) { *(lds_u64*)(size_t)addr = v; }
-__device__ __forceinline__ uint32_t lds_load32(uint32_t addr) { return *(const lds_u32*)(size_t)addr; }
-
 // One word item of a half-sweep: the LDS addresses of the word and of its
 // neighbourhood words, the byte offset of its position-20 uniform in the
 // table of the half-sweep, its Philox counter word I L + J, its row and its

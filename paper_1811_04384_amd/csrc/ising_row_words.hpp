@@ -91,11 +91,7 @@ __device__ __forceinline__ void update_row_words(const RowRun& r, int w0, uint32
                                         5u | r.c3, r.k0, r.k1, rk);
             *reinterpret_cast<uint4*>(table + 4 * lane) = make_uint4(b.x, b.y, b.z, b.w);
         }
-        // one wavefront's LDS operations complete in order; this keeps the
-        // compiler from moving them
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_order();
     }
 
 #pragma unroll 1

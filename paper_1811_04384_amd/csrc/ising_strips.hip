@@ -319,15 +319,6 @@ __global__ void __launch_bounds__(64) k_strip_apply(uint64_t* __restrict__ W, St
 constexpr int kListBlock = 256;
 constexpr uint32_t kNoPick = 0xFFFFFFFFu;
 
-// Order a wavefront's LDS stores of one step before the loads of the next (the
-// hardware completes them in issue order; this keeps the compiler from moving
-// them).
-__device__ __forceinline__ void strip_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // LDS of one applied strip: the words and the numbers of the next picks of its phase
 // columns and of the two frozen columns beside them ([width + 2][N]), the codes
 // and the pick numbers of its list (with an entry more of each, read and not
@@ -450,7 +441,7 @@ __device__ __forceinline__ void apply_strip_list(uint64_t* __restrict__ W, const
     const uint16_t* __restrict__ in_first = l.first + (size_t)p * (size_t)(sites + 1);
     const int col0 = p * a.S + a.off - 1;  // column of cell 0
     auto order = [&] {
-        if (V == 1) strip_lds_order();
+        if (V == 1) wave_lds_order();
         else __syncthreads();
     };
 #pragma unroll 4
