@@ -56,7 +56,7 @@ __device__ __forceinline__ void lds_store64(uint32_t addr, uint64_t v) { *(lds_u
 // vector instructions (add, xor, three-input bitwise) that read a scalar
 // register take about 4.4 cycles per wave64 instruction when they follow
 // each other, against about 2.6 when all operands are vector registers or
-// constants (the instruction-rate microbenchmark, valu_rates.hip); the
+// constants (the instruction-rate microbenchmark, bench_valu_rates.hip); the
 // Philox rounds therefore read their round keys from vector registers.
 __device__ __forceinline__ uint32_t in_vgpr(uint32_t s) {
     uint32_t v;

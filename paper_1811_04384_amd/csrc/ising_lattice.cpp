@@ -218,8 +218,8 @@ static int create_impl(int32_t L, uint64_t seed, int32_t init, void* dev_words, 
     // Up to 7680 columns resident tiles are faster than one launch per
     // half-sweep at every size measured (us per sweep, resident against
     // half-sweep launches, E/M every 10 sweeps: L = 294 2.7 / 8.9, 512 2.6 /
-    // 8.5, 1024 3.0 / 9.4, 2048 4.0 / 9.8, 4096 8.1 / 14.8, 5120 14.8 /
-    // 19.3, 7680 31.7 / 33.0).
+    // 8.5, 1024 3.0 / 9.4, 2048 4.0 / 9.8, 4096 8.1 / 14.8, 5120 14.5 /
+    // 19.3, 7680 31.4 / 33.0).
     // Above 7680 a band no longer fits in LDS; where the tiles do not fit the
     // lattice keeps the half-sweep launches.
     if (L <= 7680) {
