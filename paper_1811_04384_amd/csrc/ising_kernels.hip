@@ -435,20 +435,40 @@ __device__ __forceinline__ void observe_words(const uint64_t* __restrict__ W, in
     }
 }
 
-// Words of a lattice per workgroup of k_observe_multi.
+// E and M of a lattice from its sums, into its state and out (may be null).
+__device__ __forceinline__ void observed(uint64_t anti, uint64_t ups, int32_t L, LatticeState& st,
+                                         int64_t* __restrict__ out) {
+    int64_t E, M;
+    energy_magnetisation(anti, ups, L, E, M);
+    st.last_E = E;
+    st.last_M = M;
+    if (out) {
+        out[0] = E;
+        out[1] = M;
+        out[2] = st.abandoned;
+    }
+}
+
+// Words of a lattice per workgroup of k_observe_multi; and those of lattices that one
+// workgroup takes whole and finishes, without the second launch (us per read of E
+// and M with it / without: 8 lattices of L = 64 31.8 / 30.3, 500 of L = 256 42.5 / 39.5,
+// 8 of L = 340, 6120 words, 33.4 / 36).
 constexpr uint32_t kObserveWords = 2048;
+constexpr int64_t kObserveWhole = 4096;
 
 // Observables of every lattice of a table: workgroup part of `parts` of a
 // lattice takes every parts-th run of kObserveWords words and adds its sums to the
 // lattice's in device memory (a workgroup without words, of a smaller lattice of
-// the table, does not take part); k_observed, launched behind it, forms E and M.
+// the table, does not take part); k_observed, launched behind it, forms E and M, or
+// this kernel where a workgroup takes a whole lattice (parts = 1).
 // Bound by the words' bytes: 256 lattices of L = 256 ... 2048 (137 MB) 74 us,
 // against 379 with one workgroup per lattice; one of L = 4096 12 us against 790.
 // A count of arrived workgroups in this kernel instead of the second launch took
 // 287 us, for its acquire and release by each of them.
 __global__ void __launch_bounds__(256) k_observe_multi(const LatticeDesc* __restrict__ descs,
                                                        LatticeState* __restrict__ states,
-                                                       const int32_t* __restrict__ ids, int32_t parts) {
+                                                       const int32_t* __restrict__ ids, int32_t parts,
+                                                       int64_t* __restrict__ out) {
     __shared__ uint64_t red[32];
     const uint32_t k = blockIdx.x / (uint32_t)parts, part = blockIdx.x - k * (uint32_t)parts;
     const int32_t lat = ids ? ids[k] : (int32_t)k;
@@ -466,8 +486,12 @@ __global__ void __launch_bounds__(256) k_observe_multi(const LatticeDesc* __rest
     }
     block_sum2(anti, ups, red);
     if (threadIdx.x == 0) {
-        atomicAdd(&states[lat].obs_anti, (unsigned long long)anti);
-        atomicAdd(&states[lat].obs_ups, (unsigned long long)ups);
+        if (parts == 1) {
+            observed(anti, ups, L, states[lat], out ? out + kObservedWords * k : nullptr);
+        } else {
+            atomicAdd(&states[lat].obs_anti, (unsigned long long)anti);
+            atomicAdd(&states[lat].obs_ups, (unsigned long long)ups);
+        }
     }
 }
 
@@ -479,17 +503,9 @@ __global__ void __launch_bounds__(256) k_observed(const LatticeDesc* __restrict_
     if (k >= n_lat) return;
     const int32_t lat = ids ? ids[k] : k;
     LatticeState& st = states[lat];
-    int64_t E, M;
-    energy_magnetisation(st.obs_anti, st.obs_ups, descs[lat].L, E, M);
+    observed(st.obs_anti, st.obs_ups, descs[lat].L, st, out ? out + kObservedWords * k : nullptr);
     st.obs_anti = 0;
     st.obs_ups = 0;
-    st.last_E = E;
-    st.last_M = M;
-    if (out) {
-        out[kObservedWords * k] = E;
-        out[kObservedWords * k + 1] = M;
-        out[kObservedWords * k + 2] = st.abandoned;
-    }
 }
 
 // The same of one lattice, `run` words (a multiple of 256) per workgroup, as
@@ -715,11 +731,12 @@ hipError_t launch_observe_multi(const LatticeDesc* descs, LatticeState* states, 
     if (n_lat <= 0) return hipSuccess;
     // workgroups for every run of the largest lattice, up to 1024 per lattice and
     // 16384 in all (beyond, a workgroup takes several runs)
-    const int64_t runs = (max_words + kObserveWords - 1) / kObserveWords;
+    const int64_t runs = max_words <= kObserveWhole ? 1 : (max_words + kObserveWords - 1) / kObserveWords;
     const int64_t parts = std::max<int64_t>(1, std::min({runs, (int64_t)1024, (int64_t)16384 / n_lat}));
     hipLaunchKernelGGL(k_observe_multi, dim3((unsigned)(parts * n_lat)), dim3(256), 0, s, descs, states, ids,
-                       (int32_t)parts);
-    hipLaunchKernelGGL(k_observed, dim3(grid_for(n_lat, 256)), dim3(256), 0, s, descs, states, ids, n_lat, out);
+                       (int32_t)parts, out);
+    if (parts > 1)
+        hipLaunchKernelGGL(k_observed, dim3(grid_for(n_lat, 256)), dim3(256), 0, s, descs, states, ids, n_lat, out);
     return hipGetLastError();
 }
 
