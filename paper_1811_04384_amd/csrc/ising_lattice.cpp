@@ -522,11 +522,17 @@ constexpr int64_t kStripBufEntries = int64_t(1) << 22;
 constexpr size_t kStripChainLdsMax = 16 * 1024;
 constexpr size_t kStripBytes = (sizeof(uint64_t) + sizeof(uint32_t)) * kStripBufEntries;
 
-// The two sets of lists share that buffer (a call uses one form).  Words' first
-// entries and picks of a set (2 and 10 bytes each): every strip shape of at most
-// 512 words per phase has at most 2.76 million words, which leaves 1.9 million picks.
+// Lists are for phases of at most 1.5 Mi words in all strips: with more, the chip is
+// full and what counts is work, of which windows of picks have less (us per phase,
+// windows / lists, strips of two columns: L = 6048, 0.83 Mi words, 429 / 320; 8064,
+// 1.48 Mi, 670 / 640; 9072, 1.87 Mi, 927 / 1095; 10752, 2.6 Mi, 1511 / 1894).
+constexpr int64_t kStripListWords = 1536 * 1024;
+
+// The two sets of lists share that buffer (a call uses one form): words' first
+// entries (a word's, and one more per strip, of two words at least) and picks of a
+// set, 2 and 10 bytes each.
 constexpr size_t kStripListBytes = kStripBytes / 2;
-constexpr int64_t kStripListFirst = 2816 * 1024;
+constexpr int64_t kStripListFirst = kStripListWords + kStripListWords / 2;
 constexpr int64_t kStripListEntries = (int64_t)(kStripListBytes - 2 * kStripListFirst) / 20 * 2;
 
 // The buffer of the drawn picks, made when first needed; false where the device has
@@ -647,7 +653,7 @@ int ising_random_iterations(ising_lattice* h, double T, int32_t strip_cols, int6
     };
     // the right half of a strip is at least as wide as the left one
     if (n_iterations > 0 && strip_list_picks(phase(1, 1), kStripListEntries) > 0 &&
-        (int64_t)a.strips * ((int64_t)N * a.width + 1) <= kStripListFirst && strip_buffer(h)) {
+        (int64_t)a.strips * N * a.width <= kStripListWords && strip_buffer(h)) {
         const int rc = strip_list_iterations(h, n_iterations, phase, observe);
         if (rc != ISING_OK) return rc;
     } else {

@@ -79,10 +79,10 @@ def test_drawn_sweeps_that_fail_leave_the_counter_with_the_state(stub, plain):
     assert stub("drawn", plain, 0) == ["ok t right"] * 3 + ["rewritten 0 wrong 0"]
 
 
-# L, strip columns of two kinds in turn: few words per phase (lists), more (windows), or too many for either
+# L, strip columns of two kinds in turn: few words per strip and in all (lists), more (windows), or too many for either
 @pytest.mark.parametrize("L,a,b,forms", [
     (84, 2, 12, (0, 0, 1)), (1008, 2, 36, (0, 1, 1)), (1008, 36, 2, (0, 1, 1)), (4200, 2, 4, (0, 0, 1)),
-    (10752, 2, 2, (0, 0, 1)), (1008, 504, 2, (1, 0, 1)),
+    (8064, 2, 2, (0, 0, 1)), (9072, 2, 2, (0, 1, 0)), (1008, 504, 2, (1, 0, 1)),
 ])
 def test_strip_dynamics_with_little_memory_left(stub, L, a, b, forms):
     """Both forms that draw picks ahead use one buffer (48 MiB, allocated once, within which all they draw lies); and
