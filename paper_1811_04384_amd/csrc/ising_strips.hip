@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(64) k_strip_phase(uint64_t* __restrict__ W, St
         const uint64_t dn = down_word(ld, I, J, N, a.istar, a.sh_star);
         // every position draws (dead slots are masked by `live`), so lanes
         // with different rows run the same instructions
-        AcceptSelect acc;
+        AcceptChain acc;
         accept_word(
             acc, [&](int g) { return philox_lane_c1(a.t_lo, (uint32_t)p, k, (uint32_t)g + c3_word, a.k0, a.k1, rk); }, 21,
             a.t4, a.t8);
