@@ -59,6 +59,7 @@ struct ising_batch {
     WaveItem* d_waves = nullptr;
     int64_t n_waves = 0;
     bool wave_runs = true;  // the table dealt to the XCDs in runs (launch_halfsweep_multi)
+    bool wave_few = false;  // most of its wavefronts are of lattices with few live positions
     Partial* d_partials = nullptr;
     int32_t* d_ids_lds = nullptr;
     int32_t n_lds = 0;
@@ -270,7 +271,7 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
     b->part_count.assign(b->n, 0);
     std::vector<int32_t> ids_lds, ids_glb, ids_draw;
     std::vector<WaveItem> waves;
-    int64_t filling = 0;  // wavefronts of rows that fill the XCDs evenly
+    int64_t filling = 0, few = 0;  // wavefronts of rows that fill the XCDs evenly, and of lattices with few live positions
     size_t max_lds = 0;
     for (int32_t i = 0; i < b->n; ++i) {
         const Geometry& g = b->geo[i];
@@ -333,9 +334,11 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
             for (int32_t w0 = 0; w0 < g.L / 2; w0 += 64 * p.words_per_thread) waves.push_back({i, I, w0});
         b->part_count[i] = (int32_t)waves.size() - b->part_begin[i];
         if (rows_fill_xcds(g, p.words_per_thread, p.tiled_block)) filling += b->part_count[i];
+        if (few_live(g)) few += b->part_count[i];
     }
     b->n_waves = (int64_t)waves.size();
     b->wave_runs = 2 * filling <= b->n_waves;
+    b->wave_few = 2 * few > b->n_waves;
     b->n_lds = (int32_t)ids_lds.size();
     b->n_glb = (int32_t)ids_glb.size();
     b->n_tile_lat = (int32_t)ids_tile.size();
@@ -518,10 +521,10 @@ int enqueue_chunk(ising_batch* b, int32_t k, int32_t every, hipStream_t s0, hipS
     if (b->n_tiled) {
         for (int32_t s = 0; s < k; ++s) {
             ISING_HIP(launch_halfsweep_multi(p.words_per_thread, p.tiled_block, b->d_desc, b->d_state, b->d_waves,
-                                             b->n_waves, b->wave_runs, 0, (uint32_t)s, nullptr,
+                                             b->n_waves, b->wave_runs, b->wave_few, 0, (uint32_t)s, nullptr,
                                              measured(s - 1) ? b->d_partials : nullptr, (uint32_t)(s - 1), s0));
             ISING_HIP(launch_halfsweep_multi(p.words_per_thread, p.tiled_block, b->d_desc, b->d_state, b->d_waves,
-                                             b->n_waves, b->wave_runs, 1, (uint32_t)s, measured(s) ? b->d_partials : nullptr,
+                                             b->n_waves, b->wave_runs, b->wave_few, 1, (uint32_t)s, measured(s) ? b->d_partials : nullptr,
                                              nullptr, 0, s0));
         }
     }

@@ -302,6 +302,8 @@ struct AcceptSelect {
     __device__ __forceinline__ uint64_t word() const {
         return ((uint64_t)((hi << 1) | (mid >> 2)) << 32) | (mid << 30) | lo;
     }
+    __device__ __forceinline__ uint64_t a() const { return word(); }
+    __device__ __forceinline__ uint64_t b() const { return word() >> 1; }
 };
 
 // The same with the shift-or in the block of its compares and selects, for

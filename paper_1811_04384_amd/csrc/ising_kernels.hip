@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ising_device.hpp"
 #include "ising_launch.hpp"
@@ -77,19 +78,21 @@ __global__ void __launch_bounds__(256) k_init(uint64_t* __restrict__ W, Geometry
 // Half-sweep of one lattice held in global memory: every wavefront updates
 // 64 WPT words of the colour of one word row.
 // ---------------------------------------------------------------------------
-// What a half-sweep of one lattice adds to a run of words of word row I.
-template <bool MEASURE>
+// What a half-sweep of one lattice adds to a run of words of word row I (n_live
+// live positions).  FEW: blocks past the last live position are not drawn.
+template <bool MEASURE, bool FEW>
 struct LatticeRule {
+    typedef std::conditional_t<FEW, AcceptSelect, AcceptPair> Accept;
     const SweepArgs& a;
-    int I;
+    int I, n_live;
     uint64_t live;
     uint32_t anti = 0, ups = 0;
     template <class Block>
-    __device__ __forceinline__ void accept(AcceptPair& acc, const Block& block) const {
-        accept_word(acc, block, 21, a.t4, a.t8);  // the bits of dead slots are masked by `live`
+    __device__ __forceinline__ void accept(Accept& acc, const Block& block) const {
+        accept_word(acc, block, FEW ? n_live : 21, a.t4, a.t8);  // the bits of dead slots are masked by `live`
     }
-    __device__ __forceinline__ void accept20(AcceptPair& acc, uint32_t u) const {
-        acc.add<20>(u, a.t4, a.t8);  // a dead slot when n_live < 21
+    __device__ __forceinline__ void accept20(Accept& acc, uint32_t u) const {
+        acc.template add<20>(u, a.t4, a.t8);  // a dead slot when n_live < 21
     }
     __device__ __forceinline__ void vertical(uint64_t& up, uint64_t& dn, uint64_t patch) const {
         const Nbhd nb = {0, 0, 0, up, dn, patch};
@@ -103,7 +106,7 @@ struct LatticeRule {
 
 // The words w0 + 64 k + lane (k < WPT) of colour `colour` of word row I of
 // one lattice, by one wavefront; with MEASURE its sums go to *partial.
-template <int WPT, bool MEASURE>
+template <int WPT, bool MEASURE, bool FEW = false>
 __device__ __forceinline__ void update_lattice_row(uint64_t* __restrict__ W, const SweepArgs& a, int I, int w0, int colour,
                                                    uint32_t* __restrict__ table, Partial* __restrict__ partial) {
     const size_t L = (size_t)a.L;
@@ -122,7 +125,7 @@ __device__ __forceinline__ void update_lattice_row(uint64_t* __restrict__ W, con
                       a.k0,
                       a.k1,
                       n_live == 21};
-    LatticeRule<MEASURE> rule{a, I, kSpinBits & (~0ull << (3 * (21 - n_live)))};
+    LatticeRule<MEASURE, FEW> rule{a, I, n_live, kSpinBits & (~0ull << (3 * (21 - n_live)))};
     update_row_words<WPT>(r, w0, table, rule);
     if (MEASURE) {
         const uint32_t anti = wave_sum_u32(rule.anti), ups = wave_sum_u32(rule.ups);
@@ -199,9 +202,15 @@ __device__ __forceinline__ void finalize_lattice(const LatticeDesc& d, LatticeSt
 // index, thresholds) are wave-uniform and live in scalar registers.  With
 // fin_partials set, the first wavefront of every lattice first finalizes the
 // lattice's measured sweep fin_off from the partials that an earlier launch
-// left (the launch boundary orders them), which saves a launch per sample.
+// left (the launch boundary orders them), which saves a launch per sample.  FEW: a
+// kernel for tables that are mostly of lattices with at most 16 live positions a
+// word (few_live), which are over before the chip is full: their rows draw only the
+// blocks that they need, and acceptance is by selects, which wait less (us per
+// half-sweep of 8 lattices, without / with: a word per thread and 64 threads L = 4
+// 3.33 / 2.66, 16 3.31 / 2.75, 64 3.39 / 3.12, 256 threads 4.05 / 2.78, 4.07 / 3.18, 3.21 /
+// 2.99; for all lattices it would take L = 9998 from 23.7 to 24.2).
 // ---------------------------------------------------------------------------
-template <int WPT, bool MEASURE>
+template <int WPT, bool MEASURE, bool FEW>
 __global__ void __launch_bounds__(kTiledMaxBlock)
     k_halfsweep_multi(const LatticeDesc* __restrict__ descs, LatticeState* __restrict__ states,
                       const WaveItem* __restrict__ waves, uint32_t n_waves, uint32_t group, int colour,
@@ -227,7 +236,7 @@ __global__ void __launch_bounds__(kTiledMaxBlock)
     }
     const SweepArgs a = {d.L, d.N, d.istar, d.sh_star, d.pstar, (uint32_t)t, (uint32_t)(t >> 32), d.k0, d.k1, d.t4, d.t8};
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    update_lattice_row<WPT, MEASURE>(d.W, a, item.row, item.w0, colour, table + wv * row_table_words<WPT>(),
+    update_lattice_row<WPT, MEASURE, FEW>(d.W, a, item.row, item.w0, colour, table + wv * row_table_words<WPT>(),
                                      MEASURE ? partials + wave : nullptr);
 }
 
@@ -675,8 +684,9 @@ hipError_t launch_pack_words(const uint8_t* in, const Geometry& g, uint64_t* W, 
 }
 
 hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, LatticeState* states,
-                                  const WaveItem* waves, int64_t n_waves, bool runs, int colour, uint32_t sweep_off,
-                                  Partial* partials, const Partial* fin_partials, uint32_t fin_off, hipStream_t s) {
+                                  const WaveItem* waves, int64_t n_waves, bool runs, bool few, int colour,
+                                  uint32_t sweep_off, Partial* partials, const Partial* fin_partials,
+                                  uint32_t fin_off, hipStream_t s) {
     if (n_waves <= 0) return hipSuccess;
     const dim3 grid(grid_for((uint64_t)n_waves * 64, block)), blk(block);
     const bool m = partials != nullptr;
@@ -692,11 +702,14 @@ hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, 
     // and below on the XCD anyway: one L = 4096 with a word and 64 threads 8.1, in
     // runs 9.1.
     const uint32_t group = runs ? std::max(1u, std::min(grid.x / 64, 16384u / (unsigned)block)) : grid.x;
-#define ISING_LAUNCH_HM(WPT_)                                                                                       \
-    if (m) hipLaunchKernelGGL((k_halfsweep_multi<WPT_, true>), grid, blk, 0, s, descs, states, waves, nw, group, colour, \
-                              sweep_off, partials, fin_partials, fin_off);                                          \
-    else hipLaunchKernelGGL((k_halfsweep_multi<WPT_, false>), grid, blk, 0, s, descs, states, waves, nw, group, colour, \
-                            sweep_off, partials, fin_partials, fin_off);
+#define ISING_LAUNCH_HM_(WPT_, M_, F_)                                                                                 \
+    hipLaunchKernelGGL((k_halfsweep_multi<WPT_, M_, F_>), grid, blk, 0, s, descs, states, waves, nw, group, colour, \
+                       sweep_off, partials, fin_partials, fin_off)
+#define ISING_LAUNCH_HM(WPT_)                       \
+    if (m && few) ISING_LAUNCH_HM_(WPT_, true, true); \
+    else if (m) ISING_LAUNCH_HM_(WPT_, true, false);  \
+    else if (few) ISING_LAUNCH_HM_(WPT_, false, true); \
+    else ISING_LAUNCH_HM_(WPT_, false, false);
     switch (wpt) {
         case 1: ISING_LAUNCH_HM(1) break;
         case 2: ISING_LAUNCH_HM(2) break;
@@ -704,6 +717,7 @@ hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, 
         default: return hipErrorInvalidValue;
     }
 #undef ISING_LAUNCH_HM
+#undef ISING_LAUNCH_HM_
     return hipGetLastError();
 }
 

@@ -39,6 +39,10 @@ inline bool rows_fill_xcds(const Geometry& g, int32_t wpt, int block) {
     return (waves_per_colour(g, wpt) / g.N) % (8 * (block / 64)) == 0;
 }
 
+// Whether no word of a lattice has more than 16 live positions, so that five Philox
+// blocks are more than it needs (up to L = 128; L = 42 and 84 have 21).
+inline bool few_live(const Geometry& g) { return (g.L - 1) / g.N < 16; }
+
 // Zero n 64-bit words with a kernel (usable inside a captured graph).
 hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t s);
 
@@ -116,11 +120,12 @@ hipError_t launch_pack_words(const uint8_t* in, const Geometry& g, uint64_t* W, 
 // lattice's measured sweep fin_off from those partials (written by an
 // earlier launch on the same stream).  Lattices whose sweep_limit is <= an
 // offset took no part in that sweep and are skipped.  runs: the table is dealt
-// to the XCDs in runs of wavefronts, not workgroup by workgroup.
+// to the XCDs in runs of wavefronts, not workgroup by workgroup.  few: most of its
+// wavefronts are of lattices with few live positions (few_live).
 hipError_t launch_halfsweep_multi(int wpt, int block, const LatticeDesc* descs, LatticeState* states,
-                                  const WaveItem* waves, int64_t n_waves, bool runs, int colour, uint32_t sweep_off,
-                                  Partial* partials, const Partial* fin_partials, uint32_t fin_off,
-                                  hipStream_t s);
+                                  const WaveItem* waves, int64_t n_waves, bool runs, bool few, int colour,
+                                  uint32_t sweep_off, Partial* partials, const Partial* fin_partials,
+                                  uint32_t fin_off, hipStream_t s);
 // End of a chunk of k sweeps: finalize the tiled lattices' measured sweep
 // fin_off (fin_partials non-null) and advance every lattice's sweep counter
 // by min(k, sweep_limit).

@@ -60,6 +60,7 @@ __device__ __forceinline__ void replica_accept(AcceptPair& acc, const U4& o, con
 // What a half-sweep of the replicas does with a run of words: a threshold
 // pair per field, all fields live, plain neighbours on the torus.
 struct ReplicaRule {
+    typedef AcceptPair Accept;
     const ReplicaArgs& a;
     uint64_t live = kSpinBits;
     template <class Block>

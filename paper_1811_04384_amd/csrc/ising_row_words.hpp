@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "ising_device.hpp"
 
 namespace ising {
@@ -70,7 +72,8 @@ struct RowRun {
 
 using GlobalByte = __attribute__((address_space(1))) char;
 
-// Rule(run of one word) supplies the rest: rule.accept(acc, block) adds the
+// Rule(run of one word) supplies the rest: rule.accept(acc, block) adds (to a
+// Rule::Accept) the
 // acceptance bits of positions 0..19 (block(g) draws block g),
 // rule.accept20(acc, u) those of position 20, rule.vertical(up, dn, patch)
 // finishes the vertical neighbours of a row that wraps, rule.live is the
@@ -115,7 +118,7 @@ __device__ __forceinline__ void update_row_words(const RowRun& r, int w0, uint32
             const uint32_t u20 = r.last_block ? table[64 * k + lane] : 0u;
 
             const uint32_t c1 = r.row_base + (uint32_t)J;
-            AcceptPair acc;
+            typename std::remove_reference_t<Rule>::Accept acc;
             rule.accept(acc, [&](int g) {
                 return philox_lane_c1(r.t_lo, c1, r.t_hi, (uint32_t)g | r.c3, r.k0, r.k1, rk);
             });

@@ -494,9 +494,9 @@ int enqueue_quantum(ising_server* s) {
                 }
             }
             for (int32_t k = 0; k < K && n_waves; ++k) {
-                ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, 0,
+                ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, false, 0,
                                                  (uint32_t)k, nullptr, nullptr, 0, s->stream));
-                ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, 1,
+                ISING_HIP(launch_halfsweep_multi(wpt, block, s->d_desc, s->d_state, s->d_waves, n_waves, wave_runs, false, 1,
                                                  (uint32_t)k, nullptr, nullptr, 0, s->stream));
             }
             if (n_res && n_large) ISING_HIP(hipStreamWaitEvent(s->stream, s->join_ev, 0));

@@ -168,7 +168,7 @@ hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t) {
     return launch([=] { std::memset(p, 0, 8 * n); });
 }
 hipError_t launch_halfsweep_multi(int, int, const LatticeDesc* descs, LatticeState* states, const WaveItem* waves,
-                                  int64_t n_waves, bool, int colour, uint32_t sweep_off, Partial*, const Partial*,
+                                  int64_t n_waves, bool, bool, int colour, uint32_t sweep_off, Partial*, const Partial*,
                                   uint32_t, hipStream_t) {
     ++n_swept;
     return launch([=] {
