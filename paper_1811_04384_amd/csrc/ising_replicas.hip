@@ -143,6 +143,7 @@ __global__ void __launch_bounds__(256) k_replica_observe(const uint64_t* __restr
     const uint64_t end = min(n, (uint64_t)(blockIdx.x + 1) * run);
     uint64_t i = (uint64_t)blockIdx.x * run + threadIdx.x;
     int r = (int)(i / (uint64_t)L), c = (int)(i - (uint64_t)r * (uint64_t)L);
+    const int rows = 256 / L, cols = 256 - rows * L;  // from one word of a thread to its next
     while (i < end) {
         uint64_t w[4], rt[4], dn[4];
 #pragma unroll
@@ -156,8 +157,9 @@ __global__ void __launch_bounds__(256) k_replica_observe(const uint64_t* __restr
             dn[k] = below[cc];
             if (!in) w[k] = rt[k] = dn[k] = 0;
             i += 256;
-            c += 256;
-            while (c >= L) {
+            r += rows;
+            c += cols;
+            if (c >= L) {
                 c -= L;
                 r += 1;
             }
