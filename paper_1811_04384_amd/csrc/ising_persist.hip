@@ -260,9 +260,13 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
     WordItem cur0{}, cur1{}, oth0{}, oth1{};  // word items, this colour and the other
     DrawItem dcur0{}, dcur1{}, doth0{}, doth1{};  // the items whose codes this thread draws
     const int f0 = split ? B - 1 - tid : tid, f1 = tid + B;
-    // two words per thread keep the vector unit busy: the form with fewer
-    // instructions (those 16 lattices 2670 us with selects, 2600 with it)
-    typedef std::conditional_t<ITEMS == kTwo, AcceptWord, AcceptSelect> Accept;
+    // Two words per thread of a band keep the vector unit busy: the form with
+    // fewer instructions (heating of 16 lattices of L = 1008 2670 us with selects,
+    // 2600 with it).  Whole lattices wait for their slowest wavefront at every
+    // half-sweep: selects (us per sweep, without / with them: one of L = 64 in a
+    // wavefront 4.48 / 4.27, 256 of L = 128 in four 4.90 / 4.64, 1024 of them
+    // 8.66 / 8.71, 256 of L = 192 in eight 6.33 / 5.98).
+    typedef std::conditional_t<ITEMS == kTwo && !WHOLE, AcceptWord, AcceptSelect> Accept;
     auto draw_codes = [&](const DrawItem& it, int f, const LdsSweep& swc, uint32_t table) {
         // the sweep index made opaque to the compiler (see the words below)
         LdsSweep swi = swc;
