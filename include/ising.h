@@ -287,7 +287,8 @@ int ising_get_tiling(ising_lattice* h, int32_t* sweeps_per_launch, int32_t* tile
    per workgroup, a multiple of 64 in [64, 1024].  tile_cols = 0 switches it
    off; either this or ising_set_tiling is in effect, the last one set.
    EINVAL if a tile does not fit in LDS or the tiles do not all fit on the
-   device at once.  A launch whose tiles wait for a neighbour longer than
+   device at once (beside kernels of other streams, only half of what a
+   compute unit holds is sure to find room; the defaults are within that).  A launch whose tiles wait for a neighbour longer than
    about a second is abandoned: the next call on the handle returns
    ISING_EHIP, and the lattice state is undefined.  Launches of resident
    tiles on different streams of one device (of this or other handles,
@@ -387,7 +388,8 @@ int ising_batch_get_sweep_count(ising_batch* b, int32_t i, uint64_t* t);
    ising_set_tiling); with tile_exchange = 1, resident tiles that keep their
    words in LDS for a whole chunk and trade boundary words every half-sweep
    (as ising_set_resident_tiles; the lattices whose tiles would exceed what
-   the device holds at once, in index order, go to the next path); a lattice
+   the device holds at once, in index order, go to the next path; tiles
+   that might find no room beside the other paths' launches run before them); a lattice
    whose tile would not fit in LDS goes to the next path; the others
    by per-half-sweep launches over a table of (lattice, row segment) work
    items with words_per_thread words per thread.  sweeps_per_graph sweeps are

@@ -81,6 +81,7 @@ struct ising_batch {
     int32_t n_res = 0;
     size_t res_lds = 0;
     int res_form = -1;  // of the resident tiles (persist_form)
+    bool res_alone = false;  // more of them than are sure to find room beside other kernels
     uint64_t* d_exch = nullptr;
     int64_t exch_tile_words = 0;
     uint64_t* d_flags = nullptr;
@@ -255,6 +256,7 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
     b->n_res_lat = 0;
     b->res_lds = 0;
     b->res_form = -1;
+    b->res_alone = false;
     b->tile_shapes.clear();
     b->plan = p;
     const size_t res_limit = persist_lds_limit(b->device);
@@ -381,6 +383,9 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
             res_tiles.swap(by_block);
         }
         ISING_HIP(allow_persist_lds(b->device, b->res_form, b->res_lds));
+        int64_t capacity = 0, beside = 0;
+        ISING_HIP(persist_capacity(p.tile_block, b->res_lds, b->device, &capacity, &beside));
+        b->res_alone = n > beside && n > (int32_t)ids_res.size();  // (whole lattices wait for nothing)
         b->exch_tile_words = 4 * (int64_t)res_max_N;
         ISING_HIP(hipMalloc(&b->d_res, sizeof(PersistTile) * res_tiles.size()));
         ISING_HIP(hipMemcpy(b->d_res, res_tiles.data(), sizeof(PersistTile) * res_tiles.size(), hipMemcpyHostToDevice));
@@ -446,11 +451,41 @@ int apply_plan(ising_batch* b, const ising_batch_plan& p) {
 }
 
 // Enqueue one chunk of k sweeps (sample after local sweeps s with
-// (s + 1) % every == 0) on stream s0, resident work on stream s1.
+// (s + 1) % every == 0) on stream s0, resident work on stream s1; ahead of both the
+// resident tiles that have to run alone.
 int enqueue_chunk(ising_batch* b, int32_t k, int32_t every, hipStream_t s0, hipStream_t s1) {
     const ising_batch_plan& p = b->plan;
-    const bool fork =
-        (b->n_lds + b->n_glb + b->n_tile_lat + b->n_res_lat + b->n_draw) > 0 && b->n_tiled > 0 && s1 != nullptr;
+    // resident tiles: the whole chunk in one launch, its samples finalized
+    // right behind it on the same branch (chunks hold a multiple of `every`
+    // sweeps, so chunk-local sampling is the call's)
+    auto resident_tiles = [&](hipStream_t s) -> int {
+        PersistLaunch a = {};
+        a.tiles = b->d_res;
+        a.descs = b->d_desc;
+        a.states = b->d_state;
+        a.sweep_off = 0;
+        a.K = k;
+        a.every = every;
+        a.sample_base = 0;
+        a.n_tiles = b->n_res;
+        a.partials = b->d_res_part;
+        a.exch = b->d_exch;
+        a.exch_tile_words = b->exch_tile_words;
+        a.flags = b->d_flags;
+        a.error = b->d_err;
+        a.wait_ticks = 100000000ull;  // one second of the 100 MHz clock
+        ISING_HIP(launch_persist(a, b->res_form, b->n_res, p.tile_block, b->res_lds, s));
+        if (every > 0)
+            ISING_HIP(launch_finalize_resident(b->d_desc, b->d_state, b->d_ids_res, b->n_res_lat, b->d_res_part,
+                                               b->n_res, k / every, s));
+        return ISING_OK;
+    };
+    if (b->n_res_lat && b->res_alone) {
+        const int rc = resident_tiles(s0);
+        if (rc != ISING_OK) return rc;
+    }
+    const int32_t n_side = b->n_lds + b->n_glb + b->n_tile_lat + (b->res_alone ? 0 : b->n_res_lat) + b->n_draw;
+    const bool fork = n_side > 0 && b->n_tiled > 0 && s1 != nullptr;
     hipStream_t rs = fork ? s1 : s0;
     if (fork) {
         ISING_HIP(hipEventRecord(b->fork_ev, s0));
@@ -473,29 +508,9 @@ int enqueue_chunk(ising_batch* b, int32_t k, int32_t every, hipStream_t s0, hipS
     // A measured sweep s is finalized by the next launch on s0: the colour-0
     // half-sweep of sweep s + 1, or the chunk's end.
     auto measured = [&](int32_t s) { return every > 0 && s >= 0 && (s + 1) % every == 0; };
-    // resident tiles: the whole chunk in one launch, its samples finalized
-    // right behind it on the same branch (chunks hold a multiple of `every`
-    // sweeps, so chunk-local sampling is the call's)
-    if (b->n_res_lat) {
-        PersistLaunch a = {};
-        a.tiles = b->d_res;
-        a.descs = b->d_desc;
-        a.states = b->d_state;
-        a.sweep_off = 0;
-        a.K = k;
-        a.every = every;
-        a.sample_base = 0;
-        a.n_tiles = b->n_res;
-        a.partials = b->d_res_part;
-        a.exch = b->d_exch;
-        a.exch_tile_words = b->exch_tile_words;
-        a.flags = b->d_flags;
-        a.error = b->d_err;
-        a.wait_ticks = 100000000ull;  // one second of the 100 MHz clock
-        ISING_HIP(launch_persist(a, b->res_form, b->n_res, p.tile_block, b->res_lds, rs));
-        if (every > 0)
-            ISING_HIP(launch_finalize_resident(b->d_desc, b->d_state, b->d_ids_res, b->n_res_lat, b->d_res_part,
-                                               b->n_res, k / every, rs));
+    if (b->n_res_lat && !b->res_alone) {
+        const int rc = resident_tiles(rs);
+        if (rc != ISING_OK) return rc;
     }
     // tiles: up to tile_sweeps sweeps per launch, the launch's samples
     // finalized right behind it on the same branch

@@ -199,7 +199,8 @@ size_t persist_lds_limit(int device);
 hipError_t allow_persist_lds(int device, int form, size_t lds_bytes);
 // How many resident tiles of `block` threads and lds_bytes of LDS the device
 // holds at once (a launch must not exceed it).
-hipError_t persist_capacity(int block, size_t lds_bytes, int device, int64_t* tiles);
+// beside: how many are sure to find room where other kernels run beside the launch.
+hipError_t persist_capacity(int block, size_t lds_bytes, int device, int64_t* tiles, int64_t* beside = nullptr);
 // form: persist_form of the tiles of the launch (of the widest one of a lattice), or
 // persist_form_any where its lattices' differ.
 int persist_form(int32_t L, int32_t N, int32_t w, int block);

@@ -641,7 +641,14 @@ hipError_t allow_persist_lds(int device, int form, size_t lds_bytes) {
     return e;
 }
 
-hipError_t persist_capacity(int block, size_t lds_bytes, int device, int64_t* tiles) {
+// Beside other kernels a tile's registers and LDS are placed wherever theirs leave
+// room, and once those have ended the holes between the tiles may all be too small for
+// one more: then tiles wait for neighbours that are never placed (two tiles of 512
+// threads per compute unit, launched behind the first of a row of half-sweeps: 30 to
+// 40 of the 512 had found no place when the first ones gave up).  With c tiles in a
+// compute unit that nothing else uses, k of them leave no hole for another only if
+// 2 k + 1 > c, as every hole is smaller than a tile; so half of c, rounded up, is safe.
+hipError_t persist_capacity(int block, size_t lds_bytes, int device, int64_t* tiles, int64_t* beside) {
     // of the kernel that holds every form: the others need no more
     int per_cu = 0, cus = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -649,6 +656,7 @@ hipError_t persist_capacity(int block, size_t lds_bytes, int device, int64_t* ti
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (e != hipSuccess) return e;
     *tiles = (int64_t)per_cu * cus;
+    if (beside) *beside = (int64_t)(per_cu + 1) / 2 * cus;
     return hipSuccess;
 }
 

@@ -1,4 +1,4 @@
-// The library's host code (ising_server.cpp, ising_lattice.cpp) without a GPU, for
+// The library's host code (ising_server.cpp, ising_lattice.cpp, ising_batch.cpp) without a GPU, for
 // the paths that only a failure reaches: a stand-in HIP runtime that runs enqueued
 // work late, in the order of the calls and only when the host waits for it, whose
 // allocations can be made to fail, and stand-ins of the kernels' launchers that
@@ -13,6 +13,7 @@
 #include <deque>
 #include <functional>
 #include <map>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -50,8 +51,29 @@ void run_until(uint64_t seq) {
 }
 void run_all() { run_until(enqueued); }
 
+// Where asked for, the order that streams and events give the launches of resident
+// tiles and of half-sweeps: the launches that each comes after.
+bool watch_order = false;
+int n_watched = 0;
+std::map<hipStream_t, std::set<int>> behind;
+std::vector<std::pair<int, std::set<int>>> tile_launches, sweep_launches;
+
+void watch(std::vector<std::pair<int, std::set<int>>>& launches, hipStream_t s) {
+    if (!watch_order) return;
+    launches.push_back({n_watched, behind[s]});
+    behind[s].insert(n_watched++);
+}
+// Whether tiles may run beside half-sweeps.
+bool beside() {
+    for (const auto& t : tile_launches)
+        for (const auto& h : sweep_launches)
+            if (!t.second.count(h.first) && !h.second.count(t.first)) return true;
+    return false;
+}
+
 struct Event {
     uint64_t seq = 0;
+    std::set<int> behind;
 };
 
 hipError_t launch(std::function<void()> f) {
@@ -92,6 +114,10 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
     return hipSuccess;
 }
 hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) {
+    std::strcpy(p->gcnArchName, "gfx950");
+    return hipSuccess;
+}
 const char* hipGetErrorString(hipError_t) { return "stand-in error"; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
     *s = reinterpret_cast<hipStream_t>(std::malloc(1));
@@ -105,7 +131,28 @@ hipError_t hipStreamSynchronize(hipStream_t) {
     run_all();
     return hipSuccess;
 }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+    const std::set<int>& b = reinterpret_cast<Event*>(e)->behind;
+    behind[s].insert(b.begin(), b.end());
+    return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) {
+    *e = reinterpret_cast<hipEvent_t>(new Event);
+    return hipSuccess;
+}
+// A captured graph's work is enqueued once, when it is captured.
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
+    *g = nullptr;
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t* g, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+    *g = nullptr;
+    return hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
     *e = reinterpret_cast<hipEvent_t>(new Event);
     return hipSuccess;
@@ -114,8 +161,9 @@ hipError_t hipEventDestroy(hipEvent_t e) {
     delete reinterpret_cast<Event*>(e);
     return hipSuccess;
 }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t) {
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
     reinterpret_cast<Event*>(e)->seq = enqueued;
+    reinterpret_cast<Event*>(e)->behind = behind[s];
     return hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) {
@@ -169,8 +217,9 @@ hipError_t launch_zero_words(uint64_t* p, uint64_t n, hipStream_t) {
 }
 hipError_t launch_halfsweep_multi(int, int, const LatticeDesc* descs, LatticeState* states, const WaveItem* waves,
                                   int64_t n_waves, bool, bool, int colour, uint32_t sweep_off, Partial*, const Partial*,
-                                  uint32_t, hipStream_t) {
+                                  uint32_t, hipStream_t s) {
     ++n_swept;
+    watch(sweep_launches, s);
     return launch([=] {
         if (colour == 1)
             for (int64_t w = 0; w < n_waves; ++w) {
@@ -232,8 +281,9 @@ size_t wave_apply_lds_bytes(int32_t NL, int32_t) { return (size_t)NL * 8; }
 size_t resident_lds_limit(int) { return 160 * 1024; }
 
 // A wait bound of one tick expires at once: the launch leaves a state that is not the lattice's.
-hipError_t launch_persist(const PersistLaunch& a, int, int32_t, int, size_t, hipStream_t) {
+hipError_t launch_persist(const PersistLaunch& a, int, int32_t, int, size_t, hipStream_t s) {
     ++n_persist;
+    watch(tile_launches, s);
     return launch([=] {
         if (!a.states) return;  // of a single lattice
         const int32_t i = a.tiles[0].lattice;
@@ -248,10 +298,20 @@ int persist_form(int32_t, int32_t, int32_t, int) { return 0; }
 size_t persist_lds_bytes(int32_t, int32_t, int32_t, int32_t) { return 1000; }
 size_t persist_lds_limit(int) { return 160 * 1024; }
 hipError_t allow_persist_lds(int, int, size_t) { return hipSuccess; }
-hipError_t persist_capacity(int, size_t, int, int64_t* tiles) {
-    *tiles = 256;
+static int tiles_per_cu = 1;
+hipError_t persist_capacity(int, size_t, int, int64_t* tiles, int64_t* beside) {
+    *tiles = 256 * tiles_per_cu;
+    if (beside) *beside = 256 * ((tiles_per_cu + 1) / 2);
     return hipSuccess;
 }
+int persist_form_any() { return 0; }
+hipError_t launch_begin_call(LatticeState*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_reset_sums(LatticeState*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_finalize_resident(const LatticeDesc*, LatticeState*, const int32_t*, int32_t, const Partial*, int32_t, int32_t,
+                                    hipStream_t) {
+    return hipSuccess;
+}
+size_t tile_lds_limit(int) { return 160 * 1024; }
 hipError_t resident_gate(int, hipStream_t, const std::function<hipError_t()>& f, bool* captured) {
     if (capturing && captured) *captured = true;
     return f();
@@ -482,6 +542,30 @@ int main(int argc, char** argv) {
         DrawnLaunch none = {};
         sampled_as(none, 100, 5, 0);
         std::printf("bad %d none %d %d\n", bad, none.every, none.sweep_off);
+    } else if (what == "beside") {
+        // num[1] lattices of L = 512, num[2] of which are in 32 resident tiles each, num[0] of which a compute unit holds
+        tiles_per_cu = (int)num[0];
+        watch_order = true;
+        std::vector<int32_t> L(num[1], 512), init(num[1], ISING_HOT);
+        for (int64_t i = num[2]; i < num[1]; ++i) L[i] = 1024;
+        std::vector<uint64_t> seed(num[1], 1);
+        std::vector<double> T(num[1], 2.0);
+        ising_batch* b = nullptr;
+        if (ising_batch_create((int32_t)num[1], L.data(), seed.data(), init.data(), nullptr, &b) != ISING_OK) return 1;
+        ising_batch_plan p = {};
+        if (ising_batch_get_plan(b, &p) != ISING_OK) return 1;
+        p.resident_max_L = 0;
+        p.draw_sweeps = 0;
+        p.tile_max_L = 512;
+        p.tile_sweeps = 1;
+        p.tile_cols = 16;
+        p.tile_block = 512;
+        p.tile_exchange = 1;
+        if (ising_batch_set_plan(b, &p) != ISING_OK || ising_batch_sweep(b, T.data(), 10, 5, nullptr, nullptr) != ISING_OK)
+            std::printf("error: %s\n", ising_last_error());
+        run_all();
+        std::printf("tiles %d halfsweeps %d beside %d\n", (int)tile_launches.size(), (int)sweep_launches.size(), beside());
+        ising_batch_destroy(b);
     }
     std::printf("rewritten %d wrong %d\n", rewritten, wrong);
     return 0;

@@ -16,7 +16,7 @@ def stub(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-w",
                     "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
                     os.path.join(ROOT, "tests", "host_stub.cpp"), os.path.join(CSRC, "ising_server.cpp"),
-                    os.path.join(CSRC, "ising_lattice.cpp"), "-Wl,--unresolved-symbols=ignore-all", "-o", exe], check=True)
+                    os.path.join(CSRC, "ising_lattice.cpp"), os.path.join(CSRC, "ising_batch.cpp"), "-Wl,--unresolved-symbols=ignore-all", "-o", exe], check=True)
 
     def run(*args):
         out = subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True, timeout=60)
@@ -97,3 +97,13 @@ def test_strip_dynamics_with_little_memory_left(stub, L, a, b, forms):
 def test_samples_of_a_launch_at_any_interval(stub):
     """A sampling interval near 2^31 sweeps, and launches just before and over its end."""
     assert stub("samples") == ["bad 0 none 0 0", "rewritten 0 wrong 0"]
+
+
+# tiles that a compute unit holds alone, lattices in 32 tiles each, whether they may run beside the half-sweeps
+@pytest.mark.parametrize("per_cu,tiled,together", [
+    (1, 8, 1), (2, 8, 1), (2, 9, 0), (2, 16, 0), (3, 16, 1), (3, 17, 0), (4, 16, 1), (4, 17, 0), (4, 32, 0),
+])
+def test_batch_runs_tiles_that_may_find_no_room_ahead_of_the_half_sweeps(stub, per_cu, tiled, together):
+    """Tiles wait for each other, so all of a launch have to find room: beside other kernels no more than half of
+    what a compute unit holds is sure to.  More run alone."""
+    assert stub("beside", per_cu, tiled + 2, tiled) == [f"tiles 1 halfsweeps 20 beside {together}", "rewritten 0 wrong 0"]
