@@ -314,7 +314,8 @@ __global__ void __launch_bounds__(64) k_strip_apply(uint64_t* __restrict__ W, St
 // one, windows of picks with claims above / lists: L = 84 in strips of 2 columns
 // 29 / 16, 1008 of 2 47 / 24, of 6 71 / 34, 2016 of 2 73 / 36 (28 of the 30 us of
 // a launch are the application, 20 the draws beside it), of 4 90 / 37, of 6 110 / 59,
-// 4200 of 2 182 / 138.  With more than 512 words per phase the windows stay.
+// 4200 of 2 182 / 138.  The windows stay with more
+// than 512 words per phase, and with more than 1.5 Mi words in all strips.
 // ---------------------------------------------------------------------------
 constexpr int kListBlock = 256;
 constexpr uint32_t kNoPick = 0xFFFFFFFFu;
