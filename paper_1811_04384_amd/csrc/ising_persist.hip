@@ -327,9 +327,10 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
     // `want`.  Bounded twice, by the clock (a failed poll counts for at least
     // 100 ns) and by the number of polls; when a bound is reached, or another
     // tile has set the error word, the launch is abandoned after this
-    // half-sweep, whose number `stop` holds: a wavefront that is already in the
+    // sweep, whose number from 1 on `stop` holds: a wavefront that is already in the
     // next one when another reads it puts that one's number there, and all of them
-    // leave after the same half-sweep.  In small bands (kOne), whose half-sweep waits for these words
+    // leave after the same sweep (read after every half-sweep, L = 1008 2.45 us per
+    // sweep, 2.36 so; 4096 7.61 / 7.48).  In small bands (kOne), whose half-sweep waits for these words
     // alone, two more reads follow the first at 0.1 us distance, so that a word
     // that just missed one is not seen a whole round trip later (us per
     // half-sweep with one read at a time / three: L = 300 1.31 / 1.16, 1008 1.34 /
@@ -352,7 +353,7 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
                     v2 = fetch(p);
                     if (err != 0u || clock_ticks() - start > a.wait_ticks || polls > kMaxPolls) {
                         __hip_atomic_store(a.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        stop = hs + 1;
+                        stop = (hs >> 1) + 1;
                         break;
                     }
                     err = __hip_atomic_load(a.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -364,7 +365,7 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
                 if (__hip_atomic_load(a.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
                     clock_ticks() - start > a.wait_ticks || polls > kMaxPolls) {
                     __hip_atomic_store(a.error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    stop = hs + 1;
+                    stop = (hs >> 1) + 1;
                     break;
                 }
                 v = fetch(p);
@@ -377,9 +378,9 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
     uint64_t ghost0 = 0;    // the ghost word of this half-sweep's first item (code-table mode)
     // one half-sweep: the word items of its colour (cur0, cur1), the first
     // item of the next one (oth0) and the items whose codes it draws for the
-    // next one (d0, d1); returns whether the launch stops
+    // next one (d0, d1)
     auto half_sweep = [&](const int hs, const WordItem& cur0, const WordItem& cur1, const WordItem& oth0,
-                          const DrawItem& d0, const DrawItem& d1) __attribute__((always_inline)) -> bool {
+                          const DrawItem& d0, const DrawItem& d1) __attribute__((always_inline)) {
         const int c = hs & 1;
         const int j = hs >> 1;
         const LdsSweep sw = sweep_of(hs);
@@ -512,18 +513,20 @@ __device__ __forceinline__ void persist_tile(const PersistLaunch& a, const Persi
             next_sample += a.every;
             ++n_taken;
         }
-        return stop == hs + 1;
     };
     if (pre) {
         // two half-sweeps per trip, so that the items of each colour stay in
         // the same registers (no exchange of the two sets between half-sweeps)
         for (int hs = 0; hs < n_hs; hs += 2) {
-            if (half_sweep(hs, cur0, cur1, oth0, doth0, doth1)) break;
-            if (half_sweep(hs + 1, oth0, oth1, cur0, dcur0, dcur1)) break;
+            half_sweep(hs, cur0, cur1, oth0, doth0, doth1);
+            half_sweep(hs + 1, oth0, oth1, cur0, dcur0, dcur1);
+            if (stop == (hs >> 1) + 1) break;
         }
     } else {
-        for (int hs = 0; hs < n_hs; ++hs)
-            if (half_sweep(hs, cur0, cur1, oth0, doth0, doth1)) break;
+        for (int hs = 0; hs < n_hs; ++hs) {
+            half_sweep(hs, cur0, cur1, oth0, doth0, doth1);
+            if ((hs & 1) && stop == (hs >> 1) + 1) break;
+        }
     }
     // the ghost columns in LDS are stale past the first half-sweep, but the
     // band's own words are exact
