@@ -288,9 +288,10 @@ int ising_get_tiling(ising_lattice* h, int32_t* sweeps_per_launch, int32_t* tile
    off; either this or ising_set_tiling is in effect, the last one set.
    EINVAL if a tile does not fit in LDS or the tiles do not all fit on the
    device at once (beside kernels of other streams, only half of what a
-   compute unit holds is sure to find room; the defaults are within that).  A launch whose tiles wait for a neighbour longer than
-   about a second is abandoned: the next call on the handle returns
-   ISING_EHIP, and the lattice state is undefined.  Launches of resident
+   compute unit holds is sure to find room; the defaults are within that).
+   A launch whose tiles wait for a neighbour longer than about a second is
+   abandoned: the next call on the handle returns ISING_EHIP, and the
+   lattice state is undefined.  Launches of resident
    tiles on different streams of one device (of this or other handles,
    batches and servers) run one after another; those that a caller captures into
    a graph do not, and are not to be replayed beside others.  Synchronises.  Results never depend on
